@@ -31,3 +31,17 @@ FASTDIV_FN float fastdiv(float w, float s, float y) {
     const float r = fmaf(-s, t, w);
     return fmaf(r, y, t);
 }
+
+// Correctly rounded a/b for fp32 operands of any significand, given y = RN(1/b): the quotient above corrected
+// once more.  After the first correction q is within one unit in the last place of a/b (its error before rounding
+// is about 2^-46 relative), so the residual r is exact and the second correction rounds to RN(a/b) (Markstein's
+// theorem on division with a correctly rounded reciprocal).  Holds while no intermediate leaves the normal range:
+// b and y in [2^-40, 2^40] and |a| = 0 or in [2^-80, 2^60] (the range the caller checks); an |a| below that still gives a quotient
+// that is off by less than 2^-20, which is all a caller needs that only rounds it to an integer.
+FASTDIV_FN float fastdiv_full(float a, float b, float y) {
+    float q = a * y;
+    float r = fmaf(-b, q, a);
+    q = fmaf(r, y, q);
+    r = fmaf(-b, q, a);
+    return fmaf(r, y, q);
+}

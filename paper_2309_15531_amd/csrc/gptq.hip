@@ -13,15 +13,16 @@
 // panels: diagonal block in LDS, row-parallel triangular solve, tiled trailing update) and a
 // block-row triangular inverse.
 //
-// Sweep.  Rows (per-OC) or row groups (per-IC) are independent, so a workgroup keeps its rows'
-// 128-channel block in LDS and walks the channels alone: quantize channel i, e = (w - q)/U_ii,
-// w_j -= e*U_ij for the rest of the block; a second kernel applies the block's errors to the
+// Sweep.  Rows (per-OC) or row groups (per-IC) are independent.  Per-OC one launch does it all (gptq_rows.h).  Per-IC a
+// workgroup keeps its row group's 128-channel block in LDS and walks the channels alone: quantize channel i,
+// e = (w - q)/U_ii, w_j -= e*U_ij for the rest of the block; a second kernel applies the block's errors to the
 // channels behind the block, one channel's error at a time.  Every update is a rounded product
 // followed by a rounded difference (no fma), in channel order, which fixes the result bit for
 // bit.  Per-OC uses static groups (parameters computed beforehand from the original weight and
 // looked up by the channel's original index); per-IC recomputes each (row group, channel)'s
 // parameters from the channel's current values when it is visited.
 #include "common.h"
+#include "gptq_rows.h"
 #include "scale_format.h"
 
 #include <algorithm>
@@ -578,10 +579,9 @@ __global__ __launch_bounds__(256) void gq_gather_w(const __half* __restrict__ W,
     }
 }
 
-// One 128-channel block [i1, i1 + nbw) for 64 * RPL rows, by a workgroup of four wavefronts.  Lane l
-// of the first wave holds RPL rows: per-OC rows 64*block + l (RPL = 1), per-IC rows l + 64p of the
-// block's row group (RPL = g/64), so that the group's minimum and maximum are a lane-local step
-// plus one wave reduction.  The rows live in an LDS strip; the channels are walked in sub-blocks of
+// Per-IC: one 128-channel block [i1, i1 + nbw) of one row group, by a workgroup of four wavefronts.  Lane l
+// of the first wave holds the rows l + 64p of the group (RPL = g/64 of them), so that the group's minimum and
+// maximum are a lane-local step plus one wave reduction.  The rows live in an LDS strip; the channels are walked in sub-blocks of
 // 16 that the first wave holds in registers: the sub-block's own updates stay in registers, then
 // its 16 errors are posted in LDS.  All four waves apply them to the next sub-block's 16 columns at
 // once, so that the chain can go on; the columns behind those receive them from the other three
@@ -589,12 +589,10 @@ __global__ __launch_bounds__(256) void gq_gather_w(const __half* __restrict__ W,
 // read and one write per element for 16 updates, always in channel order (which wave applies them
 // does not change a bit).  The block of U is staged in LDS and read with wave-uniform addresses.
 // Codes go out in visiting order (16 bytes per row and sub-block).
-template <bool IC, int RPL>
+template <int RPL>
 __global__ __launch_bounds__(256) void gq_sweep(float* __restrict__ Wp, const float* __restrict__ U,
                                                const int32_t* __restrict__ perm, int64_t out, int64_t in, int64_t i1,
-                                               int nbw, int g, float qmax, int mfmt,
-                                               const float* __restrict__ st_scales,
-                                               const uint8_t* __restrict__ st_zeros, float* __restrict__ scales_out,
+                                               int nbw, int g, float qmax, int mfmt, float* __restrict__ scales_out,
                                                uint8_t* __restrict__ zeros_out, uint8_t* __restrict__ Qp,
                                                float* __restrict__ Ep) {
     constexpr int SB = 16, PITCH = GB + 1;
@@ -635,7 +633,7 @@ __global__ __launch_bounds__(256) void gq_sweep(float* __restrict__ Wp, const fl
     bool ok[RPL];
 #pragma unroll
     for (int p = 0; p < RPL; ++p) {
-        row[p] = IC ? int64_t(blockIdx.x) * g + lane + 64 * p : int64_t(blockIdx.x) * 64 + lane;
+        row[p] = int64_t(blockIdx.x) * g + lane + 64 * p;
         ok[p] = row[p] < out;
     }
     {
@@ -643,23 +641,22 @@ __global__ __launch_bounds__(256) void gq_sweep(float* __restrict__ Wp, const fl
         // columns
         constexpr int NR = 64 * RPL / 2;
         const int c = threadIdx.x & (GB - 1), r_first = threadIdx.x >> 7;
-        const int64_t strip_row0 = IC ? int64_t(blockIdx.x) * g : int64_t(blockIdx.x) * 64;
+        const int64_t strip_row0 = int64_t(blockIdx.x) * g;
         float wv[NR];
 #pragma unroll
         for (int j = 0; j < NR; ++j) {
-            const int r = r_first + 2 * j;                              // strip row; per-IC rows l + 64 p sit at (l * RPL + p)
+            const int r = r_first + 2 * j;                              // strip row; rows l + 64 p sit at (l * RPL + p)
             const int64_t grow = strip_row0 + r;
             wv[j] = (c < nbw && grow < out) ? Wp[grow * in + i1 + c] : 0.0f;
         }
 #pragma unroll
         for (int j = 0; j < NR; ++j) {
             const int r = r_first + 2 * j;
-            const int slot = IC ? (r & 63) * RPL + (r >> 6) : r;        // row l + 64 p of a group -> strip slot l * RPL + p
+            const int slot = (r & 63) * RPL + (r >> 6);        // row l + 64 p of a group -> strip slot l * RPL + p
             if (c < nbw) Ws[slot * PITCH + c] = wv[j];
         }
     }
     __syncthreads();
-    const int n_cg = IC ? 0 : static_cast<int>(in / g);
     // errors of a sub-block applied to columns [c_lo, c_hi), every `step`-th from c_lo + first; channel order kept
     // per element (which wave applies them does not change a bit)
     auto apply = [&](const float* Esrc, int k0, int kw, int c_lo, int c_hi, int first, int step) {
@@ -702,28 +699,7 @@ __global__ __launch_bounds__(256) void gq_sweep(float* __restrict__ Wp, const fl
 #pragma unroll
                 for (int c = 0; c < SB / 4; ++c) qpk[p][c] = 0u;
             }
-            // the sub-block's original channel indices and, for static groups, its parameters: fetched
-            // together up front, off the channel-by-channel chain
-            QP st[SB];
-            if constexpr (!IC) {
-                int32_t jo[SB];
-#pragma unroll
-                for (int c = 0; c < SB; ++c) jo[c] = (FULL || c < sbw) ? perm[i1 + s0 + c] : 0;
-#pragma unroll
-                for (int c = 0; c < SB; ++c) {
-                    const bool have = ok[0] && (FULL || c < sbw);
-                    if (mfmt) {                                            // static parameters as group words
-                        const uint32_t wd = have ? reinterpret_cast<const uint16_t*>(st_scales)[row[0] * n_cg + jo[c] / g]
-                                                 : (0x3C00u >> (mfmt - 1)) << mfmt;           // scale 1, zero 0
-                        st[c].scale = word_scale(wd, mfmt);
-                        st[c].zero = word_zero(wd, mfmt);
-                    } else {
-                        st[c].scale = have ? st_scales[row[0] * n_cg + jo[c] / g] : 1.0f;
-                        st[c].zero = have ? static_cast<float>(st_zeros[row[0] * n_cg + jo[c] / g]) : 0.0f;
-                    }
-                }
-            }
-            float my_scale = 1.0f, my_zero = 0.0f;                          // lane c: channel c's parameters (per-IC)
+            float my_scale = 1.0f, my_zero = 0.0f;                          // lane c: channel c's parameters
             // The sub-block's 16 x 16 corner of U, all of it in registers before the chain starts (16-byte reads at
             // wave-uniform addresses, every index below a constant): read row by row where it is used, each
             // channel's chain began by waiting for its row.  The fence keeps the reads up here.
@@ -744,30 +720,23 @@ __global__ __launch_bounds__(256) void gq_sweep(float* __restrict__ Wp, const fl
                 if (FULL || c < sbw) {                                      // uniform
                     const float (&u)[SB] = ub[c];
                     const float d = u[c];
-                    QP pr[RPL];
-                    if constexpr (IC) {
-                        float mn = w[0][c], nmx = -w[0][c];
+                    float mn = w[0][c], nmx = -w[0][c];
 #pragma unroll
-                        for (int p = 1; p < RPL; ++p) {
-                            mn = fminf(mn, w[p][c]);
-                            nmx = fminf(nmx, -w[p][c]);
-                        }
-                        wave_min2(mn, nmx);
-                        const QP q1 = params_of(mn, -nmx, qmax, mfmt);
-#pragma unroll
-                        for (int p = 0; p < RPL; ++p) pr[p] = q1;
-                        if (lane == c) {                                    // two selects; stored after the chain
-                            my_scale = q1.scale;
-                            my_zero = q1.zero;
-                        }
-                    } else {
-                        pr[0] = st[c];
+                    for (int p = 1; p < RPL; ++p) {
+                        mn = fminf(mn, w[p][c]);
+                        nmx = fminf(nmx, -w[p][c]);
+                    }
+                    wave_min2(mn, nmx);
+                    const QP pr = params_of(mn, -nmx, qmax, mfmt);
+                    if (lane == c) {                                        // two selects; stored after the chain
+                        my_scale = pr.scale;
+                        my_zero = pr.zero;
                     }
 #pragma unroll
                     for (int p = 0; p < RPL; ++p) {
-                        float q = rintf(w[p][c] / pr[p].scale) + pr[p].zero;
+                        float q = rintf(w[p][c] / pr.scale) + pr.zero;
                         q = fminf(fmaxf(q, 0.0f), qmax);
-                        const float wq = pr[p].scale * (q - pr[p].zero);
+                        const float wq = pr.scale * (q - pr.zero);
                         qpk[p][c / 4] |= static_cast<uint32_t>(q) << (8 * (c % 4));
                         e[p][c] = (w[p][c] - wq) / d;
                         // (constant bounds with a test, not "cc = c + 1": a trip count that depends on c is
@@ -785,10 +754,8 @@ __global__ __launch_bounds__(256) void gq_sweep(float* __restrict__ Wp, const fl
                     for (int p = 0; p < RPL; ++p) e[p][c] = 0.0f;
                 }
             }
-            if constexpr (IC) {
-                if (lane < sbw)
-                    store_params(scales_out, zeros_out, int64_t(blockIdx.x) * in + perm[i1 + s0 + lane], my_scale, my_zero, mfmt);
-            }
+            if (lane < sbw)
+                store_params(scales_out, zeros_out, int64_t(blockIdx.x) * in + perm[i1 + s0 + lane], my_scale, my_zero, mfmt);
             // the sub-block's codes and errors, in visiting order
 #pragma unroll
             for (int p = 0; p < RPL; ++p) {
@@ -1003,25 +970,23 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
                          int mfmt) {
     const size_t mat = size_t(out) * size_t(in) * sizeof(float);
     float* Wp = static_cast<float*>(adadim_workspace(ctx, WS_GPTQ_W, mat));
-    float* Ep = static_cast<float*>(adadim_workspace(ctx, WS_GPTQ_E, mat));
+    const bool ic = dim == ADADIM_DIM_IC;
+    float* Ep = static_cast<float*>(adadim_workspace(ctx, WS_GPTQ_E, ic ? mat : 256));
     uint8_t* Qp = static_cast<uint8_t*>(adadim_workspace(ctx, WS_GPTQ_Q, size_t(out) * size_t(in)));
     int32_t* visited = static_cast<int32_t*>(adadim_workspace(ctx, WS_GPTQ_V, size_t(in) * sizeof(int32_t)));
     if (!Wp || !Ep || !Qp || !visited) return ADADIM_EHIP;
     const float qmax = static_cast<float>((1 << bits) - 1);
-    const bool ic = dim == ADADIM_DIM_IC;
-    const int rpl = ic ? g / 64 : 1;                                   // rows per lane
-    const unsigned blocks = static_cast<unsigned>(ic ? out / g : (out + 63) / 64);
+    const int rpl = g / 64;                                            // per-IC: rows per lane
+    const unsigned blocks = static_cast<unsigned>(ic ? out / g : 0);
     const size_t smem = (size_t(GB) * GB + size_t(64) * rpl * (GB + 1) + size_t(2) * 64 * rpl * 17) * sizeof(float);
     static PerDeviceOnce once;
     ADADIM_HIP_TRY(ctx, once.run([] {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gq_sweep<true, 2>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gq_sweep<2>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
         if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(gq_sweep<true, 1>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(gq_sweep<1>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(gq_sweep<false, 1>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
+        if (e == hipSuccess) e = rows::allow_lds();
         // a row of W in LDS: up to 46340 halves
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(gq_gather_w),
@@ -1033,25 +998,43 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         hipLaunchKernelGGL(gq_gather_w, dim3(static_cast<unsigned>(out)), dim3(256), static_cast<size_t>(in) * 2, ctx->stream, W, out,
                            in, perm, dead, Wp);
     }
+    if (!ic) {
+        ProfScope prof(ctx, "gptq_sweep");
+        const int r = rows::rows_per_group(out, in);
+        const dim3 grid(static_cast<unsigned>((out + r - 1) / r));
+#define GQ_ROWS(R)                                                                                                      \
+    case R:                                                                                                             \
+        hipLaunchKernelGGL(rows::gq_rows<R>, grid, dim3(64 * rows::WAVES), sizeof(rows::Lds<R>), ctx->stream, Wp, U, perm, \
+                           out, in, g, qmax, mfmt, st_scales, st_zeros, Qp);                                            \
+        break
+        switch (r) {
+            GQ_ROWS(4);
+            GQ_ROWS(8);
+            GQ_ROWS(12);
+            GQ_ROWS(16);
+            GQ_ROWS(24);
+            GQ_ROWS(32);
+        }
+#undef GQ_ROWS
+    }
     // A block's errors reach the channels behind it in two launches: the next block's 128 channels at
     // once, on the main stream, so that the next sweep can start; the rest on a side stream, under
     // that sweep, which keeps only a few compute units busy.  Every element still receives the
     // blocks' errors in block order: the side stream applies them in order, and the main stream
     // waits for the side stream's last launch before it adds the following block's errors to the
     // channels that launch wrote.  With per-kernel timing on, everything runs on the main stream.
-    const bool overlap = !ctx->prof.enabled && in > 2 * GB;
+    const bool overlap = ic && !ctx->prof.enabled && in > 2 * GB;
     if (overlap && !adadim_side_stream(ctx)) return ADADIM_EHIP;
     bool side_busy = false;
-    for (int64_t i1 = 0; i1 < in; i1 += GB) {
+    for (int64_t i1 = 0; ic && i1 < in; i1 += GB) {
         const int nbw = static_cast<int>(in - i1 < GB ? in - i1 : GB);
         {
             ProfScope prof(ctx, "gptq_sweep");
-#define GQ_GO(IC_, RPL_)                                                                                          \
-    hipLaunchKernelGGL((gq_sweep<IC_, RPL_>), dim3(blocks), dim3(256), smem, ctx->stream, Wp, U, perm, out, in, i1, \
-                       nbw, g, qmax, mfmt, st_scales, st_zeros, scales_out, zeros_out, Qp, Ep)
-            if (!ic) GQ_GO(false, 1);
-            else if (rpl == 1) GQ_GO(true, 1);
-            else GQ_GO(true, 2);
+#define GQ_GO(RPL_)                                                                                                  \
+    hipLaunchKernelGGL(gq_sweep<RPL_>, dim3(blocks), dim3(256), smem, ctx->stream, Wp, U, perm, out, in, i1, nbw, g, qmax, \
+                       mfmt, scales_out, zeros_out, Qp, Ep)
+            if (rpl == 1) GQ_GO(1);
+            else GQ_GO(2);
 #undef GQ_GO
         }
         const int64_t behind = i1 + nbw;                        // first channel behind the block

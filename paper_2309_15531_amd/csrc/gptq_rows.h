@@ -1,0 +1,522 @@
+// The per-OC GPTQ sweep in one launch (gfx950).  Included by gptq.hip.
+//
+// With static groups (per-OC) the rows of W do not depend on each other, so a workgroup can take its R rows through
+// every channel without meeting another workgroup.  Eight waves:
+//   * wave 0 walks the 128 channels of block b: the chain of rounding decisions, latency bound;
+//   * meanwhile the others apply the errors of block b - 1 to the columns behind block b (VALU bound: a rounded
+//     product and a rounded difference per element and channel, which is the definition's sequence, so no fma and
+//     no matrix core); wave 0 joins them when its chain is done;
+//   * then all waves apply block b's errors to block b + 1's columns, on their way from memory into LDS.
+// Two barriers per block and nothing else to wait for.  The launches per block and the two streams this replaces
+// left the chip idle around every short launch.  The whole sweep of a 4096 x 4096 layer, 3 bits: 3.3 ms then, 2.1 ms
+// now, of which the VALU's own time is 1.75 ms (out * in^2 instructions at 64 lanes per cycle and compute unit); 64 to
+// 1024 rows of that width 0.9 ms (the chain alone).
+//
+// Rows per workgroup: few enough that the chip's 256 compute units all have a workgroup (16 at 4096 rows), so that
+// the VALU work is spread over the whole chip; the chain takes the same time for 4 rows as for 64.  rows_per_group
+// picks R from the sizes.
+//
+// Order of the updates of one element: blocks in order, channels inside a block in order, whichever wave applies
+// them; every update is one product and one difference.  Hence the same bits as a plain channel-by-channel loop.
+#pragma once
+
+#include "common.h"
+#include "fastdiv.h"
+#include "scale_format.h"
+
+#include <type_traits>
+
+namespace {
+
+namespace rows {
+
+constexpr int GB = 128;                // channels per block
+constexpr int SB = 16;                 // channels per register sub-block of the chain
+constexpr int PITCH = GB + 4;          // LDS row pitch (floats) of the strip and of the transposed block of U
+constexpr int WAVES = 8;
+
+template <int R>
+constexpr int pow2_rows() { return R <= 4 ? 4 : R <= 8 ? 8 : R <= 16 ? 16 : 32; }
+
+// LDS of one workgroup (dynamic)
+template <int R>
+struct Lds {
+    float ut[GB][PITCH];               // ut[c][k] = U[i1 + k][i1 + c], the block's corner, transposed
+    float w[R][PITCH];                 // the block's columns of the rows, as the chain finds them
+    float e[2][GB][R];                 // errors, [channel][row], of this block and the last
+    float2 sc[GB][R];                  // static scale of (channel, row) and its reciprocal (NaN: outside fastdiv's range)
+    float rd[GB];                      // 1 / U_ii of the block's channels (NaN likewise)
+    int cg[2][GB];                     // static group of the channels of this block and the next
+    uint8_t zp[GB][R];                 // static zero-point
+    int next;                          // next item of the update behind the block
+};
+
+// A whole sub-block of 16 channels for one row per lane, everything in registers.  What counts is the length of the
+// chain from one channel to the next, so it takes the short form of each quotient and checks off the chain that the
+// short form was right:
+//   code   rint(w y) in place of rint(RN(w / s)): the same unless a half-way point lies within 2^-22 |w y| of w y
+//          (w y is off by at most 2^-23 relative, RN(w / s) by 2^-24);
+//   error  fastdiv's quotient, which fastdiv_full's last correction must leave as it is; num must be 0 or at least
+//          2^-80 for that correction to be exact.  Overflows make infinities and NaN, which fail the same tests, and so
+//          do the NaN reciprocals of divisors outside fastdiv's range.
+// Returns false in a lane whose tests failed: nothing of the result is then to be used.  e: the errors; qpk: the codes.
+template <int R>
+__device__ __forceinline__ bool chain16(const float* wrow, const float* ut, const float* rd, const float2* sc, const uint8_t* zp,
+                                        float qmax, float (&e)[SB], uint32_t (&qpk)[SB / 4]) {
+    float w[SB], s[SB], y[SB], z[SB];
+#pragma unroll
+    for (int c = 0; c < SB; c += 4) {
+        const float4 t = *reinterpret_cast<const float4*>(wrow + c);
+        w[c] = t.x; w[c + 1] = t.y; w[c + 2] = t.z; w[c + 3] = t.w;
+    }
+#pragma unroll
+    for (int c = 0; c < SB; ++c) {
+        const float2 t = sc[c * R];
+        s[c] = t.x;
+        y[c] = t.y;
+        z[c] = static_cast<float>(zp[c * R]);
+    }
+#pragma unroll
+    for (int c = 0; c < SB / 4; ++c) qpk[c] = 0u;
+    bool ok = true;
+    // The corner of U (row cc of `ut` holds U[c][cc] for c <= cc) and the reciprocals of its diagonal, four columns at
+    // a time and two channels ahead of their use: all of it at once would not fit the registers.
+    float ub[SB][SB], yd[SB];
+    auto corner = [&](auto part_tag) {
+        constexpr int C0 = decltype(part_tag)::value * 4;
+#pragma unroll
+        for (int cc = 0; cc < SB; ++cc) {
+            if (cc >= C0) {
+                const float4 t = *reinterpret_cast<const float4*>(ut + cc * PITCH + C0);
+                ub[cc][C0] = t.x; ub[cc][C0 + 1] = t.y; ub[cc][C0 + 2] = t.z; ub[cc][C0 + 3] = t.w;
+            }
+        }
+        const float4 t = *reinterpret_cast<const float4*>(rd + C0);
+        yd[C0] = t.x; yd[C0 + 1] = t.y; yd[C0 + 2] = t.z; yd[C0 + 3] = t.w;
+    };
+    corner(std::integral_constant<int, 0>{});
+#pragma unroll
+    for (int c = 0; c < SB; ++c) {
+        if ((c & 3) == 2 && c < 12) {
+            asm volatile("" ::: "memory");                    // keeps these reads from moving up
+            if (c == 2) corner(std::integral_constant<int, 1>{});
+            if (c == 6) corner(std::integral_constant<int, 2>{});
+            if (c == 10) corner(std::integral_constant<int, 3>{});
+        }
+        const float d = ub[c][c];
+        // k = code - zero: clamping before or after the zero point is added is the same on integers
+        const float quo = w[c] * y[c], near = rintf(quo);
+        const float k = __builtin_amdgcn_fmed3f(near, -z[c], qmax - z[c]);
+        const float num = w[c] - s[c] * k;
+        e[c] = fastdiv(num, d, yd[c]);
+#pragma unroll
+        for (int cc = 0; cc < SB; ++cc) {
+            if (cc > c) {
+                const float upd = e[c] * ub[cc][c];
+                w[cc] = w[cc] - upd;
+            }
+        }
+        qpk[c / 4] = __builtin_amdgcn_cvt_pk_u8_f32(k + z[c], c & 3, qpk[c / 4]);
+        // (&, not &&: a branch per test would break the chain up)
+        ok = ok & (fmaf(fabsf(quo), 0x1p-22f, fabsf(quo - near)) <= 0.5f);
+        ok = ok & (fmaf(fmaf(-d, e[c], num), yd[c], e[c]) == e[c]);
+        ok = ok & ((__float_as_uint(num) << 1) - 1u >= (0x17800000u << 1) - 1u);   // zero wraps to the top
+    }
+    return ok;
+}
+
+// The same channel by channel in LDS with plain divisions: the ragged end of a row, and values outside the fast
+// quotient's range.  n <= 16 channels; `par(c)` gives channel c's scale and zero-point, `put(c, code)` takes its code.
+// Lanes that hold the same row do the same reads and writes in the same instruction.
+template <int R, typename Par, typename Put>
+__device__ __forceinline__ void chain_slow(float* wrow, const float* ut, float* es_col, int n, float qmax, Par par, Put put) {
+#pragma unroll 1
+    for (int c = 0; c < n; ++c) {
+        float sc, zp;
+        par(c, sc, zp);
+        const float w = wrow[c];
+        float q = rintf(w / sc) + zp;
+        q = fminf(fmaxf(q, 0.0f), qmax);
+        put(c, static_cast<uint8_t>(q));
+        const float e = (w - sc * (q - zp)) / ut[c * PITCH + c];
+        es_col[c * R] = e;
+#pragma unroll 1
+        for (int cc = c + 1; cc < n; ++cc) {
+            const float upd = e * ut[cc * PITCH + c];
+            wrow[cc] = wrow[cc] - upd;
+        }
+    }
+}
+
+// The value, recomputed from here on: address terms that do not change from block to block would otherwise be kept in
+// registers over the whole sweep, and there are more of them than registers.
+__device__ __forceinline__ int fresh(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ int fresh_uniform(int v) {
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
+// One item of the update behind a block: columns c0 + lane + 64 q of RT of the workgroup's rows (Wrows and es point at
+// the first of them), with the errors of the block at k0.
+// (offsets inside the workgroup's rows fit 32 bits: at most 32 rows of 46340)
+template <int R, int RT, int CPL>
+__device__ __forceinline__ void update_item(float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
+                                            int in_, int64_t k0, int c0) {
+    constexpr int KB = 8;                                      // channels per step: their U entries travel one step ahead
+    const int lane = threadIdx.x & 63, in = fresh_uniform(in_);
+    uint32_t col[CPL];
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) col[q] = static_cast<uint32_t>(min(c0 + lane + 64 * q, in - 1));   // past the end: read, never stored
+    float v[RT][CPL];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const uint32_t at = static_cast<uint32_t>(min(r, n_rows - 1)) * static_cast<uint32_t>(in);
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) v[r][q] = Wrows[at + col[q]];
+    }
+    float u[2][KB][CPL];
+    const float* urow = U + k0 * in;                           // the row to fetch next
+    auto fetch = [&](int b) {
+#pragma unroll
+        for (int kk = 0; kk < KB; ++kk) {
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) u[b][kk][q] = urow[col[q]];
+            urow += in;
+        }
+    };
+    // a channel's errors are read one channel ahead of their use, and no further (registers)
+    float4 ev[2][RT / 4];
+    auto errors = [&](int b, int k) {
+#pragma unroll
+        for (int i = 0; i < RT / 4; ++i) ev[b][i] = *reinterpret_cast<const float4*>(es + k * R + 4 * i);
+    };
+    auto step = [&](int b, int k) {
+#pragma unroll
+        for (int kk = 0; kk < KB; ++kk) {
+            errors((kk + 1) & 1, min(k + kk + 1, GB - 1));
+#pragma unroll
+            for (int i = 0; i < RT / 4; ++i) {
+                const float4 e4 = ev[kk & 1][i];
+                const float e[4] = {e4.x, e4.y, e4.z, e4.w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int q = 0; q < CPL; ++q) {
+                        const float upd = e[j] * u[b][kk][q];
+                        v[4 * i + j][q] = v[4 * i + j][q] - upd;
+                    }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    errors(0, 0);
+    fetch(0);
+#pragma unroll 1
+    for (int k = 0; k < GB; k += 2 * KB) {
+        fetch(1);
+        step(0, k);
+        if (k + 2 * KB < GB) fetch(0);
+        step(1, k + KB);
+    }
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+#pragma unroll
+        for (int q = 0; q < CPL; ++q)
+            if (r < n_rows && c0 + lane + 64 * q < in) Wrows[static_cast<uint32_t>(r) * static_cast<uint32_t>(in) + col[q]] = v[r][q];
+    }
+}
+
+// Columns of the next block (starting at c1, nbw of them) into the strip, with the errors of the block at k0 applied.
+// Wave w takes columns 16 w .. 16 w + 15, lane groups of 16 take R / 4 rows each.
+template <int R>
+__device__ __forceinline__ void update_next(const float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
+                                            int in_, int64_t k0, int c1, int nbw, Lds<R>& lds) {
+    constexpr int RQ = R / 4, KB = 16;
+    const int tid = fresh(threadIdx.x), lane = tid & 63, wave = tid >> 6, in = fresh_uniform(in_);
+    const int c = 16 * wave + (lane & 15), rq = (lane >> 4) * RQ;
+    const uint32_t col = static_cast<uint32_t>(c1 + min(c, nbw - 1));
+    float v[RQ], u[2][KB];
+    const float* urow = U + k0 * in;
+    auto fetch = [&](int b) {
+#pragma unroll
+        for (int kk = 0; kk < KB; ++kk) {
+            u[b][kk] = urow[col];
+            urow += in;
+        }
+    };
+    auto step = [&](int b, int k) {
+#pragma unroll
+        for (int kk = 0; kk < KB; ++kk) {
+#pragma unroll
+            for (int r = 0; r < RQ; ++r) {
+                const float upd = es[(k + kk) * R + rq + r] * u[b][kk];
+                v[r] = v[r] - upd;
+            }
+            if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    fetch(0);
+#pragma unroll
+    for (int r = 0; r < RQ; ++r)
+        v[r] = Wrows[static_cast<uint32_t>(min(rq + r, n_rows - 1)) * static_cast<uint32_t>(in) + col];
+#pragma unroll 1
+    for (int k = 0; k < GB; k += 2 * KB) {
+        fetch(1);
+        step(0, k);
+        if (k + 2 * KB < GB) fetch(0);
+        step(1, k + KB);
+    }
+#pragma unroll
+    for (int r = 0; r < RQ; ++r) lds.w[rq + r][c] = v[r];
+}
+
+template <int R>
+__global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp, const float* __restrict__ U,
+                                                         const int32_t* __restrict__ perm, int64_t out, int64_t in64, int g,
+                                                         float qmax, int mfmt, const float* __restrict__ st_scales,
+                                                         const uint8_t* __restrict__ st_zeros, uint8_t* __restrict__ Qp) {
+    // items of the update: RT rows x 64 CPL columns (RT x CPL accumulators; few rows take more columns, so that an
+    // LDS read of the errors serves as many products)
+    constexpr int RR = pow2_rows<R>(), CL = 64 / RR, CPL = R <= 8 ? 4 : 2, RT = R <= 16 ? R : R / 2;
+    extern __shared__ __align__(16) char smem[];
+    Lds<R>& lds = *reinterpret_cast<Lds<R>*>(smem);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t row0 = int64_t(blockIdx.x) * R;
+    const int n_rows = static_cast<int>(min(out - row0, int64_t(R)));        // > 0
+    const int in = static_cast<int>(in64), n_cg = in / g;
+    float* __restrict__ Wrows = Wp + row0 * in64;
+
+    // static groups of the channels of the block at i1 (into buffer b)
+    auto stage_groups = [&](int i1, int b) {
+        const int tid = fresh(threadIdx.x);
+        if (tid < GB)
+            lds.cg[b][tid] = i1 + tid < in ? static_cast<int>(static_cast<uint32_t>(perm[i1 + tid]) / static_cast<uint32_t>(g)) : 0;
+    };
+    // The block's corner of U (transposed), the reciprocals of its diagonal, and its static parameters (groups in cg[b]):
+    // fetched into registers first, put into LDS when the last block's corner is no longer needed.
+    // 8 lanes along a row of U (one 128-byte line), 8 rows: two-way bank conflicts at most on the turned writes.
+    constexpr int NP = GB * R / (64 * WAVES);                  // parameters per thread
+    float cu[8][4], cd, ps[NP], pz[NP];
+    auto fetch_block = [&](int i1, int nbw, int b) {
+        const int tid = fresh(threadIdx.x), in = fresh_uniform(static_cast<int>(in64));
+        const int c4 = (tid & 7) * 4, kr = tid >> 3;           // 64 rows at a time
+        const float* corner = U + i1 * in64 + i1;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k = kr + 64 * h, c = c4 + 32 * cb + j;
+                    cu[4 * h + cb][j] = (k < nbw && c < nbw) ? corner[static_cast<uint32_t>(k) * static_cast<uint32_t>(in) + c] : 0.0f;
+                }
+        cd = tid < nbw ? corner[static_cast<uint32_t>(tid) * (static_cast<uint32_t>(in) + 1u)] : 1.0f;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const int idx = tid + 64 * WAVES * j, c = idx / R, r = idx % R;
+            const int64_t at = (row0 + min(r, n_rows - 1)) * n_cg + lds.cg[b][c];
+            if (mfmt) {
+                ps[j] = __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t*>(st_scales)[at]));
+                pz[j] = 0.0f;
+            } else {
+                ps[j] = st_scales[at];
+                pz[j] = static_cast<float>(st_zeros[at]);
+            }
+        }
+    };
+    auto store_block = [&](int i1, int b) {
+        const int tid = fresh(threadIdx.x), c4 = (tid & 7) * 4, kr = tid >> 3;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) lds.ut[c4 + 32 * cb + j][kr + 64 * h] = cu[4 * h + cb][j];
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const int idx = tid + 64 * WAVES * j, c = idx / R, r = idx % R;
+            float sc = ps[j], zp = pz[j];
+            if (mfmt) {                                        // ps holds the group word's bits
+                const uint32_t wd = __float_as_uint(sc);
+                sc = word_scale(wd, mfmt);
+                zp = word_zero(wd, mfmt);
+            }
+            lds.sc[c][r] = make_float2(sc, fastdiv_ok(sc) ? 1.0f / sc : __builtin_nanf(""));
+            lds.zp[c][r] = static_cast<uint8_t>(zp);
+        }
+        if (tid < GB) lds.rd[tid] = fastdiv_ok(cd) ? 1.0f / cd : __builtin_nanf("");
+        if (tid == 0) lds.next = 0;
+        stage_groups(i1 + GB, b ^ 1);
+    };
+
+    // first block: its columns straight into the strip
+    stage_groups(0, 0);
+    __syncthreads();
+    {
+        const int nbw = min(in, GB);
+        for (int idx = tid; idx < R * GB; idx += 64 * WAVES) {
+            const int r = idx / GB, c = idx % GB;
+            lds.w[r][c] = (c < nbw && r < n_rows) ? Wrows[static_cast<uint32_t>(r) * static_cast<uint32_t>(in) + c] : 0.0f;
+        }
+        fetch_block(0, nbw, 0);
+        store_block(0, 0);
+    }
+    __syncthreads();
+
+    const int crow = lane & (RR - 1), ccol = lane / RR;        // the chain's lane: row (replicated CL times), column lane
+    const bool row_in = crow < R, row_ok = crow < n_rows;
+    for (int i1 = 0, blk = 0; i1 < in; i1 += GB, ++blk) {
+        const int nbw = min(in - i1, GB), behind = i1 + nbw;
+        float* es = &lds.e[blk & 1][0][0];
+        const float* es_last = &lds.e[(blk & 1) ^ 1][0][0];
+        if (wave == 0) {
+            // the chain the workgroup waits for: ahead of the updates that share its SIMD
+            __builtin_amdgcn_s_setprio(3);
+            float* wrow = &lds.w[row_in ? crow : 0][0];
+            for (int s0 = 0; s0 < nbw; s0 += SB) {
+                const int sbw = min(nbw - s0, SB);
+                float e[SB];
+                uint32_t qpk[SB / 4];
+                const float* ut = &lds.ut[s0][s0];
+                const float2* sc = &lds.sc[s0][row_in ? crow : 0];
+                const uint8_t* zp = &lds.zp[s0][row_in ? crow : 0];
+                uint8_t* q_out = Qp + (row0 + crow) * in64 + i1 + s0;
+                bool fine = sbw == SB;
+                if (fine) fine = chain16<R>(wrow + s0, ut, &lds.rd[s0], sc, zp, qmax, e, qpk);   // uniform
+                if (!__any(row_ok && !fine)) {
+                    // errors for the later updates (0 in rows past the end), codes in visiting order
+#pragma unroll
+                    for (int k = 0; k < SB; ++k) e[k] = row_ok ? e[k] : 0.0f;
+                    if (row_in && ccol == 0) {
+#pragma unroll
+                        for (int k = 0; k < SB; ++k) es[(s0 + k) * R + crow] = e[k];
+                    }
+                    if (row_ok && ccol == 0) {
+                        if ((reinterpret_cast<uintptr_t>(q_out) & 15u) == 0) {
+                            *reinterpret_cast<uint4*>(q_out) = make_uint4(qpk[0], qpk[1], qpk[2], qpk[3]);
+                        } else {
+#pragma unroll
+                            for (int c = 0; c < SB; ++c) q_out[c] = static_cast<uint8_t>(qpk[c / 4] >> (8 * (c % 4)));
+                        }
+                    }
+                } else if (row_in) {
+                    chain_slow<R>(wrow + s0, ut, es + s0 * R + crow, sbw, qmax,
+                                  [&](int c, float& a, float& b) { a = sc[c * R].x; b = static_cast<float>(zp[c * R]); },
+                                  [&](int c, uint8_t q) { if (row_ok && ccol == 0) q_out[c] = q; });
+#pragma unroll
+                    for (int k = 0; k < SB; ++k) e[k] = k < sbw && row_ok ? es[(s0 + k) * R + crow] : 0.0f;
+                    if (!row_ok)
+                        for (int k = 0; k < sbw; ++k) es[(s0 + k) * R + crow] = 0.0f;
+                }
+                // The block's columns behind the sub-block (only a whole sub-block has any), NC at a time: a column's
+                // sixteen differences wait for each other.
+                if (row_in) {
+                    constexpr int NC = 2;
+                    for (int c = s0 + SB + ccol; c < nbw; c += NC * CL) {
+                        float v[NC], u[NC][SB];
+#pragma unroll
+                        for (int t = 0; t < NC; ++t) {
+                            const int ct = min(c + t * CL, GB - 1);      // past the block: read, not stored
+                            v[t] = wrow[ct];
+#pragma unroll
+                            for (int k = 0; k < SB; k += 4) {
+                                const float4 q = *reinterpret_cast<const float4*>(&lds.ut[ct][s0 + k]);
+                                u[t][k] = q.x; u[t][k + 1] = q.y; u[t][k + 2] = q.z; u[t][k + 3] = q.w;
+                            }
+                        }
+#pragma unroll
+                        for (int k = 0; k < SB; ++k)
+#pragma unroll
+                            for (int t = 0; t < NC; ++t) {
+                                const float upd = e[k] * u[t][k];
+                                v[t] = v[t] - upd;
+                            }
+#pragma unroll
+                        for (int t = 0; t < NC; ++t)
+                            if (c + t * CL < nbw) wrow[c + t * CL] = v[t];
+                    }
+                }
+                // the strip is this wave's alone while the chain runs, and LDS serves a wave's accesses in order
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+            __builtin_amdgcn_s_setprio(0);
+        }
+        if (wave == WAVES - 1 && behind < in) {
+            // What the step after this block reads first, into the L2: the block's rows of U at the next block's columns,
+            // and the next block's corner (128 lines of 512 bytes each).
+            const int next_w = min(in - behind, GB);
+            for (int r = lane; r < 4 * (GB + next_w); r += 64) {
+                const int line = r >> 2, c = min((r & 3) * 32, next_w - 1);
+                const float t = U[(i1 + line) * in64 + behind + c];
+                asm volatile("" ::"v"(t));
+            }
+        }
+        // errors of the last block onto the columns behind this one, item by item
+        if (blk > 0 && behind < in) {
+            const int n_items = (in - behind + 64 * CPL - 1) / (64 * CPL) * (R / RT);
+            for (;;) {
+                int item = 0;
+                if (lane == 0) item = atomicAdd(&lds.next, 1);
+                item = __builtin_amdgcn_readfirstlane(item);
+                if (item >= n_items) break;
+                const int rt = R == RT ? 0 : (item & 1) * RT, cc = R == RT ? item : item >> 1;
+                if (rt < n_rows)
+                    update_item<R, RT, CPL>(Wrows + rt * in64, U, es_last + rt, n_rows - rt, in, int64_t(i1) - GB,
+                                            behind + cc * (64 * CPL));
+            }
+        }
+        if (behind >= in) break;                               // uniform: the last block
+        const int next_w = min(in - behind, GB), next_b = (blk + 1) & 1;
+        fetch_block(behind, next_w, next_b);
+        __syncthreads();
+        update_next<R>(Wrows, U, es, n_rows, in, i1, behind, next_w, lds);
+        store_block(behind, next_b);
+        __syncthreads();
+    }
+}
+
+// Rows per workgroup for [out, in]: the R with the least rounds x time of one workgroup.  A block of one workgroup
+// takes the longer of the chain and the updates (R rows x remaining columns x 128 channels x 2 operations at 64 per
+// cycle), then the update of the next block's columns.  The constants (us) are measured with the clock around each part,
+// at R = 4, 16 and 32 on a 4096-wide input: chain 18, 29, 45, step between two blocks 4, 7, 10.
+inline int rows_per_group(int64_t out, int64_t in) {
+    const int sizes[] = {4, 8, 12, 16, 24, 32};
+    int best = 16;
+    double best_us = 0.0;
+    for (int r : sizes) {
+        const double rounds = double((((out + r - 1) / r) + 255) / 256);
+        double us = 0.0;
+        for (int64_t i1 = 0; i1 < in; i1 += GB) {
+            const double upd = double(in - i1) * r * GB * 2.0 / 64.0 / 2.2e3;
+            us += std::max(14.0 + 0.95 * r, upd) + 3.2 + 0.23 * r;
+        }
+        us *= rounds;
+        if (best_us == 0.0 || us < best_us) {
+            best_us = us;
+            best = r;
+        }
+    }
+    return best;
+}
+
+template <int R>
+hipError_t allow_lds_of() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(gq_rows<R>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               static_cast<int>(sizeof(Lds<R>)));
+}
+inline hipError_t allow_lds() {
+    for (const hipError_t e : {allow_lds_of<4>(), allow_lds_of<8>(), allow_lds_of<12>(), allow_lds_of<16>(), allow_lds_of<24>(),
+                               allow_lds_of<32>()})
+        if (e != hipSuccess) return e;
+    return hipSuccess;
+}
+
+}  // namespace rows
+
+}  // namespace

@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <cmath>
 #include <thread>
 #include <vector>
 #include <atomic>
@@ -72,6 +73,34 @@ int main(int argc, char** argv) {
         const float ref = p[0] / p[1], got = fastdiv(p[0], p[1], 1.0f / p[1]);
         ++done;
         if (!(ref == got)) { std::printf("MISMATCH tie w=%a s=%a\n", p[0], p[1]); ++bad; }
+    }
+    // fastdiv_full: numerators of any significand.  Random operands, and numerators next to the midpoints between two
+    // quotients (a = the double product of a divisor and a half-way point, rounded up and down), which is where a
+    // quotient that is not correctly rounded would show.
+    {
+        uint64_t st = 88172645463325252ull;
+        auto rnd = [&]() { st ^= st << 13; st ^= st >> 7; st ^= st << 17; return st; };
+        const uint64_t n = 1ull << (lg >= 23 ? 30 : lg + 10);
+        for (uint64_t i = 0; i < n; ++i) {
+            const uint64_t r = rnd();
+            const float b = from_bits(((127 - 40 + static_cast<uint32_t>((r >> 48) % 80)) << 23) | (r & 0x7fffffu));
+            const float qv = from_bits(((127 - 30 + static_cast<uint32_t>((r >> 56) % 60)) << 23) | ((r >> 23) & 0x7fffffu));
+            float a;
+            if (i & 1) a = qv;
+            else {
+                const double half = static_cast<double>(qv) * (1.0 + 0x1p-24);
+                a = static_cast<float>(half * static_cast<double>(b));
+                if (i & 2) a = std::nextafterf(a, 0.0f);
+            }
+            if (!(std::fabs(a) >= 0x1p-80f && std::fabs(a) <= 0x1p60f)) continue;
+            if (i & 4) a = -a;
+            const float ref = a / b, got = fastdiv_full(a, b, 1.0f / b);
+            ++done;
+            if (!(ref == got)) {
+                if (bad < 5) std::printf("MISMATCH full a=%a b=%a ref=%a got=%a\n", a, b, ref, got);
+                ++bad;
+            }
+        }
     }
     std::printf("checked %llu quotients, %llu mismatches\n", (unsigned long long)done.load(), (unsigned long long)bad.load());
     return bad.load() ? 1 : 0;

@@ -329,3 +329,45 @@ def test_sweep_in_the_storage_format_random_shapes(ctx, out_f, in_f, dim, bits, 
     assert np.array_equal(meta.cpu().numpy().view(np.uint16), ref["meta"])
     assert np.array_equal(codes.cpu().numpy(), ref["codes"])
     assert np.array_equal(dW.cpu().numpy(), ref["dW"])
+
+
+@pytest.mark.parametrize("out_f,in_f,bits,group", [
+    (1000, 272, 3, 16),          # 4 rows per workgroup, whole blocks, in a multiple of 16 only
+    (2041, 200, 4, 40),          # 8 rows, the last workgroup short of one, ragged last sub-block
+    (3000, 129, 2, 43),          # 12 rows, a last block of one channel, odd row pitch
+    (4090, 328, 3, 0),           # 16 rows
+    (6100, 260, 4, 65),          # 24 rows
+    (8100, 136, 3, 136),         # 32 rows
+    (9000, 264, 3, 24),          # more workgroups than compute units
+])
+def test_per_oc_sweep_rows_per_workgroup(ctx, out_f, in_f, bits, group):
+    """The per-OC sweep picks its rows per workgroup by the layer's size; each choice, against the oracle bit for bit."""
+    W, X = layer(out_f, in_f, 600, seed=out_f + in_f, dead=(3,))
+    H32 = oracle.hessian(X).astype(np.float32)
+    Hp, perm, dead = G.prepare(H32, 0.01, True)
+    U32 = G.factor(Hp).astype(np.float32)
+    ref = G.sweep(W, U32, perm, dead, OC, bits, group)
+    got = gpu_sweep(ctx, W, OC, bits, group, dev(U32), dev(perm.astype(np.int32)), dev(dead.astype(np.uint8)))
+    assert np.array_equal(got["codes"], ref["codes"])
+    assert np.array_equal(got["dW"], ref["dW"])
+
+
+@pytest.mark.parametrize("dim,group", [(OC, 64), (IC, 64), (IC, 128)])
+@pytest.mark.parametrize("diag,off", [(1e-14, 1e-14), (3e13, 1e12), (1.0, 2.0 ** -90), (2.0 ** -39, 2.0 ** -40), (2.0 ** 39, 1.0)])
+def test_sweep_outside_the_fast_quotients_range(ctx, dim, group, diag, off):
+    """Factors whose diagonal or whose updates leave the range in which the sweep's corrected quotients are exact
+    (and, the last two, that just stay inside): the plain division takes over, the bits stay the oracle's."""
+    out_f, in_f, bits = 128, 192, 3
+    rng = np.random.default_rng(7)
+    W = (rng.standard_normal((out_f, in_f)) * 0.02).astype(np.float16)
+    W[:, 32:64] = 0                                       # columns that only ever hold updates
+    U32 = np.triu(rng.standard_normal((in_f, in_f)) * off, 1).astype(np.float32)
+    np.fill_diagonal(U32, (np.linspace(1.0, 2.0, in_f) * diag).astype(np.float32))
+    perm, dead = np.arange(in_f), np.zeros(in_f, bool)
+    with np.errstate(all="ignore"):
+        ref = G.sweep(W, U32, perm, dead, dim, bits, group)
+    assert np.isfinite(ref["E"]).all()
+    got = gpu_sweep(ctx, W, dim, bits, group, dev(U32), dev(perm.astype(np.int32)), dev(dead.astype(np.uint8)))
+    assert np.array_equal(got["codes"], ref["codes"])
+    assert np.array_equal(got["scales"].view(np.uint32), ref["scales"].view(np.uint32))
+    assert np.array_equal(got["dW"], ref["dW"])

@@ -22,6 +22,7 @@
 // looked up by the channel's original index); per-IC recomputes each (row group, channel)'s
 // parameters from the channel's current values when it is visited.
 #include "common.h"
+#include "gptq_groups.h"
 #include "gptq_rows.h"
 #include "scale_format.h"
 
@@ -513,54 +514,6 @@ __global__ void gq_flip(const double* __restrict__ M, int64_t n, float* __restri
 }
 
 // ------------------------------------------------------------------ sweep
-struct QP {
-    float scale, zero;
-};
-// the quantizer's parameters from a group's min and max (clip = 1): same formulas as adadim_quantize
-// (mfmt != 0: the scale rounded into the 16-bit group word first, as adadim_quantize_meta16 does)
-__device__ __forceinline__ QP params_of(float mn, float mx, float qmax, int mfmt) {
-    mx = fmaxf(mx, 0.0f);
-    mn = fminf(mn, 0.0f);
-    const float range = mx - mn;
-    float scale = range / qmax;
-    if (range == 0.0f) scale = 1.0f;
-    if (mfmt) scale = round_scale(scale, mfmt);
-    float z = rintf((-mn) / scale);
-    z = fminf(fmaxf(z, 0.0f), qmax);
-    return {scale, z};
-}
-
-// Minima of two values over the wavefront, the same in every lane (min is exact, any order gives the
-// same bits).  Butterflies inside the rows of 16 lanes, then row 0 into 1 and 2 into 3, then lane 31
-// into the upper half, all as v_min_f32 with a DPP operand; lane 63 holds the result.  The two chains
-// are interleaved and padded so that two wait states separate a write from the DPP read of it.
-// Needs every lane active.
-__device__ __forceinline__ void wave_min2(float& a, float& b) {
-    asm volatile(
-        "s_nop 1\n\t"
-        "v_min_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_min_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_min_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_min_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_min_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_min_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_min_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_min_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_min_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
-        "v_min_f32_dpp %1, %1, %1 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
-        "s_nop 0\n\t"
-        "v_min_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
-        "v_min_f32_dpp %1, %1, %1 row_bcast:31 row_mask:0xc bank_mask:0xf\n\t"
-        "s_nop 1"
-        : "+v"(a), "+v"(b));
-    a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, a), 63));
-    b = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, b), 63));
-}
-
 // Wp[r][i] = W[r][perm[i]] as fp32, zero for dead channels.  One row per workgroup: the row is read once, in
 // order, into LDS and permuted from there (a thread per element reading W[r][perm[i]] from memory fetched a
 // separate 64-byte piece for every two bytes it used).  Dynamic LDS: in halves.
@@ -576,224 +529,6 @@ __global__ __launch_bounds__(256) void gq_gather_w(const __half* __restrict__ W,
     for (int64_t i = threadIdx.x; i < in; i += 256) {
         const int32_t j = perm[i];
         Wp[r * in + i] = dead[j] ? 0.0f : __half2float(row[j]);
-    }
-}
-
-// Per-IC: one 128-channel block [i1, i1 + nbw) of one row group, by a workgroup of four wavefronts.  Lane l
-// of the first wave holds the rows l + 64p of the group (RPL = g/64 of them), so that the group's minimum and
-// maximum are a lane-local step plus one wave reduction.  The rows live in an LDS strip; the channels are walked in sub-blocks of
-// 16 that the first wave holds in registers: the sub-block's own updates stay in registers, then
-// its 16 errors are posted in LDS.  All four waves apply them to the next sub-block's 16 columns at
-// once, so that the chain can go on; the columns behind those receive them from the other three
-// waves while the first one walks the next sub-block (two error buffers, taken in turn).  One LDS
-// read and one write per element for 16 updates, always in channel order (which wave applies them
-// does not change a bit).  The block of U is staged in LDS and read with wave-uniform addresses.
-// Codes go out in visiting order (16 bytes per row and sub-block).
-template <int RPL>
-__global__ __launch_bounds__(256) void gq_sweep(float* __restrict__ Wp, const float* __restrict__ U,
-                                               const int32_t* __restrict__ perm, int64_t out, int64_t in, int64_t i1,
-                                               int nbw, int g, float qmax, int mfmt, float* __restrict__ scales_out,
-                                               uint8_t* __restrict__ zeros_out, uint8_t* __restrict__ Qp,
-                                               float* __restrict__ Ep) {
-    constexpr int SB = 16, PITCH = GB + 1;
-    extern __shared__ __align__(16) char smem[];
-    float* Us = reinterpret_cast<float*>(smem);                         // [GB][GB]: rows / columns i1.. of U
-    float* Ws = Us + GB * GB;                                           // [64 * RPL][PITCH]
-    float* Es0 = Ws + 64 * RPL * PITCH;                                 // [2][64 * RPL][SB + 1]: the errors of this sub-block and the last
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    // The block of U and the strip of W: every thread's loads are issued before the first of them is stored, so the
-    // block pays one trip to memory each, not one per loop iteration (16 and 32 of them: a fifth of the kernel).
-    {
-        constexpr int NU = GB * (GB / 4) / 256;                         // 16-byte pieces of the block of U per thread
-        float4 uv[NU];
-#pragma unroll
-        for (int q = 0; q < NU; ++q) {
-            const int e4 = threadIdx.x + 256 * q, k = e4 / (GB / 4), c4 = (e4 % (GB / 4)) * 4;
-            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (k < nbw) {                                              // in % 4 == 0 is not required: guarded
-                const float* src = U + (i1 + k) * in + i1 + c4;
-                if (c4 + 3 < nbw && ((reinterpret_cast<uintptr_t>(src) & 15u) == 0)) {
-                    v = *reinterpret_cast<const float4*>(src);
-                } else {
-                    if (c4 + 0 < nbw) v.x = src[0];
-                    if (c4 + 1 < nbw) v.y = src[1];
-                    if (c4 + 2 < nbw) v.z = src[2];
-                    if (c4 + 3 < nbw) v.w = src[3];
-                }
-            }
-            uv[q] = v;
-        }
-#pragma unroll
-        for (int q = 0; q < NU; ++q) {
-            const int e4 = threadIdx.x + 256 * q, k = e4 / (GB / 4), c4 = (e4 % (GB / 4)) * 4;
-            if (k < nbw) *reinterpret_cast<float4*>(Us + k * GB + c4) = uv[q];
-        }
-    }
-    int64_t row[RPL];
-    bool ok[RPL];
-#pragma unroll
-    for (int p = 0; p < RPL; ++p) {
-        row[p] = int64_t(blockIdx.x) * g + lane + 64 * p;
-        ok[p] = row[p] < out;
-    }
-    {
-        // strip element (r, c): thread t takes columns t % 128 of rows t / 128 + 2 j, consecutive lanes consecutive
-        // columns
-        constexpr int NR = 64 * RPL / 2;
-        const int c = threadIdx.x & (GB - 1), r_first = threadIdx.x >> 7;
-        const int64_t strip_row0 = int64_t(blockIdx.x) * g;
-        float wv[NR];
-#pragma unroll
-        for (int j = 0; j < NR; ++j) {
-            const int r = r_first + 2 * j;                              // strip row; rows l + 64 p sit at (l * RPL + p)
-            const int64_t grow = strip_row0 + r;
-            wv[j] = (c < nbw && grow < out) ? Wp[grow * in + i1 + c] : 0.0f;
-        }
-#pragma unroll
-        for (int j = 0; j < NR; ++j) {
-            const int r = r_first + 2 * j;
-            const int slot = (r & 63) * RPL + (r >> 6);        // row l + 64 p of a group -> strip slot l * RPL + p
-            if (c < nbw) Ws[slot * PITCH + c] = wv[j];
-        }
-    }
-    __syncthreads();
-    // errors of a sub-block applied to columns [c_lo, c_hi), every `step`-th from c_lo + first; channel order kept
-    // per element (which wave applies them does not change a bit)
-    auto apply = [&](const float* Esrc, int k0, int kw, int c_lo, int c_hi, int first, int step) {
-        float e[RPL][SB];
-#pragma unroll
-        for (int p = 0; p < RPL; ++p)
-#pragma unroll
-            for (int k = 0; k < SB; ++k) e[p][k] = Esrc[(lane * RPL + p) * (SB + 1) + k];
-        for (int cc = c_lo + first; cc < c_hi; cc += step) {
-            float u[SB];
-#pragma unroll
-            for (int k = 0; k < SB; ++k) u[k] = k < kw ? Us[(k0 + k) * GB + cc] : 0.0f;
-#pragma unroll
-            for (int p = 0; p < RPL; ++p) {
-                if (!ok[p]) continue;
-                float v = Ws[(lane * RPL + p) * PITCH + cc];
-#pragma unroll
-                for (int k = 0; k < SB; ++k) {
-                    const float upd = e[p][k] * u[k];
-                    v = v - upd;
-                }
-                Ws[(lane * RPL + p) * PITCH + cc] = v;
-            }
-        }
-    };
-    for (int s0 = 0; s0 < nbw; s0 += SB) {
-        const int sbw = nbw - s0 < SB ? nbw - s0 : SB;
-        float* Es = Es0 + ((s0 / SB) & 1) * (64 * RPL * (SB + 1));
-        const float* Es_last = Es0 + (((s0 / SB) & 1) ^ 1) * (64 * RPL * (SB + 1));
-        // the sequential part, one wave; FULL: all 16 channels exist (every sub-block but a ragged last
-        // one), which takes the bounds tests and their branches out of the chain
-        auto sub_block = [&](auto full_tag) {
-            constexpr bool FULL = decltype(full_tag)::value;
-            float w[RPL][SB], e[RPL][SB];
-            uint32_t qpk[RPL][SB / 4];
-#pragma unroll
-            for (int p = 0; p < RPL; ++p) {
-#pragma unroll
-                for (int c = 0; c < SB; ++c) w[p][c] = (ok[p] && (FULL || c < sbw)) ? Ws[(lane * RPL + p) * PITCH + s0 + c] : 0.0f;
-#pragma unroll
-                for (int c = 0; c < SB / 4; ++c) qpk[p][c] = 0u;
-            }
-            float my_scale = 1.0f, my_zero = 0.0f;                          // lane c: channel c's parameters
-            // The sub-block's 16 x 16 corner of U, all of it in registers before the chain starts (16-byte reads at
-            // wave-uniform addresses, every index below a constant): read row by row where it is used, each
-            // channel's chain began by waiting for its row.  The fence keeps the reads up here.
-            float ub[SB][SB];
-#pragma unroll
-            for (int c = 0; c < SB; ++c)
-#pragma unroll
-                for (int q4 = 0; q4 < SB / 4; ++q4) {
-                    const float4 t = *reinterpret_cast<const float4*>(Us + (s0 + c) * GB + s0 + 4 * q4);
-                    ub[c][4 * q4 + 0] = t.x;
-                    ub[c][4 * q4 + 1] = t.y;
-                    ub[c][4 * q4 + 2] = t.z;
-                    ub[c][4 * q4 + 3] = t.w;
-                }
-            asm volatile("" ::: "memory");
-#pragma unroll
-            for (int c = 0; c < SB; ++c) {
-                if (FULL || c < sbw) {                                      // uniform
-                    const float (&u)[SB] = ub[c];
-                    const float d = u[c];
-                    float mn = w[0][c], nmx = -w[0][c];
-#pragma unroll
-                    for (int p = 1; p < RPL; ++p) {
-                        mn = fminf(mn, w[p][c]);
-                        nmx = fminf(nmx, -w[p][c]);
-                    }
-                    wave_min2(mn, nmx);
-                    const QP pr = params_of(mn, -nmx, qmax, mfmt);
-                    if (lane == c) {                                        // two selects; stored after the chain
-                        my_scale = pr.scale;
-                        my_zero = pr.zero;
-                    }
-#pragma unroll
-                    for (int p = 0; p < RPL; ++p) {
-                        float q = rintf(w[p][c] / pr.scale) + pr.zero;
-                        q = fminf(fmaxf(q, 0.0f), qmax);
-                        const float wq = pr.scale * (q - pr.zero);
-                        qpk[p][c / 4] |= static_cast<uint32_t>(q) << (8 * (c % 4));
-                        e[p][c] = (w[p][c] - wq) / d;
-                        // (constant bounds with a test, not "cc = c + 1": a trip count that depends on c is
-                        // unrolled too late, after the loop has been vectorized with a run-time-indexed remainder)
-#pragma unroll
-                        for (int cc = 0; cc < SB; ++cc) {
-                            if (cc > c && (FULL || cc < sbw)) {
-                                const float upd = e[p][c] * u[cc];
-                                w[p][cc] = w[p][cc] - upd;
-                            }
-                        }
-                    }
-                } else {
-#pragma unroll
-                    for (int p = 0; p < RPL; ++p) e[p][c] = 0.0f;
-                }
-            }
-            if (lane < sbw)
-                store_params(scales_out, zeros_out, int64_t(blockIdx.x) * in + perm[i1 + s0 + lane], my_scale, my_zero, mfmt);
-            // the sub-block's codes and errors, in visiting order
-#pragma unroll
-            for (int p = 0; p < RPL; ++p) {
-                if (!ok[p]) continue;
-                const int64_t at = row[p] * in + i1 + s0;
-                if (FULL && ((at & 15) == 0)) {
-                    *reinterpret_cast<uint4*>(Qp + at) = make_uint4(qpk[p][0], qpk[p][1], qpk[p][2], qpk[p][3]);
-                } else {
-                    for (int c = 0; c < sbw; ++c) Qp[at + c] = static_cast<uint8_t>(qpk[p][c / 4] >> (8 * (c % 4)));
-                }
-                if (FULL && ((at & 3) == 0)) {
-#pragma unroll
-                    for (int c = 0; c < SB; c += 4)
-                        *reinterpret_cast<float4*>(Ep + at + c) = make_float4(e[p][c], e[p][c + 1], e[p][c + 2], e[p][c + 3]);
-                } else {
-                    for (int c = 0; c < sbw; ++c) Ep[at + c] = e[p][c];
-                }
-            }
-#pragma unroll
-            for (int p = 0; p < RPL; ++p)
-#pragma unroll
-                for (int k = 0; k < SB; ++k) Es[(lane * RPL + p) * (SB + 1) + k] = e[p][k];
-        };
-        if (wave == 0) {
-            // the chain every later launch waits for: ahead of the bulk update that shares the SIMD with it
-            __builtin_amdgcn_s_setprio(3);
-            if (sbw == SB) sub_block(std::true_type{});
-            else sub_block(std::false_type{});
-            __builtin_amdgcn_s_setprio(0);
-        } else if (s0 > 0 && s0 + SB < nbw) {
-            // meanwhile the other three waves bring the columns behind this sub-block up to date with the
-            // errors of the sub-block before it (this sub-block's own columns got them ahead of the chain)
-            apply(Es_last, s0 - SB, SB, s0 + SB, nbw, wave - 1, 3);
-        }
-        __syncthreads();
-        // the new errors go to the next sub-block's columns at once, all four waves, so that the chain can go on
-        if (s0 + SB < nbw) apply(Es, s0, sbw, s0 + SB, s0 + 2 * SB < nbw ? s0 + 2 * SB : nbw, wave, 4);
-        __syncthreads();
     }
 }
 
@@ -869,6 +604,63 @@ __global__ __launch_bounds__(256) void gq_trailing(float* __restrict__ Wp, const
 #pragma unroll
     for (int rr = 0; rr < 8; ++rr)
         if (r0 + rr < out) Wp[(r0 + rr) * in + jj] = v[rr];
+}
+
+// The next block's columns [col0, col0 + w), w <= 128: the same update, for the launch that two sweeps wait for.  A
+// thread takes RT rows of one column and has the column's next sixteen entries of U on their way while it works on
+// sixteen: the launch is short of waves, so what counts is that few trips to memory follow each other.
+template <int RT>
+__global__ __launch_bounds__(256) void gq_next(float* __restrict__ Wp, const float* __restrict__ U, const float* __restrict__ Ep,
+                                               int64_t out, int64_t in, int64_t i1, int64_t col0, int w) {
+    constexpr int KB = 16;
+    __shared__ __align__(16) float Es[GB][2 * RT];            // [channel][row]
+    __builtin_amdgcn_s_setprio(2);                            // a link of the chain, as the sweep
+    const int c = threadIdx.x & (GB - 1), rq = (threadIdx.x >> 7) * RT;
+    const int64_t r0 = int64_t(blockIdx.x) * (2 * RT), jj = col0 + min(c, w - 1);
+    float u[2][KB], t[RT], v[RT];
+    const float* urow = U + i1 * in;                          // the row to fetch next
+    auto fetch = [&](int b) {
+#pragma unroll
+        for (int kk = 0; kk < KB; ++kk) {
+            u[b][kk] = urow[static_cast<uint32_t>(jj)];
+            urow += in;
+        }
+        asm volatile("" ::: "memory");                        // issued here, and the reads of Es below not above
+    };
+    auto step = [&](int b, int k) {
+#pragma unroll
+        for (int kk = 0; kk < KB; ++kk) {
+#pragma unroll
+            for (int i = 0; i < RT; i += 4) {
+                const float4 e = *reinterpret_cast<const float4*>(&Es[k + kk][rq + i]);
+                const float e4[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float upd = e4[r] * u[b][kk];
+                    v[i + r] = v[i + r] - upd;
+                }
+            }
+            if (kk % 4 == 3) asm volatile("" ::: "memory");   // (or all of Es's entries would be read first)
+        }
+    };
+    fetch(0);
+#pragma unroll
+    for (int q = 0; q < RT; ++q) t[q] = Ep[min(r0 + rq + q, out - 1) * in + i1 + c];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) v[r] = Wp[min(r0 + rq + r, out - 1) * in + jj];
+#pragma unroll
+    for (int q = 0; q < RT; ++q) Es[c][rq + q] = t[q];
+    __syncthreads();
+#pragma unroll 1
+    for (int k = 0; k < GB; k += 2 * KB) {
+        fetch(1);
+        step(0, k);
+        if (k + 2 * KB < GB) fetch(0);
+        step(1, k + KB);
+    }
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+        if (c < w && r0 + rq + r < out) Wp[(r0 + rq + r) * in + jj] = v[r];
 }
 
 }  // namespace
@@ -976,16 +768,10 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
     int32_t* visited = static_cast<int32_t*>(adadim_workspace(ctx, WS_GPTQ_V, size_t(in) * sizeof(int32_t)));
     if (!Wp || !Ep || !Qp || !visited) return ADADIM_EHIP;
     const float qmax = static_cast<float>((1 << bits) - 1);
-    const int rpl = g / 64;                                            // per-IC: rows per lane
-    const unsigned blocks = static_cast<unsigned>(ic ? out / g : 0);
-    const size_t smem = (size_t(GB) * GB + size_t(64) * rpl * (GB + 1) + size_t(2) * 64 * rpl * 17) * sizeof(float);
     static PerDeviceOnce once;
     ADADIM_HIP_TRY(ctx, once.run([] {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gq_sweep<2>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(gq_sweep<1>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
+        hipError_t e = groups::allow_lds_of<1>();
+        if (e == hipSuccess) e = groups::allow_lds_of<2>();
         if (e == hipSuccess) e = rows::allow_lds();
         // a row of W in LDS: up to 46340 halves
         if (e == hipSuccess)
@@ -1030,10 +816,11 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         const int nbw = static_cast<int>(in - i1 < GB ? in - i1 : GB);
         {
             ProfScope prof(ctx, "gptq_sweep");
-#define GQ_GO(RPL_)                                                                                                  \
-    hipLaunchKernelGGL(gq_sweep<RPL_>, dim3(blocks), dim3(256), smem, ctx->stream, Wp, U, perm, out, in, i1, nbw, g, qmax, \
-                       mfmt, scales_out, zeros_out, Qp, Ep)
-            if (rpl == 1) GQ_GO(1);
+#define GQ_GO(RPL)                                                                                                       \
+    hipLaunchKernelGGL(groups::gq_group<RPL>, dim3(static_cast<unsigned>(out / g)), dim3(64 * groups::WAVES),            \
+                       sizeof(groups::Lds<RPL>), ctx->stream, Wp, U, perm, in, i1, nbw, qmax, 1.0f / qmax, mfmt,         \
+                       scales_out, zeros_out, Qp, Ep)
+            if (g == 64) GQ_GO(1);
             else GQ_GO(2);
 #undef GQ_GO
         }
@@ -1048,8 +835,8 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
             continue;
         }
         if (side_busy) ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->stream, ctx->side_ev[1], 0));
-        hipLaunchKernelGGL(gq_trailing, dim3(static_cast<unsigned>((next_end - behind + 255) / 256), rows8), dim3(256), 0,
-                           ctx->stream, Wp, U, Ep, out, in, i1, nbw, behind, next_end);
+        hipLaunchKernelGGL(gq_next<4>, dim3(static_cast<unsigned>((out + 7) / 8)), dim3(256), 0, ctx->stream, Wp, U, Ep, out, in, i1,
+                           behind, static_cast<int>(next_end - behind));
         // the side stream starts behind this short launch, not beside it: the next sweep waits for it
         ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[0], ctx->stream));
         if (next_end < in) {

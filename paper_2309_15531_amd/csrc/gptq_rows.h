@@ -22,6 +22,7 @@
 
 #include "common.h"
 #include "fastdiv.h"
+#include "gptq_chain.h"
 #include "scale_format.h"
 
 #include <type_traits>
@@ -30,9 +31,8 @@ namespace {
 
 namespace rows {
 
-constexpr int GB = 128;                // channels per block
-constexpr int SB = 16;                 // channels per register sub-block of the chain
-constexpr int PITCH = GB + 4;          // LDS row pitch (floats) of the strip and of the transposed block of U
+using namespace chain_ns;
+
 constexpr int WAVES = 8;
 
 template <int R>
@@ -51,15 +51,9 @@ struct Lds {
     int next;                          // next item of the update behind the block
 };
 
-// A whole sub-block of 16 channels for one row per lane, everything in registers.  What counts is the length of the
-// chain from one channel to the next, so it takes the short form of each quotient and checks off the chain that the
-// short form was right:
-//   code   rint(w y) in place of rint(RN(w / s)): the same unless a half-way point lies within 2^-22 |w y| of w y
-//          (w y is off by at most 2^-23 relative, RN(w / s) by 2^-24);
-//   error  fastdiv's quotient, which fastdiv_full's last correction must leave as it is; num must be 0 or at least
-//          2^-80 for that correction to be exact.  Overflows make infinities and NaN, which fail the same tests, and so
-//          do the NaN reciprocals of divisors outside fastdiv's range.
-// Returns false in a lane whose tests failed: nothing of the result is then to be used.  e: the errors; qpk: the codes.
+// A whole sub-block of 16 channels for one row per lane, everything in registers, with the short quotients
+// (gptq_chain.h).  Returns false in a lane whose checks failed: nothing of the result is then to be used.  e: the
+// errors; qpk: the codes.
 template <int R>
 __device__ __forceinline__ bool chain16(const float* wrow, const float* ut, const float* rd, const float2* sc, const uint8_t* zp,
                                         float qmax, float (&e)[SB], uint32_t (&qpk)[SB / 4]) {
@@ -78,7 +72,7 @@ __device__ __forceinline__ bool chain16(const float* wrow, const float* ut, cons
     }
 #pragma unroll
     for (int c = 0; c < SB / 4; ++c) qpk[c] = 0u;
-    bool ok = true;
+    Check check;
     // The corner of U (row cc of `ut` holds U[c][cc] for c <= cc) and the reciprocals of its diagonal, four columns at
     // a time and two channels ahead of their use: all of it at once would not fit the registers.
     float ub[SB][SB], yd[SB];
@@ -117,12 +111,10 @@ __device__ __forceinline__ bool chain16(const float* wrow, const float* ut, cons
             }
         }
         qpk[c / 4] = __builtin_amdgcn_cvt_pk_u8_f32(k + z[c], c & 3, qpk[c / 4]);
-        // (&, not &&: a branch per test would break the chain up)
-        ok = ok & (fmaf(fabsf(quo), 0x1p-22f, fabsf(quo - near)) <= 0.5f);
-        ok = ok & (fmaf(fmaf(-d, e[c], num), yd[c], e[c]) == e[c]);
-        ok = ok & ((__float_as_uint(num) << 1) - 1u >= (0x17800000u << 1) - 1u);   // zero wraps to the top
+        check.code(quo, near);
+        check.error(num, d, yd[c], e[c]);
     }
-    return ok;
+    return check.fine();
 }
 
 // The same channel by channel in LDS with plain divisions: the ragged end of a row, and values outside the fast
@@ -348,7 +340,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
             lds.sc[c][r] = make_float2(sc, fastdiv_ok(sc) ? 1.0f / sc : __builtin_nanf(""));
             lds.zp[c][r] = static_cast<uint8_t>(zp);
         }
-        if (tid < GB) lds.rd[tid] = fastdiv_ok(cd) ? 1.0f / cd : __builtin_nanf("");
+        if (tid < GB) lds.rd[tid] = block_reciprocal(cd);
         if (tid == 0) lds.next = 0;
         stage_groups(i1 + GB, b ^ 1);
     };
@@ -385,8 +377,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
                 const float2* sc = &lds.sc[s0][row_in ? crow : 0];
                 const uint8_t* zp = &lds.zp[s0][row_in ? crow : 0];
                 uint8_t* q_out = Qp + (row0 + crow) * in64 + i1 + s0;
-                bool fine = sbw == SB;
-                if (fine) fine = chain16<R>(wrow + s0, ut, &lds.rd[s0], sc, zp, qmax, e, qpk);   // uniform
+                bool fine = sbw == SB && reciprocals_ok(&lds.rd[s0]);       // uniform
+                if (fine) fine = chain16<R>(wrow + s0, ut, &lds.rd[s0], sc, zp, qmax, e, qpk);
                 if (!__any(row_ok && !fine)) {
                     // errors for the later updates (0 in rows past the end), codes in visiting order
 #pragma unroll

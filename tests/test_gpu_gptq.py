@@ -371,3 +371,18 @@ def test_sweep_outside_the_fast_quotients_range(ctx, dim, group, diag, off):
     assert np.array_equal(got["codes"], ref["codes"])
     assert np.array_equal(got["scales"].view(np.uint32), ref["scales"].view(np.uint32))
     assert np.array_equal(got["dW"], ref["dW"])
+
+
+@pytest.mark.parametrize("out_f,in_f,group", [(4160, 136, 64), (4224, 200, 128), (4096, 140, 64)])
+def test_per_ic_sweep_of_many_rows(ctx, out_f, in_f, group):
+    """Several rows per workgroup in the permuting copies on either side of the sweep (in a multiple of 8 and not)."""
+    W, X = layer(out_f, in_f, 500, seed=out_f + in_f, dead=(3, 77))
+    H32 = oracle.hessian(X).astype(np.float32)
+    Hp, perm, dead = G.prepare(H32, 0.01, True)
+    U32 = G.factor(Hp).astype(np.float32)
+    ref = G.sweep(W, U32, perm, dead, IC, 4, group)
+    got = gpu_sweep(ctx, W, IC, 4, group, dev(U32), dev(perm.astype(np.int32)), dev(dead.astype(np.uint8)), want_packed=True)
+    assert np.array_equal(got["codes"], ref["codes"])
+    assert np.array_equal(got["scales"].view(np.uint32), ref["scales"].view(np.uint32))
+    assert np.array_equal(got["dW"], ref["dW"])
+    assert np.array_equal(got["packed"], oracle.pack(ref["codes"], IC, 4))

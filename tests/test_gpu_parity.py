@@ -706,3 +706,23 @@ def test_gram_timeline_probe_stamps_every_piece(ctx):
     check_hessian(gpu_hessian(ctx, X), oracle.hessian(X))
     with pytest.raises(B.AdaDimError):
         ctx.adadim_probe_gram_timeline(dev(X[:, :1024].copy()))  # the 128-wide kernel's widths carry no stamps
+
+
+@pytest.mark.parametrize("bits", [2, 3, 5, 6, 7, 8])
+@pytest.mark.parametrize("out_f,in_f,group", [
+    (255, 63, 0),          # one tile of the column packer, one short in both directions
+    (257, 65, 0),          # one over: a second tile of one row and one column
+    (500, 208, 20),        # in a multiple of 16: vector loads; ragged last word per column
+    (36, 160, 4),          # in a multiple of 32: the row packer
+])
+def test_bit_streams_of_codes_in_memory(ctx, bits, out_f, in_f, group):
+    """Shapes and widths whose bit streams are packed from the codes afterwards, both dimensions, against the oracle."""
+    W = synth.make_weight(out_f, in_f, bits + out_f, heavy_cols=2, heavy_scale=5.0)
+    for dim in (OC, IC):
+        g = group if dim == IC or group == 0 or in_f % group == 0 else 0
+        n_ch, ln = (out_f, in_f) if dim == OC else (in_f, out_f)
+        packed = torch.full((n_ch, (ln * bits + 31) // 32), -1, dtype=torch.int32, device="cuda")
+        ctx.adadim_quantize(dev(W), dim, bits, g, 1.0, packed=packed)
+        torch.cuda.synchronize()
+        ref = oracle.pack(oracle.quantize(W, dim, bits, g)["codes"], dim, bits)
+        assert np.array_equal(packed.cpu().numpy().view(np.uint32), ref)

@@ -26,6 +26,7 @@ enum {
     WS_QPART,           // partial (min, -max) pairs of the wide-group quantizer
     WS_QPAR,            // its per-group scale, zero and reciprocal
     WS_GEMV_PART,       // per-column-chunk partial outputs of the de-quantizing matrix-vector product
+    WS_GEMV_TICKET,     // its per-output-tile counters
     WS_GPTQ_A,          // fp64 reversed, permuted, damped Hessian and its Cholesky factor
     WS_GPTQ_M,          // fp64 inverse of that factor
     WS_GPTQ_D,          // fp64 diagonal and damping term

@@ -8,13 +8,17 @@
 // form is simpler and reads the same bytes: with a[r, j] = scale[r, j] * x[j] (the per-IC
 // scale folded into the activation, as the paper does when it fills its tables)
 //     y[o] = sum_j a[o/g, j] * code[o, j]  -  sum_j a[o/g, j] * zero[o/g, j].
-// A lane owns 32 consecutive outputs (b words of every column, one 16-byte load for b = 4), a
-// wavefront 2048, so the codes of a column are read in contiguous kilobytes and no sum crosses
-// lanes; the second sum costs one fma per lane and column.  Columns are split over the eight
-// waves of a block and over blocks; partial outputs are added up in a fixed order (LDS inside
-// a block; across blocks by a second small kernel, chunk by chunk), so the result is
-// reproducible.  (Letting the last block of an output tile do that sum needs device-scope
-// fences, which write back and invalidate the XCD's whole L2 each time: 3x slower overall.)
+// A lane owns 32 consecutive outputs (b words of every column, one 16-byte load for b = 4); LO lanes of a wavefront lie
+// along the outputs, so that a column is read in pieces of LO * 4b bytes, and its other 64 / LO lanes take other
+// columns.  The second sum costs one fma per lane and column.  Columns are split over the lanes, the eight waves of a
+// block and over blocks; partial outputs are added up in a fixed order (LDS inside a block; across blocks by the block
+// of an output tile that finishes last, chunk by chunk), so the result is reproducible.
+//
+// How the last block sees the others' partial sums: they are stored and loaded as relaxed atomics at device scope, which
+// on this chip go past the XCD's L2 (to the memory side, where all XCDs meet), a block waits for its stores before it
+// takes its ticket, and only partial sums travel this way.  (Plain stores with device-scope fences write back and
+// invalidate the XCD's whole L2, where x and the group parameters live: 3x slower overall.  A second launch for the
+// sum cost 4-6 us of a call, as much as the product of a 4096 x 4096 layer.)
 #include "common.h"
 #include "code_fields.h"
 
@@ -22,14 +26,9 @@
 
 namespace {
 
-constexpr int GV_WAVES = 8, GV_OUT_PER_BLOCK = 64 * 32;
-// One block per compute unit, 256 on the chip (two would fit by registers and LDS, but half as many blocks with
-// twice the columns each are 5 % faster on the App. D shape: half the dispatches, half the partial sums, and eight
-// waves with two steps in flight each already keep the memory system busy).  The columns are dealt to blocks so
-// that one launch is a whole number of such rounds as nearly as can be: a grid a little larger than that would run
-// a second, mostly empty round, and the kernel is short enough for that to cost a third of its time.
-constexpr int GV_BLOCK_SLOTS = 256, GV_MIN_COLS_PER_WAVE = 32;
+constexpr int GV_WAVES = 8;
 constexpr int GV_NBUF = 3;                 // load buffers taken in turn (4 to 6 were measured: no faster)
+constexpr int GV_SLOTS = 256;              // blocks per round: one per compute unit (two would fit, and are 5 % slower)
 
 template <int PB>
 struct Words {
@@ -98,24 +97,27 @@ __device__ __forceinline__ void accumulate(const Words<PB>& wd, float a, float (
 // M16: the group parameters come as one 16-bit word per (group, column) in `scales` (the
 // fp16 pattern of the scale without its sign bit and its PB-1 lowest bits, above the PB-bit
 // zero-point) instead of an fp32 scale and a u8 zero-point.
-template <int PB, bool M16>
+template <int PB, bool M16, int LO>
 __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t* __restrict__ packed,
                                                                const void* __restrict__ scales,
                                                                const uint8_t* __restrict__ zeros,
                                                                const __half* __restrict__ x, int64_t out, int64_t in,
-                                                               int g, int64_t n_words, float* __restrict__ part) {
+                                                               int g, int64_t n_words, float* part,
+                                                               unsigned int* ticket, __half* __restrict__ y) {
+    constexpr int CL = 64 / LO;                               // column lanes
     __shared__ float s_acc[GV_WAVES][32][65];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t o_lane = int64_t(blockIdx.x) * GV_OUT_PER_BLOCK + lane * 32;
+    __shared__ unsigned int s_ticket;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cl = lane / LO;
+    const int64_t tile0 = int64_t(blockIdx.x) * (LO * 32);
+    const int64_t o_lane = tile0 + (lane % LO) * 32;
     const bool valid = o_lane < out;                         // out % 32 == 0: a lane's outputs are inside together
     // (32-bit divisions: out and in are below 2^24)
     const int64_t r = valid ? static_cast<uint32_t>(o_lane) / static_cast<uint32_t>(g) : 0;
-    // the in/4 column quads split evenly over the gridDim.y * 8 waves that share this output tile: the first
-    // `quads % waves` waves take one quad more
+    // The in/4 column quads go in steps of CL quads, one per column lane; the steps split evenly over the
+    // gridDim.y * 8 waves that share this output tile: the first `steps % waves` waves take one more.
     const uint32_t n_wv = gridDim.y * GV_WAVES, wv = blockIdx.y * GV_WAVES + wave, quads = static_cast<uint32_t>(in >> 2);
-    const uint32_t q_each = quads / n_wv, q_more = quads - q_each * n_wv;
-    const int64_t j_begin = int64_t(wv * q_each + min(wv, q_more)) << 2;
-    const int64_t j_end = int64_t((wv + 1) * q_each + min(wv + 1, q_more)) << 2;
+    const uint32_t steps = (quads + CL - 1) / CL, s_each = steps / n_wv, s_more = steps - s_each * n_wv;
+    const int s_begin = static_cast<int>(wv * s_each + min(wv, s_more)), s_end = static_cast<int>((wv + 1) * s_each + min(wv + 1, s_more));
     const uint32_t* wp = packed + (valid ? (o_lane >> 5) * PB : 0);
     float acc[32];
 #pragma unroll
@@ -128,8 +130,12 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
         uint32_t z4;
         uint2 m4;
         uint2 xr;
+        bool have;
     };
-    auto fetch = [&](Step& st, int64_t j0) {
+    auto fetch = [&](Step& st, int step) {
+        const uint32_t quad = static_cast<uint32_t>(step) * CL + cl;
+        const bool have = CL == 1 || quad < quads;            // the last step may be short
+        const int64_t j0 = int64_t(have ? quad : quads - 1) * 4;
 #pragma unroll
         for (int c = 0; c < 4; ++c) st.wd[c] = load_words<PB>(wp + (j0 + c) * n_words);
         if constexpr (M16) {
@@ -139,6 +145,7 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
             st.z4 = *reinterpret_cast<const uint32_t*>(zeros + r * in + j0);
         }
         st.xr = *reinterpret_cast<const uint2*>(x + j0);
+        st.have = have;
     };
     auto consume = [&](const Step& st) {
         const float2 x01 = __half22float2(*reinterpret_cast<const __half2*>(&st.xr.x));
@@ -159,6 +166,10 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
 #pragma unroll
             for (int c = 0; c < 4; ++c) z[c] = ubyte(st.z4, c);
         }
+        if constexpr (CL > 1) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a[c] = st.have ? a[c] : 0.0f;
+        }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             zsum = fmaf(a[c], z[c], zsum);
@@ -166,19 +177,18 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
             accumulate<PB>(st.wd[c], a[c], acc);
         }
     };
-    if (valid && j_begin < j_end) {
+    if (valid && s_begin < s_end) {
         // GV_NBUF buffers taken in turn, no copies: one is consumed while the others are in flight (a step is 2 to
         // 4 KB per wave; the memory system wants several of them outstanding per wave).  Fetches past the end
-        // re-read the chunk's last columns and are not consumed.
-        const int64_t j_last = j_end - 4;
+        // re-read the share's last step and are not consumed.
         Step st[GV_NBUF];
 #pragma unroll
-        for (int b = 0; b < GV_NBUF - 1; ++b) fetch(st[b], min(j_begin + 4 * b, j_last));
-        for (int64_t j0 = j_begin; j0 < j_end; j0 += 4 * GV_NBUF) {   // in % 4 == 0
+        for (int b = 0; b < GV_NBUF - 1; ++b) fetch(st[b], min(s_begin + b, s_end - 1));
+        for (int s0 = s_begin; s0 < s_end; s0 += GV_NBUF) {
 #pragma unroll
             for (int b = 0; b < GV_NBUF; ++b) {
-                fetch(st[(b + GV_NBUF - 1) % GV_NBUF], min(j0 + 4 * (b + GV_NBUF - 1), j_last));
-                if (j0 + 4 * b < j_end) consume(st[b]);
+                fetch(st[(b + GV_NBUF - 1) % GV_NBUF], min(s0 + b + GV_NBUF - 1, s_end - 1));
+                if (s0 + b < s_end) consume(st[b]);
             }
         }
     }
@@ -188,59 +198,103 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
         s_acc[wave][k][lane] = (acc[k] - code_offset<PB>(k) * asum) - zsum;
     }
     __syncthreads();
-    // thread t adds up the waves for outputs 4t .. 4t+3 of the block's 2048
+    // thread t adds up the waves and column lanes for outputs OPT * t .. of the block's LO * 32
+    constexpr int OPT = LO * 32 / (64 * GV_WAVES) > 0 ? LO * 32 / (64 * GV_WAVES) : 1;
     const int t = threadIdx.x;
-    const int64_t o0 = int64_t(blockIdx.x) * GV_OUT_PER_BLOCK + 4 * t;
-    const bool o_ok = o0 < out;                               // out % 4 == 0
-    if (o_ok) {
-        float v[4];
+    const int64_t o0 = tile0 + int64_t(OPT) * t;
+    const bool o_ok = OPT * t < LO * 32 && o0 < out;          // out % 32 == 0
+    float v[OPT];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int ol = 4 * t + e, ln = ol >> 5, k = ol & 31;
-            float sum = 0.0f;
+    for (int e = 0; e < OPT; ++e) {
+        const int ol = OPT * t + e, ln = (ol >> 5) % LO, k = ol & 31;
+        float sum = 0.0f;
 #pragma unroll
-            for (int w = 0; w < GV_WAVES; ++w) sum += s_acc[w][k][ln];
-            v[e] = sum;
-        }
-        *reinterpret_cast<float4*>(part + int64_t(blockIdx.y) * out + o0) = make_float4(v[0], v[1], v[2], v[3]);
+        for (int w = 0; w < GV_WAVES; ++w)
+#pragma unroll
+            for (int c = 0; c < CL; ++c) sum += s_acc[w][k][c * LO + ln];
+        v[e] = sum;
     }
+    if (gridDim.y > 1) {
+        float* mine = part + int64_t(blockIdx.y) * out + o0;
+        if (o_ok) {
+#pragma unroll
+            for (int e = 0; e < OPT; ++e) __hip_atomic_store(mine + e, v[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // every wave's partial sums have arrived ...
+        __syncthreads();
+        if (t == 0) s_ticket = __hip_atomic_fetch_add(ticket + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (s_ticket != gridDim.y - 1) return;                // ... before the block counts itself in
+        if (t == 0) __hip_atomic_store(ticket + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!o_ok) return;
+#pragma unroll
+        for (int e = 0; e < OPT; ++e) v[e] = 0.0f;
+        const float* src = part + o0;
+        for (unsigned c0 = 0; c0 < gridDim.y; c0 += 8) {      // eight chunks' loads in flight
+            float p[8][OPT];
+#pragma unroll
+            for (unsigned c = 0; c < 8; ++c)
+#pragma unroll
+                for (int e = 0; e < OPT; ++e)
+                    p[c][e] = c0 + c < gridDim.y ? __hip_atomic_load(src + int64_t(c0 + c) * out + e, __ATOMIC_RELAXED,
+                                                                     __HIP_MEMORY_SCOPE_AGENT)
+                                                 : 0.0f;
+#pragma unroll
+            for (unsigned c = 0; c < 8; ++c)
+#pragma unroll
+                for (int e = 0; e < OPT; ++e) v[e] += p[c][e];
+        }
+    }
+    if (!o_ok) return;
+#pragma unroll
+    for (int e = 0; e < OPT; ++e) y[o0 + e] = __float2half_rn(v[e]);
 }
 
-// y[o] = fp16 of the chunk sums in chunk order; one thread per four outputs
-__global__ __launch_bounds__(256) void gemv_ic_finish(const float* __restrict__ part, int n_chunks, int64_t out,
-                                                      __half* __restrict__ y) {
-    const int64_t o0 = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 4;
-    if (o0 >= out) return;                                    // out % 4 == 0
-    float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll 4
-    for (int c = 0; c < n_chunks; ++c) {
-        const float4 p = *reinterpret_cast<const float4*>(part + int64_t(c) * out + o0);
-        sum.x += p.x; sum.y += p.y; sum.z += p.z; sum.w += p.w;
-    }
-    uint2 o;
-    *reinterpret_cast<__half2*>(&o.x) = __floats2half2_rn(sum.x, sum.y);
-    *reinterpret_cast<__half2*>(&o.y) = __floats2half2_rn(sum.z, sum.w);
-    *reinterpret_cast<uint2*>(y + o0) = o;
+__global__ void gemv_zero(unsigned int* p, int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) p[i] = 0u;
+}
+
+// The launch: lanes along the outputs (LO) and column chunks (blocks per output tile).  Wide tiles read a column in long
+// pieces and leave few partial sums; narrow ones are what gives a small layer enough blocks.  At most one round of
+// blocks, and at least two steps per wave: with fewer the partial sums cost more than the shorter wait for the loads
+// saves.  Measured back to back from a graph, weights beyond the caches, us for LO = 8 / 16 / 32 / 64 (64, two launches
+// and at least 32 columns per wave is what was here before: 19.8 + 4 for the first):
+//   4096 x 4096, 4 bits     8.2   8.3  10.5  19.8        4096 x 4096, 3 bits     8.8   8.2  10.5  20.1
+//   1024 x 8192, 4 bits     7.6   8.6  12.6  19.8        4096 x 11008, 4 bits   12.1  12.5  15.2  31.3
+//   11008 x 4096, 4 bits   11.1  11.0  13.3  21.5        8192 x 28672, 4 bits   30.5  28.6  30.6  50.6
+//   28672 x 8192, 3 bits   35.0  24.9  24.0  32.3        49152 x 12288, 4 bits  69.9  65.3  63.0  72.4
+struct GemvShape {
+    int lo, tiles, chunks;
+};
+inline GemvShape gemv_shape(int64_t out, int64_t in, int bits) {
+    GemvShape s;
+    s.lo = out >= 16384 ? 32 : out > 4096 || (bits < 4 && out > 2048) ? 16 : 8;
+    s.tiles = static_cast<int>((out + s.lo * 32 - 1) / (s.lo * 32));
+    const int64_t quads = in / 4, steps = (quads + 64 / s.lo - 1) / (64 / s.lo);
+    s.chunks = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(GV_SLOTS / s.tiles, steps / (2 * GV_WAVES))));
+    return s;
 }
 
 // Measurement aid: the same code words read by the same grid, waves and column ranges as gemv_ic_tiles, with one
 // xor per word in place of the arithmetic and no parameters, x, LDS reduction or partial sums: what the kernel's
 // access pattern alone costs.  Each thread leaves one word in `sink` so that the loads are not dropped.
-template <int PB>
+template <int PB, int LO>
 __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_bare_read(const uint32_t* __restrict__ packed, int64_t out,
                                                                 int64_t in, int64_t n_words,
                                                                 uint32_t* __restrict__ sink) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t o_lane = int64_t(blockIdx.x) * GV_OUT_PER_BLOCK + lane * 32;
+    constexpr int CL = 64 / LO;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cl = lane / LO;
+    const int64_t o_lane = int64_t(blockIdx.x) * (LO * 32) + (lane % LO) * 32;
     const bool valid = o_lane < out;
     const uint32_t n_wv = gridDim.y * GV_WAVES, wv = blockIdx.y * GV_WAVES + wave, quads = static_cast<uint32_t>(in >> 2);
-    const uint32_t q_each = quads / n_wv, q_more = quads - q_each * n_wv;
-    const int64_t j_begin = int64_t(wv * q_each + min(wv, q_more)) << 2;
-    const int64_t j_end = int64_t((wv + 1) * q_each + min(wv + 1, q_more)) << 2;
+    const uint32_t steps = (quads + CL - 1) / CL, s_each = steps / n_wv, s_more = steps - s_each * n_wv;
+    const uint32_t s_begin = wv * s_each + min(wv, s_more), s_end = (wv + 1) * s_each + min(wv + 1, s_more);
     const uint32_t* wp = packed + (valid ? (o_lane >> 5) * PB : 0);
     uint32_t acc = 0;
     if (valid) {
-        for (int64_t j0 = j_begin; j0 < j_end; j0 += 4) {
+        for (uint32_t s = s_begin; s < s_end; ++s) {
+            const int64_t j0 = int64_t(min(s * CL + cl, quads - 1)) * 4;
             Words<PB> wd[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) wd[c] = load_words<PB>(wp + (j0 + c) * n_words);
@@ -266,26 +320,32 @@ extern "C" int adadim_probe_gemv_read(adadim_ctx* ctx, const void* packed, int64
     if (reinterpret_cast<uintptr_t>(packed) & 15u)
         return adadim_fail(ctx, ADADIM_EALIGN, "adadim_probe_gemv_read: packed must be 16-byte aligned");
     if (ctx->capturing) return adadim_fail(ctx, ADADIM_EINVAL, "adadim_probe_gemv_read: not while a graph is being recorded");
-    // the grid of launch_gemv_ic
-    const int n_tiles = static_cast<int>((out + GV_OUT_PER_BLOCK - 1) / GV_OUT_PER_BLOCK);
-    const int64_t max_chunks = std::max<int64_t>(1, in / (GV_WAVES * GV_MIN_COLS_PER_WAVE));
-    const int64_t rounds = (n_tiles + GV_BLOCK_SLOTS - 1) / GV_BLOCK_SLOTS;
-    const int n_chunks = static_cast<int>(std::min<int64_t>(max_chunks, std::max<int64_t>(1, rounds * GV_BLOCK_SLOTS / n_tiles)));
+    const GemvShape sh = gemv_shape(out, in, bits);           // as launch_gemv_ic
     uint32_t* sink = static_cast<uint32_t*>(
-        adadim_workspace(ctx, WS_GEMV_PART, size_t(n_tiles) * size_t(n_chunks) * 64 * GV_WAVES * sizeof(uint32_t)));
+        adadim_workspace(ctx, WS_GEMV_PART, size_t(sh.tiles) * size_t(sh.chunks) * 64 * GV_WAVES * sizeof(uint32_t)));
     if (!sink) return ADADIM_EHIP;
     const int64_t n_words = out * bits / 32;
-    const dim3 grid(static_cast<unsigned>(n_tiles), static_cast<unsigned>(n_chunks));
+    const dim3 grid(static_cast<unsigned>(sh.tiles), static_cast<unsigned>(sh.chunks));
     hipEvent_t e0, e1;
     ADADIM_HIP_TRY(ctx, hipEventCreate(&e0));
     ADADIM_HIP_TRY(ctx, hipEventCreate(&e1));
     ADADIM_HIP_TRY(ctx, hipEventRecord(e0, ctx->stream));
     const uint32_t* pk = static_cast<const uint32_t*>(packed);
-    switch (bits) {
-        case 2: hipLaunchKernelGGL(gemv_bare_read<2>, grid, dim3(64 * GV_WAVES), 0, ctx->stream, pk, out, in, n_words, sink); break;
-        case 3: hipLaunchKernelGGL(gemv_bare_read<3>, grid, dim3(64 * GV_WAVES), 0, ctx->stream, pk, out, in, n_words, sink); break;
-        default: hipLaunchKernelGGL(gemv_bare_read<4>, grid, dim3(64 * GV_WAVES), 0, ctx->stream, pk, out, in, n_words, sink); break;
+#define GV_LO(GO, PB)                 \
+    switch (sh.lo) {                   \
+        case 8: GO(PB, 8); break;      \
+        case 16: GO(PB, 16); break;    \
+        default: GO(PB, 32); break;    \
     }
+#define GV_PB(GO)                      \
+    switch (bits) {                    \
+        case 2: GV_LO(GO, 2) break;    \
+        case 3: GV_LO(GO, 3) break;    \
+        default: GV_LO(GO, 4) break;   \
+    }
+#define GV_READ(PB, LO) hipLaunchKernelGGL((gemv_bare_read<PB, LO>), grid, dim3(64 * GV_WAVES), 0, ctx->stream, pk, out, in, n_words, sink)
+    GV_PB(GV_READ)
+#undef GV_READ
     const hipError_t le = hipGetLastError();
     hipError_t e = hipEventRecord(e1, ctx->stream);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -301,39 +361,38 @@ extern "C" int adadim_probe_gemv_read(adadim_ctx* ctx, const void* packed, int64
 
 int launch_gemv_ic(adadim_ctx* ctx, const uint32_t* packed, const void* scales, const uint8_t* zeros, const __half* x,
                    int64_t out, int64_t in, int bits, int g, __half* y, bool meta16) {
-    const int n_tiles = static_cast<int>((out + GV_OUT_PER_BLOCK - 1) / GV_OUT_PER_BLOCK);
-    // whole rounds of GV_BLOCK_SLOTS blocks, each wave keeping at least GV_MIN_COLS_PER_WAVE columns
-    const int64_t max_chunks = std::max<int64_t>(1, in / (GV_WAVES * GV_MIN_COLS_PER_WAVE));
-    const int64_t rounds = (n_tiles + GV_BLOCK_SLOTS - 1) / GV_BLOCK_SLOTS;
-    const int n_chunks = static_cast<int>(std::min<int64_t>(max_chunks, std::max<int64_t>(1, rounds * GV_BLOCK_SLOTS / n_tiles)));
-    float* part = static_cast<float*>(adadim_workspace(ctx, WS_GEMV_PART, size_t(n_chunks) * size_t(out) * sizeof(float)));
-    if (!part) return ADADIM_EHIP;
+    const GemvShape sh = gemv_shape(out, in, bits);
+    float* part = nullptr;
+    unsigned int* ticket = nullptr;
+    if (sh.chunks > 1) {
+        part = static_cast<float*>(adadim_workspace(ctx, WS_GEMV_PART, size_t(sh.chunks) * size_t(out) * sizeof(float)));
+        // one counter per output tile: zero between launches (the block that finds itself last clears it)
+        const size_t t_bytes = size_t(sh.tiles) * sizeof(unsigned int);
+        const bool fresh = ctx->ws_bytes[WS_GEMV_TICKET] < t_bytes;
+        ticket = static_cast<unsigned int*>(adadim_workspace(ctx, WS_GEMV_TICKET, t_bytes));
+        if (!part || !ticket) return ADADIM_EHIP;
+        if (fresh) {
+            const int n = static_cast<int>(ctx->ws_bytes[WS_GEMV_TICKET] / sizeof(unsigned int));
+            hipLaunchKernelGGL(gemv_zero, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, ctx->stream, ticket, n);
+            ADADIM_LAUNCH_CHECK(ctx, "gemv_zero");
+        }
+    }
     const int64_t n_words = out * bits / 32;
-    const dim3 grid(static_cast<unsigned>(n_tiles), static_cast<unsigned>(n_chunks));
+    const dim3 grid(static_cast<unsigned>(sh.tiles), static_cast<unsigned>(sh.chunks));
     {
         ProfScope prof(ctx, "gemv_ic_tiles");
-#define GV_GO(PB)                                                                                                   \
-    do {                                                                                                            \
-        if (meta16)                                                                                                 \
-            hipLaunchKernelGGL((gemv_ic_tiles<PB, true>), grid, dim3(64 * GV_WAVES), 0, ctx->stream, packed, scales, \
-                               zeros, x, out, in, g, n_words, part);                                                \
-        else                                                                                                        \
-            hipLaunchKernelGGL((gemv_ic_tiles<PB, false>), grid, dim3(64 * GV_WAVES), 0, ctx->stream, packed, scales, \
-                               zeros, x, out, in, g, n_words, part);                                                \
+#define GV_GO(PB, LO)                                                                                                    \
+    do {                                                                                                                 \
+        if (meta16)                                                                                                      \
+            hipLaunchKernelGGL((gemv_ic_tiles<PB, true, LO>), grid, dim3(64 * GV_WAVES), 0, ctx->stream, packed, scales, \
+                               zeros, x, out, in, g, n_words, part, ticket, y);                                          \
+        else                                                                                                             \
+            hipLaunchKernelGGL((gemv_ic_tiles<PB, false, LO>), grid, dim3(64 * GV_WAVES), 0, ctx->stream, packed, scales, \
+                               zeros, x, out, in, g, n_words, part, ticket, y);                                          \
     } while (0)
-        switch (bits) {
-            case 2: GV_GO(2); break;
-            case 3: GV_GO(3); break;
-            default: GV_GO(4); break;
-        }
+        GV_PB(GV_GO)
 #undef GV_GO
     }
     ADADIM_LAUNCH_CHECK(ctx, "gemv_ic_tiles");
-    {
-        ProfScope prof(ctx, "gemv_ic_finish");
-        hipLaunchKernelGGL(gemv_ic_finish, dim3(static_cast<unsigned>((out / 4 + 255) / 256)), dim3(256), 0, ctx->stream,
-                           part, n_chunks, out, y);
-    }
-    ADADIM_LAUNCH_CHECK(ctx, "gemv_ic_finish");
     return ADADIM_OK;
 }

@@ -150,3 +150,27 @@ def test_gemv_appendix_shape_sampled(ctx, bits, group):
     rows = np.sort(rng.choice(out_f, 64, replace=False))
     rows[0], rows[-1] = 0, out_f - 1
     check(y, packed, scales, zeros, x, out_f, bits, group, rows=rows)
+
+
+@pytest.mark.parametrize("out_f,in_f,bits,group", [
+    (32, 4, 4, 32),              # one lane, one column quad
+    (288, 1100, 4, 32),          # 8 lanes along the outputs, one output tile and a bit, a short last step
+    (4096, 2052, 3, 0),          # 16 lanes, several blocks per tile
+    (4128, 1032, 2, 96),         # 16 lanes, a last tile of one lane
+    (16416, 260, 4, 32),         # 32 lanes, one block per tile
+    (16384, 2600, 3, 128),       # 32 lanes, several blocks per tile
+])
+def test_gemv_tile_shapes(ctx, out_f, in_f, bits, group):
+    """Each choice of lanes along the outputs, with one and several blocks per output tile; twice in a row, with another
+    shape in between (the counters of the blocks must be back at zero)."""
+    rng = np.random.default_rng(out_f + in_f + bits)
+    g = group or out_f
+    packed = rng.integers(0, 2 ** 32, size=(in_f, out_f * bits // 32), dtype=np.uint64).astype(np.uint32)
+    scales = rng.uniform(0.004, 0.02, size=(out_f // g, in_f)).astype(np.float32)
+    zeros = rng.integers(0, 2 ** bits, size=(out_f // g, in_f)).astype(np.uint8)
+    x = rng.standard_normal(in_f).astype(np.float16)
+    rows = np.unique(np.concatenate([[0, 31, out_f - 32, out_f - 1], rng.choice(out_f, 24)]))
+    y = run_gemv(ctx, packed, scales, zeros, x, out_f, in_f, bits, group)
+    check(y, packed, scales, zeros, x, out_f, bits, g, rows=rows)
+    run_gemv(ctx, packed[:128], scales[:, :128], zeros[:, :128], x[:128], out_f, min(in_f, 128), bits, group)
+    assert np.array_equal(y, run_gemv(ctx, packed, scales, zeros, x, out_f, in_f, bits, group))

@@ -28,6 +28,7 @@
 
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 namespace {
 
@@ -79,20 +80,21 @@ __global__ void gq_rank(const double* __restrict__ d, int64_t n, int act_order, 
 }
 
 // The same ranks in two steps that use the whole chip: block (x, y) counts, for its 256 channels j,
-// the channels of the y-th kilo-entry of the diagonal that come before j (staged in LDS) and adds the
+// the channels of the y-th 256 entries of the diagonal that come before j (staged in LDS) and adds the
 // count to rank[j] (integer atomics: any order gives the same sum); then perm[rank[j]] = j.
 __global__ void gq_zero_i32(int32_t* __restrict__ p, int64_t n) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
 }
 __global__ __launch_bounds__(256) void gq_rank_count(const double* __restrict__ d, int64_t n, int32_t* __restrict__ rank) {
-    __shared__ double s[1024];
-    const int64_t j = int64_t(blockIdx.x) * 256 + threadIdx.x, k0 = int64_t(blockIdx.y) * 1024;
-    for (int e = threadIdx.x; e < 1024; e += 256) s[e] = k0 + e < n ? d[k0 + e] : -1.0;   // diagonal entries are > 0
+    constexpr int PIECE = 256;                                // (1024: 64 blocks for 4096 channels, 77 us)
+    __shared__ double s[PIECE];
+    const int64_t j = int64_t(blockIdx.x) * 256 + threadIdx.x, k0 = int64_t(blockIdx.y) * PIECE;
+    for (int e = threadIdx.x; e < PIECE; e += 256) s[e] = k0 + e < n ? d[k0 + e] : -1.0;   // diagonal entries are > 0
     __syncthreads();
     if (j >= n) return;
     const double dj = d[j];
-    const int m = static_cast<int>(n - k0 < 1024 ? n - k0 : 1024);
+    const int m = static_cast<int>(n - k0 < PIECE ? n - k0 : PIECE);
     int c0 = 0, c1 = 0, c2 = 0, c3 = 0;                       // four counters: the adds do not wait for each other
     int e = 0;
     for (; e + 4 <= m; e += 4) {
@@ -111,8 +113,23 @@ __global__ void gq_rank_place(const int32_t* __restrict__ rank, int64_t n, int32
 
 // A = J (P (H' + damp I) P^T) J in fp64: A[a][b] = H'[perm[n-1-a]][perm[n-1-b]] (+ damp on the diagonal),
 // H' = H with dead channels' diagonal set to 1
-__global__ void gq_gather(const float* __restrict__ H, int64_t n, const int32_t* __restrict__ perm,
-                          const double* __restrict__ d, const double* __restrict__ damp, double* __restrict__ A) {
+// One row of A per workgroup: the row of H it comes from goes through LDS (a thread per element reading it from memory
+// fetched a 64-byte piece for every four bytes: 100 us for a 4096-wide H).  Dynamic LDS: n floats.  Only the lower triangle
+// is ever read (the tiles on the diagonal, which are used whole, included).
+__global__ __launch_bounds__(256) void gq_gather(const float* __restrict__ H, int64_t n, const int32_t* __restrict__ perm,
+                                                 const double* __restrict__ d, const double* __restrict__ damp,
+                                                 double* __restrict__ A) {
+    extern __shared__ __align__(16) char gg_smem[];
+    float* row = reinterpret_cast<float*>(gg_smem);
+    const int64_t a = blockIdx.x, pa = perm[n - 1 - a];
+    for (int64_t j = threadIdx.x; j < n; j += 256) row[j] = H[pa * n + j];
+    __syncthreads();
+    const int64_t end = min(n, (a / NB + 1) * NB);
+    for (int64_t b = threadIdx.x; b < end; b += 256) A[a * n + b] = b == a ? d[pa] + *damp : static_cast<double>(row[perm[n - 1 - b]]);
+}
+// the same without LDS, for rows that do not fit it
+__global__ void gq_gather_wide(const float* __restrict__ H, int64_t n, const int32_t* __restrict__ perm,
+                               const double* __restrict__ d, const double* __restrict__ damp, double* __restrict__ A) {
     const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (idx >= n * n) return;
     const int64_t a = idx / n, b = idx % n;
@@ -131,21 +148,42 @@ constexpr int GT = 64, GK = 32;                  // tile edge, contraction chunk
 // (128 x 128 tiles were measured too: one workgroup per compute unit instead of four, and the
 // products ran a third slower; the matrix pipe wants the other workgroups' waves to fill its gaps.)
 
-// acc += A B (acc -= A B with NEG_A) for one TS x TS tile (TS = 64 or 128) and k in [k_lo, k_hi), 256 threads: 2 x 2 waves,
-// each TS/2 x TS/2 = MT x MT matrix-core tiles of 16 x 16.
-//   A(i, k) = Ap[i * lda + k], rows i < m_valid;
+// acc += (acc -= with NEG_A) the product of the chunk in LDS: A(i, k) = As[k][i], B(k, j) = Bs[k][j], k < GK.  256 threads:
+// 2 x 2 waves, each TS/2 x TS/2 = MT x MT matrix-core tiles of 16 x 16.
+template <int TS, bool NEG_A>
+__device__ __forceinline__ void dgemm_chunk(const double (*As)[TS + 4], const double (*Bs)[TS + 4], double4_t (&acc)[TS / 32][TS / 32]) {
+    constexpr int MT = TS / 32;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1;
+#pragma unroll
+    for (int ks = 0; ks < GK; ks += 4) {
+        double a[MT], b[MT];
+#pragma unroll
+        for (int u = 0; u < MT; ++u) {
+            a[u] = As[ks + (lane >> 4)][wm * (TS / 2) + u * 16 + (lane & 15)];
+            if constexpr (NEG_A) a[u] = -a[u];
+            b[u] = Bs[ks + (lane >> 4)][wn * (TS / 2) + u * 16 + (lane & 15)];
+        }
+#pragma unroll
+        for (int u = 0; u < MT; ++u)
+#pragma unroll
+            for (int v = 0; v < MT; ++v) acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
+    }
+}
+
+// acc += A B (acc -= A B with NEG_A) for one TS x TS tile and k in [k_lo, k_hi), 256 threads.
+//   A(i, k) = A_KC ? Ap[i * lda + k] : Ap[k * lda + i], rows i < m_valid;
 //   B(k, j) = B_KC ? Bp[j * ldb + k] : Bp[k * ldb + j], columns j < n_valid;
 // everything outside the valid ranges reads as zero.  As, Bs: [GK][TS + 4] doubles each.
-template <int TS, bool B_KC, bool NEG_A = false>
+template <int TS, bool A_KC, bool B_KC, bool NEG_A = false>
 __device__ __forceinline__ void dgemm_tile(const double* __restrict__ Ap, int64_t lda, int m_valid,
                                            const double* __restrict__ Bp, int64_t ldb, int n_valid, int64_t k_lo,
                                            int64_t k_hi, double (*As)[TS + 4], double (*Bs)[TS + 4],
                                            double4_t (&acc)[TS / 32][TS / 32]) {
-    constexpr int MT = TS / 32, E = TS / 16;              // matrix-core tiles per wave side; elements per thread and operand
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+    constexpr int E = TS / 16;                            // elements per thread and operand
+    const int t = threadIdx.x;
     // Loads: 16 consecutive lanes read 16 consecutive doubles (one 128-byte line).  For an operand
     // that is contiguous along k they are the chunk's 16 k of one row (rows t/16 + 16 e); for the
-    // row-major B they are 16 columns of one k row (k row t/16, columns t%16 + 16 e).
+    // other form they are 16 rows or columns of one k (k = t/16, rows or columns t%16 + 16 e).
     const int l16 = t & 15, h16 = t >> 4;
     constexpr int KK = GK / 16;                           // 16-wide pieces of a chunk
     double ra[KK][E], rb[KK][E];
@@ -153,11 +191,19 @@ __device__ __forceinline__ void dgemm_tile(const double* __restrict__ Ap, int64_
     auto fetch = [&](int64_t k0) {
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
-            const int64_t k = k0 + 16 * kk + l16;
+            const int64_t k = k0 + 16 * kk + l16, kr = k0 + 16 * kk + h16;
+            if constexpr (A_KC) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int row = h16 + 16 * e;
-                ra[kk][e] = (row < m_valid && k < k_hi) ? Ap[row * lda + k] : 0.0;
+                for (int e = 0; e < E; ++e) {
+                    const int row = h16 + 16 * e;
+                    ra[kk][e] = (row < m_valid && k < k_hi) ? Ap[row * lda + k] : 0.0;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const int row = l16 + 16 * e;
+                    ra[kk][e] = (kr < k_hi && row < m_valid) ? Ap[kr * lda + row] : 0.0;
+                }
             }
             if constexpr (B_KC) {
 #pragma unroll
@@ -166,7 +212,6 @@ __device__ __forceinline__ void dgemm_tile(const double* __restrict__ Ap, int64_
                     rb[kk][e] = (row < n_valid && k < k_hi) ? Bp[row * ldb + k] : 0.0;
                 }
             } else {
-                const int64_t kr = k0 + 16 * kk + h16;
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
                     const int col = l16 + 16 * e;
@@ -181,7 +226,10 @@ __device__ __forceinline__ void dgemm_tile(const double* __restrict__ Ap, int64_
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) As[16 * kk + l16][h16 + 16 * e] = ra[kk][e];
+            for (int e = 0; e < E; ++e) {
+                if constexpr (A_KC) As[16 * kk + l16][h16 + 16 * e] = ra[kk][e];
+                else As[16 * kk + h16][l16 + 16 * e] = ra[kk][e];
+            }
             if constexpr (B_KC) {
 #pragma unroll
                 for (int e = 0; e < E; ++e) Bs[16 * kk + l16][h16 + 16 * e] = rb[kk][e];
@@ -192,20 +240,7 @@ __device__ __forceinline__ void dgemm_tile(const double* __restrict__ Ap, int64_
         }
         __syncthreads();
         if (k0 + GK < k_hi) fetch(k0 + GK);
-#pragma unroll
-        for (int ks = 0; ks < GK; ks += 4) {
-            double a[MT], b[MT];
-#pragma unroll
-            for (int u = 0; u < MT; ++u) {
-                a[u] = As[ks + (lane >> 4)][wm * (TS / 2) + u * 16 + (lane & 15)];
-                if constexpr (NEG_A) a[u] = -a[u];
-                b[u] = Bs[ks + (lane >> 4)][wn * (TS / 2) + u * 16 + (lane & 15)];
-            }
-#pragma unroll
-            for (int u = 0; u < MT; ++u)
-#pragma unroll
-                for (int v = 0; v < MT; ++v) acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
-        }
+        dgemm_chunk<TS, NEG_A>(As, Bs, acc);
     }
 }
 
@@ -238,25 +273,29 @@ __device__ __forceinline__ void dgemm_fill(double4_t (&acc)[TS / 32][TS / 32], F
 }
 
 // ------------------------------------------------------------------ Cholesky, lower, in place
-// Diagonal block A[k0.., k0..] of width w <= NB = 64, factored and inverted by one workgroup of four
-// waves, blocked by 16.  The whole factorization waits for this kernel, so what counts is the length
-// of its dependency chain, not its flops:
-//  * Cholesky, four panels of 16 columns.  Wave 0 holds the panel with lane r = row r (16 registers):
-//    column c is final once its pivot is (broadcast by a lane read; reciprocal square root plus two
-//    Newton steps), the later columns of the panel receive l_rc l_jc with l_jc read from lane j.  No
-//    LDS and no barrier inside a panel, at most 15 updates per column.  The columns behind the panel
-//    get the panel's rank-16 update from the fp64 matrix cores, the (at most six) 16 x 16 tiles dealt
-//    to the four waves.
-//  * inv(L) by doubling: the four 16 x 16 diagonal blocks at once, one per wave (lane j solves for
-//    column j, L's entries by lane reads), then the level-16 and level-32 off-diagonal blocks as
-//    -inv(B) C inv(A), two matrix-core products each.
+// Diagonal block of width w <= NB = 64, factored and inverted by one workgroup of four waves, blocked by 16.  The whole
+// factorization waits for it, so what counts is the length of its dependency chain, not its flops:
+//  * A 16 x 16 block on the diagonal is eliminated by wave 0, each of its 16-lane rows doing the same: lane r holds row r of
+//    the block and column r of the inverse that grows beside it (16 doubles each).  The chain runs through the pivots
+//    alone: pivot c + 1 = q - x^2 / pivot c, q and x being row c + 1's entries of columns c + 1 and c, so that a reciprocal
+//    and one fma lie between two of them.  Column c's entries reach the other lanes by a broadcast within the lane row,
+//    one instruction each (reads into scalar registers, with the inverse solved afterwards: 43000 cycles for a
+//    64-wide block against 23300), and serve the block and the inverse.  The pivots' reciprocal roots scale the inverse's rows at
+//    the end; L's own diagonal blocks are not needed.
+//  * The rows below are a product with that inverse and the columns behind get their rank-16 update, on the fp64 matrix
+//    cores.  Wave 0 takes the next diagonal block alone and goes on to eliminate it; meanwhile the other waves update the
+//    other blocks and make row p of the inverse's blocks, -inv(L_pp) sum_k L_pk inv(L)_kq.
 // inv(L) goes to the diagonal block of M: it turns the panel's triangular solve into a product and is
 // the first level of the triangular inverse.
-// the value `v` has in lane `src_lane` (wave-uniform), in every lane
-__device__ __forceinline__ double lane_read(double v, int src_lane) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src_lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src_lane);
-    return __hiloint2double(hi, lo);
+
+// lane J's value of every 16-lane row, in all of the row's lanes (data-parallel primitive row_newbcast)
+template <int J>
+__device__ __forceinline__ double row_bcast(double v) {
+    return __longlong_as_double(__builtin_amdgcn_mov_dpp(__double_as_longlong(v), 0x150 + J, 0xf, 0xf, false));
+}
+template <int... I, typename F>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F f) {
+    (f(std::integral_constant<int, I>{}), ...);
 }
 // LDS writes of this wave before, its LDS reads after: a wave's LDS accesses are served in order
 __device__ __forceinline__ void wave_lds_sync() {
@@ -265,212 +304,252 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// LDS of the diagonal block's factorization: 41 KB.  inv(L) grows in the upper triangle of the block that holds L
-// (transposed; its diagonal is rd), so that the workgroup fits beside three of the trailing update's workgroups on
-// a compute unit: one that needed more than a freed slot's share of LDS would wait for that launch to drain.
+// LDS of the diagonal block's factorization: 42 KB.  inv(L) grows in the block that holds L, so that the workgroup fits
+// beside three of the trailing update's workgroups on a compute unit: one that needed more than a freed slot's share of
+// LDS would wait for that launch to drain.
 struct DiagLds {
     static constexpr int LD = NB + 1;
-    double t[NB][LD];                                         // the block, then L on and below the diagonal, inv(L)^T above
-    double tt[NB / 2][NB / 2 + 1];                            // C inv(A) of the inverse's levels
-    double rd[NB];                                            // reciprocals of the diagonal of L = diagonal of inv(L)
+    double t[NB][LD];                                         // 16 x 16 blocks: L below the diagonal, inv(L) on it, inv(L)^T above
+    double s[3][16][17];                                      // sum_k L_pk inv(L)_kq of a wave's block
 };
-__device__ __forceinline__ void diag_factor(double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0, int w,
-                                            DiagLds& lds) {
-    constexpr int P = 16;
+// lds.t holds the block (identity padding behind w), visible to the whole workgroup.  Only inv(L) leaves the workgroup:
+// nothing reads the diagonal block of L afterwards.
+__device__ __forceinline__ void diag_factor(double* __restrict__ M, int64_t n, int64_t k0, int w, DiagLds& lds) {
+    constexpr int P = 16, NP = NB / P;
+    constexpr auto seq = std::make_integer_sequence<int, P>{};
     auto& t = lds.t;
-    auto& tt = lds.tt;
-    auto& rd = lds.rd;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, h16 = lane >> 4;
     // one workgroup that the whole factorization waits for: ahead of the trailing update that may share its SIMDs
     __builtin_amdgcn_s_setprio(3);
-    for (int e = tid; e < NB * NB; e += 256) {
-        const int r = e / NB, c = e % NB;
-        t[r][c] = (r < w && c < w) ? A[(k0 + r) * n + k0 + c] : (r == c ? 1.0 : 0.0);   // identity padding
-    }
-    __syncthreads();
-    // element (r, c) of inv(L) once its block is there
-    auto mval = [&](int r, int c) {
-        const double up = t[c < r ? c : r][c < r ? r : c], dg = lds.rd[r];
-        return r > c ? up : (r == c ? dg : 0.0);
-    };
-    // the pivot's reciprocal square root: the same in every lane
-    auto rsqrt_of = [](double piv) {
-        double inv = __builtin_amdgcn_rsq(piv);
-        inv = inv * fma(-0.5 * piv * inv, inv, 1.5);
-        return inv * fma(-0.5 * piv * inv, inv, 1.5);
-    };
-    for (int p = 0; p < NB / P; ++p) {
-        if (wave == 0) {
-            double x[P];
+    // block (ti, tj) -= L_ti,p L_tj,p^T
+    auto update = [&](int ti, int tj, int p) {
+        double4_t acc;
 #pragma unroll
-            for (int j = 0; j < P; ++j) x[j] = t[lane][P * p + j];
-#pragma unroll
-            for (int c = 0; c < P; ++c) {
-                const int gc = P * p + c;
-                const double piv = lane_read(x[c], gc), inv = rsqrt_of(piv);
-                const double l = lane == gc ? piv * inv : (lane > gc ? x[c] * inv : 0.0);
-                x[c] = l;
-                if (lane == gc) rd[gc] = inv;
-#pragma unroll
-                for (int j = c + 1; j < P; ++j) x[j] = fma(-l, lane_read(l, P * p + j), x[j]);
-            }
-#pragma unroll
-            for (int j = 0; j < P; ++j) t[lane][P * p + j] = x[j];
-        }
-        __syncthreads();
-        int idx = 0;
-        for (int ti = p + 1; ti < NB / P; ++ti)
-            for (int tj = p + 1; tj <= ti; ++tj, ++idx) {
-                if ((idx & 3) != wave) continue;              // whole waves
-                double4_t acc;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[r] = t[P * ti + 4 * r + h16][P * tj + l16];
-#pragma unroll
-                for (int kk = 0; kk < P; kk += 4)
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-t[P * ti + l16][P * p + kk + h16], t[P * tj + l16][P * p + kk + h16],
-                                                               acc, 0, 0, 0);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) t[P * ti + 4 * r + h16][P * tj + l16] = acc[r];
-            }
-        __syncthreads();
-    }
-    // diagonal blocks of inv(L): wave b's lanes 0..15 hold rows and solve for columns of block b (the other
-    // lanes repeat them)
-    {
-        const int b = P * wave;
-        double xr[P], a[P];
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-            xr[k] = t[b + l16][b + k];
-            a[k] = k == l16 ? 1.0 : 0.0;
-        }
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-            const double yk = a[k] * rd[b + k];
-            a[k] = yk;
-#pragma unroll
-            for (int r = k + 1; r < P; ++r) a[r] = fma(-lane_read(xr[k], r), yk, a[r]);
-        }
-        if (lane < P) {
-#pragma unroll
-            for (int r = 0; r < P; ++r)
-                if (r > lane) t[b + lane][b + r] = a[r];      // the diagonal entry is rd
-        }
-    }
-    __syncthreads();
-    // level 16: blocks (1, 0) and (3, 2), one wave each
-    if (wave < 2) {
-        const int ra = 2 * P * wave, rb = ra + P;            // first rows of inv(A)'s and inv(B)'s blocks
-        double4_t acc = {0.0, 0.0, 0.0, 0.0};
+        for (int r = 0; r < 4; ++r) acc[r] = t[P * ti + 4 * r + h16][P * tj + l16];
 #pragma unroll
         for (int kk = 0; kk < P; kk += 4)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t[rb + l16][ra + kk + h16], mval(ra + kk + h16, ra + l16), acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-t[P * ti + l16][P * p + kk + h16], t[P * tj + l16][P * p + kk + h16], acc,
+                                                       0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) tt[P * wave + 4 * r + h16][l16] = acc[r];
+        for (int r = 0; r < 4; ++r) t[P * ti + 4 * r + h16][P * tj + l16] = acc[r];
+    };
+    // block (p, q) of inv(L), q < p, into its place above the diagonal; s: the wave's own
+    auto inverse = [&](int p, int q, double (*s)[17]) {
+        double4_t acc = {0.0, 0.0, 0.0, 0.0};
+        for (int k = q; k < p; ++k)
+#pragma unroll
+            for (int kk = 0; kk < P; kk += 4) {
+                const double b = k == q ? t[P * q + kk + h16][P * q + l16] : t[P * q + l16][P * k + kk + h16];
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t[P * p + l16][P * k + kk + h16], b, acc, 0, 0, 0);
+            }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[4 * r + h16][l16] = acc[r];
         wave_lds_sync();
         acc = double4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int kk = 0; kk < P; kk += 4)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-mval(rb + l16, rb + kk + h16), tt[P * wave + kk + h16][l16], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-t[P * p + l16][P * p + kk + h16], s[kk + h16][l16], acc, 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) t[ra + l16][rb + 4 * r + h16] = acc[r];
-    }
-    __syncthreads();
-    // level 32: the 32 x 32 block below the diagonal, one 16 x 16 tile per wave
-    {
-        const int ti = wave >> 1, tj = wave & 1;
-        double4_t acc = {0.0, 0.0, 0.0, 0.0};
+        for (int r = 0; r < 4; ++r) t[P * q + l16][P * p + 4 * r + h16] = acc[r];
+        wave_lds_sync();
+    };
+    for (int p = 0; p < NP; ++p) {
+        if (wave == 0) {
+            if (p > 0) {
+                update(p, p, p - 1);
+                wave_lds_sync();
+            }
+            double x[P], y[P];                                // row l16 of the block, column l16 of the inverse
 #pragma unroll
-        for (int kk = 0; kk < 2 * P; kk += 4)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t[2 * P + P * ti + l16][kk + h16], mval(kk + h16, P * tj + l16), acc, 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) tt[P * ti + 4 * r + h16][P * tj + l16] = acc[r];
+            for (int j = 0; j < P; ++j) {
+                x[j] = t[P * p + l16][P * p + j];
+                y[j] = j == l16 ? 1.0 : 0.0;
+            }
+            double piv = row_bcast<0>(x[0]), my_piv = 1.0;    // my_piv: pivot l16
+            static_for(seq, [&](auto C) {
+                constexpr int c = C;
+                my_piv = l16 == c ? piv : my_piv;
+                double rp = __builtin_amdgcn_rcp(piv);
+                rp = fma(fma(-piv, rp, 1.0), rp, rp);
+                rp = fma(fma(-piv, rp, 1.0), rp, rp);
+                if constexpr (c + 1 < P) {
+                    const double xn = row_bcast<c + 1>(x[c]);
+                    piv = fma(-(xn * xn), rp, row_bcast<c + 1>(x[c + 1]));
+                }
+                const double m = x[c] * rp, yc = y[c] * rp;
+                static_for(seq, [&](auto J) {
+                    constexpr int j = J;
+                    if constexpr (j > c) {
+                        const double b = row_bcast<j>(x[c]);
+                        x[j] = fma(-m, b, x[j]);
+                        y[j] = fma(-b, yc, y[j]);
+                        asm volatile("" : "+v"(y[j]));        // here and now: put off to the stores, it needs every b held
+                    }
+                });
+            });
+            double inv = __builtin_amdgcn_rsq(my_piv);
+            inv = inv * fma(-0.5 * my_piv * inv, inv, 1.5);
+            inv = inv * fma(-0.5 * my_piv * inv, inv, 1.5);
+            // from a pivot that is not positive on, everything is NaN
+            const unsigned long long bad = __ballot(!(my_piv > 0.0));
+            if (bad && l16 >= __ffsll(bad) - 1) inv = __builtin_nan("");
+            static_for(seq, [&](auto J) {
+                constexpr int j = J;
+                const double v = y[j] * row_bcast<j>(inv);
+                if (lane < P) t[P * p + j][P * p + lane] = v;
+            });
+        } else {
+            // beside the elimination: the other blocks' update by column block p - 1, and row p - 1 of the inverse
+            int idx = 0;
+            for (int ti = p + 1; p > 0 && ti < NP; ++ti)
+                for (int tj = p; tj <= ti; ++tj, ++idx)
+                    if (idx % 3 == wave - 1) update(ti, tj, p - 1);
+            for (int q = 0; q < p - 1; ++q)
+                if (q == wave - 1) inverse(p - 1, q, lds.s[wave - 1]);
+        }
         __syncthreads();
-        acc = double4_t{0.0, 0.0, 0.0, 0.0};
+        // the rows below: L_ti,p = A_ti,p inv(L_pp)^T, a block per wave
+        const int ti = p + 1 + wave;
+        if (ti < NP) {
+            double4_t acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int kk = 0; kk < 2 * P; kk += 4)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-mval(2 * P + P * ti + l16, 2 * P + kk + h16), tt[kk + h16][P * tj + l16], acc,
-                                                       0, 0, 0);
+            for (int kk = 0; kk < P; kk += 4)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t[P * ti + l16][P * p + kk + h16], t[P * p + l16][P * p + kk + h16], acc,
+                                                           0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) t[P * tj + l16][2 * P + P * ti + 4 * r + h16] = acc[r];
+            for (int r = 0; r < 4; ++r) t[P * ti + 4 * r + h16][P * p + l16] = acc[r];
+        }
+        __syncthreads();
+    }
+    if (wave < NP - 1) inverse(NP - 1, wave, lds.s[wave]);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NB * NB / 256; ++i) {
+        const int r = i * (256 / NB) + wave, c = lane, br = r / P, bc = c / P;
+        const double v = br == bc ? t[r][c] : (br > bc ? t[c][r] : 0.0);
+        if (r < w && c < w) M[(k0 + r) * n + k0 + c] = v;
+    }
+}
+
+// the first block
+__global__ __launch_bounds__(256, 3) void chol_diag_inv(const double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0,
+                                                        int w) {
+    __shared__ DiagLds lds;
+    for (int e = threadIdx.x; e < NB * NB; e += 256) {
+        const int r = e / NB, c = e % NB;
+        lds.t[r][c] = (r < w && c < w) ? A[(k0 + r) * n + k0 + c] : (r == c ? 1.0 : 0.0);   // identity padding
     }
     __syncthreads();
-    for (int e = tid; e < w * w; e += 256) {
-        const int r = e / w, c = e % w;
-        A[(k0 + r) * n + k0 + c] = r >= c ? t[r][c] : 0.0;
-        M[(k0 + r) * n + k0 + c] = mval(r, c);
-    }
+    diag_factor(M, n, k0, w, lds);
 }
 
-__global__ __launch_bounds__(256) void chol_diag_inv(double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0,
+// L's blocks below the diagonal are kept transposed in the upper triangle of M, whose lower triangle takes inv(L): column c
+// of L is M[c][c + 1 ..].  A's own entries there stay as the updates left them, so that several workgroups can each make
+// the L they need from them.
+
+// rows below the diagonal block: L21^T = inv(L11) A21^T, 64 rows per block
+__global__ __launch_bounds__(256, 4) void chol_panel(const double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0,
                                                      int w) {
-    __shared__ DiagLds lds;
-    diag_factor(A, M, n, k0, w, lds);
-}
-
-// rows below the diagonal block: L21 = A21 inv(L11)^T, 64 rows per block, in place (a block reads
-// only the rows it writes, and has read them all before the first store)
-__global__ __launch_bounds__(256) void chol_panel(double* __restrict__ A, const double* __restrict__ M, int64_t n,
-                                                  int64_t k0, int w) {
     __shared__ double As[GK][GT + 4], Bs[GK][GT + 4];
     // a link of the chain the factorization waits for: its waves issue ahead of the bulk update's on a shared SIMD
     __builtin_amdgcn_s_setprio(3);
     const int64_t r0 = k0 + w + int64_t(blockIdx.x) * GT;
     const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT);
     double4_t acc[2][2] = {};
-    dgemm_tile<GT, true>(A + r0 * n + k0, n, m_valid, M + k0 * n + k0, n, w, 0, w, As, Bs, acc);
-    __syncthreads();
-    dgemm_each<GT>(acc, [&](int i, int j, double v) {
-        if (i < m_valid && j < w) A[(r0 + i) * n + k0 + j] = v;
+    dgemm_tile<GT, true, true>(M + k0 * n + k0, n, w, A + r0 * n + k0, n, m_valid, 0, w, As, Bs, acc);
+    dgemm_each<GT>(acc, [&](int c, int i, double v) {
+        if (c < w && i < m_valid) M[(k0 + c) * n + r0 + i] = v;
     });
 }
 
-// trailing update: C[r][c] -= sum_t P[r][t] P[c][t] on the TS x TS tiles (blockIdx.y, blockIdx.x <= blockIdx.y)
-// of the rows/columns from k1 on; P = A[.., k0..k0+w).  gridDim.x limits the columns that are updated
-// (inside a 512-wide outer panel only the panel's own columns; behind it all, with w = 512).
-// ct0: first tile column of this launch (the update behind an outer panel goes out in two launches).
-template <int TS>
-__global__ __launch_bounds__(256) void chol_syrk(double* __restrict__ A, int64_t n, int64_t k0, int w, int64_t k1, int ct0) {
+// Trailing update A -= L[., k0 .. k0+w) L[., k0 .. k0+w)^T of the lower triangle's tiles behind a 512-wide outer panel
+// (w = 512).  ct0: first tile column of this launch (the update goes out in two launches).
+__global__ __launch_bounds__(256, 4) void chol_syrk(double* __restrict__ A, const double* __restrict__ M, int64_t n, int64_t k0, int w,
+                                                    int64_t k1, int ct0) {
     const int ct = static_cast<int>(blockIdx.x) + ct0;
     if (ct > static_cast<int>(blockIdx.y)) return;
-    __shared__ double As[GK][TS + 4], Bs[GK][TS + 4];
-    const int64_t r0 = k1 + int64_t(blockIdx.y) * TS, c0 = k1 + int64_t(ct) * TS;
-    const int m_valid = static_cast<int>(n - r0 < TS ? n - r0 : TS), n_valid = static_cast<int>(n - c0 < TS ? n - c0 : TS);
-    // the accumulators start as the tile of C (its loads travel with the first operand chunk's) and the products are
-    // subtracted: no read-modify-write behind the loop
-    double4_t acc[TS / 32][TS / 32];
-    dgemm_fill<TS>(acc, [&](int i, int j) { return (i < m_valid && j < n_valid) ? A[(r0 + i) * n + c0 + j] : 0.0; });
-    dgemm_tile<TS, true, true>(A + r0 * n + k0, n, m_valid, A + c0 * n + k0, n, n_valid, 0, w, As, Bs, acc);
-    dgemm_each<TS>(acc, [&](int i, int j, double v) {
+    __shared__ double As[GK][GT + 4], Bs[GK][GT + 4];
+    const int64_t r0 = k1 + int64_t(blockIdx.y) * GT, c0 = k1 + int64_t(ct) * GT;
+    const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT), n_valid = static_cast<int>(n - c0 < GT ? n - c0 : GT);
+    double4_t acc[GT / 32][GT / 32];
+    dgemm_fill<GT>(acc, [&](int i, int j) { return (i < m_valid && j < n_valid) ? A[(r0 + i) * n + c0 + j] : 0.0; });
+    dgemm_tile<GT, false, false, true>(M + k0 * n + r0, n, m_valid, M + k0 * n + c0, n, n_valid, 0, w, As, Bs, acc);
+    dgemm_each<GT>(acc, [&](int i, int j, double v) {
         if (i < m_valid && c0 + j <= r0 + i) A[(r0 + i) * n + c0 + j] = v;
     });
 }
 
-// The same update with 64 x 64 tiles, and the workgroup of the first tile (the diagonal block at k1, final once
-// this update has reached it) goes on to factor and invert that block: the next step's chol_diag_inv without its
-// launch, and under the other tiles' products.  The product's staging buffers and the factorization's LDS share
-// their space.
-__global__ __launch_bounds__(256) void chol_syrk_diag(double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0, int w,
-                                                      int64_t k1) {
+// The end of an update's tile: the workgroup of the first tile (the diagonal block at k1, final once this update has
+// reached it) goes on to factor and invert that block, without a launch and under the other tiles' products; the others
+// store theirs.
+__device__ __forceinline__ void chol_tile_end(double4_t (&acc)[GT / 32][GT / 32], double* __restrict__ A, double* __restrict__ M,
+                                              int64_t n, int64_t k1, int64_t r0, int64_t c0, int m_valid, int n_valid, DiagLds& lds) {
+    if (blockIdx.x == 0 && blockIdx.y == 0) {                 // whole workgroup
+        __syncthreads();                                      // the staging buffers are free
+        dgemm_each<GT>(acc, [&](int i, int j, double v) { lds.t[i][j] = (i < m_valid && j < n_valid) ? v : (i == j ? 1.0 : 0.0); });
+        __syncthreads();
+        diag_factor(M, n, k1, m_valid, lds);
+    } else {
+        dgemm_each<GT>(acc, [&](int i, int j, double v) {
+            if (i < m_valid && c0 + j <= r0 + i) A[(r0 + i) * n + c0 + j] = v;
+        });
+    }
+}
+// LDS of the two kernels that call it: the product's staging buffers and the factorization's share their space
+constexpr size_t STEP_LDS = std::max(sizeof(DiagLds), 2 * GK * (GT + 4) * sizeof(double));
+
+// chol_syrk's first tile columns (the next outer panel's own), with the next diagonal block's factorization
+__global__ __launch_bounds__(256, 3) void chol_syrk_diag(double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0, int w,
+                                                         int64_t k1) {
     if (blockIdx.x > blockIdx.y) return;
     __builtin_amdgcn_s_setprio(3);                            // a link of the chain, as chol_panel
-    __shared__ __align__(16) char smem[sizeof(DiagLds) > 2 * GK * (GT + 4) * sizeof(double) ? sizeof(DiagLds)
-                                                                                             : 2 * GK * (GT + 4) * sizeof(double)];
+    __shared__ __align__(16) char smem[STEP_LDS];
     double(*As)[GT + 4] = reinterpret_cast<double(*)[GT + 4]>(smem);
     double(*Bs)[GT + 4] = As + GK;
     const int64_t r0 = k1 + int64_t(blockIdx.y) * GT, c0 = k1 + int64_t(blockIdx.x) * GT;
     const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT), n_valid = static_cast<int>(n - c0 < GT ? n - c0 : GT);
     double4_t acc[GT / 32][GT / 32];
     dgemm_fill<GT>(acc, [&](int i, int j) { return (i < m_valid && j < n_valid) ? A[(r0 + i) * n + c0 + j] : 0.0; });
-    dgemm_tile<GT, true, true>(A + r0 * n + k0, n, m_valid, A + c0 * n + k0, n, n_valid, 0, w, As, Bs, acc);
-    dgemm_each<GT>(acc, [&](int i, int j, double v) {
-        if (i < m_valid && c0 + j <= r0 + i) A[(r0 + i) * n + c0 + j] = v;
-    });
-    if (blockIdx.x == 0 && blockIdx.y == 0) {                 // whole workgroup
-        __syncthreads();                                      // the tile is in memory and the staging buffers are free
-        diag_factor(A, M, n, k1, static_cast<int>(n - k1 < NB ? n - k1 : NB), *reinterpret_cast<DiagLds*>(smem));
+    dgemm_tile<GT, false, false, true>(M + k0 * n + r0, n, m_valid, M + k0 * n + c0, n, n_valid, 0, w, As, Bs, acc);
+    chol_tile_end(acc, A, M, n, k1, r0, c0, m_valid, n_valid, *reinterpret_cast<DiagLds*>(smem));
+}
+
+// One 64-wide step inside an outer panel: the panel below the diagonal block at k0 and the update of the outer panel's
+// columns behind it, in one launch.  The factorization waits for every step in turn (they leave the chip nearly idle),
+// so each workgroup makes the 64 x 64 blocks of L that its tile needs by itself, at two products more, instead of waiting
+// for a launch that makes each once (a step of the 4096-wide factor: 34 us in two launches, 28 in one,
+// and 22 with the diagonal block's faster elimination).  The first tile
+// column's workgroups keep L.
+__global__ __launch_bounds__(256, 3) void chol_step(double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0) {
+    if (blockIdx.x > blockIdx.y) return;
+    __builtin_amdgcn_s_setprio(3);
+    __shared__ __align__(16) char smem[STEP_LDS];
+    double(*As)[GT + 4] = reinterpret_cast<double(*)[GT + 4]>(smem);
+    double(*Bs)[GT + 4] = As + GK;
+    const int64_t k1 = k0 + NB, r0 = k1 + int64_t(blockIdx.y) * GT, c0 = k1 + int64_t(blockIdx.x) * GT;
+    const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT), n_valid = static_cast<int>(n - c0 < GT ? n - c0 : GT);
+    const bool square = blockIdx.x == blockIdx.y;
+    double4_t ly[2][2] = {}, lx[2][2] = {}, acc[2][2];        // L^T's blocks of the tile's rows and columns; the tile
+    if (!square) dgemm_tile<GT, true, true>(M + k0 * n + k0, n, NB, A + c0 * n + k0, n, n_valid, 0, NB, As, Bs, lx);
+    dgemm_tile<GT, true, true>(M + k0 * n + k0, n, NB, A + r0 * n + k0, n, m_valid, 0, NB, As, Bs, ly);
+    dgemm_fill<GT>(acc, [&](int i, int j) { return (i < m_valid && j < n_valid) ? A[(r0 + i) * n + c0 + j] : 0.0; });
+    if (blockIdx.x == 0)
+        dgemm_each<GT>(ly, [&](int c, int i, double v) {
+            if (i < m_valid) M[(k0 + c) * n + r0 + i] = v;
+        });
+    static_assert(NB == 2 * GK && GT == NB, "a wave row's blocks are one chunk");
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        __syncthreads();
+        if (static_cast<int>(threadIdx.x >> 7) == h) {        // the waves that hold columns GK h .. of L
+            dgemm_each<GT>(ly, [&](int c, int i, double v) { As[c - GK * h][i] = v; });
+            if (!square) dgemm_each<GT>(lx, [&](int c, int i, double v) { Bs[c - GK * h][i] = v; });
+        }
+        __syncthreads();
+        dgemm_chunk<GT, true>(As, square ? As : Bs, acc);
     }
+    chol_tile_end(acc, A, M, n, k1, r0, c0, m_valid, n_valid, *reinterpret_cast<DiagLds*>(smem));
 }
 
 // ------------------------------------------------------------------ M = inv(L), lower, by doubling
@@ -481,24 +560,27 @@ __global__ __launch_bounds__(256) void chol_syrk_diag(double* __restrict__ A, do
 // first column), then M[B rows, A columns] = -inv(B) T (PASS 1, k ends with the tile's last row).
 // TS x TS tiles, TS dividing s.
 template <int PASS, int TS>
-__global__ __launch_bounds__(256) void trinv_level(const double* __restrict__ L, double* __restrict__ M,
-                                                   double* __restrict__ T, int64_t n, int64_t s) {
+__global__ __launch_bounds__(256, 4) void trinv_level(double* __restrict__ M, double* __restrict__ T, int64_t n, int64_t s) {
     const int64_t a0 = 2 * int64_t(blockIdx.z) * s, b0 = a0 + s;
     const int64_t sb = n - b0 < s ? n - b0 : s;               // > 0 for every pair in the grid
-    const int64_t m0 = int64_t(blockIdx.y) * TS, n0 = int64_t(blockIdx.x) * TS;
+    // PASS 0's tiles get shorter from left to right: every other eight tile rows run from right to left, or the workgroups
+    // that meet on a compute unit (256 apart in a launch of 32 x 32) would all be of one column (the
+    // last level of a 4096-wide factor: 415 us, now 190 with the accumulators out of the AGPRs as well).
+    const unsigned bx = PASS == 0 && ((blockIdx.y >> 3) & 1) ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    const int64_t m0 = int64_t(blockIdx.y) * TS, n0 = int64_t(bx) * TS;
     if (m0 >= sb) return;
     __shared__ double As[GK][TS + 4], Bs[GK][TS + 4];
     const int m_valid = static_cast<int>(sb - m0 < TS ? sb - m0 : TS);
     double* Tp = T + int64_t(blockIdx.z) * s * s;
     double4_t acc[TS / 32][TS / 32] = {};
     if constexpr (PASS == 0) {
-        dgemm_tile<TS, false>(L + (b0 + m0) * n + a0, n, m_valid, M + a0 * n + a0 + n0, n, TS, n0, s, As, Bs, acc);
+        dgemm_tile<TS, false, false>(M + a0 * n + b0 + m0, n, m_valid, M + a0 * n + a0 + n0, n, TS, n0, s, As, Bs, acc);
         dgemm_each<TS>(acc, [&](int i, int j, double v) {
             if (i < m_valid) Tp[(m0 + i) * s + n0 + j] = v;
         });
     } else {
         const int64_t k_hi = sb < m0 + TS ? sb : m0 + TS;
-        dgemm_tile<TS, false>(M + (b0 + m0) * n + b0, n, m_valid, Tp + n0, s, TS, 0, k_hi, As, Bs, acc);
+        dgemm_tile<TS, true, false>(M + (b0 + m0) * n + b0, n, m_valid, Tp + n0, s, TS, 0, k_hi, As, Bs, acc);
         dgemm_each<TS>(acc, [&](int i, int j, double v) {
             if (i < m_valid) M[(b0 + m0 + i) * n + a0 + n0 + j] = -v;
         });
@@ -783,12 +865,16 @@ int launch_gptq_prepare(adadim_ctx* ctx, const float* H, int64_t n, float percda
     hipLaunchKernelGGL(gq_damp, dim3(1), dim3(256), 0, ctx->stream, dvec, n, static_cast<double>(percdamp), damp);
     if (act_order) {
         hipLaunchKernelGGL(gq_zero_i32, dim3(nb1), dim3(256), 0, ctx->stream, rank, n);
-        hipLaunchKernelGGL(gq_rank_count, dim3(nb1, static_cast<unsigned>((n + 1023) / 1024)), dim3(256), 0, ctx->stream,
+        hipLaunchKernelGGL(gq_rank_count, dim3(nb1, static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, ctx->stream,
                            dvec, n, rank);
         hipLaunchKernelGGL(gq_rank_place, dim3(nb1), dim3(256), 0, ctx->stream, rank, n, perm);
     } else
         hipLaunchKernelGGL(gq_rank, dim3(nb1), dim3(256), 0, ctx->stream, dvec, n, act_order, perm);
-    hipLaunchKernelGGL(gq_gather, dim3(nb2), dim3(256), 0, ctx->stream, H, n, perm, dvec, damp, A);
+    if (n <= 16384)                                           // 64 KB of LDS
+        hipLaunchKernelGGL(gq_gather, dim3(static_cast<unsigned>(n)), dim3(256), static_cast<size_t>(n) * 4, ctx->stream, H, n, perm,
+                           dvec, damp, A);
+    else
+        hipLaunchKernelGGL(gq_gather_wide, dim3(nb2), dim3(256), 0, ctx->stream, H, n, perm, dvec, damp, A);
     ADADIM_LAUNCH_CHECK(ctx, "gptq prepare");
     // Outer panels of 512 columns: inside a panel the 64-wide steps update the panel's own columns
     // only; the columns behind it get the whole panel at once, a product with 256 contraction steps
@@ -807,12 +893,12 @@ int launch_gptq_prepare(adadim_ctx* ctx, const float* H, int64_t n, float percda
             const int64_t rest = n - k0 - w;
             if (rest > 0) {
                 const unsigned t = static_cast<unsigned>((rest + GT - 1) / GT);
-                hipLaunchKernelGGL(chol_panel, dim3(t), dim3(256), 0, ctx->stream, A, M, n, k0, w);
                 const unsigned tc = static_cast<unsigned>((K0 + W - (k0 + w) + GT - 1) / GT);
                 if (tc > 0) {
-                    hipLaunchKernelGGL(chol_syrk_diag, dim3(tc, t), dim3(256), 0, ctx->stream, A, M, n, k0, w, k0 + w);
+                    hipLaunchKernelGGL(chol_step, dim3(tc, t), dim3(256), 0, ctx->stream, A, M, n, k0);
                     diag_ready = true;
-                }
+                } else
+                    hipLaunchKernelGGL(chol_panel, dim3(t), dim3(256), 0, ctx->stream, A, M, n, k0, w);
             }
         }
         const int64_t rest = n - K0 - W;
@@ -835,7 +921,7 @@ int launch_gptq_prepare(adadim_ctx* ctx, const float* H, int64_t n, float percda
             diag_ready = true;
             if (overlap && t > tn) {
                 ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->side, ctx->side_ev[0], 0));
-                hipLaunchKernelGGL(chol_syrk<GT>, dim3(t - tn, t), dim3(256), 0, ctx->side, A, n, K0, static_cast<int>(W),
+                hipLaunchKernelGGL(chol_syrk, dim3(t - tn, t), dim3(256), 0, ctx->side, A, M, n, K0, static_cast<int>(W),
                                    K0 + W, static_cast<int>(tn));
                 ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[1], ctx->side));
                 side_busy = true;
@@ -847,8 +933,8 @@ int launch_gptq_prepare(adadim_ctx* ctx, const float* H, int64_t n, float percda
     for (int64_t s = NB; s < n; s *= 2) {
         const unsigned pairs = static_cast<unsigned>((n - s + 2 * s - 1) / (2 * s));   // those with rows below a0 + s
         const dim3 grid(static_cast<unsigned>(s / GT), static_cast<unsigned>(s / GT), pairs);
-        hipLaunchKernelGGL((trinv_level<0, GT>), grid, dim3(256), 0, ctx->stream, A, M, T, n, s);
-        hipLaunchKernelGGL((trinv_level<1, GT>), grid, dim3(256), 0, ctx->stream, A, M, T, n, s);
+        hipLaunchKernelGGL((trinv_level<0, GT>), grid, dim3(256), 0, ctx->stream, M, T, n, s);
+        hipLaunchKernelGGL((trinv_level<1, GT>), grid, dim3(256), 0, ctx->stream, M, T, n, s);
     }
     hipLaunchKernelGGL(gq_flip, dim3(nb2), dim3(256), 0, ctx->stream, M, n, U);
     ADADIM_LAUNCH_CHECK(ctx, "gptq inverse");

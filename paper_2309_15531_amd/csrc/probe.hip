@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256) void mfma_probe(float* __restrict__ out, int i
 // The same for the fp64 instruction of the GPTQ factor: eight independent v_mfma_f64_16x16x4_f64 chains per wave.
 typedef double double4_t __attribute__((ext_vector_type(4)));
 constexpr int PROBE64_ACC = 8;
-__global__ __launch_bounds__(256) void mfma_probe_f64(float* __restrict__ out, int iters) {
+__global__ __launch_bounds__(256, 4) void mfma_probe_f64(float* __restrict__ out, int iters) {
     const double a = 1.000001 + threadIdx.x * 1e-3, b = 0.999999 - threadIdx.x * 1e-3;
     double4_t acc[PROBE64_ACC];
     for (int t = 0; t < PROBE64_ACC; ++t) acc[t] = double4_t{0.0, 0.0, 0.0, 0.0};

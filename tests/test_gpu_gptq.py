@@ -98,6 +98,31 @@ def test_prepare_matches_fp64_factor(ctx, in_f, act_order):
     assert (np.abs(Ug - U_ref) <= 2e-6 * np.abs(U_ref) + 1e-7 * np.abs(U_ref).max()).all()
 
 
+@pytest.mark.parametrize("n", [1, 15, 17, 63, 65, 79, 129, 511, 577, 640, 1025, 1601, 16400])
+def test_factor_at_block_edges(ctx, n):
+    """The factor at sizes beside its 16- and 64-wide blocks, its 512-wide panels (with and without the side stream) and the
+    LDS row of the permuting copy (n > 16384).  U H' U^T = I for the damped, permuted H'.  U is rounded once to fp32 from
+    fp64, so that the residual is at most 2 2^-24 |U|_F |U^-1|_2 <= 2^-23 sqrt(n cond(H')) (fp64 errors are far below)."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    G_ = torch.randn((n, 64), generator=g, device="cuda", dtype=torch.float64)
+    H = (G_ @ G_.T / max(n, 64) + torch.diag(1.0 + torch.rand(n, generator=g, device="cuda", dtype=torch.float64))).float()
+    perm = torch.empty(n, dtype=torch.int32, device="cuda")
+    dead = torch.empty(n, dtype=torch.uint8, device="cuda")
+    U = torch.empty((n, n), dtype=torch.float32, device="cuda")
+    ctx.adadim_gptq_prepare(H, perm, dead, U, 0.01, True)
+    p = perm.long()
+    d = H.diagonal().double()
+    assert torch.equal(p.sort().values, torch.arange(n, device="cuda")) and bool((d[p].diff() <= 0).all())
+    Hp = H.double()[p][:, p]
+    Hp.diagonal().add_(0.01 * d.mean())
+    assert torch.equal(U, U.triu())
+    Ud = U.double()
+    R = Ud @ Hp @ Ud.T
+    R.diagonal().sub_(1.0)
+    top = 2.0 + float((G_.T @ G_ / max(n, 64)).norm()) + 0.1       # >= the largest eigenvalue; the smallest is > 1
+    assert float(R.norm()) <= 2.0 ** -23 * (n * top) ** 0.5
+
+
 @pytest.mark.parametrize("out_f,in_f,dim,bits,group", [
     (128, 320, OC, 3, 64),
     (200, 264, OC, 4, 0),        # ragged last block of 8 channels, ragged row tile

@@ -15,6 +15,8 @@
 #include "mfma_tile.h"
 #include "error_dma.h"
 
+#include <algorithm>
+
 
 namespace {
 
@@ -84,6 +86,16 @@ __global__ __launch_bounds__(256) void error_prologue(SrcBatch src, int dW_dtype
     if (threadIdx.x == 0) diag[o] = s_red[0];
 }
 
+// sum over the block's 256 threads, in every thread
+__device__ __forceinline__ double finish_total(double v, double* s_red) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
+    __syncthreads();                                          // (s_red may be in use from the last total)
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
+}
+
 // loss_rows[o] = diag[o] + 2*sum_slot part[slot,o] (no diag array: the tile kernel has put half
 // the diagonal term into its row sums) for 256 rows per block, a per-block total,
 // and, in the block that finishes last, loss = sum of the block totals in block order (so the
@@ -91,6 +103,10 @@ __global__ __launch_bounds__(256) void error_prologue(SrcBatch src, int dW_dtype
 // again on exit.  With `best` given, the block that writes the launch's last loss also takes the
 // argmin of sel_losses[0..n_sel) (first minimum, NaN never wins, as select_first_min): one launch
 // and one kernel boundary less than a separate selection.
+// Few blocks and little data: what counts is the chain of dependent latencies.  A row's slots are loaded sixteen at a
+// time, the totals go through lane exchanges, and what blocks hand to each other are relaxed device-scope atomics that
+// bypass the caches, ordered by the wait behind them (loads one behind the other, trees of barriers and cache write-backs:
+// 9 us at 4 slots, 11 at 16, 45 at 136; now 6 to 9).
 __global__ __launch_bounds__(256) void error_finish(const float* __restrict__ diag_all,
                                                     const float* __restrict__ part_all, int64_t out, int n_slots,
                                                     float* __restrict__ loss_rows_all, float* __restrict__ loss_all,
@@ -98,7 +114,7 @@ __global__ __launch_bounds__(256) void error_finish(const float* __restrict__ di
                                                     unsigned int* __restrict__ ticket_all,
                                                     const float* __restrict__ sel_losses, int n_sel,
                                                     int32_t* __restrict__ best) {
-    __shared__ double s_red[256];
+    __shared__ double s_red[4];
     __shared__ bool s_last;
     // blockIdx.y = candidate
     const float* __restrict__ diag = diag_all + int64_t(blockIdx.y) * out;
@@ -111,45 +127,36 @@ __global__ __launch_bounds__(256) void error_finish(const float* __restrict__ di
     double mine = 0.0;
     if (o < out) {
         float off = 0.0f;
+#pragma unroll 16
         for (int sl = 0; sl < n_slots; ++sl) off += part[int64_t(sl) * out + o];
         const float l = (diag_all ? diag[o] : 0.0f) + 2.0f * off;
         if (loss_rows) loss_rows[o] = l;
         mine = static_cast<double>(l);
     }
-    s_red[threadIdx.x] = mine;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) s_red[threadIdx.x] += s_red[threadIdx.x + s];
-        __syncthreads();
-    }
+    const double block_total = finish_total(mine, s_red);
     if (threadIdx.x == 0) {
-        block_tot[blockIdx.x] = s_red[0];
-        __threadfence();
-        s_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+        __hip_atomic_store(block_tot + blockIdx.x, block_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the total has arrived before the ticket counts it
+        s_last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     }
     __syncthreads();
     if (!s_last) return;
-    __threadfence();
     double tot = 0.0;
-    for (unsigned b = threadIdx.x; b < gridDim.x; b += 256) tot += __builtin_nontemporal_load(block_tot + b);
-    s_red[threadIdx.x] = tot;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) s_red[threadIdx.x] += s_red[threadIdx.x + s];
-        __syncthreads();
-    }
+    for (unsigned b = threadIdx.x; b < gridDim.x; b += 256)
+        tot += __hip_atomic_load(block_tot + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    tot = finish_total(tot, s_red);
     if (threadIdx.x == 0) {
-        *loss = static_cast<float>(s_red[0]);
-        *ticket = 0u;
+        __hip_atomic_store(loss, static_cast<float>(tot), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (best) {
             unsigned int* done = ticket_all + 32;             // candidates of this launch whose loss is written
-            __threadfence();
-            if (atomicAdd(done, 1u) == gridDim.y - 1) {
-                __threadfence();
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the loss has arrived, likewise
+            if (__hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.y - 1) {
                 int b = -1;
                 float bv = 0.0f;
+#pragma unroll 8
                 for (int i = 0; i < n_sel; ++i) {
-                    const float v = __builtin_nontemporal_load(sel_losses + i);
+                    const float v = __hip_atomic_load(sel_losses + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if (v != v) continue;
                     if (b < 0 || v < bv) {
                         b = i;
@@ -157,7 +164,7 @@ __global__ __launch_bounds__(256) void error_finish(const float* __restrict__ di
                     }
                 }
                 *best = b < 0 ? 0 : b;
-                *done = 0u;
+                __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     }
@@ -194,20 +201,59 @@ struct ErrScratch {
     __half* dW16;            // per candidate scaled copy of dW (prologue path only)
 };
 
-// Contraction chunk of a launch of nc candidates, in 256-k blocks, and the number of (chunk, column block) slots:
-// whole contractions (one workgroup per tile, the cheapest in prologues and epilogues) unless that leaves fewer
-// than two workgroups per compute unit; then the largest chunk that gives that many.
+// Slots of column blocks 0 .. NB - 1 cut into chunks of kb 256-k blocks.
+int count_slots(int NB, int kb) {
+    int n = 0;
+    for (int nb = 0; nb < NB; ++nb) n += nb / kb + 1;
+    return n;
+}
+
+// The finest cut that is considered, which bounds the scratch: whole contractions when these give two workgroups per
+// compute unit, else the largest of the chunks NB / 2^i that does.
+void error_slots_finest(int nc, int MB, int NB, int& kb, int& n_slots) {
+    for (kb = NB;; kb = kb > 2 ? kb / 2 : 1) {
+        n_slots = count_slots(NB, kb);
+        if (kb == 1 || int64_t(nc) * MB * n_slots >= 512) return;
+    }
+}
+
+// Contraction chunk of a launch of nc candidates, in 256-k blocks, and the number of (chunk, column block) slots.
+// Whole contractions (one workgroup per tile, the cheapest in prologues and epilogues) when they give two workgroups per
+// compute unit.  Below that the chip would run one long column block's contraction with most of it idle, or, cut finely,
+// pay the fixed costs in several rounds of workgroups: the chunk is the one whose slowest XCD is done first.  An XCD runs
+// its units of 32 workgroups (4 slots x 8 row blocks, dealt in serpentine order as the kernel does) one after the other;
+// a unit takes its longest slot's time, fixed + blocks, and an epilogue of its own where the chunk does not end in the
+// diagonal block (or the width rules the in-loop epilogue out).  Only the ratios 2 : 5 : 4 matter; fitted to measured
+// times of all chunks of 25 launches from 1 x 512 x 512 to 2 x 1024 x 11008, where the choice is within 1 % of the best chunk
+// on average.  Against the finest cut: 1 x 4096 x 4096 97 -> 75 us, 2 x 1720 x 2760 109 -> 66, 2 x 2048 x 2048 50 -> 33,
+// 1 x 8192 x 1024 34 -> 25, 2 x 1024 x 4096 66 -> 48.
 void error_slots(int nc, int MB, int NB, int64_t in, int& kb, int& n_slots) {
-    constexpr int BT = edma::BT;
-    kb = NB;
-    for (;;) {
-        n_slots = 0;
-        for (int nb = 0; nb < NB; ++nb) {
-            const int64_t kend = in < int64_t(nb + 1) * BT ? in : int64_t(nb + 1) * BT;
-            n_slots += static_cast<int>((kend + int64_t(kb) * BT - 1) / (int64_t(kb) * BT));
+    constexpr int FIXED = 2, BLOCK = 5, EPILOGUE = 4;
+    error_slots_finest(nc, MB, NB, kb, n_slots);
+    if (kb == NB) return;
+    const int kb_min = kb, rs = (nc * MB + 7) / 8;
+    const bool in_loop = score_blocked(in) && in % edma::BT == 0;
+    int best = 0;
+    for (int k = NB; k >= kb_min; --k) {
+        int load[8] = {}, unit = 0, longest = 0, slot = 0;
+        auto deal = [&] {                                     // a group of 4 slots: rs units
+            for (int r = 0; r < rs; ++r, ++unit) load[(unit / 8) & 1 ? 7 - unit % 8 : unit % 8] += longest;
+            longest = 0;
+        };
+        for (int c = 0; c * k < NB; ++c)
+            for (int nb = NB - 1; nb >= c * k; --nb) {
+                const bool diag = nb < (c + 1) * k;           // the chunk ends in the diagonal block
+                const int cost = FIXED + BLOCK * (diag ? nb + 1 - c * k : k) + (in_loop && diag ? 0 : EPILOGUE);
+                longest = std::max(longest, cost);
+                if ((++slot & 3) == 0) deal();
+            }
+        if (slot & 3) deal();
+        const int worst = *std::max_element(load, load + 8);
+        if (best == 0 || worst < best) {
+            best = worst;
+            kb = k;
+            n_slots = slot;
         }
-        if (kb == 1 || int64_t(nc) * MB * n_slots >= 512) break;
-        kb = kb > 2 ? kb / 2 : 1;
     }
 }
 
@@ -379,7 +425,7 @@ int64_t launch_layer_error_noalloc_bytes(int n, int64_t out, int64_t in) {
     constexpr int BT = edma::BT;
     const int MB = static_cast<int>((out + BT - 1) / BT), NB = static_cast<int>((in + BT - 1) / BT);
     int kb = 0, n_slots = 0;
-    error_slots(n, MB, NB, in, kb, n_slots);
+    error_slots_finest(n, MB, NB, kb, n_slots);
     const int64_t fin_blocks = (out + 255) / 256;
     return 512 + int64_t(edma::MAX_BATCH) * fin_blocks * 8 + int64_t(n) * n_slots * out * 4;
 }

@@ -315,6 +315,31 @@ def test_layer_error_prepared_matches_and_scaled_input(ctx, in_f):
     assert got == pytest.approx([ref] * 3, rel=LOSS_RTOL)
 
 
+@pytest.mark.parametrize("nc,out_f,in_f", [(1, 8, 264), (2, 520, 2048), (1, 300, 2312), (3, 264, 1504), (1, 2056, 768),
+                                           (2, 264, 3328), (8, 1032, 1280)])
+def test_batch_error_with_cut_contractions(ctx, nc, out_f, in_f):
+    """Launches too small for whole contractions: chunks of several lengths, with and without the in-loop epilogue, both
+    layouts, ragged last chunks and row blocks; every candidate's rows against the oracle, and the fused selection."""
+    W = rand_w(out_f, in_f, seed=out_f + in_f)
+    X = synth.make_activations(300, in_f, seed=in_f, n_outliers=4, scale_lo=50, scale_hi=100)
+    hp = S.PreparedHessian(ctx, in_f).update(dev(X)).prepare()
+    H64 = oracle.hessian(X)
+    clips = S.clip_grid(max(nc, 2))[::-1][:nc]
+    dWs = [ctx.alloc_score(out_f, in_f) for _ in clips]
+    for c, d in zip(clips, dWs):
+        ctx.adadim_quantize(dev(W), OC, 3, 8, c, dW=d, dW_dtype=B.DW_F16_SCALED, colscale=hp.colscale)
+    losses = torch.full((nc,), -1.0, dtype=torch.float32, device="cuda")
+    rows = torch.full((nc, out_f), -1.0, dtype=torch.float32, device="cuda")
+    best = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    ctx.adadim_layer_error_batch_select(dWs, B.DW_F16_SCALED, hp.Hs, hp.hmeta, losses, best, loss_rows=rows, shape=(out_f, in_f))
+    torch.cuda.synchronize()
+    for i, c in enumerate(clips):
+        ref = oracle.layer_error_rows(oracle.quantize(W, OC, 3, 8, c)["dW"], H64)
+        assert losses[i].item() == pytest.approx(ref.sum(), rel=LOSS_RTOL)
+        assert np.abs(rows[i].cpu().numpy() - ref).max() <= LOSS_RTOL * ref.max()
+    assert best.item() == int(torch.argmin(losses))
+
+
 def test_layer_error_zero_and_identity(ctx):
     """dW = 0 gives exactly 0; H = I gives ||dW||_F^2."""
     n = 256

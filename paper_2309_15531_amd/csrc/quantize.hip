@@ -132,6 +132,71 @@ __global__ __launch_bounds__(256) void quant_oc_generic(const __half* __restrict
     }
 }
 
+// per-OC, groups of 8 * lpg weights with any lpg <= 63 (the streaming kernel below wants a power of two): a thread per 16-byte
+// chunk, 256 / lpg whole groups per block, minima and maxima through LDS (of eight partial ones at most, each by the thread
+// that starts its sum).  Element-wise accesses and two lanes in five idle cost 1720 x 2760 in groups of 40 38 us, this 10.
+__global__ __launch_bounds__(256) void quant_oc_chunks(const uint4* __restrict__ W, unsigned n_groups, int lpg, int64_t out, int64_t in,
+                                                       float clip, float qmax, int mfmt, uint8_t* __restrict__ codes,
+                                                       float* __restrict__ scales, uint8_t* __restrict__ zeros,
+                                                       void* __restrict__ dW, int dW_dtype, const float* __restrict__ colscale) {
+    __shared__ float s_mn[256], s_mx[256];
+    const int t = threadIdx.x, per = 256 / lpg, lg = t / lpg, i = t % lpg;
+    const unsigned grp = blockIdx.x * static_cast<unsigned>(per) + lg;
+    const bool on = lg < per && grp < n_groups;
+    const int64_t chunk = int64_t(grp) * lpg + i;
+    float w[8], mn = 0.0f, mx = 0.0f;                         // the range contains zero anyway
+    if (on) {
+        unpack8(W[chunk], w);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            mn = fminf(mn, w[e]);
+            mx = fmaxf(mx, w[e]);
+        }
+    }
+    s_mn[t] = mn;
+    s_mx[t] = mx;
+    __syncthreads();
+    if (lpg > 8) {                                            // entry i < 8 of a group takes in entries i + 8, i + 16, ...
+        if (on && i < 8)
+            for (int k = i + 8; k < lpg; k += 8) {
+                mn = fminf(mn, s_mn[lg * lpg + k]);
+                mx = fmaxf(mx, s_mx[lg * lpg + k]);
+            }
+        if (on && i < 8) {
+            s_mn[t] = mn;
+            s_mx[t] = mx;
+        }
+        __syncthreads();
+    }
+    if (!on) return;
+    for (int k = 0; k < min(lpg, 8); ++k) {
+        mn = fminf(mn, s_mn[lg * lpg + k]);
+        mx = fmaxf(mx, s_mx[lg * lpg + k]);
+    }
+    const GroupParams gp = group_params(mn, mx, clip, qmax, mfmt);
+    if (i == 0) store_params(scales, zeros, grp, gp.scale, gp.zero, mfmt);
+    if (!codes && !dW) return;
+    float q[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) q[e] = quant_code(w[e], gp.scale, gp.zero, qmax);
+    if (codes) {
+        uint32_t lo = 0, hi = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            lo |= static_cast<uint32_t>(q[e]) << (8 * e);
+            hi |= static_cast<uint32_t>(q[4 + e]) << (8 * e);
+        }
+        *reinterpret_cast<uint2*>(codes + 8 * chunk) = make_uint2(lo, hi);
+    }
+    if (dW) {
+        float d[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) d[e] = weight_error(w[e], q[e], gp.scale, gp.zero);
+        const unsigned gpr = static_cast<unsigned>(in / (8 * lpg));
+        store_dw8(dW, dW_dtype, colscale, 8 * chunk, grp / gpr, (int64_t(grp % gpr) * lpg + i) * 8, out, in, d);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Fast paths.  Same arithmetic, organised for bandwidth:
 //  * the per-weight division uses the group's correctly rounded reciprocal
@@ -1044,7 +1109,8 @@ __global__ __launch_bounds__(256) void pack_rows(const uint4* __restrict__ codes
 // per-IC: a workgroup turns 256 rows x 64 columns of codes through LDS; a thread assembles 64 codes of one column, and
 // the words leave 8 * BITS consecutive ones per column (whole 128-byte lines at 4 bits).  Rows and columns past the end
 // count as code 0 and are not stored.  (One thread per word, bytes read a row apart and words written a stream apart,
-// took 59 us on 11008 x 4096, 4 bits, 45 MB read and 22 MB written; this takes 24.)
+// took 59 us on 11008 x 4096, 4 bits, 45 MB read and 22 MB written; this takes 24.  Rows that are only 8-byte aligned:
+// 1720 x 2760 14 us with byte loads, 6 with 8-byte ones.)
 template <int BITS>
 __global__ __launch_bounds__(256) void pack_columns(const uint8_t* __restrict__ codes, int64_t out, int64_t in, int64_t n_words,
                                                     int vec, unsigned tiles_c, uint32_t* __restrict__ packed) {
@@ -1061,8 +1127,13 @@ __global__ __launch_bounds__(256) void pack_columns(const uint8_t* __restrict__ 
         v[i] = make_uint4(0, 0, 0, 0);
         if (row < out && c0 + cq < in) {
             const uint8_t* src = codes + row * in + c0 + cq;
-            if (vec) {                                        // in % 16 == 0: the sixteen are inside together
+            if (vec == 16) {                                  // in % 16 == 0: the sixteen are inside together
                 v[i] = *reinterpret_cast<const uint4*>(src);
+            } else if (vec == 8) {                            // in % 8 == 0
+                const uint2 lo = *reinterpret_cast<const uint2*>(src);
+                uint2 hi = make_uint2(0, 0);
+                if (c0 + cq + 8 < in) hi = *reinterpret_cast<const uint2*>(src + 8);
+                v[i] = make_uint4(lo.x, lo.y, hi.x, hi.y);
             } else {
                 uint32_t b[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -1239,7 +1310,7 @@ int launch_pack(adadim_ctx* ctx, const uint8_t* codes, int64_t out, int64_t in, 
         const int64_t n_words = (out * bits + 31) / 32;
         const unsigned tiles_c = static_cast<unsigned>((in + 63) / 64);
         const dim3 grid(tiles_c * static_cast<unsigned>((out + 255) / 256));
-        const int vec = (in & 15) == 0 && aligned16(codes) ? 1 : 0;
+        const int vec = (in & 15) == 0 && aligned16(codes) ? 16 : (in & 7) == 0 && (reinterpret_cast<uintptr_t>(codes) & 7u) == 0 ? 8 : 1;
 #define PACK_GO(B) hipLaunchKernelGGL(pack_columns<B>, grid, dim3(256), 0, ctx->stream, codes, out, in, n_words, vec, tiles_c, packed)
         PACK_BITS(PACK_GO)
 #undef PACK_GO
@@ -1318,6 +1389,9 @@ int launch_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t in, i
     // the fast kernels assemble the bit stream themselves for these widths
     const bool oc_wide = dim == ADADIM_DIM_OC && !oc_lanes && vec && (g % 8) == 0 && g >= 512 &&
                          out * (in / g) <= (int64_t(1) << 30);
+    // whole 16-byte chunks, at least four groups per block
+    const bool oc_chunks = dim == ADADIM_DIM_OC && !oc_lanes && !oc_wide && vec && (g % 8) == 0 && lpg <= 64 &&
+                           out * (in / g) <= (int64_t(1) << 30);
     const bool fused_pack =
         packed && (((oc_lanes || oc_wide) && (in % 32) == 0 && (bits == 2 || bits == 3 || bits == 4 || bits == 8)) ||
                    (ic_stream && ic_stream_pack_ok(lpg, bits)));
@@ -1340,6 +1414,16 @@ int launch_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t in, i
                                        fused_pack ? bits : 0, fused_pack ? packed : nullptr);
             if (rc != ADADIM_OK) return rc;
             ADADIM_LAUNCH_CHECK(ctx, "quant_oc_wide");
+        } else if (oc_chunks) {
+            const int per = 256 / lpg;
+            const unsigned n_groups = static_cast<unsigned>(out * (in / g));
+            {
+                ProfScope prof(ctx, "quant_oc_chunks");
+                hipLaunchKernelGGL(quant_oc_chunks, dim3((n_groups + per - 1) / per), dim3(256), 0, ctx->stream,
+                                   reinterpret_cast<const uint4*>(W), n_groups, lpg, out, in, clip, qmax, mfmt, codes, scales, zeros,
+                                   dW, dW_dtype, colscale);
+            }
+            ADADIM_LAUNCH_CHECK(ctx, "quant_oc_chunks");
         } else {
             const int64_t n_groups = out * (in / g);
             const unsigned blocks = static_cast<unsigned>((n_groups + 3) / 4);

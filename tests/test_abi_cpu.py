@@ -191,6 +191,22 @@ def test_code_field_plan_on_the_host(tmp_path):
     assert "2 bits: 0, 3 bits: 0, 4 bits: 0 mismatches" in res.stdout
 
 
+def test_gemv_launch_shapes_on_the_host(tmp_path):
+    """csrc/gemv_plan.h (tiles, blocks and column ranges of the matrix-vector product): over many shapes every column is
+    taken once, where every lane has a range of its own it is that of a 64-lane tile (and so the order of sums), and no launch
+    has fewer blocks than whole rounds of such tiles give."""
+    import shutil
+    import subprocess
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    exe = tmp_path / "gemv_plan_check"
+    src = os.path.join(ROOT, "tests", "host", "gemv_plan_check.cpp")
+    subprocess.run(["g++", "-O2", "-std=c++17", src, "-o", str(exe)], check=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout
+    assert " 0 mistakes" in res.stdout
+
+
 def test_gram_launch_plans_cover_every_tile_once(tmp_path):
     """csrc/gram_plan.h (which workgroup of the Gram kernel runs which tile over which tokens, and where its partial
     tile goes): for the plans the library chooses over many shapes, and for hand-made ones at the corners of the
@@ -285,7 +301,8 @@ def test_binding_refuses_tensors_the_library_would_misread():
 
 
 def test_host_checks_under_sanitizers(tmp_path):
-    """The host builds of the device headers (fast division, code-field plan, Gram launch plan) compiled with the address and
+    """The host builds of the device headers (fast division, code-field plan, launch plans of the
+    matrix-vector product and of the Gram kernel) compiled with the address and
     undefined-behaviour sanitizers: the constexpr plans and the bit manipulation the kernels share with these
     checks must be free of out-of-bounds indexing, signed overflow and shifts past the width."""
     import shutil
@@ -297,6 +314,7 @@ def test_host_checks_under_sanitizers(tmp_path):
     env.pop("LD_PRELOAD", None)                   # the sanitizer runtime has to be first in the process
     for name, extra, argv, want in (("code_fields_check", [], [], "2 bits: 0, 3 bits: 0, 4 bits: 0 mismatches"),
                                     ("fastdiv_check", ["-mfma", "-ffp-contract=off", "-pthread"], ["10", "4"], " 0 mismatches"),
+                                    ("gemv_plan_check", [], [], " 0 mistakes"),
                                     ("gram_plan_check", [], [], " 0 mistakes")):
         exe = tmp_path / (name + "_san")
         build = subprocess.run(["g++", *san, *extra, os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", str(exe)],

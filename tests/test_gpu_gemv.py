@@ -20,6 +20,9 @@ that, RSS = 128 is at least 4 times the largest ratio seen on the App. D cases. 
 (every rounding at its maximum, all of one sign) is (2 L + 4) * 2^-24 * sum_j |a_j| (1024 + qmax) with L the chain
 length, hundreds of times larger than either.
 """
+import hashlib
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -174,3 +177,32 @@ def test_gemv_tile_shapes(ctx, out_f, in_f, bits, group):
     check(y, packed, scales, zeros, x, out_f, bits, g, rows=rows)
     run_gemv(ctx, packed[:128], scales[:, :128], zeros[:, :128], x[:128], out_f, min(in_f, 128), bits, group)
     assert np.array_equal(y, run_gemv(ctx, packed, scales, zeros, x, out_f, in_f, bits, group))
+
+
+def _part_order_cases():
+    path = os.path.join(os.path.dirname(__file__), "golden", "gemv_part_order.txt")
+    for line in open(path):
+        if not line.startswith("#"):
+            *nums, digest = line.split()
+            yield (*(int(n) for n in nums), digest)
+
+
+@pytest.mark.parametrize("out_f,in_f,bits,group,meta16,digest", list(_part_order_cases()))
+def test_gemv_wide_layers_keep_their_order_of_sums(ctx, out_f, in_f, bits, group, meta16, digest):
+    """Wide layers whose column lanes have ranges of their own (gemv_plan.h), with an even and an odd number of parts, one block
+    per tile and several, ragged last tiles and ranges of unequal length: the outputs are bit for bit those of 64-lane tiles
+    whose parts a second launch adds up, so the split of a tile over lanes and blocks may change but not the order of a sum."""
+    rng = np.random.default_rng(out_f + in_f + bits)
+    g = group or out_f
+    packed = rng.integers(0, 2 ** 32, size=(in_f, out_f * bits // 32), dtype=np.uint64).astype(np.uint32)
+    scales = rng.uniform(0.004, 0.02, size=(out_f // g, in_f)).astype(np.float32)
+    zeros = rng.integers(0, 2 ** bits, size=(out_f // g, in_f)).astype(np.uint8)
+    x = rng.standard_normal(in_f).astype(np.float16)
+    if meta16:
+        words = ((scales.astype(np.float16).view(np.uint16) >> (bits - 1)).astype(np.uint32) << bits | zeros).astype(np.uint16)
+        y = torch.full((out_f,), float("nan"), dtype=torch.float16, device="cuda")
+        ctx.adadim_gemv_ic_meta16(dev(packed.view(np.int32)), dev(words.view(np.int16)), dev(x), out_f, in_f, bits, group, y)
+        y = y.cpu().numpy()
+    else:
+        y = run_gemv(ctx, packed, scales, zeros, x, out_f, in_f, bits, group).astype(np.float16)
+    assert hashlib.sha256(y.tobytes()).hexdigest() == digest

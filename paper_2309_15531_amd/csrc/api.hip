@@ -46,6 +46,7 @@ void* adadim_workspace(adadim_ctx* ctx, int slot, size_t bytes) {
     if (e != hipSuccess) {
         adadim_fail(ctx, ADADIM_EHIP, "hipMalloc(%zu bytes) for scratch slot %d: %s", want, slot,
                     hipGetErrorString(e));
+        (void)hipGetLastError();                              // (or the next call's first launch would report it)
         return nullptr;
     }
     ctx->ws[slot] = p;

@@ -25,8 +25,7 @@ enum {
     WS_ZERO,            // zero-filled buffer: source of out-of-range token rows for LDS DMA
     WS_QPART,           // partial (min, -max) pairs of the wide-group quantizer
     WS_QPAR,            // its per-group scale, zero and reciprocal
-    WS_GEMV_PART,       // per-column-chunk partial outputs of the de-quantizing matrix-vector product
-    WS_GEMV_TICKET,     // its per-output-tile counters
+    WS_GEMV_PART,       // the de-quantizing matrix-vector product's per-output-tile counters, then its partial outputs
     WS_GPTQ_A,          // fp64 reversed, permuted, damped Hessian and its Cholesky factor
     WS_GPTQ_M,          // fp64 inverse of that factor
     WS_GPTQ_D,          // fp64 diagonal and damping term
@@ -62,6 +61,7 @@ struct adadim_ctx {
     void* ws[WS_COUNT];
     size_t ws_bytes[WS_COUNT];
     size_t zero_ready_bytes;         // size of WS_ZERO when it was last cleared
+    size_t gemv_ready_bytes;         // size of WS_GEMV_PART when its counters were last cleared
     // Gram launch plans already chosen, keyed by (token count, tile count, whether whole tiles may store): choosing
     // one simulates the launch's schedule (milliseconds of host time), and a model driver alternates between a few
     // input widths

@@ -258,10 +258,13 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
         if (t + STEP * e < n_out) y[tile0 + t + STEP * e] = __float2half_rn(v[e]);
 }
 
-__global__ void gemv_zero(unsigned int* p, int n) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0u;
-}
+// Counters of the output tiles (one each; a tile of several blocks is one of at most GV_SLOTS), zero between launches: the
+// block that finds itself last clears its own.
+constexpr size_t GV_COUNTERS = GV_SLOTS * sizeof(unsigned int);
+__global__ void gemv_zero(unsigned int* counters) { counters[threadIdx.x] = 0u; }
+
+// WS_GEMV_PART with room for the counters and `bytes` behind them, or nullptr.
+char* gemv_slot(adadim_ctx* ctx, size_t bytes) { return static_cast<char*>(adadim_workspace(ctx, WS_GEMV_PART, GV_COUNTERS + bytes)); }
 
 // Measurement aid: the same code words read by the same grid, waves and column ranges as gemv_ic_tiles, with one
 // xor per word in place of the arithmetic and no parameters, x, LDS reduction or partial sums: what the kernel's
@@ -305,9 +308,9 @@ extern "C" int adadim_probe_gemv_read(adadim_ctx* ctx, const void* packed, int64
         return adadim_fail(ctx, ADADIM_EALIGN, "adadim_probe_gemv_read: packed must be 16-byte aligned");
     if (ctx->capturing) return adadim_fail(ctx, ADADIM_EINVAL, "adadim_probe_gemv_read: not while a graph is being recorded");
     const GemvPlan sh = gemv_plan(out, in, bits, 128, false);   // as launch_gemv_ic with fp32 scales of groups of 128
-    uint32_t* sink = static_cast<uint32_t*>(
-        adadim_workspace(ctx, WS_GEMV_PART, size_t(sh.tiles) * size_t(sh.chunks) * 64 * GV_WAVES * sizeof(uint32_t)));
-    if (!sink) return ADADIM_EHIP;
+    char* slot = gemv_slot(ctx, size_t(sh.tiles) * size_t(sh.chunks) * 64 * GV_WAVES * sizeof(uint32_t));
+    if (!slot) return ADADIM_EHIP;
+    uint32_t* sink = reinterpret_cast<uint32_t*>(slot + GV_COUNTERS);
     const int64_t n_words = out * bits / 32;
     const dim3 grid(static_cast<unsigned>(sh.tiles), static_cast<unsigned>(sh.chunks));
     hipEvent_t e0, e1;
@@ -348,20 +351,17 @@ extern "C" int adadim_probe_gemv_read(adadim_ctx* ctx, const void* packed, int64
 int launch_gemv_ic(adadim_ctx* ctx, const uint32_t* packed, const void* scales, const uint8_t* zeros, const __half* x,
                    int64_t out, int64_t in, int bits, int g, __half* y, bool meta16) {
     const GemvPlan sh = gemv_plan(out, in, bits, g, meta16);
-    float* part = nullptr;
-    unsigned int* ticket = nullptr;
-    if (sh.chunks > 1) {
-        part = static_cast<float*>(adadim_workspace(ctx, WS_GEMV_PART, size_t(sh.parts) * size_t(out) * sizeof(float)));
-        // one counter per output tile: zero between launches (the block that finds itself last clears it)
-        const size_t t_bytes = size_t(sh.tiles) * sizeof(unsigned int);
-        const bool fresh = ctx->ws_bytes[WS_GEMV_TICKET] < t_bytes;
-        ticket = static_cast<unsigned int*>(adadim_workspace(ctx, WS_GEMV_TICKET, t_bytes));
-        if (!part || !ticket) return ADADIM_EHIP;
-        if (fresh) {
-            const int n = static_cast<int>(ctx->ws_bytes[WS_GEMV_TICKET] / sizeof(unsigned int));
-            hipLaunchKernelGGL(gemv_zero, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, ctx->stream, ticket, n);
-            ADADIM_LAUNCH_CHECK(ctx, "gemv_zero");
-        }
+    // Room for the partial sums of whole rounds of 64-lane tiles, which no form exceeds: whether a product can be recorded
+    // after another has run depends on their sizes alone.
+    char* slot = gemv_slot(ctx, size_t(gemv_round_parts(out, in)) * size_t(out) * sizeof(float));
+    if (!slot) return ADADIM_EHIP;
+    unsigned int* ticket = reinterpret_cast<unsigned int*>(slot);
+    float* part = reinterpret_cast<float*>(slot + GV_COUNTERS);
+    if (sh.chunks > 1 && ctx->gemv_ready_bytes != ctx->ws_bytes[WS_GEMV_PART]) {
+        hipLaunchKernelGGL(gemv_zero, dim3(1), dim3(GV_SLOTS), 0, ctx->stream, ticket);
+        ADADIM_LAUNCH_CHECK(ctx, "gemv_zero");
+        // a clearing that is only recorded has not happened yet for the calls outside the graph
+        if (!ctx->capturing) ctx->gemv_ready_bytes = ctx->ws_bytes[WS_GEMV_PART];
     }
     const int64_t n_words = out * bits / 32;
     const dim3 grid(static_cast<unsigned>(sh.tiles), static_cast<unsigned>(sh.chunks));

@@ -90,3 +90,70 @@ def test_capture_refuses_what_it_cannot_record():
         assert not H.any()                                    # X = 0 gives H = 0
         ctx.adadim_graph_destroy(g)
         ctx.close()
+
+
+@pytest.mark.parametrize("meta16", [False, True])
+def test_recorded_products_replay_as_eager(meta16):
+    """The matrix-vector product keeps counters from call to call: recorded (several blocks per output tile, 8 and 16 lanes
+    along the outputs, 32 and 64 with ranges, and one that needs none), every replay with new x, with eager calls of the same
+    and of other shapes between the replays, gives what the eager call gives, bit for bit."""
+    shapes = [(512, 4096, 4, 64), (11008, 1024, 3, 128), (49152, 2560, 4, 128), (45056, 2816, 2, 128), (256, 64, 4, 32)]
+    rng = torch.Generator(device="cuda").manual_seed(3)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ctx = B.Context()
+        layers = []
+        for out_f, in_f, bits, g in shapes:
+            l = {"dims": (out_f, in_f, bits, g), "x": torch.empty(in_f, dtype=torch.float16, device="cuda"),
+                 "y": torch.empty(out_f, dtype=torch.float16, device="cuda"),
+                 "packed": torch.randint(-2 ** 31, 2 ** 31 - 1, (in_f, out_f * bits // 32), dtype=torch.int32, device="cuda", generator=rng),
+                 "zeros": torch.randint(0, 2 ** bits, (out_f // g, in_f), dtype=torch.uint8, device="cuda", generator=rng)}
+            if meta16:
+                pat = torch.randint(0x1C19 >> (bits - 1), 0x251F >> (bits - 1), (out_f // g, in_f), dtype=torch.int32, device="cuda", generator=rng)
+                l["meta"] = ((pat << bits) | l["zeros"].int()).to(torch.int16)
+            else:
+                l["scales"] = torch.empty((out_f // g, in_f), device="cuda").uniform_(0.004, 0.02, generator=rng)
+            layers.append(l)
+
+        def run(l, y):
+            if meta16:
+                ctx.adadim_gemv_ic_meta16(l["packed"], l["meta"], l["x"], *l["dims"], y)
+            else:
+                ctx.adadim_gemv_ic(l["packed"], l["scales"], l["zeros"], l["x"], *l["dims"], y)
+
+        def fill():
+            for l in layers:
+                l["x"].normal_(generator=rng)
+
+        fill()
+        for l in layers:
+            run(l, l["y"])                                    # sizes the scratch
+        torch.cuda.synchronize()
+        ctx.adadim_capture_begin()
+        for l in layers:
+            run(l, l["y"])
+        graph = ctx.adadim_capture_end()
+        for rep in range(4):
+            fill()
+            ref = [torch.empty_like(l["y"]) for l in layers]
+            for l, r in zip(layers if rep % 2 else layers[::-1], ref if rep % 2 else ref[::-1]):
+                run(l, r)
+            if rep != 1:
+                torch.cuda.synchronize()
+            for l in layers:
+                l["y"].fill_(float("nan"))
+            ctx.adadim_graph_launch(graph)
+            if rep == 2:
+                ctx.adadim_graph_launch(graph)
+            torch.cuda.synchronize()
+            for l, r in zip(layers, ref):
+                assert torch.equal(l["y"], r), (rep, l["dims"])
+                if rep == 0:
+                    out_f, in_f, bits, g = l["dims"]
+                    if not meta16 and out_f * in_f < 1 << 24:
+                        exact = oracle.gemv_ic(l["packed"].cpu().numpy().view(np.uint32), l["scales"].cpu().numpy(), l["zeros"].cpu().numpy(),
+                                               l["x"].cpu().numpy(), out_f, bits, g)
+                        assert np.abs(r.cpu().numpy() - exact).max() <= 2e-3 * np.abs(exact).max()
+        ctx.adadim_graph_destroy(graph)
+        torch.cuda.synchronize()
+        ctx.close()

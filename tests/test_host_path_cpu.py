@@ -63,3 +63,68 @@ def test_a_failed_allocation_fails_no_later_call(run):
         assert call() == EHIP
         assert call() == OK, lib.adadim_last_error(ctx)
     """)
+
+
+@pytest.mark.parametrize("what", ["hipMalloc", "gemv_zero"])
+def test_gemv_counters_are_cleared_before_their_first_use(run, what):
+    """An allocation or the clearing launch fails in the first call; the next one must clear the counters before a kernel counts
+    on them (the block that does not find itself last writes nothing, and the call would return OK)."""
+    for nth in (1, 2) if what == "hipMalloc" else (1,):
+        run(f"""
+        ctx = context()
+        fake.fake_fail(b"{what}", {nth})
+        first = gemv(ctx, 4096, 4096)
+        assert first == EHIP or (first == OK and {nth} > 1), first
+        assert gemv(ctx, 4096, 4096) == OK, lib.adadim_last_error(ctx)
+        assert gemv(ctx, 4096, 4096) == OK
+        order = [c.split()[1] for c in calls() if "gemv" in c]
+        assert "gemv_zero" in order[0] and sum("gemv_zero" in c for c in order) == 1, order
+        assert "gemv_ic_tiles" in order[-1], order
+        """)
+
+
+def test_gemv_counters_after_the_slot_grew_or_was_recorded(run):
+    """Whoever grows the slot, and whether the clearing launch ran or was only recorded, the counters are cleared by a launch
+    that has run before one that counts on them."""
+    run("""
+    ctx = context()
+    us = c_double()
+    assert gemv(ctx, 1024, 1024) == OK
+    assert lib.adadim_probe_gemv_read(ctx, A, c_int64(49152), c_int64(12288), 4, byref(us)) == OK   # grows the same scratch
+    g = c_void_p()
+    assert lib.adadim_capture_begin(ctx) == OK
+    assert gemv(ctx, 1024, 1024) == OK
+    assert lib.adadim_capture_end(ctx, byref(g)) == OK
+    fake.fake_reset()
+    assert gemv(ctx, 1024, 1024) == OK                            # the recorded clearing has not run yet
+    order = [c.split()[1] for c in calls() if "gemv" in c]
+    assert "gemv_zero" in order[0] and "gemv_ic_tiles" in order[1], order
+    fake.fake_reset()
+    assert gemv(ctx, 1024, 1024) == OK and not launched("gemv_zero")
+    lib.adadim_graph_destroy(g)
+    """)
+
+
+def test_gemv_recording_needs_no_larger_scratch_than_partial_sums_by_whole_rounds(run):
+    """Whether a product can be recorded after another one has run once: exactly when whole rounds of 64-lane tiles would need
+    no more room for their partial sums, whatever form either takes."""
+    run("""
+    def need(out, inn):
+        tiles = (out + 2047) // 2048
+        rounds = (tiles + 255) // 256
+        return min(max(1, inn // 256), max(1, rounds * 256 // tiles)) * out * 4
+    up = lambda n: (n + 255) // 256 * 256
+    shapes = [(32, 4), (32, 4096), (1024, 64), (256, 1024), (288, 1100), (4096, 4096), (4096, 11008), (11008, 4096), (16384, 8192),
+              (16416, 260), (28672, 4096), (65536, 2048), (88064, 4096), (131072, 512), (151936, 768), (300032, 64)]
+    for a in shapes:
+        for b in shapes:
+            ctx = context()
+            assert gemv(ctx, *a) == OK
+            assert lib.adadim_capture_begin(ctx) == OK
+            rc = gemv(ctx, *b)
+            assert (rc == OK) == (need(*b) <= up(need(*a))), (a, b, rc, need(*a), need(*b))
+            g = c_void_p()
+            assert lib.adadim_capture_end(ctx, byref(g)) == OK
+            lib.adadim_graph_destroy(g)
+            lib.adadim_destroy(ctx)
+    """)

@@ -260,7 +260,9 @@ int64_t adadim_noalloc_scratch_bytes(int n, int64_t out, int64_t in);
  * before 'ic').  NaN entries never win.
  *   losses    fp32 device array.   best_dev  optional device int32.
  *   host_best optional HOST int32*: if given, the call waits for the stream
- *             and stores the index there.
+ *             and stores the index there.  It passes through four bytes of
+ *             pinned host memory that the context's first such call allocates;
+ *             where there are none to be had it is copied instead.
  */
 int adadim_select(adadim_ctx* ctx, const float* losses, int n, int32_t* best_dev, int32_t* host_best);
 

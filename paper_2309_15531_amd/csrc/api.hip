@@ -467,14 +467,19 @@ int adadim_select(adadim_ctx* ctx, const float* losses, int n, int32_t* best_dev
     }
     if (host_best && ctx->capturing)
         return adadim_fail(ctx, ADADIM_EINVAL, "adadim_select: no host output while a graph is being recorded");
-    // The kernel itself leaves the index in pinned memory: a copy behind it makes a call that waits 8 us longer.
-    if (host_best && !ctx->host_best)
-        ADADIM_HIP_TRY(ctx, hipHostMalloc(reinterpret_cast<void**>(&ctx->host_best), sizeof(int32_t), hipHostMallocDefault));
+    // The kernel itself leaves the index in pinned memory: a copy behind it makes a call that waits 8 us longer, but it is
+    // what is left where there is no pinned memory to be had.
+    if (host_best && !ctx->host_best &&
+        hipHostMalloc(reinterpret_cast<void**>(&ctx->host_best), sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
+        ctx->host_best = nullptr;
+        (void)hipGetLastError();
+    }
     int rc = launch_select(ctx, losses, n, dst, host_best ? ctx->host_best : nullptr);
     if (rc != ADADIM_OK) return rc;
     if (host_best) {
+        if (!ctx->host_best) ADADIM_HIP_TRY(ctx, hipMemcpyAsync(host_best, dst, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
         ADADIM_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-        *host_best = *static_cast<volatile int32_t*>(ctx->host_best);
+        if (ctx->host_best) *host_best = *static_cast<volatile int32_t*>(ctx->host_best);
     }
     return ADADIM_OK;
 }

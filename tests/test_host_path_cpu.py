@@ -128,3 +128,21 @@ def test_gemv_recording_needs_no_larger_scratch_than_partial_sums_by_whole_round
             lib.adadim_graph_destroy(g)
             lib.adadim_destroy(ctx)
     """)
+
+
+def test_select_without_pinned_memory(run):
+    """The host's index passes through pinned memory; where none can be had the call copies it, as it did before it used any,
+    and a later call takes the pinned way again."""
+    run("""
+    ctx = context()
+    dev, host = c_int32(7), c_int32(-1)
+    fake.fake_fail(b"hipHostMalloc", 1)
+    assert lib.adadim_select(ctx, A, 2, byref(dev), byref(host)) == OK, lib.adadim_last_error(ctx)
+    assert host.value == 7
+    order = [c.split()[0] for c in calls()]
+    assert order[-2:] == ["hipMemcpyAsync", "hipStreamSynchronize"], order
+    fake.fake_reset()
+    assert lib.adadim_select(ctx, A, 2, byref(dev), byref(host)) == OK
+    assert host.value == 0 and not any("hipMemcpyAsync" in c for c in calls())     # the fake kernel left nothing there
+    lib.adadim_destroy(ctx)
+    """)

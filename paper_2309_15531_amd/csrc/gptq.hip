@@ -13,7 +13,8 @@
 // steps inside 512-wide panels: diagonal block in LDS, everything else products) and a triangular
 // inverse by doubling.
 //
-// Sweep.  Rows (per-OC) or row groups (per-IC) are independent.  Per-OC one launch does it all (gptq_rows.h).  Per-IC a
+// Sweep.  Rows (per-OC) or row groups (per-IC) are independent.  Per-OC one launch does it all (gptq_rows.h)
+// where that is faster, else a launch per block (gptq_blocks.h; rows::better).  Per-IC a
 // workgroup keeps its row group's 128-channel block in LDS and walks the channels alone: quantize channel i,
 // e = (w - q)/U_ii, w_j -= e*U_ij for the rest of the block; a second kernel applies the block's errors to the
 // channels behind the block, one channel's error at a time.  Every update is a rounded product
@@ -22,6 +23,7 @@
 // looked up by the channel's original index); per-IC recomputes each (row group, channel)'s
 // parameters from the channel's current values when it is visited.
 #include "common.h"
+#include "gptq_blocks.h"
 #include "gptq_groups.h"
 #include "gptq_rows.h"
 #include "scale_format.h"
@@ -948,7 +950,8 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
     const size_t mat = size_t(out) * size_t(in) * sizeof(float);
     float* Wp = static_cast<float*>(adadim_workspace(ctx, WS_GPTQ_W, mat));
     const bool ic = dim == ADADIM_DIM_IC;
-    float* Ep = static_cast<float*>(adadim_workspace(ctx, WS_GPTQ_E, ic ? mat : 256));
+    const bool whole = !ic && rows::better(out, in);          // per-OC, the whole sweep in one launch
+    float* Ep = static_cast<float*>(adadim_workspace(ctx, WS_GPTQ_E, whole ? 256 : mat));
     uint8_t* Qp = static_cast<uint8_t*>(adadim_workspace(ctx, WS_GPTQ_Q, size_t(out) * size_t(in)));
     int32_t* visited = static_cast<int32_t*>(adadim_workspace(ctx, WS_GPTQ_V, size_t(in) * sizeof(int32_t)));
     if (!Wp || !Ep || !Qp || !visited) return ADADIM_EHIP;
@@ -958,6 +961,7 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         hipError_t e = groups::allow_lds_of<1>();
         if (e == hipSuccess) e = groups::allow_lds_of<2>();
         if (e == hipSuccess) e = rows::allow_lds();
+        if (e == hipSuccess) e = blocks::allow_lds();
         // rows of W in LDS: 64 KB of them, or one of up to 46340 halves
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(gq_gather_w<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -977,7 +981,7 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         if (vec) hipLaunchKernelGGL(gq_gather_w<true>, grid, dim3(256), lds_bytes, ctx->stream, W, out, in, nr, perm, dead, Wp);
         else hipLaunchKernelGGL(gq_gather_w<false>, grid, dim3(256), lds_bytes, ctx->stream, W, out, in, nr, perm, dead, Wp);
     }
-    if (!ic) {
+    if (whole) {
         ProfScope prof(ctx, "gptq_sweep");
         const int r = rows::rows_per_group(out, in);
         const dim3 grid(static_cast<unsigned>((out + r - 1) / r));
@@ -1002,10 +1006,10 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
     // blocks' errors in block order: the side stream applies them in order, and the main stream
     // waits for the side stream's last launch before it adds the following block's errors to the
     // channels that launch wrote.  With per-kernel timing on, everything runs on the main stream.
-    const bool overlap = ic && !ctx->prof.enabled && in > 2 * GB;
+    const bool overlap = !whole && !ctx->prof.enabled && in > 2 * GB;
     if (overlap && !adadim_side_stream(ctx)) return ADADIM_EHIP;
     bool side_busy = false;
-    for (int64_t i1 = 0; ic && i1 < in; i1 += GB) {
+    for (int64_t i1 = 0; !whole && i1 < in; i1 += GB) {
         const int nbw = static_cast<int>(in - i1 < GB ? in - i1 : GB);
         {
             ProfScope prof(ctx, "gptq_sweep");
@@ -1013,7 +1017,11 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
     hipLaunchKernelGGL(groups::gq_group<RPL>, dim3(static_cast<unsigned>(out / g)), dim3(64 * groups::WAVES),            \
                        sizeof(groups::Lds<RPL>), ctx->stream, Wp, U, perm, in, i1, nbw, qmax, 1.0f / qmax, mfmt,         \
                        scales_out, zeros_out, Qp, Ep)
-            if (g == 64) GQ_GO(1);
+            if (!ic)
+                hipLaunchKernelGGL(blocks::gq_block, dim3(static_cast<unsigned>((out + blocks::ROWS - 1) / blocks::ROWS)), dim3(256),
+                                   sizeof(blocks::Lds), ctx->stream, Wp, U, perm, out, in, i1, nbw, g, qmax, mfmt, st_scales,
+                                   st_zeros, Qp, Ep);
+            else if (g == 64) GQ_GO(1);
             else GQ_GO(2);
 #undef GQ_GO
         }

@@ -362,11 +362,14 @@ def test_sweep_in_the_storage_format_random_shapes(ctx, out_f, in_f, dim, bits, 
     (3000, 129, 2, 43),          # 12 rows, a last block of one channel, odd row pitch
     (4090, 328, 3, 0),           # 16 rows
     (6100, 260, 4, 65),          # 24 rows
-    (8100, 136, 3, 136),         # 32 rows
-    (9000, 264, 3, 24),          # more workgroups than compute units
+    (8100, 400, 3, 100),         # 32 rows
+    (8100, 136, 3, 136),         # a launch per block: 64 rows, the last workgroup short, a ragged last block
+    (9000, 264, 3, 24),          # the same, three blocks
+    (7000, 77, 2, 11),           # the same, less than a block, odd row pitch
 ])
 def test_per_oc_sweep_rows_per_workgroup(ctx, out_f, in_f, bits, group):
-    """The per-OC sweep picks its rows per workgroup by the layer's size; each choice, against the oracle bit for bit."""
+    """The per-OC sweep picks its form and its rows per workgroup by the layer's size; each choice, against the oracle bit for
+    bit."""
     W, X = layer(out_f, in_f, 600, seed=out_f + in_f, dead=(3,))
     H32 = oracle.hessian(X).astype(np.float32)
     Hp, perm, dead = G.prepare(H32, 0.01, True)
@@ -411,3 +414,39 @@ def test_per_ic_sweep_of_many_rows(ctx, out_f, in_f, group):
     assert np.array_equal(got["scales"].view(np.uint32), ref["scales"].view(np.uint32))
     assert np.array_equal(got["dW"], ref["dW"])
     assert np.array_equal(got["packed"], oracle.pack(ref["codes"], IC, 4))
+
+
+@pytest.mark.parametrize("out_f,in_f,bits,group,meta16,piece", [
+    (16384, 4096, 3, 128, False, 4096),      # 32 rows per workgroup, two rounds of workgroups; pieces of 16 rows
+    (1024, 24576, 4, 64, True, 64),          # 4 rows per workgroup; pieces with a launch per block
+    (30000, 512, 4, 32, False, 3000),        # a launch per block, 469 workgroups, the last short; pieces of 12 rows
+    (20011, 700, 2, 28, True, 5003),         # the same with a ragged last block, odd row counts
+])
+def test_per_oc_sweep_does_not_depend_on_its_rows_neighbours(ctx, out_f, in_f, bits, group, meta16, piece):
+    """Rows are independent per-OC: a layer swept whole and in pieces of rows, which take other forms, gives the same bits."""
+    g = torch.Generator(device="cuda").manual_seed(out_f)
+    W = (torch.randn((out_f, in_f), generator=g, device="cuda") * 0.02).half()
+    U = torch.triu(torch.randn((in_f, in_f), generator=g, device="cuda") * (0.3 / in_f ** 0.5), 1)
+    U.diagonal().copy_(torch.linspace(1.0, 2.0, in_f, device="cuda"))
+    perm = torch.randperm(in_f, generator=g, device="cuda").int()
+    dead = (torch.arange(in_f, device="cuda") % 97 == 5).byte()
+
+    def sweep(W):
+        rows = W.shape[0]
+        codes, dW = torch.empty((rows, in_f), dtype=torch.uint8, device="cuda"), torch.empty((rows, in_f), device="cuda")
+        if meta16:
+            meta = torch.empty((rows, in_f // group), dtype=torch.int16, device="cuda")
+            ctx.adadim_quantize_meta16(W, OC, bits, group, 1.0, meta=meta)
+            ctx.adadim_gptq_quantize_meta16(W, OC, bits, group, U, perm, dead, codes, static_meta=meta, dW=dW)
+        else:
+            sc = torch.empty((rows, in_f // group), device="cuda")
+            z = torch.empty((rows, in_f // group), dtype=torch.uint8, device="cuda")
+            ctx.adadim_quantize(W, OC, bits, group, 1.0, scales=sc, zeros=z)
+            ctx.adadim_gptq_quantize(W, OC, bits, group, U, perm, dead, codes, static_scales=sc, static_zeros=z, dW=dW)
+        return codes, dW
+
+    codes, dW = sweep(W)
+    assert bool(torch.isfinite(dW).all())
+    for r in range(0, out_f, piece):
+        c, d = sweep(W[r:r + piece].contiguous())
+        assert torch.equal(codes[r:r + piece], c) and torch.equal(dW[r:r + piece], d), r

@@ -146,3 +146,24 @@ def test_select_without_pinned_memory(run):
     assert host.value == 0 and not any("hipMemcpyAsync" in c for c in calls())     # the fake kernel left nothing there
     lib.adadim_destroy(ctx)
     """)
+
+
+def test_per_oc_sweep_takes_the_form_that_is_faster(run):
+    """Sizes at which the one-launch sweep took 1.2 to 1.9 times as long as a launch per block (many rows, or few rows of many
+    channels), and sizes at which it takes a third to nine tenths of that."""
+    run("""
+    def form(out, inn):
+        ctx = context()
+        fake.fake_reset()
+        rc = lib.adadim_gptq_quantize(ctx, A, c_int64(out), c_int64(inn), 0, 3, 64, A, A, A, A, A, A, None, None, None, None)
+        assert rc == OK, lib.adadim_last_error(ctx)
+        n = {k: len(launched(k)) for k in ("gq_rows", "gq_block", "gq_next")}
+        blocks = (inn + 127) // 128
+        assert n in ({"gq_rows": 1, "gq_block": 0, "gq_next": 0},
+                     {"gq_rows": 0, "gq_block": blocks, "gq_next": blocks - 1 if inn > 256 else 0}), n
+        return "rows" if n["gq_rows"] else "blocks"
+    for shape in ((100000, 256), (28672, 1024), (9216, 512), (6144, 128), (300, 28672), (8, 16384)):
+        assert form(*shape) == "blocks", shape
+    for shape in ((4096, 4096), (1024, 16384), (8192, 1024), (64, 2048), (3072, 128), (4096, 11008), (16384, 8192)):
+        assert form(*shape) == "rows", shape
+    """)

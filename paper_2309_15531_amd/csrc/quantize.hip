@@ -1106,14 +1106,14 @@ __global__ __launch_bounds__(256) void pack_rows(const uint4* __restrict__ codes
     for (int i = 0; i < BITS; ++i) packed[t * BITS + i] = w[i];
 }
 
-// per-IC: a workgroup turns 256 rows x 64 columns of codes through LDS; a thread assembles 64 codes of one column, and
-// the words leave 8 * BITS consecutive ones per column (whole 128-byte lines at 4 bits).  Rows and columns past the end
-// count as code 0 and are not stored.  (One thread per word, bytes read a row apart and words written a stream apart,
-// took 59 us on 11008 x 4096, 4 bits, 45 MB read and 22 MB written; this takes 24.  Rows that are only 8-byte aligned:
-// 1720 x 2760 14 us with byte loads, 6 with 8-byte ones.)
-template <int BITS>
+// per-IC, in % 8 == 0 and 8-byte aligned codes: a workgroup turns 256 rows x 64 columns of codes through LDS; a thread
+// assembles 64 codes of one column, and the words leave 8 * BITS consecutive ones per column (whole 128-byte lines at 4
+// bits).  Rows and columns past the end count as code 0 and are not stored.  (One thread per word, bytes read a row apart and
+// words written a stream apart, took 59 us on 11008 x 4096, 4 bits, 45 MB read and 22 MB written; this takes 24.)
+// V16: in % 16 == 0 and 16-byte aligned codes.
+template <int BITS, bool V16>
 __global__ __launch_bounds__(256) void pack_columns(const uint8_t* __restrict__ codes, int64_t out, int64_t in, int64_t n_words,
-                                                    int vec, unsigned tiles_c, uint32_t* __restrict__ packed) {
+                                                    unsigned tiles_c, uint32_t* __restrict__ packed) {
     constexpr int RP = 68, WP = 8 * BITS + 1;                 // LDS pitches: bytes of a row of codes, words of a column
     __shared__ __align__(16) uint8_t s_c[256 * RP];
     __shared__ uint32_t s_w[64 * WP];
@@ -1127,19 +1127,13 @@ __global__ __launch_bounds__(256) void pack_columns(const uint8_t* __restrict__ 
         v[i] = make_uint4(0, 0, 0, 0);
         if (row < out && c0 + cq < in) {
             const uint8_t* src = codes + row * in + c0 + cq;
-            if (vec == 16) {                                  // in % 16 == 0: the sixteen are inside together
+            if constexpr (V16) {                              // the sixteen are inside together
                 v[i] = *reinterpret_cast<const uint4*>(src);
-            } else if (vec == 8) {                            // in % 8 == 0
+            } else {
                 const uint2 lo = *reinterpret_cast<const uint2*>(src);
                 uint2 hi = make_uint2(0, 0);
                 if (c0 + cq + 8 < in) hi = *reinterpret_cast<const uint2*>(src + 8);
                 v[i] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-            } else {
-                uint32_t b[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    if (c0 + cq + e < in) b[e / 4] |= static_cast<uint32_t>(src[e]) << (8 * (e & 3));
-                v[i] = make_uint4(b[0], b[1], b[2], b[3]);
             }
         }
     }
@@ -1171,20 +1165,25 @@ __global__ __launch_bounds__(256) void pack_columns(const uint8_t* __restrict__ 
     }
 }
 
-// per-OC, any length: one thread assembles one 32-bit word of a row's stream
-__global__ __launch_bounds__(256) void pack_words(const uint8_t* __restrict__ codes, int64_t out, int64_t in, int bits,
+// Any length, either dimension: one thread assembles one 32-bit word of a channel's stream.  Code k of channel ch is
+// codes[ch * ch_stride + k * el_stride] (OC: in, 1; IC: 1, in); consecutive threads take consecutive words of a channel
+// (OC) or the same word of consecutive channels (IC).  (The column packer with byte loads: 11008 x 4101, 3 bits, 83 us,
+// this 52; 513 x 515 16 and 8.)
+template <bool IC>
+__global__ __launch_bounds__(256) void pack_words(const uint8_t* __restrict__ codes, int64_t n_ch, int64_t len, int bits,
                                                   int64_t n_words, uint32_t* __restrict__ packed) {
     const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= out * n_words) return;
-    const int64_t wd = t % n_words, ch = t / n_words;
+    if (t >= n_ch * n_words) return;
+    const int64_t wd = IC ? t / n_ch : t % n_words, ch = IC ? t % n_ch : t / n_words;
+    const int64_t ch_stride = IC ? 1 : len, el_stride = IC ? n_ch : 1;
     const int64_t bit0 = wd * 32;
     uint32_t word = 0;
-    for (int64_t k = bit0 / bits; k < in && k * bits < bit0 + 32; ++k) {
-        const uint32_t code = codes[ch * in + k];
+    for (int64_t k = bit0 / bits; k < len && k * bits < bit0 + 32; ++k) {
+        const uint32_t code = codes[ch * ch_stride + k * el_stride];
         const int sh = static_cast<int>(k * bits - bit0);
         word |= sh >= 0 ? (code << sh) : (code >> (-sh));
     }
-    packed[t] = word;
+    packed[ch * n_words + wd] = word;
 }
 
 template <int LPG>
@@ -1306,14 +1305,20 @@ int launch_pack(adadim_ctx* ctx, const uint8_t* codes, int64_t out, int64_t in, 
     switch (bits) { case 2: GO(2); break; case 3: GO(3); break; case 4: GO(4); break; case 5: GO(5); break; case 6: GO(6); break; \
                     case 7: GO(7); break; default: GO(8); break; }
     ProfScope prof(ctx, "pack_words");
-    if (dim == ADADIM_DIM_IC) {
-        const int64_t n_words = (out * bits + 31) / 32;
+    const int64_t n_ch = dim == ADADIM_DIM_OC ? out : in, len = dim == ADADIM_DIM_OC ? in : out, n_words = (len * bits + 31) / 32;
+    const dim3 words(static_cast<unsigned>((n_ch * n_words + 255) / 256));
+    if (dim == ADADIM_DIM_IC && (in & 7) == 0 && (reinterpret_cast<uintptr_t>(codes) & 7u) == 0) {
         const unsigned tiles_c = static_cast<unsigned>((in + 63) / 64);
         const dim3 grid(tiles_c * static_cast<unsigned>((out + 255) / 256));
-        const int vec = (in & 15) == 0 && aligned16(codes) ? 16 : (in & 7) == 0 && (reinterpret_cast<uintptr_t>(codes) & 7u) == 0 ? 8 : 1;
-#define PACK_GO(B) hipLaunchKernelGGL(pack_columns<B>, grid, dim3(256), 0, ctx->stream, codes, out, in, n_words, vec, tiles_c, packed)
+#define PACK_GO(B)                                                                                                         \
+    if ((in & 15) == 0 && aligned16(codes))                                                                                \
+        hipLaunchKernelGGL((pack_columns<B, true>), grid, dim3(256), 0, ctx->stream, codes, out, in, n_words, tiles_c, packed); \
+    else                                                                                                                   \
+        hipLaunchKernelGGL((pack_columns<B, false>), grid, dim3(256), 0, ctx->stream, codes, out, in, n_words, tiles_c, packed)
         PACK_BITS(PACK_GO)
 #undef PACK_GO
+    } else if (dim == ADADIM_DIM_IC) {
+        hipLaunchKernelGGL(pack_words<true>, words, dim3(256), 0, ctx->stream, codes, n_ch, len, bits, n_words, packed);
     } else if ((in & 31) == 0 && aligned16(codes)) {
         const int64_t n = out * (in / 32);
         const dim3 grid(static_cast<unsigned>((n + 255) / 256));
@@ -1321,9 +1326,7 @@ int launch_pack(adadim_ctx* ctx, const uint8_t* codes, int64_t out, int64_t in, 
         PACK_BITS(PACK_GO)
 #undef PACK_GO
     } else {
-        const int64_t n_words = (in * bits + 31) / 32;
-        hipLaunchKernelGGL(pack_words, dim3(static_cast<unsigned>((out * n_words + 255) / 256)), dim3(256), 0, ctx->stream, codes, out,
-                           in, bits, n_words, packed);
+        hipLaunchKernelGGL(pack_words<false>, words, dim3(256), 0, ctx->stream, codes, n_ch, len, bits, n_words, packed);
     }
 #undef PACK_BITS
     ADADIM_LAUNCH_CHECK(ctx, "pack_words");

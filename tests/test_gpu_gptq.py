@@ -401,7 +401,7 @@ def test_sweep_outside_the_fast_quotients_range(ctx, dim, group, diag, off):
     assert np.array_equal(got["dW"], ref["dW"])
 
 
-@pytest.mark.parametrize("out_f,in_f,group", [(4160, 136, 64), (4224, 200, 128), (4096, 140, 64)])
+@pytest.mark.parametrize("out_f,in_f,group", [(4160, 136, 64), (4224, 200, 128), (4096, 140, 64), (4160, 92, 64)])
 def test_per_ic_sweep_of_many_rows(ctx, out_f, in_f, group):
     """Several rows per workgroup in the permuting copies on either side of the sweep (in a multiple of 8 and not)."""
     W, X = layer(out_f, in_f, 500, seed=out_f + in_f, dead=(3, 77))

@@ -497,27 +497,29 @@ inline int rows_per_group(int64_t out, int64_t in) {
     return best;
 }
 
-// Whether this form is the faster one for [out, in]; else a launch per block (gptq_blocks.h).  Models of both, from whole
-// calls of 137 sizes in both forms (8 to 152064 rows, 128 to 28672 channels; groups of 64, 3 bits): what they choose is at
-// most 4 % slower than the better form.  This form is bound by the chain of its rows or by the updates, which take 0.86 of the
-// time above (that counts the block's own and the next block's columns as well) and longer where a few workgroups are alone
-// in waiting for U.  A launch per block takes its workgroups of 64 rows in rounds of 46 us, then a short launch for the next
-// block, and the bulk update beside the next block's chain, half of the shorter one of the two showing where the chain's
-// workgroups fill the chip.  us, this form / a launch per block:
+// Whether this form is the faster one for [out, in]; else a launch per block (gptq_blocks.h).  Models of both, fitted to whole
+// calls of 248 sizes in both forms (8 to 152064 rows, 128 to 28672 channels; groups of 64, 3 bits): what they choose is 0.1 %
+// slower than the better form on average and 4 % at worst (by their difference alone; neither is an estimate of the call).
+// This form is bound by the chain of its rows or by the updates, which many rows per workgroup make cheaper (an error read
+// from LDS serves as many products) and a few workgroups alone dearer (they wait for U by themselves).  A launch per block
+// takes its workgroups of 64 rows in rounds, then a short launch for the next block, and the bulk update beside the next
+// block's chain, half of the shorter one of the two showing where the chain's workgroups fill the chip.
+// us, this form / a launch per block:
 //   many rows     28672 x 1024  1839 / 1466     100000 x 256  1440 / 831     9216 x 512  424 / 298     6144 x 128  70 / 60
-//   few rows of many channels   300 x 28672  24700 / 19600     8 x 16384  10070 / 8740      512 x 22016  15350 / 15310
-//   the rest      4096 x 4096  2127 / 2911     1024 x 16384  9620 / 12760     8192 x 1024  478 / 630     64 x 2048  385 / 990
+//   few rows of many channels   300 x 28672  24700 / 19600     8 x 16384  10070 / 8740      256 x 22016  15230 / 14080
+//   the rest      4096 x 4096  2127 / 2911     1024 x 16384  9620 / 12760     8192 x 1024  478 / 630     256 x 2048  389 / 1114
 inline bool better(int64_t out, int64_t in) {
     const int r = rows_per_group(out, in);
-    const int64_t wgs = (out + r - 1) / r, wgs_b = (out + 63) / 64, rounds_b = (wgs_b + 255) / 256;
-    const double scale = 0.86 * (1.0 + 0.4 / double(wgs)), chain_b = 46.0 * double(rounds_b), full = std::min(1.0, double(wgs_b) / 256.0);
+    const int64_t wgs = (out + r - 1) / r, wgs_b = (out + 63) / 64;
+    const double scale = (0.69 + 1.02 / r) * (1.0 + 0.42 / double(wgs));
+    const double chain_b = 41.5 * double((wgs_b + 255) / 256), full = std::min(1.0, double(wgs_b) / 256.0);
     double here = 0.0, there = 0.0;
     for (int64_t i1 = 0; i1 < in; i1 += GB) {
         const double upd = double(in - i1) * r * GB * 2.0 / 64.0 / 2.2e3;
         here += std::max(14.0 + 0.95 * r, scale * upd) + 3.2 + 0.23 * r;
-        const double per_channel = double(out) * GB * 2.0 / 3.7e7;              // us, spread over the chip
+        const double per_channel = double(out) * GB * 2.0 / 4.2e7;              // of the updates spread over the chip
         there += chain_b;
-        if (in - i1 > GB) there += 14.0 + double(in) / 2500.0 + per_channel * GB;
+        if (in - i1 > GB) there += 14.0 + double(in) / 2300.0 + per_channel * GB;
         if (in - i1 > 2 * GB) {
             const double bulk = per_channel * double(in - i1 - 2 * GB);
             there += std::max(bulk, chain_b) - chain_b + 0.5 * full * std::min(bulk, chain_b);

@@ -969,8 +969,7 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
     const float qmax = static_cast<float>((1 << bits) - 1);
     static PerDeviceOnce once;
     ADADIM_HIP_TRY(ctx, once.run([] {
-        hipError_t e = groups::allow_lds_of<1>();
-        if (e == hipSuccess) e = groups::allow_lds_of<2>();
+        hipError_t e = groups::allow_lds();
         if (e == hipSuccess) e = rows::allow_lds();
         if (e == hipSuccess) e = blocks::allow_lds();
         // rows of W in LDS: 64 KB of them, or one of up to 46340 halves
@@ -1020,20 +1019,21 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
     const bool overlap = !whole && !ctx->prof.enabled && in > 2 * GB;
     if (overlap && !adadim_side_stream(ctx)) return ADADIM_EHIP;
     bool side_busy = false;
+    const bool four = out / g > groups::MANY;
     for (int64_t i1 = 0; !whole && i1 < in; i1 += GB) {
         const int nbw = static_cast<int>(in - i1 < GB ? in - i1 : GB);
         {
             ProfScope prof(ctx, "gptq_sweep");
-#define GQ_GO(RPL)                                                                                                       \
-    hipLaunchKernelGGL(groups::gq_group<RPL>, dim3(static_cast<unsigned>(out / g)), dim3(64 * groups::WAVES),            \
+#define GQ_GO(RPL, WAVES)                                                                                                \
+    hipLaunchKernelGGL((groups::gq_group<RPL, WAVES>), dim3(static_cast<unsigned>(out / g)), dim3(64 * WAVES),           \
                        sizeof(groups::Lds<RPL>), ctx->stream, Wp, U, perm, in, i1, nbw, qmax, 1.0f / qmax, mfmt,         \
                        scales_out, zeros_out, Qp, Ep)
             if (!ic)
                 hipLaunchKernelGGL(blocks::gq_block, dim3(static_cast<unsigned>((out + blocks::ROWS - 1) / blocks::ROWS)), dim3(256),
                                    sizeof(blocks::Lds), ctx->stream, Wp, U, perm, out, in, i1, nbw, g, qmax, mfmt, st_scales,
                                    st_zeros, Qp, Ep);
-            else if (g == 64) GQ_GO(1);
-            else GQ_GO(2);
+            else if (g == 64) { if (four) GQ_GO(1, 4); else GQ_GO(1, 8); }
+            else { if (four) GQ_GO(2, 4); else GQ_GO(2, 8); }
 #undef GQ_GO
         }
         const int64_t behind = i1 + nbw;                        // first channel behind the block

@@ -6,9 +6,14 @@
 //
 // The walk: the strip sits in LDS, wave 0 takes 16 channels at a time into registers.  Its chain of decisions is what
 // the block waits for: minimum and maximum of the group (one wave reduction), parameters, codes, errors, updates of
-// the later channels of the sixteen.  Meanwhile the other seven waves apply the errors of the sixteen before to the
-// columns behind; then all eight apply the new errors to the next sixteen columns.  Two error buffers, taken in turn.
-// 128 rows: 55-61 us per block where the chain with IEEE divisions and four waves took 76-78.
+// the later channels of the sixteen.  Meanwhile the other waves apply the errors of the sixteen before to the
+// columns behind; then all apply the new errors to the next sixteen columns.  Two error buffers, taken in turn.
+// 128 rows: 55-61 us per block with eight waves where the chain with IEEE divisions and four waves took 76-78.
+//
+// Eight waves have all of a compute unit's registers, so no update runs beside them.  That is the faster form while the groups
+// leave the update enough of the chip; beyond 160 groups four waves are.  us, eight / four waves (IEEE divisions and
+// four waves): 64 groups of 64 x 1000 453 / 482 (657); 240 x 1000 817 / 759 (821); 272 x 2048 2979 / 2652
+// (2852); 300 groups of 128 x 2048 5777 / 5202 (5712).
 //
 // Every update is one rounded product and one rounded difference in channel order, whichever wave applies it.
 // (Measured and not kept: the workgroup applying the last block's errors to its own strip first, which takes the launch
@@ -59,7 +64,7 @@ namespace groups {
 
 using namespace chain_ns;
 
-constexpr int WAVES = 8;
+constexpr int64_t MANY = 160;          // groups from which four waves walk a block
 
 template <int RPL>
 struct Lds {
@@ -222,8 +227,8 @@ __device__ __forceinline__ void apply2(const float (&e)[RPL][SB], const float* u
 }
 
 // Block [i1, i1 + nbw) of row group blockIdx.x.
-template <int RPL>
-__global__ __launch_bounds__(64 * WAVES, 2) void gq_group(const float* __restrict__ Wp, const float* __restrict__ U,
+template <int RPL, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES / 4) void gq_group(const float* __restrict__ Wp, const float* __restrict__ U,
                                                           const int32_t* __restrict__ perm, int64_t in, int64_t i1, int nbw,
                                                           float qmax, float rqmax, int mfmt, float* __restrict__ scales_out,
                                                           uint8_t* __restrict__ zeros_out, uint8_t* __restrict__ Qp,
@@ -247,26 +252,27 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_group(const float* __restric
         return t;
     };
     {
-        // The strip and the block's corner of U (transposed in LDS): 8 lanes along a row (one 128-byte line), 64 rows at
+        // The strip and the block's corner of U (transposed in LDS): 8 lanes along a row (one 128-byte line), RS rows at
         // a time, every load issued before the first value is stored.
+        constexpr int RS = 8 * WAVES, NW = 4 * (G / RS), NU = 4 * (GB / RS);
         const int c4 = (tid & 7) * 4, kr = tid >> 3;
-        float4 cu[8], cw[4 * RPL];
+        float4 cu[NU], cw[NW];
 #pragma unroll
-        for (int q = 0; q < 4 * RPL; ++q) {
-            const int r = kr + 64 * (q >> 2), c = c4 + 32 * (q & 3);
+        for (int q = 0; q < NW; ++q) {
+            const int r = kr + RS * (q >> 2), c = c4 + 32 * (q & 3);
             cw[q] = load4(Wp + (row0 + r) * in + i1 + c, nbw - c, vec);
         }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int k = kr + 64 * (q >> 2), c = c4 + 32 * (q & 3);
+        for (int q = 0; q < NU; ++q) {
+            const int k = kr + RS * (q >> 2), c = c4 + 32 * (q & 3);
             cu[q] = k < nbw ? load4(U + (i1 + k) * in + i1 + c, nbw - c, vec_u) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
         if (tid < GB) lds.rd[tid] = block_reciprocal(tid < nbw ? U[(i1 + tid) * (in + 1)] : 1.0f);
 #pragma unroll
-        for (int q = 0; q < 4 * RPL; ++q) *reinterpret_cast<float4*>(&lds.w[kr + 64 * (q >> 2)][c4 + 32 * (q & 3)]) = cw[q];
+        for (int q = 0; q < NW; ++q) *reinterpret_cast<float4*>(&lds.w[kr + RS * (q >> 2)][c4 + 32 * (q & 3)]) = cw[q];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int k = kr + 64 * (q >> 2), c = c4 + 32 * (q & 3);
+        for (int q = 0; q < NU; ++q) {
+            const int k = kr + RS * (q >> 2), c = c4 + 32 * (q & 3);
             lds.ut[c][k] = cu[q].x;
             lds.ut[c + 1][k] = cu[q].y;
             lds.ut[c + 2][k] = cu[q].z;
@@ -329,23 +335,29 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_group(const float* __restric
         }
         if (s0 + SB >= nbw) break;                             // uniform: the last sub-block
         __syncthreads();
-        // the new errors go to the next sub-block's columns at once, two for each wave, so that the chain can go on
+        // the new errors go to the next sub-block's columns at once, two or four for each wave, so that the chain can go on
         {
             float e[RPL][SB];
 #pragma unroll
             for (int p = 0; p < RPL; ++p)
 #pragma unroll
                 for (int k = 0; k < SB; ++k) e[p][k] = es[k][lane + 64 * p];
-            apply2<RPL>(e, &lds.ut[0][0], &lds.w[0][0], s0, s0 + SB + 2 * wave);
+#pragma unroll
+            for (int c = 0; c < SB; c += 2 * WAVES) apply2<RPL>(e, &lds.ut[0][0], &lds.w[0][0], s0, s0 + SB + c + 2 * wave);
         }
         __syncthreads();
     }
 }
 
-template <int RPL>
+template <int RPL, int WAVES>
 hipError_t allow_lds_of() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(gq_group<RPL>), hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(gq_group<RPL, WAVES>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                static_cast<int>(sizeof(Lds<RPL>)));
+}
+inline hipError_t allow_lds() {
+    for (const hipError_t e : {allow_lds_of<1, 4>(), allow_lds_of<1, 8>(), allow_lds_of<2, 4>(), allow_lds_of<2, 8>()})
+        if (e != hipSuccess) return e;
+    return hipSuccess;
 }
 
 }  // namespace groups

@@ -450,3 +450,34 @@ def test_per_oc_sweep_does_not_depend_on_its_rows_neighbours(ctx, out_f, in_f, b
     for r in range(0, out_f, piece):
         c, d = sweep(W[r:r + piece].contiguous())
         assert torch.equal(codes[r:r + piece], c) and torch.equal(dW[r:r + piece], d), r
+
+
+@pytest.mark.parametrize("groups,in_f,group,bits", [(176, 520, 64, 3), (290, 77, 64, 4), (165, 264, 128, 2), (161, 1000, 128, 4)])
+def test_per_ic_sweep_of_many_groups(ctx, groups, in_f, group, bits):
+    """More groups than leave the update room beside the walk's eight waves: a layer swept whole and in pieces of few groups
+    gives the same bits; the first groups against the oracle."""
+    out_f = groups * group
+    g = torch.Generator(device="cuda").manual_seed(groups)
+    W = (torch.randn((out_f, in_f), generator=g, device="cuda") * 0.02).half()
+    U = torch.triu(torch.randn((in_f, in_f), generator=g, device="cuda") * (0.3 / in_f ** 0.5), 1)
+    U.diagonal().copy_(torch.linspace(1.0, 2.0, in_f, device="cuda"))
+    perm = torch.randperm(in_f, generator=g, device="cuda").int()
+    dead = (torch.arange(in_f, device="cuda") % 97 == 5).byte()
+
+    def sweep(W):
+        rows = W.shape[0]
+        res = {"codes": torch.empty((rows, in_f), dtype=torch.uint8, device="cuda"), "dW": torch.empty((rows, in_f), device="cuda"),
+               "scales": torch.empty((rows // group, in_f), device="cuda"),
+               "zeros": torch.empty((rows // group, in_f), dtype=torch.uint8, device="cuda")}
+        ctx.adadim_gptq_quantize(W, IC, bits, group, U, perm, dead, res["codes"], dW=res["dW"], scales=res["scales"], zeros=res["zeros"])
+        return res
+
+    whole, piece = sweep(W), 60 * group
+    for r in range(0, out_f, piece):
+        part = sweep(W[r:r + piece].contiguous())
+        for k, v in part.items():
+            lo = r // group if k in ("scales", "zeros") else r
+            assert torch.equal(whole[k][lo:lo + v.shape[0]], v), (k, r)
+    ref = G.sweep(W[:2 * group].cpu().numpy(), U.cpu().numpy(), perm.cpu().numpy(), dead.cpu().numpy().astype(bool), IC, bits, group)
+    assert np.array_equal(whole["codes"][:2 * group].cpu().numpy(), ref["codes"])
+    assert np.array_equal(whole["scales"][:2].cpu().numpy().view(np.uint32), ref["scales"].view(np.uint32))

@@ -207,3 +207,18 @@ def test_permuting_copies_by_alignment(run):
     (k0, n0), (k1, n1) = copies(8192, 65)
     assert "ILb0E" in k0 and n0 == 2048 and "ILb1ELb0E" in k1 and n1 == 2048
     """)
+
+
+def test_per_ic_walk_leaves_the_update_room(run):
+    """Eight waves of the walk fill a compute unit's registers: with more groups than leave the update the rest of the chip, four
+    (eight took up to 1.14 times as long, and longer than the form before them)."""
+    run("""
+    def threads(groups, group):
+        ctx = context()
+        fake.fake_reset()
+        assert lib.adadim_gptq_quantize(ctx, A, c_int64(groups * group), c_int64(1024), 1, 3, group, A, A, A, None, None, A, A, A, None, None) == OK
+        return {int(c.split()[4]) for c in launched("gq_group")}
+    for group in (64, 128):
+        assert threads(64, group) == threads(86, group) == {512}
+        assert threads(272, group) == threads(300, group) == {256}
+    """)

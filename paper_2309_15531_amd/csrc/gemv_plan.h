@@ -42,7 +42,8 @@ inline int64_t gemv_round_parts(int64_t out, int64_t in, int64_t* by_slots = nul
 // before: with an even number where parameters or codes come in short pieces (groups shorter than 128, columns that do not
 // start on a 128-byte line, less than four bits), with an odd number where the parameters are a
 // sixteenth of a byte or more per weight, if the tiles of 32 lanes fill two thirds of a round (they have half a part less: at
-// 151936 outputs a third of the compute units has no block).
+// 151936 outputs a third of the compute units has no block), or where more than eight parts are many to add up and those
+// tiles fill seven eighths of a round.
 // Everything smaller: tiles as narrow as it takes to have enough blocks; column lanes take turns.  At most one round of
 // blocks, and at least two steps per wave: with fewer the partial sums cost more than the shorter wait for the loads saves.
 //
@@ -56,10 +57,12 @@ inline int64_t gemv_round_parts(int64_t out, int64_t in, int64_t* by_slots = nul
 //   49152 x 12288, 3 bits  56.6  50.6  55.5        16384 x 8192, 3, w     19.3  18.5  18.5
 //   32000 x 8192, 3 bits   30.9  27.4  28.6        128256 x 4096, 3 bits  52.0  44.6  47.9
 //   32032 x 5120, 4 bits   42.5  30.5  40.1        50272 x 8192, 4 bits  109.0  75.6  90.8
-// Odd parts, ranges / turns / 64 lanes in two launches (groups of 128, the last line 32):
+// Odd parts, ranges / turns / 64 lanes in two launches (groups of 128, the third line 32,
+// the last 13 and 17 parts):
 //   88064 x 4096, 4 bits   41.0  44.1  45.8        151552 x 4096, 4 bits  64.0  76.9  72.0
 //   88064 x 4096, 3 bits   34.8  37.9  35.7        151552 x 4096, 3 bits  56.1  66.0  57.4
 //   88064 x 4096, 4 bits   74.2  64.0  78.0        45056 x 8192, 3 bits   64.5  50.0  62.8
+//   38912 x 4096, 2 bits   19.4  17.4  18.5        29696 x 7336, 4 bits   29.7  25.4  31.5
 inline GemvPlan gemv_plan(int64_t out, int64_t in, int bits, int64_t g, bool meta16) {
     GemvPlan s;
     int64_t fill = 0;
@@ -67,7 +70,7 @@ inline GemvPlan gemv_plan(int64_t out, int64_t in, int bits, int64_t g, bool met
     if (out >= 16384 && parts == fill) {
         const int tiles32 = static_cast<int>((out + 1023) / 1024), turns = std::max(1, GV_SLOTS / tiles32);
         if (parts % 2 == 0) s.ranges = bits == 4 && g >= 128 && out % 256 == 0;
-        else s.ranges = (meta16 ? 2 : 5) * 16 < g || 3 * tiles32 * turns < 2 * GV_SLOTS;
+        else s.ranges = !(((meta16 ? 2 : 5) * 16 >= g && 3 * tiles32 * turns >= 2 * GV_SLOTS) || (parts > 8 && 8 * tiles32 * turns >= 7 * GV_SLOTS));
         s.lo = s.ranges && parts % 2 != 0 ? 64 : 32;
         s.tiles = s.lo == 64 ? static_cast<int>((out + 2047) / 2048) : tiles32;
         s.chunks = static_cast<int>(s.ranges ? parts * s.lo / 64 : turns);

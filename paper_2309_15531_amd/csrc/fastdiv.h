@@ -8,8 +8,10 @@
 // 11 significant bits) and every normal fp32 s for which no intermediate leaves
 // the normal range; tests/host/fastdiv_check.cpp verifies this exhaustively over
 // all significand pairs (the operations are invariant under power-of-two
-// scaling of w and s).  Callers take the plain division when fastdiv_ok(s)
-// is false.
+// scaling of w and s).  It also equals RN(w / s) for every fp32 w in
+// [2^-60, 2^60] when s is 2^bits - 1, bits 2 to 8 (the same check takes all
+// significands of w): a group's range is divided that way.  Callers take the
+// plain division when fastdiv_ok(s) is false.
 //
 // Plain C++ (fmaf), so that the same text compiles for the host-side check and,
 // through hipcc, for the device (v_fma_f32 is a single-rounding fused op).
@@ -32,16 +34,11 @@ FASTDIV_FN float fastdiv(float w, float s, float y) {
     return fmaf(r, y, t);
 }
 
-// Correctly rounded a/b for fp32 operands of any significand, given y = RN(1/b): the quotient above corrected
-// once more.  After the first correction q is within one unit in the last place of a/b (its error before rounding
-// is about 2^-46 relative), so the residual r is exact and the second correction rounds to RN(a/b) (Markstein's
-// theorem on division with a correctly rounded reciprocal).  Holds while no intermediate leaves the normal range:
-// b and y in [2^-40, 2^40] and |a| = 0 or in [2^-80, 2^60] (the range the caller checks); an |a| below that still gives a quotient
-// that is off by less than 2^-20, which is all a caller needs that only rounds it to an integer.
-FASTDIV_FN float fastdiv_full(float a, float b, float y) {
-    float q = a * y;
-    float r = fmaf(-b, q, a);
-    q = fmaf(r, y, q);
-    r = fmaf(-b, q, a);
-    return fmaf(r, y, q);
+// For numerators of any significand fastdiv's quotient is within one unit in the last place of a / b (its error before rounding
+// is about 2^-46 relative), and correcting it once more rounds to RN(a / b): the residual a - b q is then exact (Markstein's
+// theorem on division with a correctly rounded reciprocal).  So a quotient q of fastdiv's is RN(a / b) if this
+// leaves it as it is.  Holds while no intermediate leaves the normal range: b and y = RN(1 / b) in [2^-40, 2^40], and |a| = 0 or
+// in [2^-80, 2^61].
+FASTDIV_FN float fastdiv_corrected(float a, float b, float y, float q) {
+    return fmaf(fmaf(-b, q, a), y, q);
 }

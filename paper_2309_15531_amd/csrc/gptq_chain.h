@@ -6,10 +6,10 @@
 // again with plain divisions:
 //   code   rint(w y) in place of rint(RN(w / s)), y within 2^-24 and a little of 1 / s: the same unless a half-way point
 //          lies within 2^-22 |w y| of w y (w y is off by at most 2^-23 relative, RN(w / s) by 2^-24);
-//   error  fastdiv's quotient of num = w - s k by d = U_ii, which fastdiv_full's last correction must leave as it is;
-//          num must be 0 or at least 2^-80 for that correction to be exact, and 1/d RN (block_reciprocal; NaN outside
-//          fastdiv's range, which the sweeps look for before they start a sub-block).
-// NaN, infinities and quotients above 2^21 fail the first check, which so bounds w, num and the error.
+//   error  fastdiv's quotient of num = w - s k by d = U_ii, which fastdiv_corrected must leave as it is; num must be 0 or at
+//          least 2^-80 for that correction to be exact, and 1/d RN (block_reciprocal; NaN outside fastdiv's range, which the
+//          sweeps look for before they start a sub-block).
+// NaN, infinities and quotients above 2^21 fail the first check, which so bounds w, num (s is at most 2^40) and the error.
 // The three values below are kept as unsigned bit patterns (a compare per check would hold them in scalar registers,
 // of which there are too few).
 #pragma once
@@ -31,7 +31,7 @@ struct Check {
         tie = max(tie, __float_as_uint(fmaf(fabsf(quo), 0x1p-22f, fabsf(quo - near))));
     }
     __device__ __forceinline__ void error(float n, float d, float y, float e) {
-        off |= __float_as_uint(fmaf(fmaf(-d, e, n), y, e)) ^ __float_as_uint(e);
+        off |= __float_as_uint(fastdiv_corrected(n, d, y, e)) ^ __float_as_uint(e);
         num = min(num, (__float_as_uint(n) << 1) - 1u);       // zero wraps to the top
     }
     __device__ __forceinline__ bool fine() const {

@@ -56,7 +56,7 @@ int main(int argc, char** argv) {
     // range / qmax with the reciprocal of qmax = 2^b - 1: every fp32 numerator significand, several binades
     for (int b = 2; b <= 8; ++b) {
         const float qmax = (float)((1 << b) - 1), y = 1.0f / qmax;
-        const int exps[] = {0, -20, 17, -60};
+        const int exps[] = {0, -20, 17, 40, -60};
         for (int e : exps)
             for (uint32_t m = 0; m < (1u << 23); ++m) {
                 const float rng = from_bits(((127 + e) << 23) | m);
@@ -74,9 +74,10 @@ int main(int argc, char** argv) {
         ++done;
         if (!(ref == got)) { std::printf("MISMATCH tie w=%a s=%a\n", p[0], p[1]); ++bad; }
     }
-    // fastdiv_full: numerators of any significand.  Random operands, and numerators next to the midpoints between two
-    // quotients (a = the double product of a divisor and a half-way point, rounded up and down), which is where a
-    // quotient that is not correctly rounded would show.
+    // fastdiv_corrected: numerators of any significand.  The corrected quotient is RN(a / b), so that a quotient it leaves as it is
+    // is.  Random operands, and numerators next to the midpoints between two quotients (a = the double product of a divisor and
+    // a half-way point, rounded up and down), which is where a quotient that is not correctly rounded would show; a's range
+    // up to its ends.
     {
         uint64_t st = 88172645463325252ull;
         auto rnd = [&]() { st ^= st << 13; st ^= st >> 7; st ^= st << 17; return st; };
@@ -92,9 +93,11 @@ int main(int argc, char** argv) {
                 a = static_cast<float>(half * static_cast<double>(b));
                 if (i & 2) a = std::nextafterf(a, 0.0f);
             }
-            if (!(std::fabs(a) >= 0x1p-80f && std::fabs(a) <= 0x1p60f)) continue;
+            if ((i & 24) == 8) a = from_bits(((127u - 80u) << 23) | (r >> 41));                // [2^-80, 2^-79)
+            if ((i & 24) == 16) a = from_bits(((127u + 60u) << 23) | (r >> 41));               // [2^60, 2^61)
+            if (!(std::fabs(a) >= 0x1p-80f && std::fabs(a) <= 0x1p61f)) continue;
             if (i & 4) a = -a;
-            const float ref = a / b, got = fastdiv_full(a, b, 1.0f / b);
+            const float y = 1.0f / b, ref = a / b, got = fastdiv_corrected(a, b, y, fastdiv(a, b, y));
             ++done;
             if (!(ref == got)) {
                 if (bad < 5) std::printf("MISMATCH full a=%a b=%a ref=%a got=%a\n", a, b, ref, got);

@@ -156,16 +156,22 @@ def test_gemv_appendix_shape_sampled(ctx, bits, group):
 
 
 @pytest.mark.parametrize("out_f,in_f,bits,group", [
-    (32, 4, 4, 32),              # one lane, one column quad
-    (288, 1100, 4, 32),          # 8 lanes along the outputs, one output tile and a bit, a short last step
+    (32, 4, 4, 32),              # 8 lanes along the outputs, of which one has any; one column quad
+    (288, 1100, 4, 32),          # 8 lanes, one output tile and a bit, two blocks per tile, a short last step
     (4096, 2052, 3, 0),          # 16 lanes, several blocks per tile
     (4128, 1032, 2, 96),         # 16 lanes, a last tile of one lane
-    (16416, 260, 4, 32),         # 32 lanes, one block per tile
-    (16384, 2600, 3, 128),       # 32 lanes, several blocks per tile
+    (16416, 260, 4, 32),         # 16 lanes, one block per tile
+    (16384, 2600, 3, 128),       # 16 lanes, several blocks per tile
+    (180256, 516, 3, 32),        # 32 lanes that take turns, one block per tile, a last tile of one lane
+    (90144, 1284, 3, 32),        # the same, two blocks per tile
+    (180224, 516, 4, 128),       # 32 lanes with ranges, one block per tile, ranges of unequal length
+    (129024, 1036, 4, 128),      # the same, two blocks per tile
+    (264192, 24, 3, 0),          # 64 lanes, one block per tile, waves without columns
+    (88096, 1284, 4, 0),         # 64 lanes, five blocks per tile
 ])
 def test_gemv_tile_shapes(ctx, out_f, in_f, bits, group):
     """Each choice of lanes along the outputs, with one and several blocks per output tile; twice in a row, with another
-    shape in between (the counters of the blocks must be back at zero)."""
+    shape in between (the counters of the blocks must be back at zero), whose outputs are checked too."""
     rng = np.random.default_rng(out_f + in_f + bits)
     g = group or out_f
     packed = rng.integers(0, 2 ** 32, size=(in_f, out_f * bits // 32), dtype=np.uint64).astype(np.uint32)
@@ -175,7 +181,9 @@ def test_gemv_tile_shapes(ctx, out_f, in_f, bits, group):
     rows = np.unique(np.concatenate([[0, 31, out_f - 32, out_f - 1], rng.choice(out_f, 24)]))
     y = run_gemv(ctx, packed, scales, zeros, x, out_f, in_f, bits, group)
     check(y, packed, scales, zeros, x, out_f, bits, g, rows=rows)
-    run_gemv(ctx, packed[:128], scales[:, :128], zeros[:, :128], x[:128], out_f, min(in_f, 128), bits, group)
+    n = min(in_f, 128)
+    between = run_gemv(ctx, packed[:n], scales[:, :n], zeros[:, :n], x[:n], out_f, n, bits, group)
+    check(between, packed[:n], scales[:, :n], zeros[:, :n], x[:n], out_f, bits, g, rows=rows)
     assert np.array_equal(y, run_gemv(ctx, packed, scales, zeros, x, out_f, in_f, bits, group))
 
 

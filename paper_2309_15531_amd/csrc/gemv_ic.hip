@@ -227,6 +227,7 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
         __syncthreads();
         if (s_ticket != gridDim.y - 1) return;                // ... before the block counts itself in
         if (t == 0) __hip_atomic_store(ticket + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (t >= n_out) return;
 #pragma unroll
         for (int e = 0; e < OPT; ++e) v[e] = 0.0f;
         const float* const src = part + tile0;
@@ -237,7 +238,7 @@ __global__ __launch_bounds__(64 * GV_WAVES, 4) void gemv_ic_tiles(const uint32_t
             for (unsigned c = 0; c < 8; ++c)
 #pragma unroll
                 for (int e = 0; e < OPT; ++e)
-                    p[c][e] = c0 + c < n_parts && t + STEP * e < n_out
+                    p[c][e] = c0 + c < n_parts && (e == 0 || t + STEP * e < n_out)
                                   ? __hip_atomic_load(src + int64_t(c0 + c) * out + t + STEP * e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                                   : 0.0f;
 #pragma unroll

@@ -15,6 +15,8 @@
 // four waves): 64 groups of 64 x 1000 453 / 482 (657); 240 x 1000 817 / 759 (821); 272 x 2048 2979 / 2652
 // (2852); 300 groups of 128 x 2048 5777 / 5202 (5712).
 //
+// Registers: the form of 128 rows and eight waves spills 8, read back once per sub-block outside the chain.
+//
 // Every update is one rounded product and one rounded difference in channel order, whichever wave applies it.
 // (Measured and not kept: the workgroup applying the last block's errors to its own strip first, which takes the launch
 // between two sweeps out: 25 to 50 us of one compute unit's time against 10 to 19 of the chip's; and walk and update in

@@ -16,6 +16,10 @@
 // the VALU work is spread over the whole chip; the chain takes the same time for 4 rows as for 64.  rows_per_group
 // picks R from the sizes.
 //
+// Registers: with 16 and 32 rows 24 vector registers do not fit and live in scratch (80 bytes per lane), with 8 rows 9, with 4,
+// 12 and 24 none.  They are values that hold over the block loop, read back once per block or, some six of them, once per
+// sub-block of 16 channels; none is read inside the sixteen channels' chain or the updates' product loops.
+//
 // Order of the updates of one element: blocks in order, channels inside a block in order, whichever wave applies
 // them; every update is one product and one difference.  Hence the same bits as a plain channel-by-channel loop.
 #pragma once
@@ -476,7 +480,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
 // Rows per workgroup for [out, in]: the R with the least rounds x time of one workgroup.  A block of one workgroup
 // takes the longer of the chain and the updates (R rows x remaining columns x 128 channels x 2 operations at 64 per
 // cycle), then the update of the next block's columns.  The constants (us) are measured with the clock around each part,
-// at R = 4, 16 and 32 on a 4096-wide input: chain 18, 29, 45, step between two blocks 4, 7, 10.
+// at R = 4, 16 and 32 on a 4096-wide input alone: chain 18, 29, 45, step between two blocks 4, 7, 10.
 inline int rows_per_group(int64_t out, int64_t in) {
     const int sizes[] = {4, 8, 12, 16, 24, 32};
     int best = 16;

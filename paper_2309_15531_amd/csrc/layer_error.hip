@@ -228,9 +228,10 @@ void error_slots_finest(int nc, int MB, int NB, int& kb, int& n_slots) {
 // block (or the width rules the in-loop epilogue out), by as many of the compute units as it has row blocks for.  Up to 32
 // workgroups take the longest unit's time, more the units' sum, and a round that is not full half its last unit more.  Only
 // the ratios 2 : 5 : 4 matter; compared with measured times of all chunks of 38 launches from 1 x 64 x 4096 to
-// 2 x 256 x 16384 the choice is within 1 % of the best chunk on average.  Against the finest cut: 1 x 4096 x 4096 97 -> 75 us,
-// 2 x 1720 x 2760 109 -> 66, 2 x 2048 x 2048 50 -> 33, 1 x 8192 x 1024 34 -> 25, 2 x 1024 x 4096 66 -> 48,
-// 1 x 256 x 11008 71 -> 41.
+// 2 x 256 x 16384 the choice is 1.1 % slower than the best chunk on average and 10 % at worst.  Against the finest cut:
+// 1 x 4096 x 4096 97 -> 75 us, 2 x 1720 x 2760 109 -> 66, 2 x 2048 x 2048 50 -> 33, 1 x 8192 x 1024 34 -> 25,
+// 2 x 1024 x 4096 66 -> 48, 1 x 256 x 11008 71 -> 41.  Choosing takes the host up to 1 us at ordinary sizes and 11 us at
+// 1 x 64 x 28672, on every call (profiles/scoring_chunks.md).
 void error_slots(int nc, int MB, int NB, int64_t in, int& kb, int& n_slots) {
     constexpr int FIXED = 2, BLOCK = 5, EPILOGUE = 4;
     error_slots_finest(nc, MB, NB, kb, n_slots);

@@ -157,3 +157,54 @@ def test_recorded_products_replay_as_eager(meta16):
         ctx.adadim_graph_destroy(graph)
         torch.cuda.synchronize()
         ctx.close()
+
+
+@pytest.mark.parametrize("out_f,in_f,dim,group", [
+    (9216, 520, 0, 65),          # per-OC, a launch per block, updates on the side stream
+    (1024, 520, 0, 65),          # per-OC in one launch
+    (10560, 392, 1, 64),         # per-IC, more groups than eight waves serve
+])
+def test_recorded_sweeps_replay_as_eager(out_f, in_f, dim, group):
+    """GPTQ sweeps recorded with the work they put on the context's side stream: every replay with a new weight, with eager
+    sweeps between the replays, gives the eager call's bits."""
+    rng = torch.Generator(device="cuda").manual_seed(out_f)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ctx = B.Context()
+        W = torch.empty((out_f, in_f), dtype=torch.float16, device="cuda")
+        U = torch.triu(torch.randn((in_f, in_f), generator=rng, device="cuda") * (0.3 / in_f ** 0.5), 1)
+        U.diagonal().copy_(torch.linspace(1.0, 2.0, in_f, device="cuda"))
+        perm = torch.randperm(in_f, generator=rng, device="cuda").int()
+        dead = torch.zeros(in_f, dtype=torch.uint8, device="cuda")
+        shape = (out_f, in_f // group) if dim == B.DIM_OC else (out_f // group, in_f)
+        par = {"scales": torch.empty(shape, device="cuda"), "zeros": torch.empty(shape, dtype=torch.uint8, device="cuda")}
+        kw = {"static_" + k: v for k, v in par.items()} if dim == B.DIM_OC else par
+
+        def outputs():
+            return torch.empty((out_f, in_f), dtype=torch.uint8, device="cuda"), torch.empty((out_f, in_f), device="cuda")
+
+        def sweep(codes, dW):
+            if dim == B.DIM_OC:
+                ctx.adadim_quantize(W, B.DIM_OC, 3, group, 1.0, **par)
+            ctx.adadim_gptq_quantize(W, dim, 3, group, U, perm, dead, codes, dW=dW, **kw)
+
+        W.normal_(generator=rng)
+        codes, dW = outputs()
+        sweep(codes, dW)                                      # sizes the scratch
+        torch.cuda.synchronize()
+        ctx.adadim_capture_begin()
+        sweep(codes, dW)
+        graph = ctx.adadim_capture_end()
+        for rep in range(3):
+            W.normal_(generator=rng)
+            ref = outputs()
+            sweep(*ref)
+            if rep:
+                torch.cuda.synchronize()
+            codes.fill_(255); dW.fill_(float("nan"))
+            ctx.adadim_graph_launch(graph)
+            torch.cuda.synchronize()
+            assert torch.equal(codes, ref[0]) and torch.equal(dW, ref[1]), rep
+        ctx.adadim_graph_destroy(graph)
+        torch.cuda.synchronize()
+        ctx.close()

@@ -962,7 +962,8 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
     float* Wp = static_cast<float*>(adadim_workspace(ctx, WS_GPTQ_W, mat));
     const bool ic = dim == ADADIM_DIM_IC;
     const bool whole = !ic && rows::better(out, in);          // per-OC, the whole sweep in one launch
-    float* Ep = static_cast<float*>(adadim_workspace(ctx, WS_GPTQ_E, whole ? 256 : mat));
+    // (not used by a whole sweep; with it, whether a sweep can be recorded after another depends on their sizes alone)
+    float* Ep = static_cast<float*>(adadim_workspace(ctx, WS_GPTQ_E, mat));
     uint8_t* Qp = static_cast<uint8_t*>(adadim_workspace(ctx, WS_GPTQ_Q, size_t(out) * size_t(in)));
     int32_t* visited = static_cast<int32_t*>(adadim_workspace(ctx, WS_GPTQ_V, size_t(in) * sizeof(int32_t)));
     if (!Wp || !Ep || !Qp || !visited) return ADADIM_EHIP;

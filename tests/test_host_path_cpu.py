@@ -222,3 +222,23 @@ def test_per_ic_walk_leaves_the_update_room(run):
         assert threads(64, group) == threads(86, group) == {512}
         assert threads(272, group) == threads(300, group) == {256}
     """)
+
+
+def test_sweep_recording_depends_on_sizes_alone(run):
+    """A sweep can be recorded after one of at least its size has run, whichever dimension or form either takes."""
+    run("""
+    def sweep(ctx, out, inn, dim):
+        tail = (A, A, A, None, None, None, None) if dim == 0 else (None, None, A, A, A, None, None)
+        return lib.adadim_gptq_quantize(ctx, A, c_int64(out), c_int64(inn), dim, 3, 64, A, A, A, *tail)
+    for warm in ((16384, 4096, 0), (16384, 4096, 1), (100032, 512, 0), (4096, 4096, 0)):
+        for call in ((9216, 512, 0), (4096, 4096, 0), (4096, 4096, 1), (100032, 128, 0), (300, 8192, 0)):
+            ctx = context()
+            assert sweep(ctx, *warm) == OK
+            assert lib.adadim_capture_begin(ctx) == OK
+            rc = sweep(ctx, *call)
+            assert (rc == OK) == (call[0] * call[1] <= warm[0] * warm[1] and call[1] <= warm[1]), (warm, call, rc)
+            g = c_void_p()
+            assert lib.adadim_capture_end(ctx, byref(g)) == OK
+            lib.adadim_graph_destroy(g)
+            lib.adadim_destroy(ctx)
+    """)

@@ -354,11 +354,13 @@ int launch_layer_error(adadim_ctx* ctx, int n, const void* const* dW, int dW_dty
     for (int c0 = 0; c0 < n; c0 += edma::MAX_BATCH) {
         const int nc = n - c0 < edma::MAX_BATCH ? n - c0 : edma::MAX_BATCH;
         int kb = 0, n_slots = 0;
-        error_slots(nc, MB, NB, in, kb, n_slots);
-        // scratch: per candidate [n_slots, out] row partials; then per candidate [out] diagonal terms
+        error_slots_finest(nc, MB, NB, kb, n_slots);
+        // scratch: per candidate [n_slots, out] row partials; then per candidate [out] diagonal terms.  Room for the finest cut,
+        // so that which calls can be recorded after which does not hang on the chunk that is chosen.
         sc.part = static_cast<float*>(adadim_workspace(
             ctx, WS_ERR_PART, size_t(nc) * size_t(n_slots + 1) * size_t(out) * sizeof(float)));
         if (!sc.part) return ADADIM_EHIP;
+        error_slots(nc, MB, NB, in, kb, n_slots);
         sc.diag = sc.part + size_t(nc) * size_t(n_slots) * size_t(out);
         // scratch of the final reduction: per candidate one double per 256 rows; then the tickets
         const unsigned fin_blocks = static_cast<unsigned>((out + 255) / 256);

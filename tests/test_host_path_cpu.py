@@ -242,3 +242,38 @@ def test_sweep_recording_depends_on_sizes_alone(run):
             lib.adadim_graph_destroy(g)
             lib.adadim_destroy(ctx)
     """)
+
+
+def test_scoring_recording_depends_on_the_finest_cut(run):
+    """Whether a scoring call can be recorded after another: when the finest cut of its contractions that is considered needs no
+    more room for row partials, whatever chunk either is given."""
+    run("""
+    def need(n, out, inn):
+        MB, NB = (out + 255) // 256, (inn + 255) // 256
+        kb = NB
+        while True:
+            slots = sum(nb // kb + 1 for nb in range(NB))
+            if kb == 1 or n * MB * slots >= 512:
+                break
+            kb = kb // 2 if kb > 2 else 1
+        return n * (slots + 1) * out * 4
+    def totals(out):
+        return 8 * ((out + 255) // 256) * 8 + 256
+    up = lambda n: (n + 255) // 256 * 256
+    def score(ctx, n, out, inn):
+        arr = (c_void_p * n)(*[A.value] * n)
+        return lib.adadim_layer_error_batch(ctx, n, arr, 2, c_int64(out), c_int64(inn), A, A, None, A)
+    shapes = [(1, 64, 64), (2, 512, 512), (1, 4096, 4096), (2, 1720, 2760), (2, 2048, 2048), (1, 8192, 1024), (1, 256, 11008),
+              (8, 256, 4096), (3, 600, 3072), (1, 64, 16384), (2, 4096, 4096), (4, 300, 3000)]
+    for a in shapes:
+        for b in shapes:
+            ctx = context()
+            assert score(ctx, *a) == OK, lib.adadim_last_error(ctx)
+            assert lib.adadim_capture_begin(ctx) == OK
+            rc = score(ctx, *b)
+            assert (rc == OK) == (need(*b) <= up(need(*a)) and totals(b[1]) <= up(totals(a[1]))), (a, b, rc)
+            g = c_void_p()
+            assert lib.adadim_capture_end(ctx, byref(g)) == OK
+            lib.adadim_graph_destroy(g)
+            lib.adadim_destroy(ctx)
+    """)

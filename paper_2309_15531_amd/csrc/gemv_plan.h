@@ -44,8 +44,9 @@ inline int64_t gemv_round_parts(int64_t out, int64_t in, int64_t* by_slots = nul
 // sixteenth of a byte or more per weight, if the tiles of 32 lanes fill two thirds of a round (they have half a part less: at
 // 151936 outputs a third of the compute units has no block), or where more than eight parts are many to add up and those
 // tiles fill seven eighths of a round.
-// Everything smaller: tiles as narrow as it takes to have enough blocks; column lanes take turns.  At most one round of
-// blocks, and at least two steps per wave: with fewer the partial sums cost more than the shorter wait for the loads saves.
+// Everything smaller: tiles as narrow as it takes to have enough blocks; column lanes take turns.  Tiles are cut into several
+// blocks up to one round of them, with at least two steps per wave: with fewer the partial sums cost more than the shorter
+// wait for the loads saves.
 //
 // Measured back to back, weights beyond the caches, us.  Small, LO = 8 / 16, and 64 in two launches:
 //   4096 x 4096, 4 bits     8.2   8.3  19.8        4096 x 4096, 3 bits     8.8   8.2  20.1

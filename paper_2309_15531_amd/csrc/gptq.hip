@@ -1020,7 +1020,7 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
     const bool overlap = !whole && !ctx->prof.enabled && in > 2 * GB;
     if (overlap && !adadim_side_stream(ctx)) return ADADIM_EHIP;
     bool side_busy = false;
-    const bool four = out / g > groups::MANY;
+    const bool four = in > 2 * GB && out / g > groups::MANY;   // an update beside the walk, and many groups
     for (int64_t i1 = 0; !whole && i1 < in; i1 += GB) {
         const int nbw = static_cast<int>(in - i1 < GB ? in - i1 : GB);
         {

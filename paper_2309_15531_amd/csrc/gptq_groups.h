@@ -13,7 +13,8 @@
 // Eight waves have all of a compute unit's registers, so no update runs beside them.  That is the faster form while the groups
 // leave the update enough of the chip; beyond 160 groups four waves are.  us, eight / four waves (IEEE divisions and
 // four waves): 64 groups of 64 x 1000 453 / 482 (657); 240 x 1000 817 / 759 (821); 272 x 2048 2979 / 2652
-// (2852); 300 groups of 128 x 2048 5777 / 5202 (5712).
+// (2852); 300 groups of 128 x 2048 5777 / 5202 (5712).  Up to 256 channels there is no update to leave room for, and eight are
+// the faster form of any number: 389 groups of 64 x 256 201 / 211; 389 x 128 96 / 100.
 //
 // Registers: the form of 128 rows and eight waves spills 8, read back once per sub-block outside the chain.
 //
@@ -66,7 +67,7 @@ namespace groups {
 
 using namespace chain_ns;
 
-constexpr int64_t MANY = 160;          // groups from which four waves walk a block
+constexpr int64_t MANY = 160;          // groups beyond which four waves walk a block that has updates beside it
 
 template <int RPL>
 struct Lds {

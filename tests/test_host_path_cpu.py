@@ -211,16 +211,18 @@ def test_permuting_copies_by_alignment(run):
 
 def test_per_ic_walk_leaves_the_update_room(run):
     """Eight waves of the walk fill a compute unit's registers: with more groups than leave the update the rest of the chip, four
-    (eight took up to 1.14 times as long, and longer than the form before them)."""
+    (eight took up to 1.14 times as long, and longer than the form before them).  Up to 256 channels nothing runs beside the walk
+    and eight serve (four took up to 1.08 times as long)."""
     run("""
-    def threads(groups, group):
+    def threads(groups, group, inn=1024):
         ctx = context()
         fake.fake_reset()
-        assert lib.adadim_gptq_quantize(ctx, A, c_int64(groups * group), c_int64(1024), 1, 3, group, A, A, A, None, None, A, A, A, None, None) == OK
+        assert lib.adadim_gptq_quantize(ctx, A, c_int64(groups * group), c_int64(inn), 1, 3, group, A, A, A, None, None, A, A, A, None, None) == OK
         return {int(c.split()[4]) for c in launched("gq_group")}
     for group in (64, 128):
         assert threads(64, group) == threads(86, group) == {512}
-        assert threads(272, group) == threads(300, group) == {256}
+        assert threads(272, group) == threads(300, group) == threads(300, group, 260) == {256}
+        assert threads(300, group, 128) == threads(300, group, 151) == threads(300, group, 256) == {512}
     """)
 
 

@@ -602,9 +602,8 @@ __global__ void gq_flip(const double* __restrict__ M, int64_t n, float* __restri
 // into LDS (dead channels as zero) and permuted from there (a thread per element reading W[r][perm[i]] from memory
 // fetched a separate 64-byte piece for every two bytes it used).  Dynamic LDS: nr * in halves.
 // VEC: in % 8 == 0 and 16-byte aligned W and perm, 8-byte aligned dead: 8 channels per load, 4 per store, and a piece of
-// perm serves the nr rows.  11008 x 4096, 270 MB: 53 us, where an element at a time takes 113.  An element at a time nr is 1
-// unless a row leaves half of the threads idle: what counts is how many workgroups there are to hide the trips (11008 x 4090
-// 113 us, with four rows per workgroup 192; 100032 x 66 49 and 44).
+// perm serves the nr rows.  11008 x 4096, 270 MB: 53 us, where an element at a time takes 68 (11008 x 4090; with a row
+// per workgroup 88; 25600 x 2047 70 and 140; 76800 x 259 34 and 72).
 template <bool VEC>
 __global__ __launch_bounds__(256) void gq_gather_w(const __half* __restrict__ W, int64_t out, int64_t in, int nr,
                                                    const int32_t* __restrict__ perm, const uint8_t* __restrict__ dead,
@@ -665,8 +664,9 @@ __global__ void gq_invperm(const int32_t* __restrict__ perm, int64_t in, int32_t
 // group per-IC: nr divides 64): their codes in visiting order are read once into LDS and looked up there; the writes
 // (and the reads of W and the parameters) are consecutive.  Dynamic LDS: nr * in bytes.
 // VEC: in % 8 == 0 and 16-byte aligned W, dW and parameters, 8-byte aligned codes and dead: 8 channels at a time.
-// 11008 x 4096 with dW, 360 MB: 79 us, where an element at a time takes 224.  An element at a time nr is as for
-// the copy before the sweep (11008 x 4090 226 us, with four rows per workgroup 266; 100032 x 66 76 and 60).
+// 11008 x 4096 with dW, 360 MB: 79 us, where an element at a time takes 218.  An element at a time nr is 1
+// unless the rows are short and many: what counts is how many workgroups there are to hide the trips (11008 x 4090 218 us,
+// with four rows per workgroup 258; 4096 x 1022 16 and 22; 38400 x 514 96 and 87; 76800 x 259 110 and 88).
 template <bool IC, bool VEC>
 __global__ __launch_bounds__(256) void gq_scatter(const uint8_t* __restrict__ Qp, const int32_t* __restrict__ visited,
                                                   const uint8_t* __restrict__ dead, const __half* __restrict__ W, int64_t out,
@@ -986,7 +986,7 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         ProfScope prof(ctx, "gptq_gather");
         // up to four rows per workgroup, as long as four workgroups fit a compute unit's LDS and the chip stays full
         const bool vec = (in & 7) == 0 && aligned16(W) && aligned16(perm) && (reinterpret_cast<uintptr_t>(dead) & 7u) == 0;
-        const int nr = in <= (vec ? 5000 : 128) && out >= 4096 ? 4 : vec && in <= 10000 && out >= 2048 ? 2 : 1;
+        const int nr = in <= 5000 && out >= 4096 ? 4 : in <= 10000 && out >= 2048 ? 2 : 1;
         const dim3 grid(static_cast<unsigned>((out + nr - 1) / nr));
         const size_t lds_bytes = size_t(nr) * size_t(in) * 2;
         if (vec) hipLaunchKernelGGL(gq_gather_w<true>, grid, dim3(256), lds_bytes, ctx->stream, W, out, in, nr, perm, dead, Wp);
@@ -1070,7 +1070,8 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         const bool vec = (in & 7) == 0 && aligned16(W) && aligned16(dW) && (reinterpret_cast<uintptr_t>(dead) & 7u) == 0 &&
                          (reinterpret_cast<uintptr_t>(codes) & 7u) == 0 &&
                          (!ic || (aligned16(sc) && (reinterpret_cast<uintptr_t>(zp) & 7u) == 0));
-        const int nr = in <= (vec ? 10000 : 128) && out >= 4096 ? 4 : 1;       // (nr divides a per-IC group)
+        const bool share = vec ? in <= 10000 && out >= 4096 : in <= 128 ? out >= 4096 : in <= 600 && out >= 8192;
+        const int nr = share ? 4 : 1;                                          // (divides a per-IC group)
         const dim3 grid(static_cast<unsigned>((out + nr - 1) / nr));
         const size_t lds_bytes = size_t(nr) * size_t(in);
 #define GQ_SC(IC, VEC)                                                                                                   \

@@ -190,18 +190,22 @@ def test_packers_by_alignment(run):
 
 
 def test_permuting_copies_by_alignment(run):
-    """Rows share a workgroup in the copies on either side of the sweep where several channels are read at a time, or where a
-    row alone leaves half of the threads idle (else sharing took up to twice as long)."""
+    """Rows share a workgroup in the copy before the sweep at any alignment (a row each took up to twice as long), in the copy
+    after it where several channels are read at a time or a short row leaves threads idle (else sharing took up to 1.4 times as
+    long)."""
     run("""
     def copies(out, inn):
         ctx = context()
         fake.fake_reset()
         assert lib.adadim_gptq_quantize(ctx, A, c_int64(out), c_int64(inn), 1, 3, 64, A, A, A, None, None, A, A, A, None, None) == OK
         return [(c.split()[1], int(c.split()[2])) for c in launched("gq_gather_w") + launched("gq_scatter")]
-    for out, inn in ((4096, 4090), (4096, 513), (2048, 9999)):
+    for out, inn, share in ((4096, 4090, 4), (4096, 513, 4), (2048, 9999, 2), (1024, 514, 1)):
         (k0, n0), (k1, n1) = copies(out, inn)
-        assert "ILb0E" in k0 and n0 == out, (k0, n0)
+        assert "ILb0E" in k0 and n0 == out // share, (k0, n0)
         assert "ILb1ELb0E" in k1 and n1 == out, (k1, n1)
+    for out, inn in ((8192, 514), (16384, 259)):
+        (k1, n1) = copies(out, inn)[1]
+        assert "ILb1ELb0E" in k1 and n1 == out // 4, (k1, n1)
     (k0, n0), (k1, n1) = copies(4096, 4096)
     assert "ILb1E" in k0 and n0 == 1024 and "ILb1ELb1E" in k1 and n1 == 1024
     (k0, n0), (k1, n1) = copies(8192, 65)

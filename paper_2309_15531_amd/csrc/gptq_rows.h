@@ -507,16 +507,19 @@ inline int rows_per_group(int64_t out, int64_t in) {
 // This form is bound by the chain of its rows or by the updates, which many rows per workgroup make cheaper (an error read
 // from LDS serves as many products) and a few workgroups alone dearer (they wait for U by themselves).  A launch per block
 // takes its workgroups of 64 rows in rounds, then a short launch for the next block, and the bulk update beside the next
-// block's chain, half of the shorter one of the two showing where the chain's workgroups fill the chip.
+// block's chain, half of the shorter one of the two showing where the chain's workgroups fill the chip.  Channels that are no
+// multiple of four make a launch per block dearer: it stores codes and errors one at a time (fitted to 169 more sizes, 512 to
+// 40000 rows of 131 to 4098 channels: 0.1 % on average, 8 % at worst).
 // us, this form / a launch per block:
 //   many rows     28672 x 1024  1839 / 1466     100000 x 256  1440 / 831     9216 x 512  424 / 298     6144 x 128  70 / 60
 //   few rows of many channels   300 x 28672  24700 / 19600     8 x 16384  10070 / 8740      256 x 22016  15230 / 14080
 //   the rest      4096 x 4096  2127 / 2911     1024 x 16384  9620 / 12760     8192 x 1024  478 / 630     256 x 2048  389 / 1114
+//   ragged        8192 x 333  172 / 222    7280 x 493  247 / 326    16384 x 2159  2596 / 2981    16384 x 493  466 / 370
 inline bool better(int64_t out, int64_t in) {
     const int r = rows_per_group(out, in);
     const int64_t wgs = (out + r - 1) / r, wgs_b = (out + 63) / 64;
     const double scale = (0.69 + 1.02 / r) * (1.0 + 0.42 / double(wgs));
-    const double chain_b = 41.5 * double((wgs_b + 255) / 256), full = std::min(1.0, double(wgs_b) / 256.0);
+    const double chain_b = (in % 4 ? 55.0 : 41.5) * double((wgs_b + 255) / 256), full = std::min(1.0, double(wgs_b) / 256.0);
     double here = 0.0, there = 0.0;
     for (int64_t i1 = 0; i1 < in; i1 += GB) {
         const double upd = double(in - i1) * r * GB * 2.0 / 64.0 / 2.2e3;

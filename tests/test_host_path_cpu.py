@@ -155,7 +155,7 @@ def test_per_oc_sweep_takes_the_form_that_is_faster(run):
     def form(out, inn):
         ctx = context()
         fake.fake_reset()
-        rc = lib.adadim_gptq_quantize(ctx, A, c_int64(out), c_int64(inn), 0, 3, 64, A, A, A, A, A, A, None, None, None, None)
+        rc = lib.adadim_gptq_quantize(ctx, A, c_int64(out), c_int64(inn), 0, 3, 64 if inn % 64 == 0 else inn, A, A, A, A, A, A, None, None, None, None)
         assert rc == OK, lib.adadim_last_error(ctx)
         n = {k: len(launched(k)) for k in ("gq_rows", "gq_block", "gq_next")}
         blocks = (inn + 127) // 128
@@ -166,6 +166,11 @@ def test_per_oc_sweep_takes_the_form_that_is_faster(run):
         assert form(*shape) == "blocks", shape
     for shape in ((4096, 4096), (1024, 16384), (8192, 1024), (64, 2048), (3072, 128), (4096, 11008), (16384, 8192)):
         assert form(*shape) == "rows", shape
+    # channels that are no multiple of four: the launches per block store element by element (1.07 to 1.3 times as long)
+    for shape in ((8192, 131), (7280, 493), (40000, 1533), (16384, 2159)):
+        assert form(*shape) == "rows", shape
+    for shape in ((9216, 493), (40000, 1003), (28672, 3003)):
+        assert form(*shape) == "blocks", shape
     """)
 
 

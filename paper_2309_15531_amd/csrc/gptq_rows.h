@@ -502,37 +502,39 @@ inline int rows_per_group(int64_t out, int64_t in) {
 }
 
 // Whether this form is the faster one for [out, in]; else a launch per block (gptq_blocks.h).  Models of both, fitted to whole
-// calls of 248 sizes in both forms (8 to 152064 rows, 128 to 28672 channels; groups of 64, 3 bits): what they choose is 0.1 %
-// slower than the better form on average and 4 % at worst (by their difference alone; neither is an estimate of the call).
+// calls of 657 sizes in both forms (8 to 152064 rows, 128 to 28672 channels, ragged ones among them; 3 bits): what they choose
+// is 0.1 % slower than the better form on average and 8 % at worst (by their difference alone; neither estimates the call).
 // This form is bound by the chain of its rows or by the updates, which many rows per workgroup make cheaper (an error read
 // from LDS serves as many products) and a few workgroups alone dearer (they wait for U by themselves).  A launch per block
 // takes its workgroups of 64 rows in rounds, then a short launch for the next block, and the bulk update beside the next
-// block's chain, half of the shorter one of the two showing where the chain's workgroups fill the chip.  Channels that are no
-// multiple of four make a launch per block dearer: it stores codes and errors one at a time (fitted to 169 more sizes, 512 to
-// 40000 rows of 131 to 4098 channels: 0.1 % on average, 8 % at worst).
+// block's chain, part of the shorter one of the two showing where the chain's workgroups fill the chip.  Channels that are no
+// multiple of four make its chain dearer: codes and errors are stored one at a time.  A narrow last block costs its width in
+// either form.
 // us, this form / a launch per block:
 //   many rows     28672 x 1024  1839 / 1466     100000 x 256  1440 / 831     9216 x 512  424 / 298     6144 x 128  70 / 60
 //   few rows of many channels   300 x 28672  24700 / 19600     8 x 16384  10070 / 8740      256 x 22016  15230 / 14080
 //   the rest      4096 x 4096  2127 / 2911     1024 x 16384  9620 / 12760     8192 x 1024  478 / 630     256 x 2048  389 / 1114
 //   ragged        8192 x 333  172 / 222    7280 x 493  247 / 326    16384 x 2159  2596 / 2981    16384 x 493  466 / 370
+//   a narrow last block   8192 x 260  139 / 182    7168 x 320  157 / 188    8192 x 200  108 / 116    9216 x 260  241 / 185
 inline bool better(int64_t out, int64_t in) {
     const int r = rows_per_group(out, in);
     const int64_t wgs = (out + r - 1) / r, wgs_b = (out + 63) / 64;
-    const double scale = (0.69 + 1.02 / r) * (1.0 + 0.42 / double(wgs));
-    const double chain_b = (in % 4 ? 55.0 : 41.5) * double((wgs_b + 255) / 256), full = std::min(1.0, double(wgs_b) / 256.0);
+    const double scale = (0.71 + 1.22 / r) * (1.0 + 0.41 / double(wgs));
+    const double chain_b = (in % 4 ? 58.0 : 47.0) * double((wgs_b + 255) / 256), full = std::min(1.0, double(wgs_b) / 256.0);
     double here = 0.0, there = 0.0;
     for (int64_t i1 = 0; i1 < in; i1 += GB) {
+        const double part = double(std::min<int64_t>(in - i1, GB)) / GB;        // of a block
         const double upd = double(in - i1) * r * GB * 2.0 / 64.0 / 2.2e3;
-        here += std::max(14.0 + 0.95 * r, scale * upd) + 3.2 + 0.23 * r;
-        const double per_channel = double(out) * GB * 2.0 / 4.2e7;              // of the updates spread over the chip
-        there += chain_b;
-        if (in - i1 > GB) there += 14.0 + double(in) / 2300.0 + per_channel * GB;
+        here += (std::max(14.0 + 0.95 * r, scale * upd) + 3.2 + 0.23 * r) * part;
+        const double per_channel = double(out) * GB * 2.0 / 4.1e7;              // of the updates spread over the chip
+        there += chain_b * part;
+        if (in - i1 > GB) there += 15.0 + double(in) / 2200.0 + per_channel * GB;
         if (in - i1 > 2 * GB) {
             const double bulk = per_channel * double(in - i1 - 2 * GB);
-            there += std::max(bulk, chain_b) - chain_b + 0.5 * full * std::min(bulk, chain_b);
+            there += std::max(bulk, chain_b) - chain_b + 0.43 * full * std::min(bulk, chain_b);
         }
     }
-    return here * double((wgs + 255) / 256) + 10.0 <= there;
+    return here * double((wgs + 255) / 256) + 6.0 <= there;
 }
 
 template <int R>

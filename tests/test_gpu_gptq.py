@@ -363,7 +363,8 @@ def test_sweep_in_the_storage_format_random_shapes(ctx, out_f, in_f, dim, bits, 
     (4090, 328, 3, 0),           # 16 rows
     (6100, 260, 4, 65),          # 24 rows
     (8100, 520, 3, 130),         # 32 rows
-    (8100, 136, 3, 136),         # a launch per block: 64 rows, the last workgroup short, a ragged last block
+    (8100, 136, 3, 136),         # 32 rows, a last block of eight channels
+    (10100, 136, 3, 136),        # a launch per block: 64 rows, the last workgroup short, a ragged last block
     (9000, 264, 3, 24),          # the same, three blocks
     (7000, 77, 2, 11),           # the same, less than a block, odd row pitch
 ])

@@ -509,7 +509,8 @@ inline int rows_per_group(int64_t out, int64_t in) {
 // takes its workgroups of 64 rows in rounds, then a short launch for the next block, and the bulk update beside the next
 // block's chain, part of the shorter one of the two showing where the chain's workgroups fill the chip.  Channels that are no
 // multiple of four make its chain dearer: codes and errors are stored one at a time.  A narrow last block costs its width in
-// either form.
+// either form.  Layers of less than one block (16 to 120 channels, 190 sizes), where a call is 18 to 60 us, are not among them:
+// 1.3 % on average and up to 6 us there (3432 x 64 31 / 37; 28672 x 64 107 / 74).
 // us, this form / a launch per block:
 //   many rows     28672 x 1024  1839 / 1466     100000 x 256  1440 / 831     9216 x 512  424 / 298     6144 x 128  70 / 60
 //   few rows of many channels   300 x 28672  24700 / 19600     8 x 16384  10070 / 8740      256 x 22016  15230 / 14080

@@ -26,6 +26,7 @@
 #include "gptq_blocks.h"
 #include "gptq_groups.h"
 #include "gptq_rows.h"
+#include "gptq_update.h"
 #include "scale_format.h"
 
 #include <algorithm>
@@ -767,39 +768,6 @@ __global__ __launch_bounds__(256) void gq_scatter(const uint8_t* __restrict__ Qp
     }
 }
 
-// channels behind the block, columns [col0, col1): Wp[r][jj] -= E[r][k] * U[k][jj], k = i1 .. i2-1 in order
-// (product, then difference)
-__global__ __launch_bounds__(256) void gq_trailing(float* __restrict__ Wp, const float* __restrict__ U,
-                                                   const float* __restrict__ Ep, int64_t out, int64_t in, int64_t i1,
-                                                   int nbw, int64_t col0, int64_t col1) {
-    __shared__ __align__(16) float Es[GB][8];                 // [channel][row]: a channel's eight errors in two 16-byte reads
-    const int64_t jj = col0 + int64_t(blockIdx.x) * 256 + threadIdx.x;
-    const int64_t r0 = int64_t(blockIdx.y) * 8;
-    for (int e = threadIdx.x; e < 8 * nbw; e += 256) {
-        const int rr = e / nbw, k = e % nbw;
-        Es[k][rr] = r0 + rr < out ? Ep[(r0 + rr) * in + i1 + k] : 0.0f;
-    }
-    __syncthreads();
-    if (jj >= col1) return;
-    float v[8];
-#pragma unroll
-    for (int rr = 0; rr < 8; ++rr) v[rr] = r0 + rr < out ? Wp[(r0 + rr) * in + jj] : 0.0f;
-#pragma unroll 4
-    for (int k = 0; k < nbw; ++k) {
-        const float u = U[(i1 + k) * in + jj];
-        const float4 ea = *reinterpret_cast<const float4*>(&Es[k][0]), eb = *reinterpret_cast<const float4*>(&Es[k][4]);
-        const float e8[8] = {ea.x, ea.y, ea.z, ea.w, eb.x, eb.y, eb.z, eb.w};
-#pragma unroll
-        for (int rr = 0; rr < 8; ++rr) {
-            const float upd = e8[rr] * u;
-            v[rr] = v[rr] - upd;
-        }
-    }
-#pragma unroll
-    for (int rr = 0; rr < 8; ++rr)
-        if (r0 + rr < out) Wp[(r0 + rr) * in + jj] = v[rr];
-}
-
 // The next block's columns [col0, col0 + w), w <= 128: the same update, for the launch that two sweeps wait for.  A
 // thread takes RT rows of one column and has the column's next sixteen entries of U on their way while it works on
 // sixteen: the launch is short of waves, so what counts is that few trips to memory follow each other.
@@ -1040,11 +1008,14 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         const int64_t behind = i1 + nbw;                        // first channel behind the block
         if (behind >= in) break;
         const int64_t next_end = behind + GB < in ? behind + GB : in;
-        const unsigned rows8 = static_cast<unsigned>((out + 7) / 8);
+        auto trailing = [&](hipStream_t stream, int64_t col0) {
+            const dim3 grid(static_cast<unsigned>((in - col0 + update::COLS - 1) / update::COLS),
+                            static_cast<unsigned>((out + update::ROWS - 1) / update::ROWS));
+            hipLaunchKernelGGL(update::gq_trailing, grid, dim3(256), 0, stream, Wp, U, Ep, out, in, i1, col0, in);
+        };
         if (!overlap) {
             ProfScope prof(ctx, "gptq_trailing");
-            hipLaunchKernelGGL(gq_trailing, dim3(static_cast<unsigned>((in - behind + 255) / 256), rows8), dim3(256), 0,
-                               ctx->stream, Wp, U, Ep, out, in, i1, nbw, behind, in);
+            trailing(ctx->stream, behind);
             continue;
         }
         if (side_busy) ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->stream, ctx->side_ev[1], 0));
@@ -1054,8 +1025,7 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[0], ctx->stream));
         if (next_end < in) {
             ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->side, ctx->side_ev[0], 0));
-            hipLaunchKernelGGL(gq_trailing, dim3(static_cast<unsigned>((in - next_end + 255) / 256), rows8), dim3(256), 0,
-                               ctx->side, Wp, U, Ep, out, in, i1, nbw, next_end, in);
+            trailing(ctx->side, next_end);
             ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[1], ctx->side));
             side_busy = true;
         }

@@ -1,0 +1,148 @@
+// The update of the channels behind a block, products on the matrix cores (gfx950).  Included by gptq.hip.
+//
+// The definition's sequence per element and channel is a rounded product and a rounded difference, so the contraction
+// cannot go through a multiply-add.  A matrix instruction of depth one with a zero addend gives the rounded products alone:
+// fma(e, u, +0) is RN(e u) for every e and u (subnormals, infinities and NaN included; compared over all these kinds by
+// tests/test_gpu_gptq.py) but for the sign of a zero product, -0 becoming +0.  That sign decides at most the sign of a
+// zero channel value, and neither codes, parameters nor dW depend on the latter.  The vector pipes are left with the
+// differences, one instruction per element and channel where they had two, and the matrix cores, which need half that
+// time for the products, work beside them: 3.7e13 elements per second in a bare loop of both with two waves per SIMD, where
+// the unpacked pair of product and difference is held to 1.96e13.
+#pragma once
+
+#include "common.h"
+#include "gptq_chain.h"
+
+namespace {
+
+namespace update {
+
+using chain_ns::GB;
+using chain_ns::PITCH;
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x32 __attribute__((ext_vector_type(32)));
+
+// 64 x 32 products of one channel: lane l gives the error of row l and the entry of U of column l % 32.  Register r of lane l
+// is row row_of(r, l), column l % 32.
+__device__ __forceinline__ f32x32 products64x32(float e, float u) {
+    f32x32 zero;
+#pragma unroll
+    for (int r = 0; r < 32; ++r) zero[r] = 0.0f;
+    return __builtin_amdgcn_mfma_f32_32x32x1f32(e, u, zero, 0, 0, 0);
+}
+__device__ __forceinline__ int row_of(int r, int lane) { return 32 * (r >> 4) + 8 * ((r & 15) >> 2) + 4 * (lane >> 5) + (r & 3); }
+
+// The element `bytes` behind a wave-uniform address, which is kept in scalar registers (the compiler would rather add it up in
+// 64 bits in every lane): the lanes' 32-bit offsets are then part of the load or store.
+template <typename T>
+using Global = __attribute__((address_space(1))) T;
+template <typename T>
+__device__ __forceinline__ Global<T>* at(T* base, uint32_t bytes) {
+    uintptr_t b = reinterpret_cast<uintptr_t>(base);
+    asm("" : "+s"(b));
+    return (Global<T>*)((Global<char>*)b + bytes);
+}
+
+constexpr int ROWS = 64, COLS = 128;   // of a workgroup; a wave takes 32 of the columns
+
+// Wp[r][jj] -= E[r][k] * U[k][jj], k = i1 .. i1 + GB - 1 in order (product, then difference), for the columns [col0, col1).
+// The workgroup's errors go to LDS once; a column's entries of U travel KB channels ahead of their use.  The next channel's
+// products are issued before this channel's differences, so that another wave's matrix instruction runs beside them.  Three
+// waves per SIMD: two keep the vector pipes busy, the third starts or ends a tile.  11008 rows x 3840 columns 277 -> 217 us
+// (2.5e13 elements per second, at 2.05 GHz: both units busy cost clock), x 2048 columns 148 -> 106.
+__global__ __launch_bounds__(256, 3) void gq_trailing(float* __restrict__ Wp, const float* __restrict__ U, const float* __restrict__ Ep,
+                                                      int64_t out, int64_t in64, int64_t i1, int64_t col0, int64_t col1) {
+    constexpr int KB = 8;
+    __shared__ __align__(16) float es[ROWS][PITCH];            // [row][channel]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int in = static_cast<int>(in64);
+    const int64_t r0 = int64_t(blockIdx.y) * ROWS;
+    const int n_rows = static_cast<int>(min(out - r0, int64_t(ROWS)));         // > 0
+    const uint32_t pitch = 4u * static_cast<uint32_t>(in);                     // bytes (64 rows of up to 46340 channels fit 32 bits)
+    float* __restrict__ Wrows = Wp + r0 * in64;
+    const float* __restrict__ Erows = Ep + r0 * in64 + i1;
+    const int c_end = static_cast<int>(col1);
+    const int c = static_cast<int>(col0) + static_cast<int>(blockIdx.x) * COLS + 32 * wave + (lane & 31);
+    const uint32_t col = 4u * static_cast<uint32_t>(min(c, c_end - 1));        // past the end: read, never stored
+
+    float u[2][KB];
+    const float* __restrict__ Ublock = U + i1 * in64;
+    auto fetch = [&](int b, int k) {
+        const float* urow = Ublock + k * in64;
+#pragma unroll
+        for (int kk = 0; kk < KB; ++kk) {
+            u[b][kk] = *at(urow, col);
+            urow += in;
+        }
+    };
+    fetch(0, 0);
+    if ((in & 3) == 0) {                                       // Ep is scratch, 16-byte aligned; i1 is a multiple of GB
+#pragma unroll
+        for (int q = 0; q < ROWS * GB / 4 / 256; ++q) {
+            const int idx = tid + 256 * q, r = idx / (GB / 4), k = idx % (GB / 4) * 4;
+            *reinterpret_cast<f32x4*>(&es[r][k]) =
+                *at(reinterpret_cast<const f32x4*>(Erows), static_cast<uint32_t>(min(r, n_rows - 1)) * pitch + 4u * k);
+        }
+    } else {
+#pragma unroll 8
+        for (int q = 0; q < ROWS * GB / 256; ++q) {
+            const int idx = tid + 256 * q, r = idx / GB, k = idx % GB;
+            es[r][k] = *at(Erows, static_cast<uint32_t>(min(r, n_rows - 1)) * pitch + 4u * k);
+        }
+    }
+    const uint32_t first = static_cast<uint32_t>(row_of(0, lane)) * pitch + col;
+    float v[32];
+    if (n_rows == ROWS) {
+#pragma unroll
+        for (int r = 0; r < 32; ++r) v[r] = *at(Wrows + row_of(r, 0) * in64, first);
+    } else {
+#pragma unroll
+        for (int r = 0; r < 32; ++r) v[r] = *at(Wrows, static_cast<uint32_t>(min(row_of(r, lane), n_rows - 1)) * pitch + col);
+    }
+    __syncthreads();
+    f32x4 ev[2];
+    auto errors = [&](int b, int k) { ev[b] = *reinterpret_cast<const f32x4*>(&es[lane][k & (GB - 1)]); };
+    auto error = [&](int kk) {                                 // of channel kk of 16, the group of four being in its buffer
+        const f32x4 t = ev[(kk >> 2) & 1];
+        return (kk & 3) == 0 ? t.x : (kk & 3) == 1 ? t.y : (kk & 3) == 2 ? t.z : t.w;
+    };
+    f32x32 p[2];
+    errors(0, 0);
+    p[0] = products64x32(error(0), u[0][0]);
+#pragma unroll 1
+    for (int k = 0; k < GB; k += 2 * KB) {
+#pragma unroll
+        for (int kk = 0; kk < 2 * KB; ++kk) {
+            // (behind the block's last channel the first ones are read again and not used)
+            if (kk == 0) fetch(1, k + KB);
+            if (kk == KB) fetch(0, (k + 2 * KB) & (GB - 1));
+            if ((kk & 3) == 0) errors(((kk >> 2) + 1) & 1, k + kk + 4);
+            const int nk = kk + 1;
+            __builtin_amdgcn_sched_barrier(0);
+            p[nk & 1] = products64x32(error(nk), u[(nk / KB) & 1][nk % KB]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < 32; ++r) v[r] = v[r] - p[kk & 1][r];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if (c >= c_end) return;
+    if (n_rows == ROWS) {
+#pragma unroll
+        for (int r = 0; r < 32; ++r) *at(Wrows + row_of(r, 0) * in64, first) = v[r];
+    } else {
+        int lane_s = lane;                                     // row offsets are worked out again, not held over the loop
+        asm volatile("" : "+v"(lane_s));
+#pragma unroll
+        for (int r = 0; r < 32; ++r) {
+            const int row = row_of(r, lane_s);
+            if (row < n_rows) *at(Wrows, static_cast<uint32_t>(row) * pitch + col) = v[r];
+        }
+    }
+}
+
+}  // namespace update
+
+}  // namespace

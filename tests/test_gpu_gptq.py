@@ -147,6 +147,56 @@ def test_sweep_bit_exact_given_u(ctx, out_f, in_f, dim, bits, group):
     assert np.array_equal(got["packed"], oracle.pack(ref["codes"], dim, bits))
 
 
+def _synthetic_factor(in_f, rng, tiny=False):
+    """An upper triangular U with a positive diagonal.  tiny: the entries behind the first 128 columns are so small that their
+    products with the errors are subnormal, and a fifth of them are zeros of either sign."""
+    U = np.triu(rng.standard_normal((in_f, in_f)) * (0.4 / np.sqrt(in_f)), 1).astype(np.float32)
+    if tiny:
+        U[:128, 128:] = rng.standard_normal((128, in_f - 128)).astype(np.float32) * np.float32(1e-37)
+        U[128:, 128:] = 0.0
+        hole = np.triu(rng.random((in_f, in_f)) < 0.2, 1)
+        U[hole] = np.copysign(np.float32(0.0), rng.standard_normal(int(hole.sum())).astype(np.float32))
+    np.fill_diagonal(U, (1.0 + rng.random(in_f)).astype(np.float32))
+    return U
+
+
+@pytest.mark.parametrize("out_f,in_f,dim,bits,group,tiny", [
+    (9220, 260, OC, 3, 0, False),     # a launch per block; 4 rows and 4 columns past whole tiles of the update
+    (9217, 259, OC, 4, 0, False),     # the same with rows of Wp at any alignment
+    (9220, 420, OC, 4, 0, False),     # with an update on the side stream
+    (64, 385, IC, 3, 64, False),      # one column behind whole blocks
+    (192, 641, IC, 4, 64, False),
+    (384, 545, IC, 2, 128, False),
+    (16, 2100, OC, 3, 0, False),      # one launch, rows below a workgroup's
+    (4099, 300, OC, 3, 0, False),     # one launch, 16 rows per workgroup, the last with three
+    (6150, 290, OC, 3, 0, False),
+    (128, 400, IC, 4, 64, True),
+    (256, 400, IC, 4, 128, True),
+    (4099, 300, OC, 4, 0, True),
+])
+def test_update_of_later_channels_bit_exact(ctx, out_f, in_f, dim, bits, group, tiny):
+    """The update of the channels behind a block at the edges of its tiles, against the oracle's one product and one
+    difference per element and channel.  tiny: with a weight that is zero (of either sign) behind the first visited block, the
+    later channels consist of subnormal products alone, so that a lost or flushed product shows in scales and codes."""
+    rng = np.random.default_rng(out_f * 7 + in_f)
+    W = synth.make_weight(out_f, in_f, in_f, heavy_cols=2, heavy_scale=5.0)
+    U = _synthetic_factor(in_f, rng, tiny)
+    perm = rng.permutation(in_f)
+    dead = np.zeros(in_f, dtype=bool)
+    dead[perm[3]] = True
+    if tiny:
+        W[:, perm[128:]] = np.copysign(np.float16(0.0), rng.standard_normal((out_f, in_f - 128)).astype(np.float16))
+    ref = G.sweep(W, U, perm, dead, dim, bits, group)
+    got = gpu_sweep(ctx, W, dim, bits, group, dev(U), dev(perm.astype(np.int32)), dev(dead.astype(np.uint8)))
+    assert np.array_equal(got["scales"].view(np.uint32), ref["scales"].view(np.uint32))
+    assert np.array_equal(got["zeros"], ref["zeros"])
+    assert np.array_equal(got["codes"], ref["codes"])
+    assert np.array_equal(got["dW"], ref["dW"])
+    if tiny and dim == IC:
+        late = ref["scales"][:, perm[128:]]
+        assert ((late > 0) & (late < 1e-37)).any()
+
+
 @pytest.mark.parametrize("dim,group", [(OC, 128), (IC, 128)])
 def test_end_to_end_improves_on_rtn(ctx, dim, group):
     out_f, in_f, bits = 256, 768, 3

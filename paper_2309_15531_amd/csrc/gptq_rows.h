@@ -3,22 +3,20 @@
 // With static groups (per-OC) the rows of W do not depend on each other, so a workgroup can take its R rows through
 // every channel without meeting another workgroup.  Eight waves:
 //   * wave 0 walks the 128 channels of block b: the chain of rounding decisions, latency bound;
-//   * meanwhile the others apply the errors of block b - 1 to the columns behind block b (VALU bound: a rounded
-//     product and a rounded difference per element and channel, which is the definition's sequence, so no fma and
-//     no matrix core); wave 0 joins them when its chain is done;
+//   * meanwhile the others apply the errors of block b - 1 to the columns behind block b (a rounded product and a rounded
+//     difference per element and channel, which is the definition's sequence, so no fma); wave 0 joins them when its
+//     chain is done;
 //   * then all waves apply block b's errors to block b + 1's columns, on their way from memory into LDS.
 // Two barriers per block and nothing else to wait for.  The launches per block and the two streams this replaces
 // left the chip idle around every short launch.  The whole sweep of a 4096 x 4096 layer, 3 bits: 3.3 ms then, 2.1 ms
-// now, of which the VALU's own time is 1.75 ms (out * in^2 instructions at 64 lanes per cycle and compute unit); 64 to
-// 1024 rows of that width 0.9 ms (the chain alone).
-//
+// in one launch with products and differences in vector instructions, 1.9 ms with the products behind the block on the
+// matrix cores (12 rows and more per workgroup); 64 to 1024 rows of that width 0.9 ms (the chain alone).
 // Rows per workgroup: few enough that the chip's 256 compute units all have a workgroup (16 at 4096 rows), so that
 // the VALU work is spread over the whole chip; the chain takes the same time for 4 rows as for 64.  rows_per_group
 // picks R from the sizes.
 //
-// Registers: with 16 and 32 rows 24 vector registers do not fit and live in scratch (80 bytes per lane), with 8 rows 9, with 4,
-// 12 and 24 none.  They are values that hold over the block loop, read back once per block or, some six of them, once per
-// sub-block of 16 channels; none is read inside the sixteen channels' chain or the updates' product loops.
+// Registers: with 32 rows 20 vector registers do not fit and live in scratch, with 8 rows 4, otherwise none.  They are values
+// that hold over the block loop; none is read inside the sixteen channels' chain or the updates' product loops.
 //
 // Order of the updates of one element: blocks in order, channels inside a block in order, whichever wave applies
 // them; every update is one product and one difference.  Hence the same bits as a plain channel-by-channel loop.
@@ -27,6 +25,7 @@
 #include "common.h"
 #include "fastdiv.h"
 #include "gptq_chain.h"
+#include "gptq_update.h"
 #include "scale_format.h"
 
 #include <type_traits>
@@ -155,8 +154,8 @@ __device__ __forceinline__ int fresh_uniform(int v) {
     return v;
 }
 
-// One item of the update behind a block: columns c0 + lane + 64 q of RT of the workgroup's rows (Wrows and es point at
-// the first of them), with the errors of the block at k0.
+// One item of the update behind a block, for 4 and 8 rows, which would leave most of a matrix instruction's 16 unused: columns
+// c0 + lane + 64 q of the workgroup's rows, with the errors of the block at k0.
 // (offsets inside the workgroup's rows fit 32 bits: at most 32 rows of 46340)
 template <int R, int RT, int CPL>
 __device__ __forceinline__ void update_item(float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
@@ -225,6 +224,109 @@ __device__ __forceinline__ void update_item(float* __restrict__ Wrows, const flo
     }
 }
 
+// The update behind a block for workgroups of 12 rows and more, the products on the matrix cores (gptq_update.h): items of RT
+// rows (12 take the place of 16) x 64 columns from column c_first on, as `next` gives them out.  Two waves per SIMD keep the
+// vector pipes busy only if neither waits for memory, so the next item's columns of W, and its first entries of U, are on
+// their way while this one is worked on.  4096 x 4096, 16 rows: the sweep 2.1 ms with vector products and differences on items
+// of 128 columns, 1.86 so.
+template <int R, int RT>
+__device__ __forceinline__ void update_behind(float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
+                                              int in_, int64_t k0, int c_first, int* next) {
+    using update::at;
+    constexpr int KB = 16;                                     // channels per step: their U entries travel one step ahead
+    const int lane = fresh(threadIdx.x & 63), in = fresh_uniform(in_);
+    const uint32_t pitch = 4u * static_cast<uint32_t>(in);
+    const int halves = n_rows > RT ? 2 : 1, n_items = (in - c_first + 63) / 64 * halves;
+    auto take = [&] {
+        int item = 0;
+        if (lane == 0) item = atomicAdd(next, 1);
+        return __builtin_amdgcn_readfirstlane(item);
+    };
+    int item = take();
+    if (item >= n_items) return;
+    auto row0_of = [&](int item) { return halves == 1 ? 0 : (item & 1) * RT; };
+    auto col0_of = [&](int item) { return c_first + (halves == 1 ? item : item >> 1) * 64; };
+    auto u_offset = [&](int item) { return 4u * static_cast<uint32_t>(min(col0_of(item) + lane, in - 1)); };
+    auto e_first = [&](int item) { return es + row0_of(item) + min(lane & 15, RT - 1); };
+    // past the last row or column: read, never stored
+    auto load = [&](int item, update::f32x16& v) {
+        const int rt = row0_of(item), c0 = col0_of(item);
+        uint32_t col[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) col[b] = 4u * static_cast<uint32_t>(min(c0 + 16 * b + (lane & 15), in - 1));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t row = static_cast<uint32_t>(min(rt + 4 * (lane >> 4) + r, n_rows - 1)) * pitch;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) v[4 * b + r] = *at(Wrows, row + col[b]);
+        }
+    };
+    float u[2][KB];
+    const float* Ublock = U + k0 * in;
+    auto fetch = [&](int b, int k, uint32_t col) {
+        const float* urow = Ublock + k * in;
+#pragma unroll
+        for (int kk = 0; kk < KB; ++kk) {
+            u[b][kk] = *at(urow, col);
+            urow += in;
+        }
+    };
+    update::f32x16 v, v_next, p[2];
+    uint32_t ucol = u_offset(item);
+    const float* e_row = e_first(item);
+    fetch(0, 0, ucol);
+    load(item, v);
+    float e[4] = {e_row[0], e_row[R], 0.0f, 0.0f};             // a channel's errors are read two channels ahead of their use
+    p[0] = update::products16x64(e[0], u[0][0]);
+    for (;;) {
+        const int taken = take();
+        const bool more = taken < n_items;
+        const int then = more ? taken : item;                  // (none left: this one's are read again and not used)
+        const uint32_t ucol_next = u_offset(then);
+        const float* e_next = e_first(then);
+        auto steps = [&](int k_begin) {
+#pragma unroll 1
+            for (int k = k_begin; k < k_begin + GB / 2; k += 2 * KB) {
+                const bool last = k + 2 * KB == GB;            // behind the block's last channel come the next item's first
+                const float* e_at = last ? e_next - GB * R : e_row;
+                const uint32_t ucol2 = last ? ucol_next : ucol;
+#pragma unroll
+                for (int kk = 0; kk < 2 * KB; ++kk) {
+                    if (kk == 0) fetch(1, k + KB, ucol);
+                    if (kk == KB) fetch(0, (k + 2 * KB) & (GB - 1), ucol2);
+                    e[(kk + 2) & 3] = (kk + 2 < 2 * KB ? e_row : e_at)[(k + kk + 2) * R];
+                    const int nk = kk + 1;
+                    __builtin_amdgcn_sched_barrier(0);
+                    p[nk & 1] = update::products16x64(e[nk & 3], u[(nk / KB) & 1][nk % KB]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    v = v - p[kk & 1];
+                    asm volatile("" : "+v"(v));                // here, and not behind the next products
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        };
+        steps(0);
+        load(then, v_next);
+        steps(GB / 2);
+        {
+            const int lane_s = fresh(lane), rt = row0_of(item), c0 = col0_of(item);
+            float* Wr = Wrows + static_cast<uint32_t>(rt) * static_cast<uint32_t>(in) + c0;
+            const int rows_here = min(n_rows - rt, RT), cols_here = in - c0;
+            const uint32_t first = static_cast<uint32_t>(4 * (lane_s >> 4)) * pitch + 4u * static_cast<uint32_t>(lane_s & 15);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    if (4 * (lane_s >> 4) + r < rows_here && 16 * b + (lane_s & 15) < cols_here) *at(Wr + r * in + 16 * b, first) = v[4 * b + r];
+        }
+        if (!more) break;
+        item = then;
+        ucol = ucol_next;
+        e_row = e_next;
+        v = v_next;
+    }
+}
+
 // Columns of the next block (starting at c1, nbw of them) into the strip, with the errors of the block at k0 applied.
 // Wave w takes columns 16 w .. 16 w + 15, lane groups of 16 take R / 4 rows each.
 template <int R>
@@ -274,9 +376,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
                                                          const int32_t* __restrict__ perm, int64_t out, int64_t in64, int g,
                                                          float qmax, int mfmt, const float* __restrict__ st_scales,
                                                          const uint8_t* __restrict__ st_zeros, uint8_t* __restrict__ Qp) {
-    // items of the update: RT rows x 64 CPL columns (RT x CPL accumulators; few rows take more columns, so that an
-    // LDS read of the errors serves as many products)
-    constexpr int RR = pow2_rows<R>(), CL = 64 / RR, CPL = R <= 8 ? 4 : 2, RT = R <= 16 ? R : R / 2;
+    // items of the update: 64 CPL columns of 4 or 8 rows (an LDS read of the errors serves CPL products), 64 of RT rows otherwise
+    constexpr int RR = pow2_rows<R>(), CL = 64 / RR, CPL = 4, RT = R <= 16 ? R : R / 2;
     extern __shared__ __align__(16) char smem[];
     Lds<R>& lds = *reinterpret_cast<Lds<R>*>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -455,16 +556,17 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
         }
         // errors of the last block onto the columns behind this one, item by item
         if (blk > 0 && behind < in) {
-            const int n_items = (in - behind + 64 * CPL - 1) / (64 * CPL) * (R / RT);
-            for (;;) {
-                int item = 0;
-                if (lane == 0) item = atomicAdd(&lds.next, 1);
-                item = __builtin_amdgcn_readfirstlane(item);
-                if (item >= n_items) break;
-                const int rt = R == RT ? 0 : (item & 1) * RT, cc = R == RT ? item : item >> 1;
-                if (rt < n_rows)
-                    update_item<R, RT, CPL>(Wrows + rt * in64, U, es_last + rt, n_rows - rt, in, int64_t(i1) - GB,
-                                            behind + cc * (64 * CPL));
+            if constexpr (R >= 12) {
+                update_behind<R, RT>(Wrows, U, es_last, n_rows, in, int64_t(i1) - GB, behind, &lds.next);
+            } else {
+                const int n_items = (in - behind + 64 * CPL - 1) / (64 * CPL);
+                for (;;) {
+                    int item = 0;
+                    if (lane == 0) item = atomicAdd(&lds.next, 1);
+                    item = __builtin_amdgcn_readfirstlane(item);
+                    if (item >= n_items) break;
+                    update_item<R, R, CPL>(Wrows, U, es_last, n_rows, in, int64_t(i1) - GB, behind + item * (64 * CPL));
+                }
             }
         }
         if (behind >= in) break;                               // uniform: the last block

@@ -2,12 +2,13 @@
 //
 // The definition's sequence per element and channel is a rounded product and a rounded difference, so the contraction
 // cannot go through a multiply-add.  A matrix instruction of depth one with a zero addend gives the rounded products alone:
-// fma(e, u, +0) is RN(e u) for every e and u (subnormals, infinities and NaN included; compared over all these kinds by
-// tests/test_gpu_gptq.py) but for the sign of a zero product, -0 becoming +0.  That sign decides at most the sign of a
-// zero channel value, and neither codes, parameters nor dW depend on the latter.  The vector pipes are left with the
-// differences, one instruction per element and channel where they had two, and the matrix cores, which need half that
-// time for the products, work beside them: 3.7e13 elements per second in a bare loop of both with two waves per SIMD, where
-// the unpacked pair of product and difference is held to 1.96e13.
+// fma(e, u, +0) is RN(e u) for every e and u (subnormals, infinities and NaN included) but for the sign of a zero product, -0
+// becoming +0.  That sign decides at most the sign of a zero channel value, and neither codes, parameters nor dW depend on
+// the latter.  What it saves is operands: one register each of errors and of U makes 1024 or 2048 products, where the product
+// and the difference in vector instructions read an error from LDS for every two to four of them and waited for those
+// reads.  The fp32 matrix instruction does not run beside vector instructions: a bare loop of products and differences makes
+// 3.7e13 elements per second with two waves per SIMD (132 cycles per 2048), as the pair of vector instructions does from
+// registers alone (2.1 cycles each with two waves, 4.3 with one); with one wave it is 2.4e13 against 1.9e13.
 #pragma once
 
 #include "common.h"
@@ -32,6 +33,14 @@ __device__ __forceinline__ f32x32 products64x32(float e, float u) {
     for (int r = 0; r < 32; ++r) zero[r] = 0.0f;
     return __builtin_amdgcn_mfma_f32_32x32x1f32(e, u, zero, 0, 0, 0);
 }
+// 16 x 64 products: lane l gives the error of row l % 16 and the entry of U of column l.  Register r of lane l is row
+// 4 * (l / 16) + r % 4, column 16 * (r / 4) + l % 16.
+__device__ __forceinline__ f32x16 products16x64(float e, float u) {
+    f32x16 zero;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+    return __builtin_amdgcn_mfma_f32_16x16x1f32(e, u, zero, 0, 0, 0);
+}
 __device__ __forceinline__ int row_of(int r, int lane) { return 32 * (r >> 4) + 8 * ((r & 15) >> 2) + 4 * (lane >> 5) + (r & 3); }
 
 // The element `bytes` behind a wave-uniform address, which is kept in scalar registers (the compiler would rather add it up in
@@ -49,9 +58,9 @@ constexpr int ROWS = 64, COLS = 128;   // of a workgroup; a wave takes 32 of the
 
 // Wp[r][jj] -= E[r][k] * U[k][jj], k = i1 .. i1 + GB - 1 in order (product, then difference), for the columns [col0, col1).
 // The workgroup's errors go to LDS once; a column's entries of U travel KB channels ahead of their use.  The next channel's
-// products are issued before this channel's differences, so that another wave's matrix instruction runs beside them.  Three
-// waves per SIMD: two keep the vector pipes busy, the third starts or ends a tile.  11008 rows x 3840 columns 277 -> 217 us
-// (2.5e13 elements per second, at 2.05 GHz: both units busy cost clock), x 2048 columns 148 -> 106.
+// products are issued before this channel's differences, so that a wave does not wait for them.  Three waves per SIMD: two keep
+// the pipes busy, the third starts or ends a tile.  11008 rows x 3840 columns: 248 us with vector instructions alone (eight
+// rows per thread), 187 so, 145 for the bare loop.
 __global__ __launch_bounds__(256, 3) void gq_trailing(float* __restrict__ Wp, const float* __restrict__ U, const float* __restrict__ Ep,
                                                       int64_t out, int64_t in64, int64_t i1, int64_t col0, int64_t col1) {
     constexpr int KB = 8;

@@ -604,11 +604,13 @@ __global__ void gq_flip(const double* __restrict__ M, int64_t n, float* __restri
 // fetched a separate 64-byte piece for every two bytes it used).  Dynamic LDS: nr * in halves.
 // VEC: in % 8 == 0 and 16-byte aligned W and perm, 8-byte aligned dead: 8 channels per load, 4 per store, and a piece of
 // perm serves the nr rows.  11008 x 4096, 270 MB: 53 us, where an element at a time takes 68 (11008 x 4090; with a row
-// per workgroup 88; 25600 x 2047 70 and 140; 76800 x 259 34 and 72).
+// per workgroup 88; 25600 x 2047 70 and 140; 76800 x 259 34 and 72).  The first workgroup clears `clear`, too.
 template <bool VEC>
 __global__ __launch_bounds__(256) void gq_gather_w(const __half* __restrict__ W, int64_t out, int64_t in, int nr,
                                                    const int32_t* __restrict__ perm, const uint8_t* __restrict__ dead,
-                                                   float* __restrict__ Wp) {
+                                                   float* __restrict__ Wp, int32_t* __restrict__ clear, int n_clear) {
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n_clear; i += 256) clear[i] = 0;
     extern __shared__ __align__(16) char gw_smem[];
     __half* row = reinterpret_cast<__half*>(gw_smem);
     const int64_t r0 = int64_t(blockIdx.x) * nr;
@@ -950,6 +952,8 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
                                     96 * 1024);
         return e;
     }));
+    // per-IC: a counter per block's launch, in the room of `visited`, which is filled in behind the sweep
+    const int n_blocks = ic ? static_cast<int>((in + GB - 1) / GB) : 0;
     {
         ProfScope prof(ctx, "gptq_gather");
         // up to four rows per workgroup, as long as four workgroups fit a compute unit's LDS and the chip stays full
@@ -957,8 +961,8 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         const int nr = in <= 5000 && out >= 4096 ? 4 : in <= 10000 && out >= 2048 ? 2 : 1;
         const dim3 grid(static_cast<unsigned>((out + nr - 1) / nr));
         const size_t lds_bytes = size_t(nr) * size_t(in) * 2;
-        if (vec) hipLaunchKernelGGL(gq_gather_w<true>, grid, dim3(256), lds_bytes, ctx->stream, W, out, in, nr, perm, dead, Wp);
-        else hipLaunchKernelGGL(gq_gather_w<false>, grid, dim3(256), lds_bytes, ctx->stream, W, out, in, nr, perm, dead, Wp);
+        if (vec) hipLaunchKernelGGL(gq_gather_w<true>, grid, dim3(256), lds_bytes, ctx->stream, W, out, in, nr, perm, dead, Wp, visited, n_blocks);
+        else hipLaunchKernelGGL(gq_gather_w<false>, grid, dim3(256), lds_bytes, ctx->stream, W, out, in, nr, perm, dead, Wp, visited, n_blocks);
     }
     if (whole) {
         ProfScope prof(ctx, "gptq_sweep");
@@ -979,31 +983,36 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         }
 #undef GQ_ROWS
     }
-    // A block's errors reach the channels behind it in two launches: the next block's 128 channels at
-    // once, on the main stream, so that the next sweep can start; the rest on a side stream, under
-    // that sweep, which keeps only a few compute units busy.  Every element still receives the
+    for (int64_t i1 = 0; ic && i1 < in; i1 += GB) {
+        ProfScope prof(ctx, "gptq_sweep");
+        const int nbw = static_cast<int>(in - i1 < GB ? in - i1 : GB);
+        const int64_t n_groups = out / g, n_items = n_groups + groups::n_pieces(out, in, i1);
+        const dim3 grid(static_cast<unsigned>(std::min<int64_t>(n_items, 256)));
+#define GQ_GO(RPL)                                                                                                       \
+    hipLaunchKernelGGL(groups::gq_step<RPL>, grid, dim3(64 * groups::WAVES), sizeof(groups::Lds<RPL>), ctx->stream, Wp, U, perm, in, \
+                       i1, nbw, static_cast<int>(n_groups), static_cast<int>(n_items), qmax, 1.0f / qmax, mfmt, scales_out, \
+                       zeros_out, Qp, Ep, visited + i1 / GB)
+        if (g == 64) GQ_GO(1);
+        else GQ_GO(2);
+#undef GQ_GO
+    }
+    // Per-OC with a launch per block: a block's errors reach the channels behind it in two launches: the next block's 128
+    // channels at once, on the main stream, so that the next sweep can start; the rest on a side stream, under
+    // that sweep.  Every element still receives the
     // blocks' errors in block order: the side stream applies them in order, and the main stream
     // waits for the side stream's last launch before it adds the following block's errors to the
     // channels that launch wrote.  With per-kernel timing on, everything runs on the main stream.
-    const bool overlap = !whole && !ctx->prof.enabled && in > 2 * GB;
+    const bool by_block = !ic && !whole;
+    const bool overlap = by_block && !ctx->prof.enabled && in > 2 * GB;
     if (overlap && !adadim_side_stream(ctx)) return ADADIM_EHIP;
     bool side_busy = false;
-    const bool four = in > 2 * GB && out / g > groups::MANY;   // an update beside the walk, and many groups
-    for (int64_t i1 = 0; !whole && i1 < in; i1 += GB) {
+    for (int64_t i1 = 0; by_block && i1 < in; i1 += GB) {
         const int nbw = static_cast<int>(in - i1 < GB ? in - i1 : GB);
         {
             ProfScope prof(ctx, "gptq_sweep");
-#define GQ_GO(RPL, WAVES)                                                                                                \
-    hipLaunchKernelGGL((groups::gq_group<RPL, WAVES>), dim3(static_cast<unsigned>(out / g)), dim3(64 * WAVES),           \
-                       sizeof(groups::Lds<RPL>), ctx->stream, Wp, U, perm, in, i1, nbw, qmax, 1.0f / qmax, mfmt,         \
-                       scales_out, zeros_out, Qp, Ep)
-            if (!ic)
-                hipLaunchKernelGGL(blocks::gq_block, dim3(static_cast<unsigned>((out + blocks::ROWS - 1) / blocks::ROWS)), dim3(256),
-                                   sizeof(blocks::Lds), ctx->stream, Wp, U, perm, out, in, i1, nbw, g, qmax, mfmt, st_scales,
-                                   st_zeros, Qp, Ep);
-            else if (g == 64) { if (four) GQ_GO(1, 4); else GQ_GO(1, 8); }
-            else { if (four) GQ_GO(2, 4); else GQ_GO(2, 8); }
-#undef GQ_GO
+            hipLaunchKernelGGL(blocks::gq_block, dim3(static_cast<unsigned>((out + blocks::ROWS - 1) / blocks::ROWS)), dim3(256),
+                               sizeof(blocks::Lds), ctx->stream, Wp, U, perm, out, in, i1, nbw, g, qmax, mfmt, st_scales, st_zeros,
+                               Qp, Ep);
         }
         const int64_t behind = i1 + nbw;                        // first channel behind the block
         if (behind >= in) break;

@@ -46,6 +46,17 @@ __device__ __forceinline__ bool reciprocals_ok(const float* rd) {
     return !__any(r != r);
 }
 
+// The value, recomputed from here on: address terms that do not change from block to block would otherwise be kept in
+// registers over the whole sweep (or loop of work items), and there are more of them than registers.
+__device__ __forceinline__ int fresh(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ int fresh_uniform(int v) {
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
 }  // namespace chain_ns
 
 }  // namespace

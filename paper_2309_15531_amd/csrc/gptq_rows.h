@@ -10,12 +10,12 @@
 // Two barriers per block and nothing else to wait for.  The launches per block and the two streams this replaces
 // left the chip idle around every short launch.  The whole sweep of a 4096 x 4096 layer, 3 bits: 3.3 ms then, 2.1 ms
 // in one launch with products and differences in vector instructions, 1.9 ms with the products behind the block on the
-// matrix cores (12 rows and more per workgroup); 64 to 1024 rows of that width 0.9 ms (the chain alone).
+// matrix cores (16 and 32 rows per workgroup); 64 to 1024 rows of that width 0.9 ms (the chain alone).
 // Rows per workgroup: few enough that the chip's 256 compute units all have a workgroup (16 at 4096 rows), so that
 // the VALU work is spread over the whole chip; the chain takes the same time for 4 rows as for 64.  rows_per_group
 // picks R from the sizes.
 //
-// Registers: with 32 rows 20 vector registers do not fit and live in scratch, with 8 rows 4, otherwise none.  They are values
+// Registers: with 32 rows 20 vector registers do not fit and live in scratch, with 8 rows 9, otherwise none.  They are values
 // that hold over the block loop; none is read inside the sixteen channels' chain or the updates' product loops.
 //
 // Order of the updates of one element: blocks in order, channels inside a block in order, whichever wave applies
@@ -143,19 +143,10 @@ __device__ __forceinline__ void chain_slow(float* wrow, const float* ut, float* 
     }
 }
 
-// The value, recomputed from here on: address terms that do not change from block to block would otherwise be kept in
-// registers over the whole sweep, and there are more of them than registers.
-__device__ __forceinline__ int fresh(int v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-__device__ __forceinline__ int fresh_uniform(int v) {
-    asm volatile("" : "+s"(v));
-    return v;
-}
-
-// One item of the update behind a block, for 4 and 8 rows, which would leave most of a matrix instruction's 16 unused: columns
-// c0 + lane + 64 q of the workgroup's rows, with the errors of the block at k0.
+// One item of the update behind a block in vector instructions, for 4, 8 and 12 rows (24 as twice 12): columns c0 + lane + 64 q
+// of RT of the workgroup's rows (Wrows and es point at the first of them), with the errors of the block at k0.  A matrix
+// instruction makes 16 rows of products whether they exist or not, and it and the 16 differences take the pipes for as long
+// as 30 vector instructions: 2618 x 8541 in twelves 6.19 ms so, 6.74 with the products of update_behind.
 // (offsets inside the workgroup's rows fit 32 bits: at most 32 rows of 46340)
 template <int R, int RT, int CPL>
 __device__ __forceinline__ void update_item(float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
@@ -224,18 +215,18 @@ __device__ __forceinline__ void update_item(float* __restrict__ Wrows, const flo
     }
 }
 
-// The update behind a block for workgroups of 12 rows and more, the products on the matrix cores (gptq_update.h): items of RT
-// rows (12 take the place of 16) x 64 columns from column c_first on, as `next` gives them out.  Two waves per SIMD keep the
+// The update behind a block for workgroups of 16 and 32 rows, the products on the matrix cores (gptq_update.h): items of 16
+// rows x 64 columns from column c_first on, as `next` gives them out.  Two waves per SIMD keep the
 // vector pipes busy only if neither waits for memory, so the next item's columns of W, and its first entries of U, are on
 // their way while this one is worked on.  4096 x 4096, 16 rows: the sweep 2.1 ms with vector products and differences on items
 // of 128 columns, 1.86 so.
-template <int R, int RT>
+template <int R>
 __device__ __forceinline__ void update_behind(float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
                                               int in_, int64_t k0, int c_first, int* next) {
-    using update::at;
-    constexpr int KB = 16;                                     // channels per step: their U entries travel one step ahead
+    constexpr int RT = 16, KB = 16;                            // KB channels per step: their U entries travel one step ahead
     const int lane = fresh(threadIdx.x & 63), in = fresh_uniform(in_);
     const uint32_t pitch = 4u * static_cast<uint32_t>(in);
+    const update::Matrix W(Wrows), Urows(U + k0 * in);
     const int halves = n_rows > RT ? 2 : 1, n_items = (in - c_first + 63) / 64 * halves;
     auto take = [&] {
         int item = 0;
@@ -247,7 +238,7 @@ __device__ __forceinline__ void update_behind(float* __restrict__ Wrows, const f
     auto row0_of = [&](int item) { return halves == 1 ? 0 : (item & 1) * RT; };
     auto col0_of = [&](int item) { return c_first + (halves == 1 ? item : item >> 1) * 64; };
     auto u_offset = [&](int item) { return 4u * static_cast<uint32_t>(min(col0_of(item) + lane, in - 1)); };
-    auto e_first = [&](int item) { return es + row0_of(item) + min(lane & 15, RT - 1); };
+    auto e_first = [&](int item) { return es + row0_of(item) + (lane & 15); };
     // past the last row or column: read, never stored
     auto load = [&](int item, update::f32x16& v) {
         const int rt = row0_of(item), c0 = col0_of(item);
@@ -258,18 +249,13 @@ __device__ __forceinline__ void update_behind(float* __restrict__ Wrows, const f
         for (int r = 0; r < 4; ++r) {
             const uint32_t row = static_cast<uint32_t>(min(rt + 4 * (lane >> 4) + r, n_rows - 1)) * pitch;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) v[4 * b + r] = *at(Wrows, row + col[b]);
+            for (int b = 0; b < 4; ++b) v[4 * b + r] = W.load(row + col[b], 0);
         }
     };
     float u[2][KB];
-    const float* Ublock = U + k0 * in;
     auto fetch = [&](int b, int k, uint32_t col) {
-        const float* urow = Ublock + k * in;
 #pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-            u[b][kk] = *at(urow, col);
-            urow += in;
-        }
+        for (int kk = 0; kk < KB; ++kk) u[b][kk] = Urows.load(col, (k + kk) * pitch);
     };
     update::f32x16 v, v_next, p[2];
     uint32_t ucol = u_offset(item);
@@ -310,14 +296,14 @@ __device__ __forceinline__ void update_behind(float* __restrict__ Wrows, const f
         steps(GB / 2);
         {
             const int lane_s = fresh(lane), rt = row0_of(item), c0 = col0_of(item);
-            float* Wr = Wrows + static_cast<uint32_t>(rt) * static_cast<uint32_t>(in) + c0;
             const int rows_here = min(n_rows - rt, RT), cols_here = in - c0;
             const uint32_t first = static_cast<uint32_t>(4 * (lane_s >> 4)) * pitch + 4u * static_cast<uint32_t>(lane_s & 15);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int b = 0; b < 4; ++b)
-                    if (4 * (lane_s >> 4) + r < rows_here && 16 * b + (lane_s & 15) < cols_here) *at(Wr + r * in + 16 * b, first) = v[4 * b + r];
+                    if (4 * (lane_s >> 4) + r < rows_here && 16 * b + (lane_s & 15) < cols_here) 
+                        W.store(v[4 * b + r], first, (rt + r) * pitch + 4 * (c0 + 16 * b));
         }
         if (!more) break;
         item = then;
@@ -376,8 +362,9 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
                                                          const int32_t* __restrict__ perm, int64_t out, int64_t in64, int g,
                                                          float qmax, int mfmt, const float* __restrict__ st_scales,
                                                          const uint8_t* __restrict__ st_zeros, uint8_t* __restrict__ Qp) {
-    // items of the update: 64 CPL columns of 4 or 8 rows (an LDS read of the errors serves CPL products), 64 of RT rows otherwise
-    constexpr int RR = pow2_rows<R>(), CL = 64 / RR, CPL = 4, RT = R <= 16 ? R : R / 2;
+    // items of the update: RT rows x 64 columns on the matrix cores where RT is 16, else RT rows x 64 CPL columns (RT x CPL
+    // accumulators; few rows take more columns, so that an LDS read of the errors serves as many products)
+    constexpr int RR = pow2_rows<R>(), CL = 64 / RR, CPL = R <= 8 ? 4 : 2, RT = R <= 16 ? R : R / 2;
     extern __shared__ __align__(16) char smem[];
     Lds<R>& lds = *reinterpret_cast<Lds<R>*>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -556,16 +543,19 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
         }
         // errors of the last block onto the columns behind this one, item by item
         if (blk > 0 && behind < in) {
-            if constexpr (R >= 12) {
-                update_behind<R, RT>(Wrows, U, es_last, n_rows, in, int64_t(i1) - GB, behind, &lds.next);
+            if constexpr (RT == 16) {
+                update_behind<R>(Wrows, U, es_last, n_rows, in, int64_t(i1) - GB, behind, &lds.next);
             } else {
-                const int n_items = (in - behind + 64 * CPL - 1) / (64 * CPL);
+                const int n_items = (in - behind + 64 * CPL - 1) / (64 * CPL) * (R / RT);
                 for (;;) {
                     int item = 0;
                     if (lane == 0) item = atomicAdd(&lds.next, 1);
                     item = __builtin_amdgcn_readfirstlane(item);
                     if (item >= n_items) break;
-                    update_item<R, R, CPL>(Wrows, U, es_last, n_rows, in, int64_t(i1) - GB, behind + item * (64 * CPL));
+                    const int rt = R == RT ? 0 : (item & 1) * RT, cc = R == RT ? item : item >> 1;
+                    if (rt < n_rows)
+                        update_item<R, RT, CPL>(Wrows + rt * in64, U, es_last + rt, n_rows - rt, in, int64_t(i1) - GB,
+                                                behind + cc * (64 * CPL));
                 }
             }
         }

@@ -43,16 +43,21 @@ __device__ __forceinline__ f32x16 products16x64(float e, float u) {
 }
 __device__ __forceinline__ int row_of(int r, int lane) { return 32 * (r >> 4) + 8 * ((r & 15) >> 2) + 4 * (lane >> 5) + (r & 3); }
 
-// The element `bytes` behind a wave-uniform address, which is kept in scalar registers (the compiler would rather add it up in
-// 64 bits in every lane): the lanes' 32-bit offsets are then part of the load or store.
-template <typename T>
-using Global = __attribute__((address_space(1))) T;
-template <typename T>
-__device__ __forceinline__ Global<T>* at(T* base, uint32_t bytes) {
-    uintptr_t b = reinterpret_cast<uintptr_t>(base);
-    asm("" : "+s"(b));
-    return (Global<T>*)((Global<char>*)b + bytes);
-}
+// A matrix whose element a lane reaches by a wave-uniform offset (of the row) and one of its own (of the column), in bytes: a
+// load or store is then one instruction, the row's offset one scalar addition.  (Global addresses cost 64-bit additions, in
+// every lane or in scalar registers, and with two waves per SIMD each instruction beside the differences shows.)  The offsets
+// must stay below 2^31: 128 rows of up to 46340 floats do.
+struct Matrix {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ explicit Matrix(const float* p)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, 0x7fffffff, 0x00020000)) {}
+    __device__ __forceinline__ float load(uint32_t lane_bytes, uint32_t uniform_bytes) const {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_bytes, uniform_bytes, 0));
+    }
+    __device__ __forceinline__ void store(float v, uint32_t lane_bytes, uint32_t uniform_bytes) const {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, lane_bytes, uniform_bytes, 0);
+    }
+};
 
 constexpr int ROWS = 64, COLS = 128;   // of a workgroup; a wave takes 32 of the columns
 
@@ -70,21 +75,16 @@ __global__ __launch_bounds__(256, 3) void gq_trailing(float* __restrict__ Wp, co
     const int64_t r0 = int64_t(blockIdx.y) * ROWS;
     const int n_rows = static_cast<int>(min(out - r0, int64_t(ROWS)));         // > 0
     const uint32_t pitch = 4u * static_cast<uint32_t>(in);                     // bytes (64 rows of up to 46340 channels fit 32 bits)
-    float* __restrict__ Wrows = Wp + r0 * in64;
+    const Matrix Wrows(Wp + r0 * in64), Urows(U + i1 * in64);
     const float* __restrict__ Erows = Ep + r0 * in64 + i1;
     const int c_end = static_cast<int>(col1);
     const int c = static_cast<int>(col0) + static_cast<int>(blockIdx.x) * COLS + 32 * wave + (lane & 31);
     const uint32_t col = 4u * static_cast<uint32_t>(min(c, c_end - 1));        // past the end: read, never stored
 
     float u[2][KB];
-    const float* __restrict__ Ublock = U + i1 * in64;
     auto fetch = [&](int b, int k) {
-        const float* urow = Ublock + k * in64;
 #pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-            u[b][kk] = *at(urow, col);
-            urow += in;
-        }
+        for (int kk = 0; kk < KB; ++kk) u[b][kk] = Urows.load(col, (k + kk) * pitch);
     };
     fetch(0, 0);
     if ((in & 3) == 0) {                                       // Ep is scratch, 16-byte aligned; i1 is a multiple of GB
@@ -92,23 +92,23 @@ __global__ __launch_bounds__(256, 3) void gq_trailing(float* __restrict__ Wp, co
         for (int q = 0; q < ROWS * GB / 4 / 256; ++q) {
             const int idx = tid + 256 * q, r = idx / (GB / 4), k = idx % (GB / 4) * 4;
             *reinterpret_cast<f32x4*>(&es[r][k]) =
-                *at(reinterpret_cast<const f32x4*>(Erows), static_cast<uint32_t>(min(r, n_rows - 1)) * pitch + 4u * k);
+                *reinterpret_cast<const f32x4*>(Erows + static_cast<uint32_t>(min(r, n_rows - 1)) * static_cast<uint32_t>(in) + k);
         }
     } else {
 #pragma unroll 8
         for (int q = 0; q < ROWS * GB / 256; ++q) {
             const int idx = tid + 256 * q, r = idx / GB, k = idx % GB;
-            es[r][k] = *at(Erows, static_cast<uint32_t>(min(r, n_rows - 1)) * pitch + 4u * k);
+            es[r][k] = Erows[static_cast<uint32_t>(min(r, n_rows - 1)) * static_cast<uint32_t>(in) + k];
         }
     }
     const uint32_t first = static_cast<uint32_t>(row_of(0, lane)) * pitch + col;
     float v[32];
     if (n_rows == ROWS) {
 #pragma unroll
-        for (int r = 0; r < 32; ++r) v[r] = *at(Wrows + row_of(r, 0) * in64, first);
+        for (int r = 0; r < 32; ++r) v[r] = Wrows.load(first, row_of(r, 0) * pitch);
     } else {
 #pragma unroll
-        for (int r = 0; r < 32; ++r) v[r] = *at(Wrows, static_cast<uint32_t>(min(row_of(r, lane), n_rows - 1)) * pitch + col);
+        for (int r = 0; r < 32; ++r) v[r] = Wrows.load(static_cast<uint32_t>(min(row_of(r, lane), n_rows - 1)) * pitch + col, 0);
     }
     __syncthreads();
     f32x4 ev[2];
@@ -140,14 +140,14 @@ __global__ __launch_bounds__(256, 3) void gq_trailing(float* __restrict__ Wp, co
     if (c >= c_end) return;
     if (n_rows == ROWS) {
 #pragma unroll
-        for (int r = 0; r < 32; ++r) *at(Wrows + row_of(r, 0) * in64, first) = v[r];
+        for (int r = 0; r < 32; ++r) Wrows.store(v[r], first, row_of(r, 0) * pitch);
     } else {
         int lane_s = lane;                                     // row offsets are worked out again, not held over the loop
         asm volatile("" : "+v"(lane_s));
 #pragma unroll
         for (int r = 0; r < 32; ++r) {
             const int row = row_of(r, lane_s);
-            if (row < n_rows) *at(Wrows, static_cast<uint32_t>(row) * pitch + col) = v[r];
+            if (row < n_rows) Wrows.store(v[r], static_cast<uint32_t>(row) * pitch + col, 0);
         }
     }
 }

@@ -13,6 +13,11 @@
 // 4650, the launches 230 us where 3840 columns are behind the block, 75 to 78 where few are.)  Beyond the walks the update is
 // bound by the pipes (3.0e13 elements per second of the 3.7e13 of gptq_update.h's bare loop).
 //
+// Beyond 160 groups, where columns are left behind the first two blocks, the launches are those of the form before, the walk by
+// four waves so that the update finds room beside it (gq_group, gq_next, gq_trailing): tests/test_host_path_cpu.py holds that
+// dispatch.  One list is the faster form there as well (us, launches of their own / one list: 165 groups of 64 x 1000 629 / 499;
+// 260 of 128 x 2048 4230 / 3575; 440 of 64 x 2678 5461 / 5350; 600 of 64 x 1024 1622 / 1455).
+//
 // The walk: the strip sits in LDS, wave 0 takes 16 channels at a time into registers.  Its chain of decisions is what
 // the block waits for: minimum and maximum of the group (one wave reduction), parameters, codes, errors, updates of
 // the later channels of the sixteen.  Meanwhile the other waves apply the errors of the sixteen before to the
@@ -65,7 +70,8 @@ namespace groups {
 
 using namespace chain_ns;
 
-constexpr int WAVES = 8, ROWS = 64, COLS = 256;               // of a workgroup; of a piece of the update
+constexpr int WAVES = 8, ROWS = 64, COLS = 256;               // of a launch's workgroup; of a piece of the update
+constexpr int64_t MANY = 160;          // groups beyond which a block with columns behind it takes launches of their own
 
 template <int RPL>
 struct Walk {
@@ -325,8 +331,8 @@ __device__ __forceinline__ void updated_strip(const float* __restrict__ Wrows, c
         }
 }
 
-// Block [i1, i1 + nbw) of a row group.
-template <int RPL>
+// Block [i1, i1 + nbw) of a row group.  BEHIND: its columns still lack the last block's errors.
+template <int RPL, int WAVES, bool BEHIND>
 __device__ __forceinline__ void walk(Walk<RPL>& lds, int group, const float* __restrict__ Wp, const float* __restrict__ U,
                                      const int32_t* __restrict__ perm, int64_t in, int64_t i1, int nbw, float qmax, float rqmax,
                                      int mfmt, float* __restrict__ scales_out, uint8_t* __restrict__ zeros_out,
@@ -351,7 +357,7 @@ __device__ __forceinline__ void walk(Walk<RPL>& lds, int group, const float* __r
         }
         if (tid < nbw) cd = U[(i1 + tid) * (in + 1)];
     };
-    if (i1 == 0) {
+    if (!BEHIND || i1 == 0) {
         float4 cw[NW];
 #pragma unroll
         for (int q = 0; q < NW; ++q) {
@@ -361,7 +367,7 @@ __device__ __forceinline__ void walk(Walk<RPL>& lds, int group, const float* __r
         corner();
 #pragma unroll
         for (int q = 0; q < NW; ++q) *reinterpret_cast<float4*>(&lds.w[kr + RS * (q >> 2)][c4 + 32 * (q & 3)]) = cw[q];
-    } else {
+    } else if constexpr (BEHIND) {
         updated_strip<RPL>(Wp + row0 * in, U, Ep + row0 * in + i1 - GB, in, i1, nbw, vec, lds);
         corner();
     }
@@ -572,7 +578,7 @@ __device__ __forceinline__ void pieces(Piece& lds, int* taken, int32_t* __restri
 // The launch of block [i1, i1 + nbw): items 0 .. n_groups - 1 are the groups' walks, the rest the pieces of the update.  A
 // workgroup's first item is its own number, the later ones come from `counter` (0 at the start).
 template <int RPL>
-__global__ __launch_bounds__(64 * WAVES, 2) void gq_step(float* __restrict__ Wp, const float* __restrict__ U,
+__global__ __launch_bounds__(64 * WAVES, 2) void gq_group_step(float* __restrict__ Wp, const float* __restrict__ U,
                                                          const int32_t* __restrict__ perm, int64_t in, int64_t i1, int nbw, int n_groups,
                                                          int n_items, float qmax, float rqmax, int mfmt, float* __restrict__ scales_out,
                                                          uint8_t* __restrict__ zeros_out, uint8_t* __restrict__ Qp,
@@ -581,13 +587,24 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_step(float* __restrict__ Wp,
     Lds<RPL>& lds = *reinterpret_cast<Lds<RPL>*>(smem);
     int item = static_cast<int>(blockIdx.x);
     while (item < n_groups) {
-        walk<RPL>(lds.walk, item, Wp, U, perm, in, i1, nbw, qmax, rqmax, mfmt, scales_out, zeros_out, Qp, Ep);
+        walk<RPL, WAVES, true>(lds.walk, item, Wp, U, perm, in, i1, nbw, qmax, rqmax, mfmt, scales_out, zeros_out, Qp, Ep);
         if (threadIdx.x == 0) lds.taken = static_cast<int>(gridDim.x) + atomicAdd(counter, 1);
         __syncthreads();                                       // (the walk's last reads of LDS are behind it, too)
         item = __builtin_amdgcn_readfirstlane(lds.taken);
         __syncthreads();
     }
     if (item < n_items) pieces(lds.piece, &lds.taken, counter, item, n_groups, n_items, Wp, U, Ep, in, i1 - GB, static_cast<int>(i1) + nbw);
+}
+
+// The walk alone, four waves, for a block whose columns are up to date.
+template <int RPL>
+__global__ __launch_bounds__(256, 1) void gq_group(const float* __restrict__ Wp, const float* __restrict__ U,
+                                                   const int32_t* __restrict__ perm, int64_t in, int64_t i1, int nbw, float qmax, float rqmax,
+                                                   int mfmt, float* __restrict__ scales_out, uint8_t* __restrict__ zeros_out,
+                                                   uint8_t* __restrict__ Qp, float* __restrict__ Ep) {
+    extern __shared__ __align__(16) char smem[];
+    walk<RPL, 4, false>(*reinterpret_cast<Walk<RPL>*>(smem), static_cast<int>(blockIdx.x), Wp, U, perm, in, i1, nbw, qmax, rqmax, mfmt,
+                        scales_out, zeros_out, Qp, Ep);
 }
 
 // Pieces of the update in the launch of the block at i1 (none in the first one's).
@@ -598,8 +615,10 @@ inline int64_t n_pieces(int64_t out, int64_t in, int64_t i1) {
 
 template <int RPL>
 hipError_t allow_lds_of() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(gq_step<RPL>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               static_cast<int>(sizeof(Lds<RPL>)));
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gq_group_step<RPL>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             static_cast<int>(sizeof(Lds<RPL>)));
+    return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(gq_group<RPL>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     static_cast<int>(sizeof(Walk<RPL>)));
 }
 inline hipError_t allow_lds() {
     const hipError_t e = allow_lds_of<1>();

@@ -467,20 +467,22 @@ __global__ __launch_bounds__(256, 4) void chol_panel(const double* __restrict__ 
 }
 
 // Trailing update A -= L[., k0 .. k0+w) L[., k0 .. k0+w)^T of the lower triangle's tiles behind a 512-wide outer panel
-// (w = 512).  ct0: first tile column of this launch (the update goes out in two launches).
+// (w = 512).  ct0: first tile column of this launch (the update goes out in two launches); tile rows x columns: rows x cols.
 __global__ __launch_bounds__(256, 4) void chol_syrk(double* __restrict__ A, const double* __restrict__ M, int64_t n, int64_t k0, int w,
-                                                    int64_t k1, int ct0) {
-    const int ct = static_cast<int>(blockIdx.x) + ct0;
-    if (ct > static_cast<int>(blockIdx.y)) return;
+                                                    int64_t k1, int ct0, int rows, int cols) {
     __shared__ double As[GK][GT + 4], Bs[GK][GT + 4];
-    const int64_t r0 = k1 + int64_t(blockIdx.y) * GT, c0 = k1 + int64_t(ct) * GT;
-    const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT), n_valid = static_cast<int>(n - c0 < GT ? n - c0 : GT);
-    double4_t acc[GT / 32][GT / 32];
-    dgemm_fill<GT>(acc, [&](int i, int j) { return (i < m_valid && j < n_valid) ? A[(r0 + i) * n + c0 + j] : 0.0; });
-    dgemm_tile<GT, false, false, true>(M + k0 * n + r0, n, m_valid, M + k0 * n + c0, n, n_valid, 0, w, As, Bs, acc);
-    dgemm_each<GT>(acc, [&](int i, int j, double v) {
-        if (i < m_valid && c0 + j <= r0 + i) A[(r0 + i) * n + c0 + j] = v;
-    });
+    for (int tile = static_cast<int>(blockIdx.x); tile < rows * cols; tile += static_cast<int>(gridDim.x)) {
+        const int ct = tile % cols + ct0, rt = tile / cols;
+        if (ct > rt) continue;
+        const int64_t r0 = k1 + int64_t(rt) * GT, c0 = k1 + int64_t(ct) * GT;
+        const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT), n_valid = static_cast<int>(n - c0 < GT ? n - c0 : GT);
+        double4_t acc[GT / 32][GT / 32];
+        dgemm_fill<GT>(acc, [&](int i, int j) { return (i < m_valid && j < n_valid) ? A[(r0 + i) * n + c0 + j] : 0.0; });
+        dgemm_tile<GT, false, false, true>(M + k0 * n + r0, n, m_valid, M + k0 * n + c0, n, n_valid, 0, w, As, Bs, acc);
+        dgemm_each<GT>(acc, [&](int i, int j, double v) {
+            if (i < m_valid && c0 + j <= r0 + i) A[(r0 + i) * n + c0 + j] = v;
+        });
+    }
 }
 
 // The end of an update's tile: the workgroup of the first tile (the diagonal block at k1, final once this update has
@@ -555,20 +557,20 @@ __global__ __launch_bounds__(256, 3) void chol_step(double* __restrict__ A, doub
     chol_tile_end(acc, A, M, n, k1, r0, c0, m_valid, n_valid, *reinterpret_cast<DiagLds*>(smem));
 }
 
-// ------------------------------------------------------------------ M = inv(L), lower, by doubling
-// inv [[A, 0], [C, B]] = [[inv A, 0], [-inv(B) C inv(A), inv B]].  With the diagonal blocks of
-// size s inverted, level s pairs them up: pair p = blockIdx.z covers rows a0 = 2 p s (A, s rows)
-// and b0 = a0 + s (B, sb <= s rows at the matrix end).  Two products per level, every pair and
+// ------------------------------------------------------------------ M = inv(L), lower
+// inv [[A, 0], [C, B]] = [[inv A, 0], [-inv(B) C inv(A), inv B]].  Diagonal blocks of up to a panel by doubling: with the
+// blocks of size s inverted, a level pairs them up: pair blockIdx.z covers rows a0 = 2 s blockIdx.z (A) and a0 + s (B, at
+// most s rows at the end) of the `size` rows from `base` on.  Two products, every pair and
 // every tile in parallel: T = C inv(A) (PASS 0, inv(A) lower triangular: k starts at the tile's
 // first column), then M[B rows, A columns] = -inv(B) T (PASS 1, k ends with the tile's last row).
 // TS x TS tiles, TS dividing s.
 template <int PASS, int TS>
-__global__ __launch_bounds__(256, 4) void trinv_level(double* __restrict__ M, double* __restrict__ T, int64_t n, int64_t s) {
-    const int64_t a0 = 2 * int64_t(blockIdx.z) * s, b0 = a0 + s;
-    const int64_t sb = n - b0 < s ? n - b0 : s;               // > 0 for every pair in the grid
-    // PASS 0's tiles get shorter from left to right: every other eight tile rows run from right to left, or the workgroups
-    // that meet on a compute unit (256 apart in a launch of 32 x 32) would all be of one column (the
-    // last level of a 4096-wide factor: 415 us, now 190 with the accumulators out of the AGPRs as well).
+__global__ __launch_bounds__(256, 4) void trinv_level(double* __restrict__ M, double* __restrict__ T, int64_t n, int64_t base, int64_t size,
+                                                      int64_t s) {
+    const int64_t a = 2 * int64_t(blockIdx.z) * s, a0 = base + a, b0 = a0 + s;
+    const int64_t sb = size - a - s < s ? size - a - s : s;   // > 0 for every pair in the grid
+    // (the larger levels:) PASS 0's tiles get shorter from left to right: every other eight tile rows run from right to left,
+    // or the workgroups that meet on a compute unit would all be of one column.
     const unsigned bx = PASS == 0 && ((blockIdx.y >> 3) & 1) ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
     const int64_t m0 = int64_t(blockIdx.y) * TS, n0 = int64_t(bx) * TS;
     if (m0 >= sb) return;
@@ -590,12 +592,48 @@ __global__ __launch_bounds__(256, 4) void trinv_level(double* __restrict__ M, do
     }
 }
 
-// U[a][b] = fp32(M[n-1-a][n-1-b]): upper triangular, visiting order
-__global__ void gq_flip(const double* __restrict__ M, int64_t n, float* __restrict__ U) {
-    const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= n * n) return;
-    const int64_t a = idx / n, b = idx % n;
-    U[idx] = b >= a ? static_cast<float>(M[(n - 1 - a) * n + (n - 1 - b)]) : 0.0f;
+// Panel by panel: the rows below the panel at k0 (w wide) gather R = L X, X = inv(L) of the panels so far, in the part of M that
+// their own inverse will take, and a panel's rows become X = -inv(diagonal block) R when their turn comes.  That product
+// goes to the lower triangle of A, whose columns left of the panel nobody reads any more (R is read by several workgroups).
+// Every product is at most 512 deep and as many tiles wide as there are columns.  (T = C inv(A) in one product when a panel's
+// turn comes has tiles up to 3584 deep at 4096, 250 us each.)
+//
+// R's rows from k0 + w on, columns 0 .. k0 + w (a multiple of 64)
+__global__ __launch_bounds__(256, 4) void trinv_spread(const double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0, int w) {
+    __shared__ double As[GK][GT + 4], Bs[GK][GT + 4];
+    const int64_t k1 = k0 + w;
+    const int cols = static_cast<int>(k1 / GT), tiles = static_cast<int>((n - k1 + GT - 1) / GT) * cols;
+    for (int tile = static_cast<int>(blockIdx.x); tile < tiles; tile += static_cast<int>(gridDim.x)) {
+        const int64_t r0 = k1 + int64_t(tile / cols) * GT, c0 = int64_t(tile % cols) * GT;
+        const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT);
+        const bool own = c0 >= k0;                            // columns of the panel itself, which nothing was added to yet
+        double4_t acc[GT / 32][GT / 32] = {};
+        if (!own) dgemm_fill<GT>(acc, [&](int i, int j) { return i < m_valid ? M[(r0 + i) * n + c0 + j] : 0.0; });
+        dgemm_tile<GT, false, false>(M + k0 * n + r0, n, m_valid, (own ? M : A) + k0 * n + c0, n, GT, own ? c0 - k0 : 0, w, As, Bs, acc);
+        dgemm_each<GT>(acc, [&](int i, int j, double v) {
+            if (i < m_valid) M[(r0 + i) * n + c0 + j] = v;
+        });
+    }
+}
+// X's rows of the panel at k0 (w of them), columns left of it
+__global__ __launch_bounds__(256, 4) void trinv_rows(double* __restrict__ A, const double* __restrict__ M, int64_t n, int64_t k0, int w) {
+    __shared__ double As[GK][GT + 4], Bs[GK][GT + 4];
+    const int64_t m0 = int64_t(blockIdx.y) * GT, c0 = int64_t(blockIdx.x) * GT;
+    const int m_valid = static_cast<int>(w - m0 < GT ? w - m0 : GT);
+    double4_t acc[GT / 32][GT / 32] = {};
+    dgemm_tile<GT, true, false, true>(M + (k0 + m0) * n + k0, n, m_valid, M + k0 * n + c0, n, GT, 0, m0 + m_valid, As, Bs, acc);
+    dgemm_each<GT>(acc, [&](int i, int j, double v) {
+        if (i < m_valid) A[(k0 + m0 + i) * n + c0 + j] = v;
+    });
+}
+
+// U[a][b] = fp32(inv(L)[n-1-a][n-1-b]): upper triangular, visiting order; the rows of U that come from row r0 + blockIdx.y, whose
+// columns left of r0 are in A, the others in M
+__global__ void gq_flip(const double* __restrict__ A, const double* __restrict__ M, int64_t n, int64_t r0, float* __restrict__ U) {
+    const int64_t r = r0 + blockIdx.y, a = n - 1 - r, b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (b >= n) return;
+    const int64_t c = n - 1 - b;
+    U[a * n + b] = c <= r ? static_cast<float>((c < r0 ? A : M)[r * n + c]) : 0.0f;
 }
 
 // ------------------------------------------------------------------ sweep
@@ -859,16 +897,49 @@ int launch_gptq_prepare(adadim_ctx* ctx, const float* H, int64_t n, float percda
     else
         hipLaunchKernelGGL(gq_gather_wide, dim3(nb2), dim3(256), 0, ctx->stream, H, n, perm, dvec, damp, A);
     ADADIM_LAUNCH_CHECK(ctx, "gptq prepare");
+    // Workgroups of a launch on the side streams take its tiles in turn, two or three per compute unit: more would leave no room
+    // (LDS and registers) for the main stream's short launches, which then wait for tiles to end (4096: 3240 us with a
+    // workgroup per tile, steps of 20 us taking 60 to 90).  The line, us with two / three per unit: 2900 1378 / 1391, 4096 2213 / 2260,
+    // 5120 3700 / 3501, 11008 23800 / 22040; and the next panel's columns updated ahead / not: 2048 918 / 975, 2900 1391 / 1438,
+    // 4096 2260 / 2256, 5120 3501 / 3418, 11008 22040 / 21605.
+    const bool narrow = n <= 4608;                            // the chain of steps is the longer part
+    const unsigned bulk = narrow ? 2 * 256 : 3 * 256;
     // Outer panels of 512 columns: inside a panel the 64-wide steps update the panel's own columns
     // only; the columns behind it get the whole panel at once, a product with 256 contraction steps
     // per pass over the trailing matrix instead of 64.
     const bool overlap = n > 2 * NBO;
     if (overlap && !adadim_side_stream(ctx)) return ADADIM_EHIP;
-    bool side_busy = false;
+    // The inverse: the diagonal block of a panel by doubling, then the panel's rows, then what they add to the rows below.  From
+    // three panels on that happens on a stream of its own, while the main stream works on the next panel's
+    // steps, so that only the last panel's rows are inverted behind the factorization.  (Not on the update's stream: the main
+    // stream waits for each update, and would for the inverse before it.)
+    // (T holds the doubling's products of a panel, twice, as the last panel's run beside that stream's.)
+    double* t_level[2] = {T, T + NBO / 2 * (NBO / 2)};
+    auto invert_diagonal = [&](hipStream_t stream, int64_t base, int64_t size, double* t) {
+        for (int64_t s = NB; s < size; s *= 2) {
+            const unsigned pairs = static_cast<unsigned>((size - s + 2 * s - 1) / (2 * s));   // those with rows below a0 + s
+            const dim3 grid(static_cast<unsigned>(s / GT), static_cast<unsigned>(s / GT), pairs);
+            hipLaunchKernelGGL((trinv_level<0, GT>), grid, dim3(256), 0, stream, M, t, n, base, size, s);
+            hipLaunchKernelGGL((trinv_level<1, GT>), grid, dim3(256), 0, stream, M, t, n, base, size, s);
+        }
+    };
+    auto finish_rows = [&](hipStream_t stream, int64_t k0, int64_t w) {
+        if (k0 > 0)
+            hipLaunchKernelGGL(trinv_rows, dim3(static_cast<unsigned>(k0 / GT), static_cast<unsigned>((w + GT - 1) / GT)), dim3(256), 0,
+                               stream, A, M, n, k0, static_cast<int>(w));
+        hipLaunchKernelGGL(gq_flip, dim3(nb1, static_cast<unsigned>(w)), dim3(256), 0, stream, A, M, n, k0, U);
+    };
+    auto spread_rows = [&](int64_t k0) {                      // of a whole panel with rows below it
+        const int64_t k1 = k0 + NBO;
+        const unsigned tiles = static_cast<unsigned>(k1 / GT * ((n - k1 + GT - 1) / GT));
+        hipLaunchKernelGGL(trinv_spread, dim3(std::min(tiles, bulk)), dim3(256), 0, ctx->side2, A, M, n, k0, NBO);
+    };
+    bool side_used = false;                                   // (a stream that is not yet part of a recording is not waited for)
     bool diag_ready = false;                                  // the block at the next k0 is already factored (chol_syrk_diag)
     static_assert(GT == NB, "chol_syrk_diag's first tile is the next diagonal block");
     for (int64_t K0 = 0; K0 < n; K0 += NBO) {
         const int64_t W = n - K0 < NBO ? n - K0 : NBO;
+        int64_t ahead = 0;                                    // of this panel's columns, how many the next panel's have had
         for (int64_t k0 = K0; k0 < K0 + W; k0 += NB) {
             const int w = static_cast<int>(n - k0 < NB ? n - k0 : NB);
             if (!diag_ready) hipLaunchKernelGGL(chol_diag_inv, dim3(1), dim3(256), 0, ctx->stream, A, M, n, k0, w);
@@ -880,9 +951,28 @@ int launch_gptq_prepare(adadim_ctx* ctx, const float* H, int64_t n, float percda
                 if (tc > 0) {
                     hipLaunchKernelGGL(chol_step, dim3(tc, t), dim3(256), 0, ctx->stream, A, M, n, k0);
                     diag_ready = true;
+                    // The next panel's columns get what is final of this panel's L ahead of the panel's end, on the side stream,
+                    // which leaves the main stream a product of 128 steps (its seven launches of 40 to 80 us at 4096 take 20 to 45 so).
+                    const int64_t k_done = k0 + NB - K0;
+                    if (overlap && narrow && n > K0 + NBO && (k_done == NBO / 2 || k_done == 3 * NBO / 4)) {
+                        const int64_t k1 = K0 + NBO, from = k_done == NBO / 2 ? 0 : NBO / 2;
+                        const unsigned rows = static_cast<unsigned>((n - k1 + GT - 1) / GT);
+                        const unsigned cols = std::min<unsigned>(rows, NBO / GT);
+                        ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[0], ctx->stream));
+                        ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->side, ctx->side_ev[0], 0));
+                        side_used = true;
+                        hipLaunchKernelGGL(chol_syrk, dim3(std::min(rows * cols, bulk)), dim3(256), 0, ctx->side, A, M, n, K0 + from,
+                                           static_cast<int>(k_done - from), k1, 0, static_cast<int>(rows), static_cast<int>(cols));
+                        ahead = k_done;
+                    }
                 } else
                     hipLaunchKernelGGL(chol_panel, dim3(t), dim3(256), 0, ctx->stream, A, M, n, k0, w);
             }
+        }
+        if (overlap && K0 > 0) {
+            invert_diagonal(ctx->side2, K0 - NBO, NBO, t_level[0]);
+            finish_rows(ctx->side2, K0 - NBO, NBO);
+            spread_rows(K0 - NBO);
         }
         const int64_t rest = n - K0 - W;
         if (rest > 0) {
@@ -894,32 +984,38 @@ int launch_gptq_prepare(adadim_ctx* ctx, const float* H, int64_t n, float percda
             // side stream's last launch before it updates columns that launch wrote.
             const unsigned t = static_cast<unsigned>((rest + GT - 1) / GT);
             const unsigned tn = static_cast<unsigned>(((rest < NBO ? rest : NBO) + GT - 1) / GT);
-            if (side_busy) ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->stream, ctx->side_ev[1], 0));
-            side_busy = false;
-            // both launches need the finished panel, and write different tile columns: the side stream starts with
-            // the main stream's launch, not behind it
-            if (overlap && t > tn) ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[0], ctx->stream));
-            hipLaunchKernelGGL(chol_syrk_diag, dim3(overlap ? tn : t, t), dim3(256), 0, ctx->stream, A, M, n, K0,
-                               static_cast<int>(W), K0 + W);
+            if (side_used) {                                  // its earlier launches wrote these columns
+                ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[1], ctx->side));
+                ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->stream, ctx->side_ev[1], 0));
+            }
+            if (overlap) {
+                // both launches need the finished panel, and write different tile columns: the side stream starts with
+                // the main stream's launch, not behind it
+                ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[0], ctx->stream));
+            }
+            hipLaunchKernelGGL(chol_syrk_diag, dim3(overlap ? tn : t, t), dim3(256), 0, ctx->stream, A, M, n, K0 + ahead,
+                               static_cast<int>(W - ahead), K0 + W);
             diag_ready = true;
             if (overlap && t > tn) {
                 ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->side, ctx->side_ev[0], 0));
-                hipLaunchKernelGGL(chol_syrk, dim3(t - tn, t), dim3(256), 0, ctx->side, A, M, n, K0, static_cast<int>(W),
-                                   K0 + W, static_cast<int>(tn));
-                ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[1], ctx->side));
-                side_busy = true;
+                side_used = true;
+                hipLaunchKernelGGL(chol_syrk, dim3(std::min((t - tn) * t, bulk)), dim3(256), 0, ctx->side, A, M, n, K0,
+                                   static_cast<int>(W), K0 + W, static_cast<int>(tn), static_cast<int>(t), static_cast<int>(t - tn));
             }
+            if (overlap) ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->side2, ctx->side_ev[0], 0));
         }
     }
-    if (side_busy) ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->stream, ctx->side_ev[1], 0));   // join
     ADADIM_LAUNCH_CHECK(ctx, "gptq cholesky");
-    for (int64_t s = NB; s < n; s *= 2) {
-        const unsigned pairs = static_cast<unsigned>((n - s + 2 * s - 1) / (2 * s));   // those with rows below a0 + s
-        const dim3 grid(static_cast<unsigned>(s / GT), static_cast<unsigned>(s / GT), pairs);
-        hipLaunchKernelGGL((trinv_level<0, GT>), grid, dim3(256), 0, ctx->stream, M, T, n, s);
-        hipLaunchKernelGGL((trinv_level<1, GT>), grid, dim3(256), 0, ctx->stream, M, T, n, s);
+    if (overlap) {
+        const int64_t last = (n - 1) / NBO * NBO;
+        ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[2], ctx->side2));
+        invert_diagonal(ctx->stream, last, n - last, t_level[1]);
+        ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->stream, ctx->side_ev[2], 0));               // join
+        finish_rows(ctx->stream, last, n - last);
+    } else {
+        invert_diagonal(ctx->stream, 0, n, T);
+        hipLaunchKernelGGL(gq_flip, dim3(nb1, static_cast<unsigned>(n)), dim3(256), 0, ctx->stream, A, M, n, int64_t(0), U);
     }
-    hipLaunchKernelGGL(gq_flip, dim3(nb2), dim3(256), 0, ctx->stream, M, n, U);
     ADADIM_LAUNCH_CHECK(ctx, "gptq inverse");
     return ADADIM_OK;
 }

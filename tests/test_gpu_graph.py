@@ -208,3 +208,45 @@ def test_recorded_sweeps_replay_as_eager(out_f, in_f, dim, group):
         ctx.adadim_graph_destroy(graph)
         torch.cuda.synchronize()
         ctx.close()
+
+
+@pytest.mark.parametrize("n", [700, 1025, 1700, 4700])       # one stream; the smallest with more; columns updated ahead; not
+def test_recorded_factor_replays_as_eager(n):
+    """The factor recorded with the work it puts on the context's side streams: every replay with a new H gives the eager call's
+    bits."""
+    rng = torch.Generator(device="cuda").manual_seed(n)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ctx = B.Context()
+        H = torch.empty((n, n), device="cuda")
+
+        def fill():
+            A = torch.randn((n, 64), generator=rng, device="cuda")
+            S = A @ A.t() / 64 + torch.diag(1.0 + torch.rand(n, generator=rng, device="cuda"))
+            H.copy_(torch.triu(S) + torch.triu(S, 1).t())
+
+        def outputs():
+            return (torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty(n, dtype=torch.uint8, device="cuda"),
+                    torch.empty((n, n), device="cuda"))
+
+        fill()
+        out = outputs()
+        ctx.adadim_gptq_prepare(H, *out, 0.01, True)          # sizes the scratch
+        torch.cuda.synchronize()
+        ctx.adadim_capture_begin()
+        ctx.adadim_gptq_prepare(H, *out, 0.01, True)
+        graph = ctx.adadim_capture_end()
+        for rep in range(3):
+            fill()
+            ref = outputs()
+            ctx.adadim_gptq_prepare(H, *ref, 0.01, True)
+            if rep:
+                torch.cuda.synchronize()
+            out[2].fill_(float("nan"))
+            ctx.adadim_graph_launch(graph)
+            torch.cuda.synchronize()
+            for a, b in zip(out, ref):
+                assert torch.equal(a, b), rep
+        ctx.adadim_graph_destroy(graph)
+        torch.cuda.synchronize()
+        ctx.close()

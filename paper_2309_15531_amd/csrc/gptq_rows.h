@@ -2,20 +2,22 @@
 //
 // With static groups (per-OC) the rows of W do not depend on each other, so a workgroup can take its R rows through
 // every channel without meeting another workgroup.  Eight waves:
-//   * wave 0 walks the 128 channels of block b: the chain of rounding decisions, latency bound;
+//   * wave 0 walks the 128 channels of block b: the chain of rounding decisions, latency bound; with 12 rows and more a
+//     second wave takes the block's columns behind the next 16;
 //   * meanwhile the others apply the errors of block b - 1 to the columns behind block b (a rounded product and a rounded
 //     difference per element and channel, which is the definition's sequence, so no fma); wave 0 joins them when its
 //     chain is done;
 //   * then all waves apply block b's errors to block b + 1's columns, on their way from memory into LDS.
-// Two barriers per block and nothing else to wait for.  The launches per block and the two streams this replaces
+// Two barriers per block, two counters between the chain's waves, and nothing else to wait for.  The launches per block and the two streams this replaces
 // left the chip idle around every short launch.  The whole sweep of a 4096 x 4096 layer, 3 bits: 3.3 ms then, 2.1 ms
-// in one launch with products and differences in vector instructions, 1.9 ms with the products behind the block on the
-// matrix cores (16 and 32 rows per workgroup); 64 to 1024 rows of that width 0.9 ms (the chain alone).
+// in one launch with products and differences in vector instructions, 1.7 ms with the products behind the block on the
+// matrix cores (16 and 32 rows per workgroup) and two waves at the chain; 64 to 1024 rows of that width 0.9 ms (the chain alone).
+//
 // Rows per workgroup: few enough that the chip's 256 compute units all have a workgroup (16 at 4096 rows), so that
 // the VALU work is spread over the whole chip; the chain takes the same time for 4 rows as for 64.  rows_per_group
 // picks R from the sizes.
 //
-// Registers: with 32 rows 20 vector registers do not fit and live in scratch, with 8 rows 9, otherwise none.  They are values
+// Registers: with 32 rows 26 vector registers do not fit and live in scratch, with 8 rows 12, otherwise none.  They are values
 // that hold over the block loop; none is read inside the sixteen channels' chain or the updates' product loops.
 //
 // Order of the updates of one element: blocks in order, channels inside a block in order, whichever wave applies
@@ -37,21 +39,32 @@ namespace rows {
 using namespace chain_ns;
 
 constexpr int WAVES = 8;
+constexpr int SECOND = 4;               // the wave beside wave 0's chain, on the same SIMD
 
 template <int R>
 constexpr int pow2_rows() { return R <= 4 ? 4 : R <= 8 ? 8 : R <= 16 ? 16 : 32; }
+
+// Errors in LDS: [row][channel] where the matrix cores make the products (four channels of a row in one read), else
+// [channel][row] (four rows of a channel).  Where channel c of row r is, and the words of a buffer.
+template <int R>
+constexpr bool BY_ROW = R == 16 || R == 32;
+template <int R>
+__device__ __forceinline__ constexpr int e_at(int c, int r) { return BY_ROW<R> ? r * PITCH + c : c * R + r; }
+template <int R>
+constexpr int E_WORDS = BY_ROW<R> ? R * PITCH : R * GB;
 
 // LDS of one workgroup (dynamic)
 template <int R>
 struct Lds {
     float ut[GB][PITCH];               // ut[c][k] = U[i1 + k][i1 + c], the block's corner, transposed
     float w[R][PITCH];                 // the block's columns of the rows, as the chain finds them
-    float e[2][GB][R];                 // errors, [channel][row], of this block and the last
+    float e[2][E_WORDS<R>];            // errors (e_at) of this block and the last
     float2 sc[GB][R];                  // static scale of (channel, row) and its reciprocal (NaN: outside fastdiv's range)
     float rd[GB];                      // 1 / U_ii of the block's channels (NaN likewise)
     int cg[2][GB];                     // static group of the channels of this block and the next
     uint8_t zp[GB][R];                 // static zero-point
     int next;                          // next item of the update behind the block
+    int posted, done;                  // sub-blocks whose errors are in `e`; whose errors the second wave has applied
 };
 
 // A whole sub-block of 16 channels for one row per lane, everything in registers, with the short quotients
@@ -134,7 +147,7 @@ __device__ __forceinline__ void chain_slow(float* wrow, const float* ut, float* 
         q = fminf(fmaxf(q, 0.0f), qmax);
         put(c, static_cast<uint8_t>(q));
         const float e = (w - sc * (q - zp)) / ut[c * PITCH + c];
-        es_col[c * R] = e;
+        es_col[e_at<R>(c, 0)] = e;
 #pragma unroll 1
         for (int cc = c + 1; cc < n; ++cc) {
             const float upd = e * ut[cc * PITCH + c];
@@ -216,18 +229,19 @@ __device__ __forceinline__ void update_item(float* __restrict__ Wrows, const flo
 }
 
 // The update behind a block for workgroups of 16 and 32 rows, the products on the matrix cores (gptq_update.h): items of 16
-// rows x 64 columns from column c_first on, as `next` gives them out.  Two waves per SIMD keep the
+// rows x 128 columns from column c_first on, as `next` gives them out.  Two waves per SIMD keep the
 // vector pipes busy only if neither waits for memory, so the next item's columns of W, and its first entries of U, are on
-// their way while this one is worked on.  4096 x 4096, 16 rows: the sweep 2.1 ms with vector products and differences on items
-// of 128 columns, 1.86 so.
+// their way while this one is worked on; and an instruction beside the differences costs a wave as much as one of them, so
+// two products share a channel's errors and row of U, and four channels a read of the errors (64 columns and a read per
+// channel: 12 us per pair of items, 90 us for the 3712 columns of the third block of 4096 x 4096, 16 rows; 83 so).
 template <int R>
 __device__ __forceinline__ void update_behind(float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
                                               int in_, int64_t k0, int c_first, int* next) {
-    constexpr int RT = 16, KB = 16;                            // KB channels per step: their U entries travel one step ahead
+    constexpr int RT = 16, COLS = 128, KB = 8;                 // KB channels per step: their U entries travel one step ahead
     const int lane = fresh(threadIdx.x & 63), in = fresh_uniform(in_);
     const uint32_t pitch = 4u * static_cast<uint32_t>(in);
     const update::Matrix W(Wrows), Urows(U + k0 * in);
-    const int halves = n_rows > RT ? 2 : 1, n_items = (in - c_first + 63) / 64 * halves;
+    const int halves = n_rows > RT ? 2 : 1, n_items = (in - c_first + COLS - 1) / COLS * halves;
     auto take = [&] {
         int item = 0;
         if (lane == 0) item = atomicAdd(next, 1);
@@ -236,58 +250,63 @@ __device__ __forceinline__ void update_behind(float* __restrict__ Wrows, const f
     int item = take();
     if (item >= n_items) return;
     auto row0_of = [&](int item) { return halves == 1 ? 0 : (item & 1) * RT; };
-    auto col0_of = [&](int item) { return c_first + (halves == 1 ? item : item >> 1) * 64; };
-    auto u_offset = [&](int item) { return 4u * static_cast<uint32_t>(min(col0_of(item) + lane, in - 1)); };
-    auto e_first = [&](int item) { return es + row0_of(item) + (lane & 15); };
+    auto col0_of = [&](int item) { return c_first + (halves == 1 ? item : item >> 1) * COLS; };
+    auto u_offset = [&](int item, int q) { return 4u * static_cast<uint32_t>(min(col0_of(item) + 64 * q + lane, in - 1)); };
+    auto e_first = [&](int item) { return es + e_at<R>(0, row0_of(item) + (lane & 15)); };
     // past the last row or column: read, never stored
-    auto load = [&](int item, update::f32x16& v) {
+    auto load = [&](int item, update::f32x16 (&v)[2]) {
         const int rt = row0_of(item), c0 = col0_of(item);
-        uint32_t col[4];
-#pragma unroll
-        for (int b = 0; b < 4; ++b) col[b] = 4u * static_cast<uint32_t>(min(c0 + 16 * b + (lane & 15), in - 1));
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const uint32_t row = static_cast<uint32_t>(min(rt + 4 * (lane >> 4) + r, n_rows - 1)) * pitch;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) v[4 * b + r] = W.load(row + col[b], 0);
+            for (int b = 0; b < 8; ++b)
+                v[b >> 2][4 * (b & 3) + r] = W.load(row + 4u * static_cast<uint32_t>(min(c0 + 16 * b + (lane & 15), in - 1)), 0);
         }
     };
-    float u[2][KB];
-    auto fetch = [&](int b, int k, uint32_t col) {
+    float u[2][KB][2];
+    auto fetch = [&](int b, int k, const uint32_t (&col)[2]) {
 #pragma unroll
-        for (int kk = 0; kk < KB; ++kk) u[b][kk] = Urows.load(col, (k + kk) * pitch);
+        for (int kk = 0; kk < KB; ++kk)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) u[b][kk][q] = Urows.load(col[q], (k + kk) * pitch);
     };
-    update::f32x16 v, v_next, p[2];
-    uint32_t ucol = u_offset(item);
+    update::f32x16 v[2], v_next[2], p[2];
+    uint32_t ucol[2] = {u_offset(item, 0), u_offset(item, 1)};
     const float* e_row = e_first(item);
     fetch(0, 0, ucol);
     load(item, v);
-    float e[4] = {e_row[0], e_row[R], 0.0f, 0.0f};             // a channel's errors are read two channels ahead of their use
-    p[0] = update::products16x64(e[0], u[0][0]);
+    update::f32x4 ev[2];
+    ev[0] = *reinterpret_cast<const update::f32x4*>(e_row);
+    p[0] = update::products16x64(ev[0].x, u[0][0][0]);
     for (;;) {
         const int taken = take();
         const bool more = taken < n_items;
         const int then = more ? taken : item;                  // (none left: this one's are read again and not used)
-        const uint32_t ucol_next = u_offset(then);
+        const uint32_t ucol_next[2] = {u_offset(then, 0), u_offset(then, 1)};
         const float* e_next = e_first(then);
         auto steps = [&](int k_begin) {
 #pragma unroll 1
             for (int k = k_begin; k < k_begin + GB / 2; k += 2 * KB) {
                 const bool last = k + 2 * KB == GB;            // behind the block's last channel come the next item's first
-                const float* e_at = last ? e_next - GB * R : e_row;
-                const uint32_t ucol2 = last ? ucol_next : ucol;
+                const float* e_behind = last ? e_next : e_row + k + 2 * KB;
+                const uint32_t ucol2[2] = {last ? ucol_next[0] : ucol[0], last ? ucol_next[1] : ucol[1]};
 #pragma unroll
                 for (int kk = 0; kk < 2 * KB; ++kk) {
                     if (kk == 0) fetch(1, k + KB, ucol);
                     if (kk == KB) fetch(0, (k + 2 * KB) & (GB - 1), ucol2);
-                    e[(kk + 2) & 3] = (kk + 2 < 2 * KB ? e_row : e_at)[(k + kk + 2) * R];
-                    const int nk = kk + 1;
-                    __builtin_amdgcn_sched_barrier(0);
-                    p[nk & 1] = update::products16x64(e[nk & 3], u[(nk / KB) & 1][nk % KB]);
-                    __builtin_amdgcn_sched_barrier(0);
-                    v = v - p[kk & 1];
-                    asm volatile("" : "+v"(v));                // here, and not behind the next products
-                    __builtin_amdgcn_sched_barrier(0);
+                    if ((kk & 3) == 0)
+                        ev[((kk >> 2) + 1) & 1] = *reinterpret_cast<const update::f32x4*>(kk + 4 < 2 * KB ? e_row + k + kk + 4 : e_behind);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const int nk = kk + q;
+                        __builtin_amdgcn_sched_barrier(0);
+                        p[q ^ 1] = update::products16x64(ev[(nk >> 2) & 1][nk & 3], u[(nk / KB) & 1][nk % KB][q ^ 1]);
+                        __builtin_amdgcn_sched_barrier(0);
+                        v[q] = v[q] - p[q];
+                        asm volatile("" : "+v"(v[q]));         // here, and not behind the next products
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
             }
         };
@@ -298,18 +317,27 @@ __device__ __forceinline__ void update_behind(float* __restrict__ Wrows, const f
             const int lane_s = fresh(lane), rt = row0_of(item), c0 = col0_of(item);
             const int rows_here = min(n_rows - rt, RT), cols_here = in - c0;
             const uint32_t first = static_cast<uint32_t>(4 * (lane_s >> 4)) * pitch + 4u * static_cast<uint32_t>(lane_s & 15);
+            if (rows_here == RT && cols_here >= COLS) {        // uniform
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+                for (int r = 0; r < 4; ++r)
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    if (4 * (lane_s >> 4) + r < rows_here && 16 * b + (lane_s & 15) < cols_here) 
-                        W.store(v[4 * b + r], first, (rt + r) * pitch + 4 * (c0 + 16 * b));
+                    for (int b = 0; b < 8; ++b) W.store(v[b >> 2][4 * (b & 3) + r], first, (rt + r) * pitch + 4 * (c0 + 16 * b));
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int b = 0; b < 8; ++b)
+                        if (4 * (lane_s >> 4) + r < rows_here && 16 * b + (lane_s & 15) < cols_here)
+                            W.store(v[b >> 2][4 * (b & 3) + r], first, (rt + r) * pitch + 4 * (c0 + 16 * b));
+            }
         }
         if (!more) break;
         item = then;
-        ucol = ucol_next;
+        ucol[0] = ucol_next[0];
+        ucol[1] = ucol_next[1];
         e_row = e_next;
-        v = v_next;
+        v[0] = v_next[0];
+        v[1] = v_next[1];
     }
 }
 
@@ -336,7 +364,7 @@ __device__ __forceinline__ void update_next(const float* __restrict__ Wrows, con
         for (int kk = 0; kk < KB; ++kk) {
 #pragma unroll
             for (int r = 0; r < RQ; ++r) {
-                const float upd = es[(k + kk) * R + rq + r] * u[b][kk];
+                const float upd = es[e_at<R>(k + kk, rq + r)] * u[b][kk];
                 v[r] = v[r] - upd;
             }
             if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
@@ -357,6 +385,47 @@ __device__ __forceinline__ void update_next(const float* __restrict__ Wrows, con
     for (int r = 0; r < RQ; ++r) lds.w[rq + r][c] = v[r];
 }
 
+// The 16 errors e of the sub-block at s0 onto the columns c0, c0 + CL .. of a row of the strip, up to c_end, NC at a time: a
+// column's sixteen differences wait for each other.
+template <int R, int CL>
+__device__ __forceinline__ void apply16(const Lds<R>& lds, float* wrow, const float (&e)[SB], int s0, int c0, int c_end) {
+    constexpr int NC = 2;
+    for (int c = c0; c < c_end; c += NC * CL) {
+        float v[NC], u[NC][SB];
+#pragma unroll
+        for (int t = 0; t < NC; ++t) {
+            const int ct = min(c + t * CL, GB - 1);              // past the block: read, not stored
+            v[t] = wrow[ct];
+#pragma unroll
+            for (int k = 0; k < SB; k += 4) {
+                const float4 q = *reinterpret_cast<const float4*>(&lds.ut[ct][s0 + k]);
+                u[t][k] = q.x; u[t][k + 1] = q.y; u[t][k + 2] = q.z; u[t][k + 3] = q.w;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < SB; ++k)
+#pragma unroll
+            for (int t = 0; t < NC; ++t) {
+                const float upd = e[k] * u[t][k];
+                v[t] = v[t] - upd;
+            }
+#pragma unroll
+        for (int t = 0; t < NC; ++t)
+            if (c + t * CL < c_end) wrow[c + t * CL] = v[t];
+    }
+}
+
+// One wave tells another of its workgroup how far it is (everything it has put into LDS included), and waits for that.  Every
+// wait of gq_rows ends: wave 0 waits only for what the second wave does with errors posted before, and the second wave
+// only for wave 0's next sub-block.
+__device__ __forceinline__ void tell(int* count, int n) {
+    if ((threadIdx.x & 63) == 0) __hip_atomic_store(count, n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void wait_for(const int* count, int n) {
+    while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(count, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) < n)
+        __builtin_amdgcn_s_sleep(1);
+}
+
 template <int R>
 __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp, const float* __restrict__ U,
                                                          const int32_t* __restrict__ perm, int64_t out, int64_t in64, int g,
@@ -365,6 +434,9 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
     // items of the update: RT rows x 64 columns on the matrix cores where RT is 16, else RT rows x 64 CPL columns (RT x CPL
     // accumulators; few rows take more columns, so that an LDS read of the errors serves as many products)
     constexpr int RR = pow2_rows<R>(), CL = 64 / RR, CPL = R <= 8 ? 4 : 2, RT = R <= 16 ? R : R / 2;
+    // Two waves for the chain: with 16 rows a block's chain takes 23 us so and 31 alone.  Few rows have few columns per lane
+    // behind a sub-block, and telling and waiting costs more (4 and 8 rows: 2 % of the sweep).
+    constexpr bool TWO = R >= 12;
     extern __shared__ __align__(16) char smem[];
     Lds<R>& lds = *reinterpret_cast<Lds<R>*>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -433,7 +505,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
             lds.zp[c][r] = static_cast<uint8_t>(zp);
         }
         if (tid < GB) lds.rd[tid] = block_reciprocal(cd);
-        if (tid == 0) lds.next = 0;
+        if (tid == 0) lds.next = lds.posted = lds.done = 0;
         stage_groups(i1 + GB, b ^ 1);
     };
 
@@ -455,8 +527,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
     const bool row_in = crow < R, row_ok = crow < n_rows;
     for (int i1 = 0, blk = 0; i1 < in; i1 += GB, ++blk) {
         const int nbw = min(in - i1, GB), behind = i1 + nbw;
-        float* es = &lds.e[blk & 1][0][0];
-        const float* es_last = &lds.e[(blk & 1) ^ 1][0][0];
+        float* es = lds.e[blk & 1];
+        const float* es_last = lds.e[(blk & 1) ^ 1];
         if (wave == 0) {
             // the chain the workgroup waits for: ahead of the updates that share its SIMD
             __builtin_amdgcn_s_setprio(3);
@@ -477,7 +549,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
                     for (int k = 0; k < SB; ++k) e[k] = row_ok ? e[k] : 0.0f;
                     if (row_in && ccol == 0) {
 #pragma unroll
-                        for (int k = 0; k < SB; ++k) es[(s0 + k) * R + crow] = e[k];
+                        for (int k = 0; k < SB; ++k) es[e_at<R>(s0 + k, crow)] = e[k];
                     }
                     if (row_ok && ccol == 0) {
                         if ((reinterpret_cast<uintptr_t>(q_out) & 15u) == 0) {
@@ -488,46 +560,42 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
                         }
                     }
                 } else if (row_in) {
-                    chain_slow<R>(wrow + s0, ut, es + s0 * R + crow, sbw, qmax,
+                    chain_slow<R>(wrow + s0, ut, es + e_at<R>(s0, crow), sbw, qmax,
                                   [&](int c, float& a, float& b) { a = sc[c * R].x; b = static_cast<float>(zp[c * R]); },
                                   [&](int c, uint8_t q) { if (row_ok && ccol == 0) q_out[c] = q; });
 #pragma unroll
-                    for (int k = 0; k < SB; ++k) e[k] = k < sbw && row_ok ? es[(s0 + k) * R + crow] : 0.0f;
+                    for (int k = 0; k < SB; ++k) e[k] = k < sbw && row_ok ? es[e_at<R>(s0 + k, crow)] : 0.0f;
                     if (!row_ok)
-                        for (int k = 0; k < sbw; ++k) es[(s0 + k) * R + crow] = 0.0f;
+                        for (int k = 0; k < sbw; ++k) es[e_at<R>(s0 + k, crow)] = 0.0f;
                 }
-                // The block's columns behind the sub-block (only a whole sub-block has any), NC at a time: a column's
-                // sixteen differences wait for each other.
-                if (row_in) {
-                    constexpr int NC = 2;
-                    for (int c = s0 + SB + ccol; c < nbw; c += NC * CL) {
-                        float v[NC], u[NC][SB];
-#pragma unroll
-                        for (int t = 0; t < NC; ++t) {
-                            const int ct = min(c + t * CL, GB - 1);      // past the block: read, not stored
-                            v[t] = wrow[ct];
-#pragma unroll
-                            for (int k = 0; k < SB; k += 4) {
-                                const float4 q = *reinterpret_cast<const float4*>(&lds.ut[ct][s0 + k]);
-                                u[t][k] = q.x; u[t][k + 1] = q.y; u[t][k + 2] = q.z; u[t][k + 3] = q.w;
-                            }
-                        }
-#pragma unroll
-                        for (int k = 0; k < SB; ++k)
-#pragma unroll
-                            for (int t = 0; t < NC; ++t) {
-                                const float upd = e[k] * u[t][k];
-                                v[t] = v[t] - upd;
-                            }
-#pragma unroll
-                        for (int t = 0; t < NC; ++t)
-                            if (c + t * CL < nbw) wrow[c + t * CL] = v[t];
+                // The block's columns behind the sub-block (only a whole sub-block has any); TWO: the next sub-block's, which
+                // the second wave has brought up to the sub-block before (the columns behind those are its business).
+                if (s0 + SB < nbw) {
+                    if constexpr (TWO) {
+                        tell(&lds.posted, s0 / SB + 1);
+                        if (s0 > 0) wait_for(&lds.done, s0 / SB);
                     }
+                    if (row_in) apply16<R, CL>(lds, wrow, e, s0, s0 + SB + ccol, TWO ? min(nbw, s0 + 2 * SB) : nbw);
                 }
-                // the strip is this wave's alone while the chain runs, and LDS serves a wave's accesses in order
+                // these columns of the strip are this wave's alone while the chain runs, and LDS serves a wave's accesses in order
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+            __builtin_amdgcn_s_setprio(0);
+        } else if (TWO && wave == SECOND) {
+            // A sub-block's errors onto the columns behind the next one, beside the next one's chain
+            __builtin_amdgcn_s_setprio(2);
+            float* wrow = &lds.w[row_in ? crow : 0][0];
+            for (int s0 = 0; s0 + 2 * SB < nbw; s0 += SB) {
+                wait_for(&lds.posted, s0 / SB + 1);
+                if (row_in) {
+                    float e[SB];
+#pragma unroll
+                    for (int k = 0; k < SB; ++k) e[k] = es[e_at<R>(s0 + k, crow)];
+                    apply16<R, CL>(lds, wrow, e, s0, s0 + 2 * SB + ccol, nbw);
+                }
+                tell(&lds.done, s0 / SB + 1);
             }
             __builtin_amdgcn_s_setprio(0);
         }
@@ -572,7 +640,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
 // Rows per workgroup for [out, in]: the R with the least rounds x time of one workgroup.  A block of one workgroup
 // takes the longer of the chain and the updates (R rows x remaining columns x 128 channels x 2 operations at 64 per
 // cycle), then the update of the next block's columns.  The constants (us) are measured with the clock around each part,
-// at R = 4, 16 and 32 on a 4096-wide input alone: chain 18, 29, 45, step between two blocks 4, 7, 10.
+// at R = 4, 16 and 32 on a 4096-wide input alone: chain 18, 29, 45, step between two blocks 4, 7, 10 (with one wave at the chain;
+// with two the chain of 16 rows takes 23).
 inline int rows_per_group(int64_t out, int64_t in) {
     const int sizes[] = {4, 8, 12, 16, 24, 32};
     int best = 16;
@@ -603,12 +672,16 @@ inline int rows_per_group(int64_t out, int64_t in) {
 // multiple of four make its chain dearer: codes and errors are stored one at a time.  A narrow last block costs its width in
 // either form.  Layers of less than one block (16 to 120 channels, 190 sizes), where a call is 18 to 60 us, are not among them:
 // 1.3 % on average and up to 6 us there (3432 x 64 31 / 37; 28672 x 64 107 / 74).
-// us, this form / a launch per block:
-//   many rows     28672 x 1024  1839 / 1466     100000 x 256  1440 / 831     9216 x 512  424 / 298     6144 x 128  70 / 60
-//   few rows of many channels   300 x 28672  24700 / 19600     8 x 16384  10070 / 8740      256 x 22016  15230 / 14080
-//   the rest      4096 x 4096  2127 / 2911     1024 x 16384  9620 / 12760     8192 x 1024  478 / 630     256 x 2048  389 / 1114
-//   ragged        8192 x 333  172 / 222    7280 x 493  247 / 326    16384 x 2159  2596 / 2981    16384 x 493  466 / 370
-//   a narrow last block   8192 x 260  139 / 182    7168 x 320  157 / 188    8192 x 200  108 / 116    9216 x 260  241 / 185
+// The constants are those of the time before the updates' products went to the matrix cores and the chain of 12 rows and more to
+// two waves.  Of 122 sizes (1500 to 60000 rows of 130 to 5000 channels, and few rows of many) timed since, the choice is 1.3 % slower
+// than the better form on average and 13 % at worst (18057 x 504 493 / 559; 12288 x 4096 5768 / 5259); none fits better by more than
+// 0.2 % that leaves the choices as tests/test_host_path_cpu.py holds them.
+// us, this form / a launch per block (4096 x 4096, 1024 x 16384, 256 x 22016 and the narrow last blocks but one: before that):
+//   many rows     28672 x 1024  1470 / 1438     100000 x 256  1087 / 816     9216 x 512  342 / 297     6144 x 128  57 / 58
+//   few rows of many channels   300 x 28672  24600 / 16700     8 x 16384  10080 / 8770      256 x 22016  15230 / 14080
+//   the rest      4096 x 4096  2127 / 2911     1024 x 16384  9620 / 12760     6144 x 4096  2888 / 3245
+//   ragged        7280 x 493  190 / 322    16384 x 2159  2218 / 2658    16384 x 493  352 / 364
+//   a narrow last block   8192 x 260  139 / 182    7168 x 320  157 / 188    8192 x 200  108 / 116    9216 x 260  200 / 186
 inline bool better(int64_t out, int64_t in) {
     const int r = rows_per_group(out, in);
     const int64_t wgs = (out + r - 1) / r, wgs_b = (out + 63) / 64;

@@ -11,12 +11,12 @@
 // costs what an unpacked fp32 fma costs, and the sweep's rounding decisions then see the same
 // U (rounded once to fp32) as an fp64 reference.  Blocked right-looking Cholesky (64-wide
 // steps inside 512-wide panels: diagonal block in LDS, everything else products) and a triangular
-// inverse by doubling.
+// inverse, by doubling and panel by panel.
 //
 // Sweep.  Rows (per-OC) or row groups (per-IC) are independent.  Per-OC one launch does it all (gptq_rows.h)
 // where that is faster, else a launch per block (gptq_blocks.h; rows::better).  Per-IC a
-// workgroup keeps its row group's 128-channel block in LDS and walks the channels alone: quantize channel i,
-// e = (w - q)/U_ii, w_j -= e*U_ij for the rest of the block; a second kernel applies the block's errors to the
+// workgroup keeps its row group's 128-channel block in LDS and walks the channels alone (gptq_groups.h): quantize channel i,
+// e = (w - q)/U_ii, w_j -= e*U_ij for the rest of the block; gptq_update.h and gq_next, or the next block's launch, apply the block's errors to the
 // channels behind the block, one channel's error at a time.  Every update is a rounded product
 // followed by a rounded difference (no fma), in channel order, which fixes the result bit for
 // bit.  Per-OC uses static groups (parameters computed beforehand from the original weight and
@@ -569,10 +569,7 @@ __global__ __launch_bounds__(256, 4) void trinv_level(double* __restrict__ M, do
                                                       int64_t s) {
     const int64_t a = 2 * int64_t(blockIdx.z) * s, a0 = base + a, b0 = a0 + s;
     const int64_t sb = size - a - s < s ? size - a - s : s;   // > 0 for every pair in the grid
-    // (the larger levels:) PASS 0's tiles get shorter from left to right: every other eight tile rows run from right to left,
-    // or the workgroups that meet on a compute unit would all be of one column.
-    const unsigned bx = PASS == 0 && ((blockIdx.y >> 3) & 1) ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
-    const int64_t m0 = int64_t(blockIdx.y) * TS, n0 = int64_t(bx) * TS;
+    const int64_t m0 = int64_t(blockIdx.y) * TS, n0 = int64_t(blockIdx.x) * TS;
     if (m0 >= sb) return;
     __shared__ double As[GK][TS + 4], Bs[GK][TS + 4];
     const int m_valid = static_cast<int>(sb - m0 < TS ? sb - m0 : TS);
@@ -873,7 +870,8 @@ int launch_gptq_prepare(adadim_ctx* ctx, const float* H, int64_t n, float percda
     double* A = static_cast<double*>(adadim_workspace(ctx, WS_GPTQ_A, mat));
     double* M = static_cast<double*>(adadim_workspace(ctx, WS_GPTQ_M, mat));
     double* dvec = static_cast<double*>(adadim_workspace(ctx, WS_GPTQ_D, size_t(n + 1) * sizeof(double)));
-    // products C inv(A) of the inverse's doubling levels: pairs * s * s doubles at level s
+    // products C inv(A) of the inverse's doubling levels: pairs * s * s doubles at level s.  (As many as doubling over the whole
+    // matrix takes, which a matrix of more than one panel no longer needs: what can be recorded after it stays the same.)
     size_t t_elems = 1;
     for (int64_t s = NB; s < n; s *= 2) t_elems = std::max(t_elems, size_t((n - s + 2 * s - 1) / (2 * s)) * size_t(s) * size_t(s));
     double* T = static_cast<double*>(adadim_workspace(ctx, WS_GPTQ_T, t_elems * sizeof(double)));

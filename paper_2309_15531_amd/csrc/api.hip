@@ -56,23 +56,20 @@ void* adadim_workspace(adadim_ctx* ctx, int slot, size_t bytes) {
 
 bool adadim_side_stream(adadim_ctx* ctx) {
     if (ctx->side) return true;
-    hipStream_t st[2] = {nullptr, nullptr};
-    hipError_t e = hipSuccess;
-    for (int i = 0; e == hipSuccess && i < 2; ++i) e = hipStreamCreateWithFlags(&st[i], hipStreamNonBlocking);
-    for (int i = 0; e == hipSuccess && i < 3; ++i) e = hipEventCreateWithFlags(&ctx->side_ev[i], hipEventDisableTiming);
+    hipStream_t st = nullptr;
+    hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
+    for (int i = 0; e == hipSuccess && i < 2; ++i) e = hipEventCreateWithFlags(&ctx->side_ev[i], hipEventDisableTiming);
     if (e != hipSuccess) {
-        adadim_fail(ctx, ADADIM_EHIP, "creating the side streams: %s", hipGetErrorString(e));
-        for (int i = 0; i < 3; ++i)
+        adadim_fail(ctx, ADADIM_EHIP, "creating the side stream: %s", hipGetErrorString(e));
+        for (int i = 0; i < 2; ++i)
             if (ctx->side_ev[i]) {
                 (void)hipEventDestroy(ctx->side_ev[i]);
                 ctx->side_ev[i] = nullptr;
             }
-        for (int i = 0; i < 2; ++i)
-            if (st[i]) (void)hipStreamDestroy(st[i]);
+        if (st) (void)hipStreamDestroy(st);
         return false;
     }
-    ctx->side = st[0];
-    ctx->side2 = st[1];
+    ctx->side = st;
     return true;
 }
 
@@ -208,9 +205,9 @@ void adadim_destroy(adadim_ctx* ctx) {
         ctx->capturing = false;
     }
     if (ctx->side) {
-        for (hipStream_t st : {ctx->side, ctx->side2}) (void)hipStreamSynchronize(st);
-        for (int i = 0; i < 3; ++i) (void)hipEventDestroy(ctx->side_ev[i]);
-        for (hipStream_t st : {ctx->side, ctx->side2}) (void)hipStreamDestroy(st);
+        (void)hipStreamSynchronize(ctx->side);
+        for (int i = 0; i < 2; ++i) (void)hipEventDestroy(ctx->side_ev[i]);
+        (void)hipStreamDestroy(ctx->side);
     }
     if (ctx->host_best) {
         (void)hipStreamSynchronize(ctx->stream);

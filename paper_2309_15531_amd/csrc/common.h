@@ -68,8 +68,8 @@ struct adadim_ctx {
     struct GramSplit { GramPlan plan; GramOrder order; bool whole_ok; } gram_split[8];
     int gram_split_n, gram_split_next;
     bool capturing;                  // between adadim_capture_begin and adadim_capture_end
-    hipStream_t side, side2;         // further streams for work that may overlap the main one (created on first use)
-    hipEvent_t side_ev[3];           // main -> sides, side -> main and side2 -> main hand-overs
+    hipStream_t side;                // second stream for work that may overlap the main one (created on first use)
+    hipEvent_t side_ev[2];           // main -> side and side -> main hand-overs
     int32_t* host_best;              // pinned: where a selection leaves its index for the host (created on first use)
     adadim_prof prof;
 };
@@ -84,7 +84,7 @@ struct ProfScope {
 
 int adadim_fail(adadim_ctx* ctx, int code, const char* fmt, ...);
 
-// Creates the context's side streams and their events on first use (default priority, like every
+// Creates the context's side stream and its two events on first use (default priority, like every
 // stream here).  Returns false with the error recorded.
 bool adadim_side_stream(adadim_ctx* ctx);
 

@@ -11,7 +11,7 @@
 // costs what an unpacked fp32 fma costs, and the sweep's rounding decisions then see the same
 // U (rounded once to fp32) as an fp64 reference.  Blocked right-looking Cholesky (64-wide
 // steps inside 512-wide panels: diagonal block in LDS, everything else products) and a triangular
-// inverse, by doubling and panel by panel.
+// inverse, by doubling and panel by panel, in the same launches (factor_plan.h).
 //
 // Sweep.  Rows (per-OC) or row groups (per-IC) are independent.  Per-OC one launch does it all (gptq_rows.h)
 // where that is faster, else a launch per block (gptq_blocks.h; rows::better).  Per-IC a
@@ -23,6 +23,7 @@
 // looked up by the channel's original index); per-IC recomputes each (row group, channel)'s
 // parameters from the channel's current values when it is visited.
 #include "common.h"
+#include "factor_plan.h"
 #include "gptq_blocks.h"
 #include "gptq_groups.h"
 #include "gptq_rows.h"
@@ -35,9 +36,9 @@
 
 namespace {
 
-constexpr int NB = 64;        // panel width of the factorization
-constexpr int NBO = 512;      // its outer panel: trailing updates are applied 512 columns at a time
-constexpr int GB = 128;       // channels per sweep block
+constexpr int NB = FACTOR_NB;     // step of the factorization
+constexpr int NBO = FACTOR_NBO;   // its panel: the columns behind are updated 512 at a time
+constexpr int GB = 128;           // channels per sweep block
 
 // ------------------------------------------------------------------ prepare: order and matrix
 __global__ void gq_diag(const float* __restrict__ H, int64_t n, double* __restrict__ d, uint8_t* __restrict__ dead) {
@@ -147,7 +148,7 @@ __global__ void gq_gather_wide(const float* __restrict__ H, int64_t n, const int
 // result is D[4 r + l / 16][l % 16].  The vector and the matrix pipe have the same fp64 peak on this
 // chip; the matrix form needs a quarter of the LDS reads per flop and no issue slots for the products.
 typedef double double4_t __attribute__((ext_vector_type(4)));
-constexpr int GT = 64, GK = 32;                  // tile edge, contraction chunk
+constexpr int GT = FACTOR_NB, GK = 32;           // tile edge, contraction chunk
 // (128 x 128 tiles were measured too: one workgroup per compute unit instead of four, and the
 // products ran a third slower; the matrix pipe wants the other workgroups' waves to fill its gaps.)
 
@@ -275,6 +276,120 @@ __device__ __forceinline__ void dgemm_fill(double4_t (&acc)[TS / 32][TS / 32], F
                 acc[u][v][r] = f(wm * (TS / 2) + u * 16 + 4 * r + (lane >> 4), wn * (TS / 2) + v * 16 + (lane & 15));
 }
 
+// ------------------------------------------------------------------ M = inv(L), lower
+// inv [[A, 0], [C, B]] = [[inv A, 0], [-inv(B) C inv(A), inv B]].  Diagonal blocks of up to a panel by doubling: with the
+// blocks of size s inverted, a level pairs them up: a pair covers rows a0 = base + 2 s pair (A) and a0 + s (B, at
+// most s rows at the end) of the `w` rows from `base` on.  Two products, every pair and
+// every tile in parallel: T = C inv(A) (inv(A) lower triangular: k starts at the tile's
+// first column), then M[B rows, A columns] = -inv(B) T (k ends with the tile's last row).
+//
+// Panel by panel: the rows below the panel at k0 (w wide) gather R = L X, X = inv(L) of the panels so far, in the part of M that
+// their own inverse will take, and a panel's rows become X = -inv(diagonal block) R when their turn comes.  That product
+// goes to the lower triangle of A, whose columns left of the panel nobody reads any more (R is read by several workgroups).
+// Every product is at most 512 deep and as many tiles wide as there are columns.  (T = C inv(A) in one product when a panel's
+// turn comes has tiles up to 3584 deep at 4096, 250 us each.)
+//
+// These products, and the update behind a panel, are the jobs that the factorization's launches carry (factor_plan.h), a workgroup
+// per tile.
+
+// tile `tile` of the launch's jobs (none: past their end)
+__device__ __forceinline__ void job_tile(const FactorJobs& jobs, int tile, double* __restrict__ A, double* __restrict__ M,
+                                         double* __restrict__ T, float* __restrict__ U, int64_t n, double (*As)[GT + 4], double (*Bs)[GT + 4]) {
+    // (the first job's fields are read at once, not when it is known that it is the first)
+    int i = 0, kind = jobs.job[0].kind, from = jobs.job[0].from, w = jobs.job[0].w, s = jobs.job[0].s, lo = jobs.job[0].lo, hi = jobs.job[0].hi;
+    int64_t k0 = jobs.job[0].k0;
+    while (i < jobs.n && tile >= jobs.job[i].tiles) tile -= jobs.job[i++].tiles;
+    if (i == jobs.n) return;
+    if (i > 0) {
+        kind = jobs.job[i].kind;
+        from = jobs.job[i].from;
+        w = jobs.job[i].w;
+        s = jobs.job[i].s;
+        lo = jobs.job[i].lo;
+        hi = jobs.job[i].hi;
+        k0 = jobs.job[i].k0;
+    }
+    tile += from;
+    if (kind == FACTOR_FLIP) {
+        // U[a][b] = fp32(inv(L)[n-1-a][n-1-b]): upper triangular, visiting order; columns of X left of the panel are in A, the
+        // others in M
+        const int64_t r = k0 + tile, a = n - 1 - r;
+        for (int64_t b = threadIdx.x; b < n; b += 256) {
+            const int64_t c = n - 1 - b;
+            U[a * n + b] = c <= r ? static_cast<float>((c < k0 ? A : M)[r * n + c]) : 0.0f;
+        }
+        return;
+    }
+    double4_t acc[GT / 32][GT / 32] = {};
+    if (kind == FACTOR_T || kind == FACTOR_LEVEL) {
+        const int across = s / GT, lg = __ffs(across) - 1;           // a power of two
+        const int pair = tile >> (2 * lg), m0 = ((tile >> lg) & (across - 1)) * GT, n0 = (tile & (across - 1)) * GT;
+        const int64_t a0 = k0 + 2 * int64_t(pair) * s, b0 = a0 + s;
+        const int sb = min(static_cast<int>(k0 + w - b0), s);     // > 0 for every pair
+        if (m0 >= sb) return;
+        const int m_valid = min(sb - m0, GT);
+        double* Tp = T + int64_t(pair) * s * s;
+        if (kind == FACTOR_T) {
+            dgemm_tile<GT, false, false>(M + a0 * n + b0 + m0, n, m_valid, M + a0 * n + a0 + n0, n, GT, n0, s, As, Bs, acc);
+            dgemm_each<GT>(acc, [&](int i, int j, double v) {
+                if (i < m_valid) Tp[int64_t(m0 + i) * s + n0 + j] = v;
+            });
+        } else {
+            dgemm_tile<GT, true, false>(M + (b0 + m0) * n + b0, n, m_valid, Tp + n0, s, GT, 0, min(sb, m0 + GT), As, Bs, acc);
+            dgemm_each<GT>(acc, [&](int i, int j, double v) {
+                if (i < m_valid) M[(b0 + m0 + i) * n + a0 + n0 + j] = -v;
+            });
+        }
+    } else if (kind == FACTOR_ROWS) {
+        // X's rows of the panel at k0 (w of them), columns left of it
+        const int cols = static_cast<int>(k0 / GT), m0 = tile / cols * GT, m_valid = min(w - m0, GT), end = min(hi, m0 + m_valid);
+        const int64_t c0 = int64_t(tile % cols) * GT;
+        if (lo > 0) dgemm_fill<GT>(acc, [&](int i, int j) { return i < m_valid ? A[(k0 + m0 + i) * n + c0 + j] : 0.0; });
+        dgemm_tile<GT, true, false, true>(M + (k0 + m0) * n + k0, n, m_valid, M + k0 * n + c0, n, GT, lo, end, As, Bs, acc);
+        dgemm_each<GT>(acc, [&](int i, int j, double v) {
+            if (i < m_valid) A[(k0 + m0 + i) * n + c0 + j] = v;
+        });
+    } else if (kind == FACTOR_SPREAD) {
+        // R's rows from k0 + w on, columns 0 .. k0 + w (a multiple of 64)
+        const int64_t k1 = k0 + w;
+        const int cols = static_cast<int>(k1 / GT);
+        const int64_t r0 = k1 + int64_t(tile / cols) * GT, c0 = int64_t(tile % cols) * GT;
+        const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT);
+        const bool own = c0 >= k0;                            // columns of the panel itself, which nothing was added to yet
+        const int first = own ? static_cast<int>(c0 - k0) : 0, begin = max(lo, first);
+        if (begin >= hi) return;
+        if (!own || begin > first) dgemm_fill<GT>(acc, [&](int i, int j) { return i < m_valid ? M[(r0 + i) * n + c0 + j] : 0.0; });
+        dgemm_tile<GT, false, false>(M + k0 * n + r0, n, m_valid, (own ? M : A) + k0 * n + c0, n, GT, begin, hi, As, Bs, acc);
+        dgemm_each<GT>(acc, [&](int i, int j, double v) {
+            if (i < m_valid) M[(r0 + i) * n + c0 + j] = v;
+        });
+    } else {
+        // A -= L L^T: the tiles of the next panel's columns (`s` of them, those above the diagonal included), or those behind
+        const int64_t k1 = k0 + NBO;
+        int rt, ct;
+        if (kind == FACTOR_NEXT) {
+            rt = tile / s;
+            ct = tile % s;
+            if (ct > rt) return;
+        } else {
+            factor_behind(tile, rt, ct);
+        }
+        const int64_t r0 = k1 + int64_t(rt) * GT, c0 = k1 + int64_t(ct) * GT;
+        const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT), n_valid = static_cast<int>(n - c0 < GT ? n - c0 : GT);
+        dgemm_fill<GT>(acc, [&](int i, int j) { return (i < m_valid && j < n_valid) ? A[(r0 + i) * n + c0 + j] : 0.0; });
+        dgemm_tile<GT, false, false, true>(M + k0 * n + r0, n, m_valid, M + k0 * n + c0, n, n_valid, lo, hi, As, Bs, acc);
+        dgemm_each<GT>(acc, [&](int i, int j, double v) {
+            if (i < m_valid && c0 + j <= r0 + i) A[(r0 + i) * n + c0 + j] = v;
+        });
+    }
+}
+// jobs that no step is left to carry
+__global__ __launch_bounds__(256, 4) void factor_jobs(double* __restrict__ A, double* __restrict__ M, double* __restrict__ T,
+                                                      float* __restrict__ U, int64_t n, FactorJobs jobs) {
+    __shared__ double As[GK][GT + 4], Bs[GK][GT + 4];
+    job_tile(jobs, static_cast<int>(blockIdx.x), A, M, T, U, n, As, Bs);
+}
+
 // ------------------------------------------------------------------ Cholesky, lower, in place
 // Diagonal block of width w <= NB = 64, factored and inverted by one workgroup of four waves, blocked by 16.  The whole
 // factorization waits for it, so what counts is the length of its dependency chain, not its flops:
@@ -307,9 +422,8 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// LDS of the diagonal block's factorization: 42 KB.  inv(L) grows in the block that holds L, so that the workgroup fits
-// beside three of the trailing update's workgroups on a compute unit: one that needed more than a freed slot's share of
-// LDS would wait for that launch to drain.
+// LDS of the diagonal block's factorization: 39 KB.  inv(L) grows in the block that holds L, so that the launches that end in it
+// have four workgroups' LDS on a compute unit (registers allow three).
 struct DiagLds {
     static constexpr int LD = NB + 1;
     double t[NB][LD];                                         // 16 x 16 blocks: L below the diagonal, inv(L) on it, inv(L)^T above
@@ -323,7 +437,7 @@ __device__ __forceinline__ void diag_factor(double* __restrict__ M, int64_t n, i
     auto& t = lds.t;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, h16 = lane >> 4;
-    // one workgroup that the whole factorization waits for: ahead of the trailing update that may share its SIMDs
+    // one workgroup that the whole factorization waits for: ahead of the jobs that may share its SIMDs
     __builtin_amdgcn_s_setprio(3);
     // block (ti, tj) -= L_ti,p L_tj,p^T
     auto update = [&](int ti, int tj, int p) {
@@ -455,8 +569,6 @@ __global__ __launch_bounds__(256, 3) void chol_diag_inv(const double* __restrict
 __global__ __launch_bounds__(256, 4) void chol_panel(const double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0,
                                                      int w) {
     __shared__ double As[GK][GT + 4], Bs[GK][GT + 4];
-    // a link of the chain the factorization waits for: its waves issue ahead of the bulk update's on a shared SIMD
-    __builtin_amdgcn_s_setprio(3);
     const int64_t r0 = k0 + w + int64_t(blockIdx.x) * GT;
     const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT);
     double4_t acc[2][2] = {};
@@ -464,25 +576,6 @@ __global__ __launch_bounds__(256, 4) void chol_panel(const double* __restrict__ 
     dgemm_each<GT>(acc, [&](int c, int i, double v) {
         if (c < w && i < m_valid) M[(k0 + c) * n + r0 + i] = v;
     });
-}
-
-// Trailing update A -= L[., k0 .. k0+w) L[., k0 .. k0+w)^T of the lower triangle's tiles behind a 512-wide outer panel
-// (w = 512).  ct0: first tile column of this launch (the update goes out in two launches); tile rows x columns: rows x cols.
-__global__ __launch_bounds__(256, 4) void chol_syrk(double* __restrict__ A, const double* __restrict__ M, int64_t n, int64_t k0, int w,
-                                                    int64_t k1, int ct0, int rows, int cols) {
-    __shared__ double As[GK][GT + 4], Bs[GK][GT + 4];
-    for (int tile = static_cast<int>(blockIdx.x); tile < rows * cols; tile += static_cast<int>(gridDim.x)) {
-        const int ct = tile % cols + ct0, rt = tile / cols;
-        if (ct > rt) continue;
-        const int64_t r0 = k1 + int64_t(rt) * GT, c0 = k1 + int64_t(ct) * GT;
-        const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT), n_valid = static_cast<int>(n - c0 < GT ? n - c0 : GT);
-        double4_t acc[GT / 32][GT / 32];
-        dgemm_fill<GT>(acc, [&](int i, int j) { return (i < m_valid && j < n_valid) ? A[(r0 + i) * n + c0 + j] : 0.0; });
-        dgemm_tile<GT, false, false, true>(M + k0 * n + r0, n, m_valid, M + k0 * n + c0, n, n_valid, 0, w, As, Bs, acc);
-        dgemm_each<GT>(acc, [&](int i, int j, double v) {
-            if (i < m_valid && c0 + j <= r0 + i) A[(r0 + i) * n + c0 + j] = v;
-        });
-    }
 }
 
 // The end of an update's tile: the workgroup of the first tile (the diagonal block at k1, final once this update has
@@ -504,15 +597,22 @@ __device__ __forceinline__ void chol_tile_end(double4_t (&acc)[GT / 32][GT / 32]
 // LDS of the two kernels that call it: the product's staging buffers and the factorization's share their space
 constexpr size_t STEP_LDS = std::max(sizeof(DiagLds), 2 * GK * (GT + 4) * sizeof(double));
 
-// chol_syrk's first tile columns (the next outer panel's own), with the next diagonal block's factorization
-__global__ __launch_bounds__(256, 3) void chol_syrk_diag(double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0, int w,
-                                                         int64_t k1) {
-    if (blockIdx.x > blockIdx.y) return;
-    __builtin_amdgcn_s_setprio(3);                            // a link of the chain, as chol_panel
+// The update A -= L[., k0 .. k0+w) L[., k0 .. k0+w)^T of the next panel's columns, from k1 on (of everything, where there is no panel
+// behind that), with the next diagonal block's factorization.  gridDim.x x rows tiles, then jobs.
+__global__ __launch_bounds__(256, 3) void chol_syrk_diag(double* __restrict__ A, double* __restrict__ M, double* __restrict__ T,
+                                                         float* __restrict__ U, int64_t n, int64_t k0, int w, int64_t k1, int rows,
+                                                         FactorJobs jobs) {
     __shared__ __align__(16) char smem[STEP_LDS];
     double(*As)[GT + 4] = reinterpret_cast<double(*)[GT + 4]>(smem);
     double(*Bs)[GT + 4] = As + GK;
-    const int64_t r0 = k1 + int64_t(blockIdx.y) * GT, c0 = k1 + int64_t(blockIdx.x) * GT;
+    const int ct = static_cast<int>(blockIdx.x), rt = static_cast<int>(blockIdx.y);
+    if (rt >= rows) {
+        job_tile(jobs, (rt - rows) * static_cast<int>(gridDim.x) + ct, A, M, T, U, n, As, Bs);
+        return;
+    }
+    if (ct > rt) return;
+    __builtin_amdgcn_s_setprio(3);                            // a link of the chain: ahead of the jobs on a shared SIMD
+    const int64_t r0 = k1 + int64_t(rt) * GT, c0 = k1 + int64_t(ct) * GT;
     const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT), n_valid = static_cast<int>(n - c0 < GT ? n - c0 : GT);
     double4_t acc[GT / 32][GT / 32];
     dgemm_fill<GT>(acc, [&](int i, int j) { return (i < m_valid && j < n_valid) ? A[(r0 + i) * n + c0 + j] : 0.0; });
@@ -520,26 +620,32 @@ __global__ __launch_bounds__(256, 3) void chol_syrk_diag(double* __restrict__ A,
     chol_tile_end(acc, A, M, n, k1, r0, c0, m_valid, n_valid, *reinterpret_cast<DiagLds*>(smem));
 }
 
-// One 64-wide step inside an outer panel: the panel below the diagonal block at k0 and the update of the outer panel's
-// columns behind it, in one launch.  The factorization waits for every step in turn (they leave the chip nearly idle),
+// One 64-wide step inside a panel: the rows below the diagonal block at k0 and the update of the panel's columns behind it, in one
+// launch; gridDim.x x rows tiles, then jobs.  The factorization waits for every step in turn (they leave the chip nearly idle),
 // so each workgroup makes the 64 x 64 blocks of L that its tile needs by itself, at two products more, instead of waiting
 // for a launch that makes each once (a step of the 4096-wide factor: 34 us in two launches, 28 in one,
 // and 22 with the diagonal block's faster elimination).  The first tile
 // column's workgroups keep L.
-__global__ __launch_bounds__(256, 3) void chol_step(double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0) {
-    if (blockIdx.x > blockIdx.y) return;
-    __builtin_amdgcn_s_setprio(3);
+__global__ __launch_bounds__(256, 3) void chol_step(double* __restrict__ A, double* __restrict__ M, double* __restrict__ T,
+                                                    float* __restrict__ U, int64_t n, int64_t k0, int rows, FactorJobs jobs) {
     __shared__ __align__(16) char smem[STEP_LDS];
     double(*As)[GT + 4] = reinterpret_cast<double(*)[GT + 4]>(smem);
     double(*Bs)[GT + 4] = As + GK;
-    const int64_t k1 = k0 + NB, r0 = k1 + int64_t(blockIdx.y) * GT, c0 = k1 + int64_t(blockIdx.x) * GT;
+    const int ct = static_cast<int>(blockIdx.x), rt = static_cast<int>(blockIdx.y);
+    if (rt >= rows) {
+        job_tile(jobs, (rt - rows) * static_cast<int>(gridDim.x) + ct, A, M, T, U, n, As, Bs);
+        return;
+    }
+    if (ct > rt) return;
+    __builtin_amdgcn_s_setprio(3);
+    const int64_t k1 = k0 + NB, r0 = k1 + int64_t(rt) * GT, c0 = k1 + int64_t(ct) * GT;
     const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT), n_valid = static_cast<int>(n - c0 < GT ? n - c0 : GT);
-    const bool square = blockIdx.x == blockIdx.y;
+    const bool square = ct == rt;
     double4_t ly[2][2] = {}, lx[2][2] = {}, acc[2][2];        // L^T's blocks of the tile's rows and columns; the tile
     if (!square) dgemm_tile<GT, true, true>(M + k0 * n + k0, n, NB, A + c0 * n + k0, n, n_valid, 0, NB, As, Bs, lx);
     dgemm_tile<GT, true, true>(M + k0 * n + k0, n, NB, A + r0 * n + k0, n, m_valid, 0, NB, As, Bs, ly);
     dgemm_fill<GT>(acc, [&](int i, int j) { return (i < m_valid && j < n_valid) ? A[(r0 + i) * n + c0 + j] : 0.0; });
-    if (blockIdx.x == 0)
+    if (ct == 0)
         dgemm_each<GT>(ly, [&](int c, int i, double v) {
             if (i < m_valid) M[(k0 + c) * n + r0 + i] = v;
         });
@@ -555,82 +661,6 @@ __global__ __launch_bounds__(256, 3) void chol_step(double* __restrict__ A, doub
         dgemm_chunk<GT, true>(As, square ? As : Bs, acc);
     }
     chol_tile_end(acc, A, M, n, k1, r0, c0, m_valid, n_valid, *reinterpret_cast<DiagLds*>(smem));
-}
-
-// ------------------------------------------------------------------ M = inv(L), lower
-// inv [[A, 0], [C, B]] = [[inv A, 0], [-inv(B) C inv(A), inv B]].  Diagonal blocks of up to a panel by doubling: with the
-// blocks of size s inverted, a level pairs them up: pair blockIdx.z covers rows a0 = 2 s blockIdx.z (A) and a0 + s (B, at
-// most s rows at the end) of the `size` rows from `base` on.  Two products, every pair and
-// every tile in parallel: T = C inv(A) (PASS 0, inv(A) lower triangular: k starts at the tile's
-// first column), then M[B rows, A columns] = -inv(B) T (PASS 1, k ends with the tile's last row).
-// TS x TS tiles, TS dividing s.
-template <int PASS, int TS>
-__global__ __launch_bounds__(256, 4) void trinv_level(double* __restrict__ M, double* __restrict__ T, int64_t n, int64_t base, int64_t size,
-                                                      int64_t s) {
-    const int64_t a = 2 * int64_t(blockIdx.z) * s, a0 = base + a, b0 = a0 + s;
-    const int64_t sb = size - a - s < s ? size - a - s : s;   // > 0 for every pair in the grid
-    const int64_t m0 = int64_t(blockIdx.y) * TS, n0 = int64_t(blockIdx.x) * TS;
-    if (m0 >= sb) return;
-    __shared__ double As[GK][TS + 4], Bs[GK][TS + 4];
-    const int m_valid = static_cast<int>(sb - m0 < TS ? sb - m0 : TS);
-    double* Tp = T + int64_t(blockIdx.z) * s * s;
-    double4_t acc[TS / 32][TS / 32] = {};
-    if constexpr (PASS == 0) {
-        dgemm_tile<TS, false, false>(M + a0 * n + b0 + m0, n, m_valid, M + a0 * n + a0 + n0, n, TS, n0, s, As, Bs, acc);
-        dgemm_each<TS>(acc, [&](int i, int j, double v) {
-            if (i < m_valid) Tp[(m0 + i) * s + n0 + j] = v;
-        });
-    } else {
-        const int64_t k_hi = sb < m0 + TS ? sb : m0 + TS;
-        dgemm_tile<TS, true, false>(M + (b0 + m0) * n + b0, n, m_valid, Tp + n0, s, TS, 0, k_hi, As, Bs, acc);
-        dgemm_each<TS>(acc, [&](int i, int j, double v) {
-            if (i < m_valid) M[(b0 + m0 + i) * n + a0 + n0 + j] = -v;
-        });
-    }
-}
-
-// Panel by panel: the rows below the panel at k0 (w wide) gather R = L X, X = inv(L) of the panels so far, in the part of M that
-// their own inverse will take, and a panel's rows become X = -inv(diagonal block) R when their turn comes.  That product
-// goes to the lower triangle of A, whose columns left of the panel nobody reads any more (R is read by several workgroups).
-// Every product is at most 512 deep and as many tiles wide as there are columns.  (T = C inv(A) in one product when a panel's
-// turn comes has tiles up to 3584 deep at 4096, 250 us each.)
-//
-// R's rows from k0 + w on, columns 0 .. k0 + w (a multiple of 64)
-__global__ __launch_bounds__(256, 4) void trinv_spread(const double* __restrict__ A, double* __restrict__ M, int64_t n, int64_t k0, int w) {
-    __shared__ double As[GK][GT + 4], Bs[GK][GT + 4];
-    const int64_t k1 = k0 + w;
-    const int cols = static_cast<int>(k1 / GT), tiles = static_cast<int>((n - k1 + GT - 1) / GT) * cols;
-    for (int tile = static_cast<int>(blockIdx.x); tile < tiles; tile += static_cast<int>(gridDim.x)) {
-        const int64_t r0 = k1 + int64_t(tile / cols) * GT, c0 = int64_t(tile % cols) * GT;
-        const int m_valid = static_cast<int>(n - r0 < GT ? n - r0 : GT);
-        const bool own = c0 >= k0;                            // columns of the panel itself, which nothing was added to yet
-        double4_t acc[GT / 32][GT / 32] = {};
-        if (!own) dgemm_fill<GT>(acc, [&](int i, int j) { return i < m_valid ? M[(r0 + i) * n + c0 + j] : 0.0; });
-        dgemm_tile<GT, false, false>(M + k0 * n + r0, n, m_valid, (own ? M : A) + k0 * n + c0, n, GT, own ? c0 - k0 : 0, w, As, Bs, acc);
-        dgemm_each<GT>(acc, [&](int i, int j, double v) {
-            if (i < m_valid) M[(r0 + i) * n + c0 + j] = v;
-        });
-    }
-}
-// X's rows of the panel at k0 (w of them), columns left of it
-__global__ __launch_bounds__(256, 4) void trinv_rows(double* __restrict__ A, const double* __restrict__ M, int64_t n, int64_t k0, int w) {
-    __shared__ double As[GK][GT + 4], Bs[GK][GT + 4];
-    const int64_t m0 = int64_t(blockIdx.y) * GT, c0 = int64_t(blockIdx.x) * GT;
-    const int m_valid = static_cast<int>(w - m0 < GT ? w - m0 : GT);
-    double4_t acc[GT / 32][GT / 32] = {};
-    dgemm_tile<GT, true, false, true>(M + (k0 + m0) * n + k0, n, m_valid, M + k0 * n + c0, n, GT, 0, m0 + m_valid, As, Bs, acc);
-    dgemm_each<GT>(acc, [&](int i, int j, double v) {
-        if (i < m_valid) A[(k0 + m0 + i) * n + c0 + j] = v;
-    });
-}
-
-// U[a][b] = fp32(inv(L)[n-1-a][n-1-b]): upper triangular, visiting order; the rows of U that come from row r0 + blockIdx.y, whose
-// columns left of r0 are in A, the others in M
-__global__ void gq_flip(const double* __restrict__ A, const double* __restrict__ M, int64_t n, int64_t r0, float* __restrict__ U) {
-    const int64_t r = r0 + blockIdx.y, a = n - 1 - r, b = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (b >= n) return;
-    const int64_t c = n - 1 - b;
-    U[a * n + b] = c <= r ? static_cast<float>((c < r0 ? A : M)[r * n + c]) : 0.0f;
 }
 
 // ------------------------------------------------------------------ sweep
@@ -895,126 +925,29 @@ int launch_gptq_prepare(adadim_ctx* ctx, const float* H, int64_t n, float percda
     else
         hipLaunchKernelGGL(gq_gather_wide, dim3(nb2), dim3(256), 0, ctx->stream, H, n, perm, dvec, damp, A);
     ADADIM_LAUNCH_CHECK(ctx, "gptq prepare");
-    // Workgroups of a launch on the side streams take its tiles in turn, two or three per compute unit: more would leave no room
-    // (LDS and registers) for the main stream's short launches, which then wait for tiles to end (4096: 3240 us with a
-    // workgroup per tile, steps of 20 us taking 60 to 90).  The line, us with two / three per unit: 2900 1378 / 1391, 4096 2213 / 2260,
-    // 5120 3700 / 3501, 11008 23800 / 22040; and the next panel's columns updated ahead / not: 2048 918 / 975, 2900 1391 / 1438,
-    // 4096 2260 / 2256, 5120 3501 / 3418, 11008 22040 / 21605.
-    const bool narrow = n <= 4608;                            // the chain of steps is the longer part
-    const unsigned bulk = narrow ? 2 * 256 : 3 * 256;
-    // Outer panels of 512 columns: inside a panel the 64-wide steps update the panel's own columns
-    // only; the columns behind it get the whole panel at once, a product with 256 contraction steps
-    // per pass over the trailing matrix instead of 64.
-    const bool overlap = n > 2 * NBO;
-    if (overlap && !adadim_side_stream(ctx)) return ADADIM_EHIP;
-    // The inverse: the diagonal block of a panel by doubling, then the panel's rows, then what they add to the rows below.  From
-    // three panels on that happens on a stream of its own, while the main stream works on the next panel's
-    // steps, so that only the last panel's rows are inverted behind the factorization.  (Not on the update's stream: the main
-    // stream waits for each update, and would for the inverse before it.)
-    // (T holds the doubling's products of a panel, twice, as the last panel's run beside that stream's.)
-    double* t_level[2] = {T, T + NBO / 2 * (NBO / 2)};
-    auto invert_diagonal = [&](hipStream_t stream, int64_t base, int64_t size, double* t) {
-        for (int64_t s = NB; s < size; s *= 2) {
-            const unsigned pairs = static_cast<unsigned>((size - s + 2 * s - 1) / (2 * s));   // those with rows below a0 + s
-            const dim3 grid(static_cast<unsigned>(s / GT), static_cast<unsigned>(s / GT), pairs);
-            hipLaunchKernelGGL((trinv_level<0, GT>), grid, dim3(256), 0, stream, M, t, n, base, size, s);
-            hipLaunchKernelGGL((trinv_level<1, GT>), grid, dim3(256), 0, stream, M, t, n, base, size, s);
+    static_assert(GT == NB, "the first tile of a step or an update is the next diagonal block");
+    FactorPlan(n).run([&](const FactorLaunch& l) {
+        // the jobs in further rows of workgroups (at most 52000, for 46340 channels and one column)
+        const unsigned cols = static_cast<unsigned>(l.cols), tiles = static_cast<unsigned>(l.jobs.tiles());
+        const dim3 grid(cols, static_cast<unsigned>(l.rows) + (cols > 0 ? (tiles + cols - 1) / cols : 0));
+        switch (l.kind) {
+            case FACTOR_DIAG:
+                hipLaunchKernelGGL(chol_diag_inv, dim3(1), dim3(256), 0, ctx->stream, A, M, n, l.k0, l.w);
+                break;
+            case FACTOR_STEP:
+                hipLaunchKernelGGL(chol_step, grid, dim3(256), 0, ctx->stream, A, M, T, U, n, l.k0, l.rows, l.jobs);
+                break;
+            case FACTOR_BELOW:
+                hipLaunchKernelGGL(chol_panel, dim3(static_cast<unsigned>(l.rows)), dim3(256), 0, ctx->stream, A, M, n, l.k0, l.w);
+                break;
+            case FACTOR_UPDATE:
+                hipLaunchKernelGGL(chol_syrk_diag, grid, dim3(256), 0, ctx->stream, A, M, T, U, n, l.k0, l.w, l.k1, l.rows, l.jobs);
+                break;
+            default:
+                hipLaunchKernelGGL(factor_jobs, dim3(tiles), dim3(256), 0, ctx->stream, A, M, T, U, n, l.jobs);
         }
-    };
-    auto finish_rows = [&](hipStream_t stream, int64_t k0, int64_t w) {
-        if (k0 > 0)
-            hipLaunchKernelGGL(trinv_rows, dim3(static_cast<unsigned>(k0 / GT), static_cast<unsigned>((w + GT - 1) / GT)), dim3(256), 0,
-                               stream, A, M, n, k0, static_cast<int>(w));
-        hipLaunchKernelGGL(gq_flip, dim3(nb1, static_cast<unsigned>(w)), dim3(256), 0, stream, A, M, n, k0, U);
-    };
-    auto spread_rows = [&](int64_t k0) {                      // of a whole panel with rows below it
-        const int64_t k1 = k0 + NBO;
-        const unsigned tiles = static_cast<unsigned>(k1 / GT * ((n - k1 + GT - 1) / GT));
-        hipLaunchKernelGGL(trinv_spread, dim3(std::min(tiles, bulk)), dim3(256), 0, ctx->side2, A, M, n, k0, NBO);
-    };
-    bool side_used = false;                                   // (a stream that is not yet part of a recording is not waited for)
-    bool diag_ready = false;                                  // the block at the next k0 is already factored (chol_syrk_diag)
-    static_assert(GT == NB, "chol_syrk_diag's first tile is the next diagonal block");
-    for (int64_t K0 = 0; K0 < n; K0 += NBO) {
-        const int64_t W = n - K0 < NBO ? n - K0 : NBO;
-        int64_t ahead = 0;                                    // of this panel's columns, how many the next panel's have had
-        for (int64_t k0 = K0; k0 < K0 + W; k0 += NB) {
-            const int w = static_cast<int>(n - k0 < NB ? n - k0 : NB);
-            if (!diag_ready) hipLaunchKernelGGL(chol_diag_inv, dim3(1), dim3(256), 0, ctx->stream, A, M, n, k0, w);
-            diag_ready = false;
-            const int64_t rest = n - k0 - w;
-            if (rest > 0) {
-                const unsigned t = static_cast<unsigned>((rest + GT - 1) / GT);
-                const unsigned tc = static_cast<unsigned>((K0 + W - (k0 + w) + GT - 1) / GT);
-                if (tc > 0) {
-                    hipLaunchKernelGGL(chol_step, dim3(tc, t), dim3(256), 0, ctx->stream, A, M, n, k0);
-                    diag_ready = true;
-                    // The next panel's columns get what is final of this panel's L ahead of the panel's end, on the side stream,
-                    // which leaves the main stream a product of 128 steps (its seven launches of 40 to 80 us at 4096 take 20 to 45 so).
-                    const int64_t k_done = k0 + NB - K0;
-                    if (overlap && narrow && n > K0 + NBO && (k_done == NBO / 2 || k_done == 3 * NBO / 4)) {
-                        const int64_t k1 = K0 + NBO, from = k_done == NBO / 2 ? 0 : NBO / 2;
-                        const unsigned rows = static_cast<unsigned>((n - k1 + GT - 1) / GT);
-                        const unsigned cols = std::min<unsigned>(rows, NBO / GT);
-                        ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[0], ctx->stream));
-                        ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->side, ctx->side_ev[0], 0));
-                        side_used = true;
-                        hipLaunchKernelGGL(chol_syrk, dim3(std::min(rows * cols, bulk)), dim3(256), 0, ctx->side, A, M, n, K0 + from,
-                                           static_cast<int>(k_done - from), k1, 0, static_cast<int>(rows), static_cast<int>(cols));
-                        ahead = k_done;
-                    }
-                } else
-                    hipLaunchKernelGGL(chol_panel, dim3(t), dim3(256), 0, ctx->stream, A, M, n, k0, w);
-            }
-        }
-        if (overlap && K0 > 0) {
-            invert_diagonal(ctx->side2, K0 - NBO, NBO, t_level[0]);
-            finish_rows(ctx->side2, K0 - NBO, NBO);
-            spread_rows(K0 - NBO);
-        }
-        const int64_t rest = n - K0 - W;
-        if (rest > 0) {
-            // The panel's update of everything behind it.  The next panel's own columns first, on the main
-            // stream (its first tile's workgroup factors the next diagonal block as well): the panel's 64-wide
-            // steps need nothing else.  The columns behind those on the side stream, under those steps (which are
-            // chains of small launches that leave the chip idle).  Every element still receives the panels'
-            // updates in panel order: the side stream applies them in order, and the main stream waits for the
-            // side stream's last launch before it updates columns that launch wrote.
-            const unsigned t = static_cast<unsigned>((rest + GT - 1) / GT);
-            const unsigned tn = static_cast<unsigned>(((rest < NBO ? rest : NBO) + GT - 1) / GT);
-            if (side_used) {                                  // its earlier launches wrote these columns
-                ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[1], ctx->side));
-                ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->stream, ctx->side_ev[1], 0));
-            }
-            if (overlap) {
-                // both launches need the finished panel, and write different tile columns: the side stream starts with
-                // the main stream's launch, not behind it
-                ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[0], ctx->stream));
-            }
-            hipLaunchKernelGGL(chol_syrk_diag, dim3(overlap ? tn : t, t), dim3(256), 0, ctx->stream, A, M, n, K0 + ahead,
-                               static_cast<int>(W - ahead), K0 + W);
-            diag_ready = true;
-            if (overlap && t > tn) {
-                ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->side, ctx->side_ev[0], 0));
-                side_used = true;
-                hipLaunchKernelGGL(chol_syrk, dim3(std::min((t - tn) * t, bulk)), dim3(256), 0, ctx->side, A, M, n, K0,
-                                   static_cast<int>(W), K0 + W, static_cast<int>(tn), static_cast<int>(t), static_cast<int>(t - tn));
-            }
-            if (overlap) ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->side2, ctx->side_ev[0], 0));
-        }
-    }
-    ADADIM_LAUNCH_CHECK(ctx, "gptq cholesky");
-    if (overlap) {
-        const int64_t last = (n - 1) / NBO * NBO;
-        ADADIM_HIP_TRY(ctx, hipEventRecord(ctx->side_ev[2], ctx->side2));
-        invert_diagonal(ctx->stream, last, n - last, t_level[1]);
-        ADADIM_HIP_TRY(ctx, hipStreamWaitEvent(ctx->stream, ctx->side_ev[2], 0));               // join
-        finish_rows(ctx->stream, last, n - last);
-    } else {
-        invert_diagonal(ctx->stream, 0, n, T);
-        hipLaunchKernelGGL(gq_flip, dim3(nb1, static_cast<unsigned>(n)), dim3(256), 0, ctx->stream, A, M, n, int64_t(0), U);
-    }
-    ADADIM_LAUNCH_CHECK(ctx, "gptq inverse");
+    });
+    ADADIM_LAUNCH_CHECK(ctx, "gptq factor");
     return ADADIM_OK;
 }
 

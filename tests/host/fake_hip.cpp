@@ -89,7 +89,11 @@ int hipEventDestroy(void* e) { std::free(e); return 0; }
 int hipEventRecord(void*, void*) { return 0; }
 int hipEventSynchronize(void*) { return 0; }
 int hipEventElapsedTime(float* ms, void*, void*) { *ms = 1.0f; return 0; }
-int hipStreamCreateWithFlags(void** s, unsigned) { *s = std::malloc(1); return 0; }
+int hipStreamCreateWithFlags(void** s, unsigned) {
+    calls.push_back("hipStreamCreateWithFlags");
+    *s = std::malloc(1);
+    return 0;
+}
 int hipStreamDestroy(void* s) { std::free(s); return 0; }
 int hipStreamWaitEvent(void*, void*, unsigned) { return 0; }
 int hipStreamBeginCapture(void*, int) { return 0; }

@@ -229,6 +229,22 @@ def test_gram_launch_plans_cover_every_tile_once(tmp_path):
     assert len(share) == 2 and min(share) >= 0.95, res.stdout
 
 
+def test_factor_launches_in_order_on_the_host(tmp_path):
+    """csrc/factor_plan.h (which tiles of the factor and of its inverse each launch carries): followed tile by tile over many sizes,
+    every workgroup finds what it reads finished by earlier launches, nobody writes what another workgroup of the launch reads or
+    writes, every element gets its products in order and every row of U is written once."""
+    import shutil
+    import subprocess
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    exe = tmp_path / "factor_plan_check"
+    src = os.path.join(ROOT, "tests", "host", "factor_plan_check.cpp")
+    subprocess.run(["g++", "-O2", "-std=c++17", src, "-o", str(exe)], check=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout
+    assert " 0 mistakes" in res.stdout
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU per box: bench.py --gpus 2 says so and exits before anything touches a GPU."""
     import subprocess
@@ -302,7 +318,7 @@ def test_binding_refuses_tensors_the_library_would_misread():
 
 def test_host_checks_under_sanitizers(tmp_path):
     """The host builds of the device headers (fast division, code-field plan, launch plans of the
-    matrix-vector product and of the Gram kernel) compiled with the address and
+    matrix-vector product, of the Gram kernel and of the factor) compiled with the address and
     undefined-behaviour sanitizers: the constexpr plans and the bit manipulation the kernels share with these
     checks must be free of out-of-bounds indexing, signed overflow and shifts past the width."""
     import shutil
@@ -315,7 +331,8 @@ def test_host_checks_under_sanitizers(tmp_path):
     for name, extra, argv, want in (("code_fields_check", [], [], "2 bits: 0, 3 bits: 0, 4 bits: 0 mismatches"),
                                     ("fastdiv_check", ["-mfma", "-ffp-contract=off", "-pthread"], ["10", "4"], " 0 mismatches"),
                                     ("gemv_plan_check", [], [], " 0 mistakes"),
-                                    ("gram_plan_check", [], [], " 0 mistakes")):
+                                    ("gram_plan_check", [], [], " 0 mistakes"),
+                                    ("factor_plan_check", [], [], " 0 mistakes")):
         exe = tmp_path / (name + "_san")
         build = subprocess.run(["g++", *san, *extra, os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", str(exe)],
                                capture_output=True, text=True)

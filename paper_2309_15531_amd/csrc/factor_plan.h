@@ -33,6 +33,9 @@ constexpr int64_t FACTOR_HALVES = 8192;    // tiles of a product beyond which th
 // 2048 833 / 891, 4096 2251 / 2265, 5120 3577 / 3535, 8192 10770 / 10650
 constexpr int64_t FACTOR_AHEAD = 4608;
 
+// Elements of T: a level of size s has pairs of s x s, in a panel of 512 (256 squared at most) or in all of up to 1024 channels.
+constexpr int64_t FACTOR_T_ELEMS = int64_t(FACTOR_NBO) * FACTOR_NBO;
+
 enum FactorJobKind {
     FACTOR_T,          // T = C inv(A) of a doubling level of size s (a panel's diagonal block)
     FACTOR_LEVEL,      // M[B rows, A columns] = -inv(B) T of it

@@ -900,11 +900,7 @@ int launch_gptq_prepare(adadim_ctx* ctx, const float* H, int64_t n, float percda
     double* A = static_cast<double*>(adadim_workspace(ctx, WS_GPTQ_A, mat));
     double* M = static_cast<double*>(adadim_workspace(ctx, WS_GPTQ_M, mat));
     double* dvec = static_cast<double*>(adadim_workspace(ctx, WS_GPTQ_D, size_t(n + 1) * sizeof(double)));
-    // products C inv(A) of the inverse's doubling levels: pairs * s * s doubles at level s.  (As many as doubling over the whole
-    // matrix takes, which a matrix of more than one panel no longer needs: what can be recorded after it stays the same.)
-    size_t t_elems = 1;
-    for (int64_t s = NB; s < n; s *= 2) t_elems = std::max(t_elems, size_t((n - s + 2 * s - 1) / (2 * s)) * size_t(s) * size_t(s));
-    double* T = static_cast<double*>(adadim_workspace(ctx, WS_GPTQ_T, t_elems * sizeof(double)));
+    double* T = static_cast<double*>(adadim_workspace(ctx, WS_GPTQ_T, FACTOR_T_ELEMS * sizeof(double)));
     int32_t* rank = static_cast<int32_t*>(adadim_workspace(ctx, WS_GPTQ_V, size_t(n) * sizeof(int32_t)));   // free here
     if (!A || !M || !dvec || !T || !rank) return ADADIM_EHIP;
     double* damp = dvec + n;

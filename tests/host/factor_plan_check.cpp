@@ -76,6 +76,7 @@ struct Matrix {
                     need_l(a0 + k, b0 + mt, wg);
                     need_inverse(a0 + k, a0 + nn, wg);
                 }
+                expect((id + 1) * 64 * 64 <= FACTOR_T_ELEMS, "T is too small", id, j.s);
                 write(T(id), wg, &t[id], j.s + static_cast<int>(j.k0));
             } else {
                 for (int64_t k = 0; k <= mt; ++k) {

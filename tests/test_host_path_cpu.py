@@ -251,6 +251,36 @@ def test_factor_stays_on_its_stream(run):
     """)
 
 
+def test_factor_needs_two_matrices_of_scratch(run):
+    """Beside the two fp64 matrices the factor allocates a few MiB, whatever its width (the doubling's products are kept for one
+    panel; for the whole matrix they were an eighth to a half of the two, which nothing read).  A factor can be recorded
+    after one of at least its width has run."""
+    run("""
+    def factor(ctx, n):
+        return lib.adadim_gptq_prepare(ctx, A, c_int64(n), ctypes.c_float(0.01), 1, A, A, A)
+    for n in (64, 1000, 1024, 1025, 5000, 8192):
+        ctx = context()
+        fake.fake_reset()
+        assert factor(ctx, n) == OK, lib.adadim_last_error(ctx)
+        sizes = sorted(int(c.split()[1]) for c in calls() if c.startswith("hipMalloc "))
+        for _ in "AM":
+            sizes.remove((8 * n * n + 255) // 256 * 256)
+        assert sum(sizes) < 4 << 20, (n, sizes)
+        lib.adadim_destroy(ctx)
+    for warm in (64, 512, 1024, 1100, 3000):
+        for call in (1, 64, 65, 512, 1000, 1024, 1025, 1100, 2900, 3000, 3100):
+            ctx = context()
+            assert factor(ctx, warm) == OK
+            assert lib.adadim_capture_begin(ctx) == OK
+            rc = factor(ctx, call)
+            assert (rc == OK) == (call <= warm), (warm, call, rc)
+            g = c_void_p()
+            assert lib.adadim_capture_end(ctx, byref(g)) == OK
+            lib.adadim_graph_destroy(g)
+            lib.adadim_destroy(ctx)
+    """)
+
+
 def test_sweep_recording_depends_on_sizes_alone(run):
     """A sweep can be recorded after one of at least its size has run, whichever dimension or form either takes."""
     run("""

@@ -1006,8 +1006,7 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         }
 #undef GQ_ROWS
     }
-    const bool many = ic && in > 2 * GB && out / g > groups::MANY;
-    for (int64_t i1 = 0; ic && !many && i1 < in; i1 += GB) {
+    for (int64_t i1 = 0; ic && i1 < in; i1 += GB) {
         ProfScope prof(ctx, "gptq_sweep");
         const int nbw = static_cast<int>(in - i1 < GB ? in - i1 : GB);
         const int64_t n_groups = out / g, n_items = n_groups + groups::n_pieces(out, in, i1);
@@ -1020,13 +1019,13 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         else GQ_GO(2);
 #undef GQ_GO
     }
-    // A launch per block for the walk alone: a block's errors reach the channels behind it in two launches: the next block's 128
-    // channels at once, on the main stream, so that the next sweep can start; the rest on a side stream, under
+    // Per-OC a launch per block for the walk alone: a block's errors reach the channels behind it in two launches: the next block's
+    // 128 channels at once, on the main stream, so that the next sweep can start; the rest on a side stream, under
     // that sweep.  Every element still receives the
     // blocks' errors in block order: the side stream applies them in order, and the main stream
     // waits for the side stream's last launch before it adds the following block's errors to the
     // channels that launch wrote.  With per-kernel timing on, everything runs on the main stream.
-    const bool by_block = ic ? many : !whole;
+    const bool by_block = !ic && !whole;
     const bool overlap = by_block && !ctx->prof.enabled && in > 2 * GB;
     if (overlap && !adadim_side_stream(ctx)) return ADADIM_EHIP;
     bool side_busy = false;
@@ -1034,16 +1033,8 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         const int nbw = static_cast<int>(in - i1 < GB ? in - i1 : GB);
         {
             ProfScope prof(ctx, "gptq_sweep");
-#define GQ_GO(RPL)                                                                                                       \
-    hipLaunchKernelGGL(groups::gq_group<RPL>, dim3(static_cast<unsigned>(out / g)), dim3(256), sizeof(groups::Walk<RPL>), ctx->stream, \
-                       Wp, U, perm, in, i1, nbw, qmax, 1.0f / qmax, mfmt, scales_out, zeros_out, Qp, Ep)
-            if (!ic)
-                hipLaunchKernelGGL(blocks::gq_block, dim3(static_cast<unsigned>((out + blocks::ROWS - 1) / blocks::ROWS)), dim3(256),
-                                   sizeof(blocks::Lds), ctx->stream, Wp, U, perm, out, in, i1, nbw, g, qmax, mfmt, st_scales, st_zeros,
-                                   Qp, Ep);
-            else if (g == 64) GQ_GO(1);
-            else GQ_GO(2);
-#undef GQ_GO
+            hipLaunchKernelGGL(blocks::gq_block, dim3(static_cast<unsigned>((out + blocks::ROWS - 1) / blocks::ROWS)), dim3(256),
+                               sizeof(blocks::Lds), ctx->stream, Wp, U, perm, out, in, i1, nbw, g, qmax, mfmt, st_scales, st_zeros, Qp, Ep);
         }
         const int64_t behind = i1 + nbw;                        // first channel behind the block
         if (behind >= in) break;

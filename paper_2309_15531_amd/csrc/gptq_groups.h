@@ -1,7 +1,7 @@
 // The per-IC GPTQ sweep: one launch per 128-channel block (gfx950).  Included by gptq.hip.
 //
 // The parameters of (row group, channel) come from the channel's current values in all 64 or 128 rows of the group, so
-// a group stays with one workgroup, and there are fewer groups than compute units.  A block's launch therefore holds two kinds
+// a group stays with one workgroup.  A block's launch holds two kinds
 // of work that do not depend on each other, one workgroup of eight waves per compute unit taking them from one list:
 //   * the walks, first in the list: a group's 128 columns get the last block's errors on their way from memory into LDS, then
 //     its channels are visited one after the other;
@@ -10,13 +10,11 @@
 // else has to wait: no launch between two walks, no second stream, no event.  (The form before: the walk, a launch for the next
 // block's columns, and the rest on a side stream, which the next block's launch had to wait for.  11008 x 4096, groups of
 // 128: 60 + 17 us and 25 us of gaps per block beside updates of 210 to 20 us, 5260 us in all with the copies and the score; so
-// 4650, the launches 230 us where 3840 columns are behind the block, 75 to 78 where few are.)  Beyond the walks the update is
+// 4650, the launches 230 us where 3840 columns are behind the block, 75 to 78 where few are.  More groups than compute units are
+// no reason for the other form, with walks by four waves to leave the update room: us, launches of their own / one list, 172
+// groups of 64 x 4096 4838 / 4352, 260 of 128 x 2048 4313 / 3582, 418 of 64 x 408 439 / 361, 1000 of 64 x 300 628 / 521; of 50
+// sizes from 161 to 2000 groups 1.03 to 1.28 times as fast.)  Beyond the walks the update is
 // bound by the pipes (3.0e13 elements per second of the 3.7e13 of gptq_update.h's bare loop).
-//
-// Beyond 160 groups, where columns are left behind the first two blocks, the launches are those of the form before, the walk by
-// four waves so that the update finds room beside it (gq_group, gq_next, gq_trailing): tests/test_host_path_cpu.py holds that
-// dispatch.  One list is the faster form there as well (us, launches of their own / one list: 165 groups of 64 x 1000 629 / 499;
-// 260 of 128 x 2048 4230 / 3575; 440 of 64 x 2678 5461 / 5350; 600 of 64 x 1024 1622 / 1455).
 //
 // The walk: the strip sits in LDS, wave 0 takes 16 channels at a time into registers.  Its chain of decisions is what
 // the block waits for: minimum and maximum of the group (one wave reduction), parameters, codes, errors, updates of
@@ -71,7 +69,6 @@ namespace groups {
 using namespace chain_ns;
 
 constexpr int WAVES = 8, ROWS = 64, COLS = 256;               // of a launch's workgroup; of a piece of the update
-constexpr int64_t MANY = 160;          // groups beyond which a block with columns behind it takes launches of their own
 
 template <int RPL>
 struct Walk {
@@ -331,8 +328,8 @@ __device__ __forceinline__ void updated_strip(const float* __restrict__ Wrows, c
         }
 }
 
-// Block [i1, i1 + nbw) of a row group.  BEHIND: its columns still lack the last block's errors.
-template <int RPL, int WAVES, bool BEHIND>
+// Block [i1, i1 + nbw) of a row group, whose columns still lack the last block's errors.
+template <int RPL>
 __device__ __forceinline__ void walk(Walk<RPL>& lds, int group, const float* __restrict__ Wp, const float* __restrict__ U,
                                      const int32_t* __restrict__ perm, int64_t in, int64_t i1, int nbw, float qmax, float rqmax,
                                      int mfmt, float* __restrict__ scales_out, uint8_t* __restrict__ zeros_out,
@@ -357,7 +354,7 @@ __device__ __forceinline__ void walk(Walk<RPL>& lds, int group, const float* __r
         }
         if (tid < nbw) cd = U[(i1 + tid) * (in + 1)];
     };
-    if (!BEHIND || i1 == 0) {
+    if (i1 == 0) {
         float4 cw[NW];
 #pragma unroll
         for (int q = 0; q < NW; ++q) {
@@ -367,7 +364,7 @@ __device__ __forceinline__ void walk(Walk<RPL>& lds, int group, const float* __r
         corner();
 #pragma unroll
         for (int q = 0; q < NW; ++q) *reinterpret_cast<float4*>(&lds.w[kr + RS * (q >> 2)][c4 + 32 * (q & 3)]) = cw[q];
-    } else if constexpr (BEHIND) {
+    } else {
         updated_strip<RPL>(Wp + row0 * in, U, Ep + row0 * in + i1 - GB, in, i1, nbw, vec, lds);
         corner();
     }
@@ -417,7 +414,7 @@ __device__ __forceinline__ void walk(Walk<RPL>& lds, int group, const float* __r
         const int sbw = min(nbw - s0, SB);
         float(*es)[G] = lds.es[(s0 / SB) & 1];
         if (wave == 0) {
-            // the chain every later launch waits for: ahead of the bulk update that shares the SIMD with it
+            // the chain the walk waits for: ahead of the wave that shares the SIMD with it
             __builtin_amdgcn_s_setprio(3);
             float e[RPL][SB], my_scale = 1.0f, my_zero = 0.0f;
             uint32_t qpk[RPL][SB / 4];
@@ -587,24 +584,13 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_group_step(float* __restrict
     Lds<RPL>& lds = *reinterpret_cast<Lds<RPL>*>(smem);
     int item = static_cast<int>(blockIdx.x);
     while (item < n_groups) {
-        walk<RPL, WAVES, true>(lds.walk, item, Wp, U, perm, in, i1, nbw, qmax, rqmax, mfmt, scales_out, zeros_out, Qp, Ep);
+        walk<RPL>(lds.walk, item, Wp, U, perm, in, i1, nbw, qmax, rqmax, mfmt, scales_out, zeros_out, Qp, Ep);
         if (threadIdx.x == 0) lds.taken = static_cast<int>(gridDim.x) + atomicAdd(counter, 1);
         __syncthreads();                                       // (the walk's last reads of LDS are behind it, too)
         item = __builtin_amdgcn_readfirstlane(lds.taken);
         __syncthreads();
     }
     if (item < n_items) pieces(lds.piece, &lds.taken, counter, item, n_groups, n_items, Wp, U, Ep, in, i1 - GB, static_cast<int>(i1) + nbw);
-}
-
-// The walk alone, four waves, for a block whose columns are up to date.
-template <int RPL>
-__global__ __launch_bounds__(256, 1) void gq_group(const float* __restrict__ Wp, const float* __restrict__ U,
-                                                   const int32_t* __restrict__ perm, int64_t in, int64_t i1, int nbw, float qmax, float rqmax,
-                                                   int mfmt, float* __restrict__ scales_out, uint8_t* __restrict__ zeros_out,
-                                                   uint8_t* __restrict__ Qp, float* __restrict__ Ep) {
-    extern __shared__ __align__(16) char smem[];
-    walk<RPL, 4, false>(*reinterpret_cast<Walk<RPL>*>(smem), static_cast<int>(blockIdx.x), Wp, U, perm, in, i1, nbw, qmax, rqmax, mfmt,
-                        scales_out, zeros_out, Qp, Ep);
 }
 
 // Pieces of the update in the launch of the block at i1 (none in the first one's).
@@ -615,10 +601,8 @@ inline int64_t n_pieces(int64_t out, int64_t in, int64_t i1) {
 
 template <int RPL>
 hipError_t allow_lds_of() {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gq_group_step<RPL>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             static_cast<int>(sizeof(Lds<RPL>)));
-    return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(gq_group<RPL>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     static_cast<int>(sizeof(Walk<RPL>)));
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(gq_group_step<RPL>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               static_cast<int>(sizeof(Lds<RPL>)));
 }
 inline hipError_t allow_lds() {
     const hipError_t e = allow_lds_of<1>();

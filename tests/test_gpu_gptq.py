@@ -503,10 +503,11 @@ def test_per_oc_sweep_does_not_depend_on_its_rows_neighbours(ctx, out_f, in_f, b
         assert torch.equal(codes[r:r + piece], c) and torch.equal(dW[r:r + piece], d), r
 
 
-@pytest.mark.parametrize("groups,in_f,group,bits", [(176, 520, 64, 3), (290, 77, 64, 4), (165, 264, 128, 2), (161, 1000, 128, 4)])
+@pytest.mark.parametrize("groups,in_f,group,bits", [(176, 520, 64, 3), (290, 77, 64, 4), (165, 264, 128, 2), (161, 1000, 128, 4),
+                                                    (300, 401, 64, 3), (270, 392, 128, 4)])
 def test_per_ic_sweep_of_many_groups(ctx, groups, in_f, group, bits):
-    """More groups than leave the update room beside the walk's eight waves: a layer swept whole and in pieces of few groups
-    gives the same bits; the first groups against the oracle."""
+    """Groups that take most of the compute units and more than there are, so that walks come from the list as pieces of the update
+    do: a layer swept whole and in pieces of few groups gives the same bits; the first groups against the oracle."""
     out_f = groups * group
     g = torch.Generator(device="cuda").manual_seed(groups)
     W = (torch.randn((out_f, in_f), generator=g, device="cuda") * 0.02).half()

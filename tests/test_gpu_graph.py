@@ -162,8 +162,8 @@ def test_recorded_products_replay_as_eager(meta16):
 @pytest.mark.parametrize("out_f,in_f,dim,group", [
     (9216, 520, 0, 65),          # per-OC, a launch per block, updates on the side stream
     (1024, 520, 0, 65),          # per-OC in one launch
-    (10560, 392, 1, 64),         # per-IC, more groups than eight waves serve
-    (1024, 520, 1, 64),          # per-IC, walks and update in one launch per block
+    (10560, 392, 1, 64),         # per-IC, walks and update in one launch per block: 165 groups
+    (1024, 520, 1, 64),          # the same, 16 groups
 ])
 def test_recorded_sweeps_replay_as_eager(out_f, in_f, dim, group):
     """GPTQ sweeps recorded with the work they put on the context's side stream: every replay with a new weight, with eager

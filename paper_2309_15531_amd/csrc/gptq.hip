@@ -1040,9 +1040,11 @@ int launch_gptq_quantize(adadim_ctx* ctx, const __half* W, int64_t out, int64_t 
         if (behind >= in) break;
         const int64_t next_end = behind + GB < in ? behind + GB : in;
         auto trailing = [&](hipStream_t stream, int64_t col0) {
-            const dim3 grid(static_cast<unsigned>((in - col0 + update::COLS - 1) / update::COLS),
+            const bool narrow = in - col0 <= update::COLS_NARROW;
+            const dim3 grid(narrow ? 1 : static_cast<unsigned>((in - col0 + update::COLS - 1) / update::COLS),
                             static_cast<unsigned>((out + update::ROWS - 1) / update::ROWS));
-            hipLaunchKernelGGL(update::gq_trailing, grid, dim3(256), 0, stream, Wp, U, Ep, out, in, i1, col0, in);
+            hipLaunchKernelGGL(narrow ? update::gq_trailing<true> : update::gq_trailing<false>, grid, dim3(256), 0, stream, Wp, U, Ep, out, in,
+                               i1, col0, in);
         };
         if (!overlap) {
             ProfScope prof(ctx, "gptq_trailing");

@@ -14,6 +14,8 @@
 #include "common.h"
 #include "gptq_chain.h"
 
+#include <type_traits>
+
 namespace {
 
 namespace update {
@@ -59,16 +61,22 @@ struct Matrix {
     }
 };
 
-constexpr int ROWS = 64, COLS = 128;   // of a workgroup; a wave takes 32 of the columns
+constexpr int ROWS = 64;               // of a workgroup
+constexpr int COLS = 128, COLS_NARROW = 64;
 
 // Wp[r][jj] -= E[r][k] * U[k][jj], k = i1 .. i1 + GB - 1 in order (product, then difference), for the columns [col0, col1).
 // The workgroup's errors go to LDS once; a column's entries of U travel KB channels ahead of their use.  The next channel's
 // products are issued before this channel's differences, so that a wave does not wait for them.  Three waves per SIMD: two keep
 // the pipes busy, the third starts or ends a tile.  11008 rows x 3840 columns: 248 us with vector instructions alone (eight
 // rows per thread), 187 so, 145 for the bare loop.
+// A wave takes all rows and 32 of the columns; NARROW, for at most 64 columns, 16 of the rows and all columns, as otherwise two or
+// three of the four waves would have none (whole sweeps, us, eight rows per thread / a wave all rows / so: 34154 x 148 248 / 256 /
+// 242, 57538 x 138 335 / 344 / 324, 12551 x 192 111 / 111 / 104; 12551 x 200, of 72 columns, 128 / 124).
+template <bool NARROW>
 __global__ __launch_bounds__(256, 3) void gq_trailing(float* __restrict__ Wp, const float* __restrict__ U, const float* __restrict__ Ep,
                                                       int64_t out, int64_t in64, int64_t i1, int64_t col0, int64_t col1) {
-    constexpr int KB = 8;
+    constexpr int KB = 8, NR = NARROW ? 16 : 32;               // NR elements per lane
+    using Products = std::conditional_t<NARROW, f32x16, f32x32>;
     __shared__ __align__(16) float es[ROWS][PITCH];            // [row][channel]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int in = static_cast<int>(in64);
@@ -78,13 +86,16 @@ __global__ __launch_bounds__(256, 3) void gq_trailing(float* __restrict__ Wp, co
     const Matrix Wrows(Wp + r0 * in64), Urows(U + i1 * in64);
     const float* __restrict__ Erows = Ep + r0 * in64 + i1;
     const int c_end = static_cast<int>(col1);
-    const int c = static_cast<int>(col0) + static_cast<int>(blockIdx.x) * COLS + 32 * wave + (lane & 31);
-    const uint32_t col = 4u * static_cast<uint32_t>(min(c, c_end - 1));        // past the end: read, never stored
+    const int c0 = static_cast<int>(col0) + static_cast<int>(blockIdx.x) * (NARROW ? COLS_NARROW : COLS) + (NARROW ? 0 : 32 * wave);
+    // past the end: read, never stored
+    const uint32_t ucol = 4u * static_cast<uint32_t>(min(c0 + (NARROW ? lane : lane & 31), c_end - 1));
+    auto row = [&](int r, int lane) { return NARROW ? 16 * wave + 4 * (lane >> 4) + (r & 3) : row_of(r, lane); };
+    auto col = [&](int r, int lane) { return c0 + (NARROW ? 16 * (r >> 2) + (lane & 15) : lane & 31); };
 
     float u[2][KB];
     auto fetch = [&](int b, int k) {
 #pragma unroll
-        for (int kk = 0; kk < KB; ++kk) u[b][kk] = Urows.load(col, (k + kk) * pitch);
+        for (int kk = 0; kk < KB; ++kk) u[b][kk] = Urows.load(ucol, (k + kk) * pitch);
     };
     fetch(0, 0);
     if ((in & 3) == 0) {                                       // Ep is scratch, 16-byte aligned; i1 is a multiple of GB
@@ -101,25 +112,31 @@ __global__ __launch_bounds__(256, 3) void gq_trailing(float* __restrict__ Wp, co
             es[r][k] = Erows[static_cast<uint32_t>(min(r, n_rows - 1)) * static_cast<uint32_t>(in) + k];
         }
     }
-    const uint32_t first = static_cast<uint32_t>(row_of(0, lane)) * pitch + col;
-    float v[32];
-    if (n_rows == ROWS) {
+    const uint32_t first = static_cast<uint32_t>(row_of(0, lane)) * pitch + ucol;
+    float v[NR];
+    if (!NARROW && n_rows == ROWS) {
 #pragma unroll
-        for (int r = 0; r < 32; ++r) v[r] = Wrows.load(first, row_of(r, 0) * pitch);
+        for (int r = 0; r < NR; ++r) v[r] = Wrows.load(first, row_of(r, 0) * pitch);
     } else {
 #pragma unroll
-        for (int r = 0; r < 32; ++r) v[r] = Wrows.load(static_cast<uint32_t>(min(row_of(r, lane), n_rows - 1)) * pitch + col, 0);
+        for (int r = 0; r < NR; ++r)
+            v[r] = Wrows.load(static_cast<uint32_t>(min(row(r, lane), n_rows - 1)) * pitch + 4u * static_cast<uint32_t>(min(col(r, lane), c_end - 1)), 0);
     }
     __syncthreads();
     f32x4 ev[2];
-    auto errors = [&](int b, int k) { ev[b] = *reinterpret_cast<const f32x4*>(&es[lane][k & (GB - 1)]); };
+    const float* e_row = es[NARROW ? 16 * wave + (lane & 15) : lane];
+    auto errors = [&](int b, int k) { ev[b] = *reinterpret_cast<const f32x4*>(e_row + (k & (GB - 1))); };
     auto error = [&](int kk) {                                 // of channel kk of 16, the group of four being in its buffer
         const f32x4 t = ev[(kk >> 2) & 1];
         return (kk & 3) == 0 ? t.x : (kk & 3) == 1 ? t.y : (kk & 3) == 2 ? t.z : t.w;
     };
-    f32x32 p[2];
+    auto products = [&](float e, float u) {
+        if constexpr (NARROW) return products16x64(e, u);
+        else return products64x32(e, u);
+    };
+    Products p[2];
     errors(0, 0);
-    p[0] = products64x32(error(0), u[0][0]);
+    p[0] = products(error(0), u[0][0]);
 #pragma unroll 1
     for (int k = 0; k < GB; k += 2 * KB) {
 #pragma unroll
@@ -130,24 +147,24 @@ __global__ __launch_bounds__(256, 3) void gq_trailing(float* __restrict__ Wp, co
             if ((kk & 3) == 0) errors(((kk >> 2) + 1) & 1, k + kk + 4);
             const int nk = kk + 1;
             __builtin_amdgcn_sched_barrier(0);
-            p[nk & 1] = products64x32(error(nk), u[(nk / KB) & 1][nk % KB]);
+            p[nk & 1] = products(error(nk), u[(nk / KB) & 1][nk % KB]);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int r = 0; r < 32; ++r) v[r] = v[r] - p[kk & 1][r];
+            for (int r = 0; r < NR; ++r) v[r] = v[r] - p[kk & 1][r];
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    if (c >= c_end) return;
-    if (n_rows == ROWS) {
+    if (!NARROW && n_rows == ROWS) {
+        if (c0 + (lane & 31) >= c_end) return;
 #pragma unroll
-        for (int r = 0; r < 32; ++r) Wrows.store(v[r], first, row_of(r, 0) * pitch);
+        for (int r = 0; r < NR; ++r) Wrows.store(v[r], first, row_of(r, 0) * pitch);
     } else {
-        int lane_s = lane;                                     // row offsets are worked out again, not held over the loop
+        int lane_s = lane;                                     // offsets are worked out again, not held over the loop
         asm volatile("" : "+v"(lane_s));
 #pragma unroll
-        for (int r = 0; r < 32; ++r) {
-            const int row = row_of(r, lane_s);
-            if (row < n_rows) Wrows.store(v[r], static_cast<uint32_t>(row) * pitch + col, 0);
+        for (int r = 0; r < NR; ++r) {
+            const int rr = row(r, lane_s), c = col(r, lane_s);
+            if (rr < n_rows && c < c_end) Wrows.store(v[r], static_cast<uint32_t>(rr) * pitch + 4u * static_cast<uint32_t>(c), 0);
         }
     }
 }

@@ -164,6 +164,10 @@ def _synthetic_factor(in_f, rng, tiny=False):
     (9220, 260, OC, 3, 0, False),     # a launch per block; 4 rows and 4 columns past whole tiles of the update
     (9217, 259, OC, 4, 0, False),     # the same with rows of Wp at any alignment
     (9220, 420, OC, 4, 0, False),     # with an update on the side stream
+    (10007, 129, OC, 3, 0, False),    # updates of 1, 49, 64 and 65 columns, rows short of a tile
+    (10007, 177, OC, 4, 0, False),
+    (10050, 192, OC, 3, 0, False),
+    (10050, 193, OC, 3, 0, False),
     (64, 385, IC, 3, 64, False),      # one column behind whole blocks
     (192, 641, IC, 4, 64, False),
     (384, 545, IC, 2, 128, False),

@@ -177,6 +177,22 @@ def test_per_oc_sweep_takes_the_form_that_is_faster(run):
     """)
 
 
+def test_narrow_updates_keep_every_wave_busy(run):
+    """The update behind a block of the per-OC sweep's launches per block: up to 64 columns the four waves share the rows, beyond
+    that the columns (two or three of them had none, and sweeps of 129 to 192 channels took up to 1.03 times as long as with
+    vector instructions)."""
+    run("""
+    def forms(out, inn):
+        ctx = context()
+        fake.fake_reset()
+        assert lib.adadim_gptq_quantize(ctx, A, c_int64(out), c_int64(inn), 0, 3, inn, A, A, A, A, A, A, None, None, None, None) == OK
+        assert launched("gq_block")
+        return ["ILb1E" in c for c in launched("gq_trailing")]
+    for inn, want in ((129, [True]), (148, [True]), (192, [True]), (193, [False]), (256, [False]), (257, [True]), (448, [False, True])):
+        assert forms(100000, inn) == want, (inn, forms(100000, inn))
+    """)
+
+
 def test_packers_by_alignment(run):
     """The packers that read several codes at a time serve the widths and addresses that allow it, a thread per word the others
     (byte loads in the tiled packer took up to 2.6 times as long)."""

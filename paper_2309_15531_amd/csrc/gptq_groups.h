@@ -1,8 +1,8 @@
 // The per-IC GPTQ sweep: one launch per 128-channel block (gfx950).  Included by gptq.hip.
 //
 // The parameters of (row group, channel) come from the channel's current values in all 64 or 128 rows of the group, so
-// a group stays with one workgroup.  A block's launch holds two kinds
-// of work that do not depend on each other, one workgroup of eight waves per compute unit taking them from one list:
+// a group stays with one workgroup.  A block's launch holds two kinds of work that do not depend on each other, one workgroup
+// of eight waves per compute unit taking them from one list:
 //   * the walks, first in the list: a group's 128 columns get the last block's errors on their way from memory into LDS, then
 //     its channels are visited one after the other;
 //   * the update of the columns behind the block with the last block's errors, in pieces of 64 rows x 256 columns.
@@ -21,6 +21,10 @@
 // the later channels of the sixteen.  Meanwhile the other waves apply the errors of the sixteen before to the
 // columns behind; then all apply the new errors to the next sixteen columns.  Two error buffers, taken in turn.
 // 128 rows, cycles of a block: strip 53000 (loads 9500, products and differences 37000), chains 84000, the rest 20000.
+//
+// Registers: with 128 rows 13 vector registers do not fit and live in scratch (56 bytes per lane), eleven of them read back once
+// per sub-block behind the chain's short form, the others outside the loop over sub-blocks; with 64 rows none.  71 and 50 scalar
+// ones live in lanes of vector registers.
 //
 // Every update is one rounded product and one rounded difference in channel order, whichever wave applies it.
 #pragma once

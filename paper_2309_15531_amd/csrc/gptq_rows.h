@@ -14,7 +14,7 @@
 // matrix cores (16 and 32 rows per workgroup) and two waves at the chain; 64 to 1024 rows of that width 0.9 ms (the chain alone).
 //
 // Rows per workgroup: few enough that the chip's 256 compute units all have a workgroup (16 at 4096 rows), so that
-// the VALU work is spread over the whole chip; the chain takes the same time for 4 rows as for 64.  rows_per_group
+// the update is spread over the whole chip; the chain takes much the same time for 4 rows as for 64.  rows_per_group
 // picks R from the sizes.
 //
 // Registers: with 32 rows 26 vector registers do not fit and live in scratch, with 8 rows 12, otherwise none.  They are values
@@ -637,71 +637,66 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
     }
 }
 
-// Rows per workgroup for [out, in]: the R with the least rounds x time of one workgroup.  A block of one workgroup
-// takes the longer of the chain and the updates (R rows x remaining columns x 128 channels x 2 operations at 64 per
-// cycle), then the update of the next block's columns.  The constants (us) are measured with the clock around each part,
-// at R = 4, 16 and 32 on a 4096-wide input alone: chain 18, 29, 45, step between two blocks 4, 7, 10 (with one wave at the chain;
-// with two the chain of 16 rows takes 23).
-inline int rows_per_group(int64_t out, int64_t in) {
-    const int sizes[] = {4, 8, 12, 16, 24, 32};
-    int best = 16;
-    double best_us = 0.0;
-    for (int r : sizes) {
-        const double rounds = double((((out + r - 1) / r) + 255) / 256);
-        double us = 0.0;
-        for (int64_t i1 = 0; i1 < in; i1 += GB) {
-            const double upd = double(in - i1) * r * GB * 2.0 / 64.0 / 2.2e3;
-            us += std::max(14.0 + 0.95 * r, upd) + 3.2 + 0.23 * r;
-        }
-        us *= rounds;
-        if (best_us == 0.0 || us < best_us) {
-            best_us = us;
-            best = r;
-        }
+// Which form and how many rows per workgroup: the least of the models below, whose constants (us) are fitted to whole calls of 1341
+// sizes (8 to 152064 rows, 16 to 28672 channels, a quarter of them no multiple of 16; 2 to 4 bits), in launches per block and with every
+// number of rows within 1.3 of the best.  What they choose is 0.2 % slower than the best on average (0.1 % from 128 channels on) and
+// 9 % at worst, 14 % below 128 channels, where a call is 17 to 60 us.  They compare; neither estimates the call, which holds two
+// permuting copies as well.  The lines they draw, us, one launch [rows per workgroup] / a launch per block:
+//   rows in one round of workgroups   2048 x 2048  496 [8] / 1103      4096 x 4096  1729 [16] / 2659   8192 x 1024  385 [32] / 613
+//   more rows than that               9216 x 512   336 [24] / 295      28672 x 1024  1471 [32] / 1414  100000 x 256  1083 [32] / 809
+//   rounds of 32 rows nearly full     6676 x 384   141 [32] / 211      16384 x 2159  2216 [32] / 2652  40000 x 1000  1832 [32] / 2024
+//   many channels, updates dear       8704 x 8192  17220 [12] / 13210  5632 x 11008  17650 [24] / 15520  8 x 16384  10030 [4] / 8760
+//   rows per workgroup                3072 x 3072  1067 [12], 1102 [16]   50000 x 1280  4129 [24], 3515 [32]   12288 x 6144  12200 [24], 10373 [16]
+//
+// In one launch: rounds of workgroups, each of which takes, block by block, the longer of its chain and the update of the
+// columns behind it, and a step to the next block.  With 16 and 32 rows the update's products are on the matrix cores, with 12 and
+// more the chain has two waves.  (few: a workgroup or two alone wait for U by themselves.)
+struct Parts {
+    int rows;
+    double chain, step, column;        // of a block; to the next one; of a block's update per column
+};
+constexpr Parts PARTS[] = {{4, 10.5, 11.4, 7.1e-3},  {8, 12.0, 14.6, 11.4e-3},  {12, 12.4, 15.6, 16.1e-3},
+                           {16, 9.3, 16.7, 18.2e-3}, {24, 18.8, 18.4, 32.6e-3}, {32, 18.2, 19.2, 37.5e-3}};
+
+inline double rows_us(const Parts& p, int64_t out, int64_t in) {
+    const int64_t wgs = (out + p.rows - 1) / p.rows;
+    const double few = 1.0 + 0.14 / double(wgs);
+    double us = 9.3 + 0.265 * p.rows;
+    for (int64_t i1 = 0; i1 < in; i1 += GB) {
+        const int64_t w = std::min<int64_t>(in - i1, GB), behind = in - i1 - w;
+        const double update = i1 > 0 ? few * p.column * double(behind) : 0.0;
+        us += std::max(p.chain * double(w) / GB, update) + (behind > 0 ? p.step : 0.0);
     }
-    return best;
+    return us * double((wgs + 255) / 256);
+}
+inline const Parts& best_parts(int64_t out, int64_t in) {
+    const Parts* best = PARTS;
+    for (const Parts& p : PARTS)
+        if (rows_us(p, out, in) < rows_us(*best, out, in)) best = &p;
+    return *best;
 }
 
-// Whether this form is the faster one for [out, in]; else a launch per block (gptq_blocks.h).  Models of both, fitted to whole
-// calls of 657 sizes in both forms (8 to 152064 rows, 128 to 28672 channels, ragged ones among them; 3 bits): what they choose
-// is 0.1 % slower than the better form on average and 8 % at worst (by their difference alone; neither estimates the call).
-// This form is bound by the chain of its rows or by the updates, which many rows per workgroup make cheaper (an error read
-// from LDS serves as many products) and a few workgroups alone dearer (they wait for U by themselves).  A launch per block
-// takes its workgroups of 64 rows in rounds, then a short launch for the next block, and the bulk update beside the next
-// block's chain, part of the shorter one of the two showing where the chain's workgroups fill the chip.  Channels that are no
-// multiple of four make its chain dearer: codes and errors are stored one at a time.  A narrow last block costs its width in
-// either form.  Layers of less than one block (16 to 120 channels, 190 sizes), where a call is 18 to 60 us, are not among them:
-// 1.3 % on average and up to 6 us there (3432 x 64 31 / 37; 28672 x 64 107 / 74).
-// The constants are those of the time before the updates' products went to the matrix cores and the chain of 12 rows and more to
-// two waves.  Of 122 sizes (1500 to 60000 rows of 130 to 5000 channels, and few rows of many) timed since, the choice is 1.3 % slower
-// than the better form on average and 13 % at worst (18057 x 504 493 / 559; 12288 x 4096 5768 / 5259); none fits better by more than
-// 0.2 % that leaves the choices as tests/test_host_path_cpu.py holds them.
-// us, this form / a launch per block (4096 x 4096, 1024 x 16384, 256 x 22016 and the narrow last blocks but one: before that):
-//   many rows     28672 x 1024  1470 / 1438     100000 x 256  1087 / 816     9216 x 512  342 / 297     6144 x 128  57 / 58
-//   few rows of many channels   300 x 28672  24600 / 16700     8 x 16384  10080 / 8770      256 x 22016  15230 / 14080
-//   the rest      4096 x 4096  2127 / 2911     1024 x 16384  9620 / 12760     6144 x 4096  2888 / 3245
-//   ragged        7280 x 493  190 / 322    16384 x 2159  2218 / 2658    16384 x 493  352 / 364
-//   a narrow last block   8192 x 260  139 / 182    7168 x 320  157 / 188    8192 x 200  108 / 116    9216 x 260  200 / 186
-inline bool better(int64_t out, int64_t in) {
-    const int r = rows_per_group(out, in);
-    const int64_t wgs = (out + r - 1) / r, wgs_b = (out + 63) / 64;
-    const double scale = (0.71 + 1.22 / r) * (1.0 + 0.41 / double(wgs));
-    const double chain_b = (in % 4 ? 58.0 : 47.0) * double((wgs_b + 255) / 256), full = std::min(1.0, double(wgs_b) / 256.0);
-    double here = 0.0, there = 0.0;
+// A launch per block (gptq_blocks.h): workgroups of 64 rows, in rounds; a short launch for the next block's columns; the rest of
+// the update beside the next block's chain, most of the shorter one of the two showing where the chain's workgroups fill the chip.  Channels
+// that are no multiple of 16 or of four store codes and errors in smaller pieces.
+inline double blocks_us(int64_t out, int64_t in) {
+    const int64_t wgs = (out + 63) / 64;
+    const double rounds = double((wgs + 255) / 256), full = std::min(1.0, double(wgs) / 256.0), column = 4.54e-6 * double(out);
+    const double block = 44.0 + (in % 4 ? 3.6 : 0.0) + (in % 16 ? 6.5 : 0.0);
+    double us = 7.0, bulk = 0.0;
     for (int64_t i1 = 0; i1 < in; i1 += GB) {
-        const double part = double(std::min<int64_t>(in - i1, GB)) / GB;        // of a block
-        const double upd = double(in - i1) * r * GB * 2.0 / 64.0 / 2.2e3;
-        here += (std::max(14.0 + 0.95 * r, scale * upd) + 3.2 + 0.23 * r) * part;
-        const double per_channel = double(out) * GB * 2.0 / 4.1e7;              // of the updates spread over the chip
-        there += chain_b * part;
-        if (in - i1 > GB) there += 15.0 + double(in) / 2200.0 + per_channel * GB;
-        if (in - i1 > 2 * GB) {
-            const double bulk = per_channel * double(in - i1 - 2 * GB);
-            there += std::max(bulk, chain_b) - chain_b + 0.43 * full * std::min(bulk, chain_b);
-        }
+        const int64_t w = std::min<int64_t>(in - i1, GB), behind = in - i1 - w;
+        const double chain = std::max(0.0, block * double(w) / GB - 4.6) * rounds;
+        us += std::max(bulk, chain) + 0.645 * full * std::min(bulk, chain);
+        if (behind > 0) us += 22.4 + 0.62e-3 * double(in) + column * double(std::min<int64_t>(behind, GB));
+        bulk = column * double(std::max<int64_t>(behind - GB, 0));
     }
-    return here * double((wgs + 255) / 256) + 6.0 <= there;
+    return us;
 }
+
+inline int rows_per_group(int64_t out, int64_t in) { return best_parts(out, in).rows; }
+// Whether this form is the faster one for [out, in]; else a launch per block.
+inline bool better(int64_t out, int64_t in) { return rows_us(best_parts(out, in), out, in) <= blocks_us(out, in); }
 
 template <int R>
 hipError_t allow_lds_of() {

@@ -8,6 +8,7 @@ import textwrap
 
 import pytest
 
+from gptq_forms import GPTQ_FORMS
 from paper_2309_15531_amd import binding as B
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -149,32 +150,59 @@ def test_select_without_pinned_memory(run):
 
 
 def test_per_oc_sweep_takes_the_form_that_is_faster(run):
-    """Sizes at which the one-launch sweep took 1.2 to 1.9 times as long as a launch per block (many rows, or few rows of many
-    channels), and sizes at which it takes a third to nine tenths of that."""
+    """Rows per workgroup of the sweep in one launch, or a launch per 128-channel block (0), beside the times (us) that say so.  A size
+    stands here with its times if the two forms, or the best and the second best number of rows, were measured at least 1.015 times apart."""
     run("""
     def form(out, inn):
         ctx = context()
         fake.fake_reset()
         rc = lib.adadim_gptq_quantize(ctx, A, c_int64(out), c_int64(inn), 0, 3, 64 if inn % 64 == 0 else inn, A, A, A, A, A, A, None, None, None, None)
         assert rc == OK, lib.adadim_last_error(ctx)
-        n = {k: len(launched(k)) for k in ("gq_rows", "gq_block", "gq_next")}
+        rows = [c.split()[1] for c in launched("gq_rows")]
+        n = {k: len(launched(k)) for k in ("gq_block", "gq_next")}
         blocks = (inn + 127) // 128
-        assert n in ({"gq_rows": 1, "gq_block": 0, "gq_next": 0},
-                     {"gq_rows": 0, "gq_block": blocks, "gq_next": blocks - 1 if inn > 256 else 0}), n
-        return "rows" if n["gq_rows"] else "blocks"
-    for shape in ((100000, 256), (28672, 1024), (9216, 512), (6144, 128), (300, 28672), (8, 16384)):
-        assert form(*shape) == "blocks", shape
-    for shape in ((4096, 4096), (1024, 16384), (8192, 1024), (64, 2048), (3072, 128), (4096, 11008), (16384, 8192)):
-        assert form(*shape) == "rows", shape
-    # channels that are no multiple of four: the launches per block store element by element (1.07 to 1.3 times as long)
-    for shape in ((8192, 131), (7280, 493), (40000, 1533), (16384, 2159)):
-        assert form(*shape) == "rows", shape
-    # a narrow last block is cheap in one launch (up to 1.3 times as long in launches per block)
-    for shape in ((8192, 260), (6676, 384), (7168, 320), (8192, 200), (7680, 448)):
-        assert form(*shape) == "rows", shape
-    for shape in ((9216, 493), (40000, 1003), (28672, 3003), (9216, 260), (12288, 384)):
-        assert form(*shape) == "blocks", shape
-    """)
+        if not rows:
+            assert n == {"gq_block": blocks, "gq_next": blocks - 1 if inn > 256 else 0}, n
+            return 0
+        assert len(rows) == 1 and n == {"gq_block": 0, "gq_next": 0}, (rows, n)
+        return int(rows[0].split("gq_rowsILi")[1].split("E")[0])
+    for (out, inn), want in {
+        # in one launch / a launch per block
+        (300, 2048): 4,         # 382 / 1041
+        (2048, 2048): 8,        # 496 / 1103
+        (3072, 3072): 12,       # 1067 / 1746; 16 rows 1102
+        (4096, 4096): 16,       # 1729 / 2659
+        (4096, 11008): 16,      # 10280 / 12000
+        (4608, 4096): 24,       # 2762 / 2875
+        (8192, 1024): 32,       # 385 / 613
+        (8192, 256): 32,        # 102 / 128
+        (6676, 384): 32,        # 141 / 211
+        (12288, 6144): 16,      # 10370 / 10540; 24 rows 12200
+        (1024, 16384): 4,       # 9710 / 10650
+        (16384, 2159): 32,      # 2216 / 2652
+        (40000, 1000): 32,      # 1832 / 2024
+        (100000, 256): 0,       # 1083 / 809
+        (28672, 1024): 0,       # 1471 / 1414
+        (9216, 512): 0,         # 336 / 295
+        (9216, 264): 0,         # 195 / 185
+        (12288, 384): 0,        # 259 / 223
+        (8704, 8192): 0,        # 17220 / 13210
+        (5632, 11008): 0,       # 17650 / 15520
+        (256, 28672): 0,        # 24670 / 16470
+        (8, 16384): 0,          # 10030 / 8760
+    }.items():
+        assert form(out, inn) == want, (out, inn, form(out, inn))
+    # channels that are no multiple of four, which the launches per block store element by element, and narrow last blocks
+    for shape in ((8192, 131), (7280, 493), (40000, 1533), (8192, 260), (7168, 320), (8192, 200), (7680, 448)):
+        assert form(*shape) == 32, shape
+    for shape in ((9216, 493), (28672, 3003), (9216, 260)):
+        assert form(*shape) == 0, shape
+    for shape, rows in (((64, 2048), 4), ((3072, 128), 16), ((16384, 8192), 32)):
+        assert form(*shape) == rows, shape
+    # the sizes whose tests on the GPU aim at a form
+    for (out, inn), want in FORMS.items():
+        assert form(out, inn) == want, (out, inn, form(out, inn))
+    """.replace("FORMS", repr(GPTQ_FORMS)))
 
 
 def test_narrow_updates_keep_every_wave_busy(run):

@@ -12,6 +12,7 @@ import pytest
 import torch
 
 import oracle
+from gptq_forms import GPTQ_FORMS
 from oracle import OC, IC
 from oracle import gptq_oracle as G
 from paper_2309_15531_amd import binding as B
@@ -51,7 +52,8 @@ def gpu_prepare(ctx, H32, percdamp=0.01, act_order=True):
     return perm, dead, U
 
 
-def gpu_sweep(ctx, W, dim, bits, group, U, perm, dead, want_packed=False):
+def gpu_sweep(ctx, W, dim, bits, group, U, perm, dead, want_packed=False, static=None):
+    """static: per-OC parameters (scales, zeros) to take instead of the quantizer's."""
     out_f, in_f = W.shape
     Wd = dev(W)
     codes = torch.full((out_f, in_f), 255, dtype=torch.uint8, device="cuda")
@@ -64,6 +66,8 @@ def gpu_sweep(ctx, W, dim, bits, group, U, perm, dead, want_packed=False):
         Wz = Wd.clone()
         Wz[:, dead.bool()] = 0                         # static parameters of the weight with dead channels zeroed
         ctx.adadim_quantize(Wz, OC, bits, group, 1.0, scales=ss, zeros=sz)
+        if static is not None:
+            ss, sz = dev(static[0]), dev(static[1])
         kw = dict(static_scales=ss, static_zeros=sz)
         res["scales"], res["zeros"] = ss, sz
     else:
@@ -171,17 +175,18 @@ def _synthetic_factor(in_f, rng, tiny=False):
     (64, 385, IC, 3, 64, False),      # one column behind whole blocks
     (192, 641, IC, 4, 64, False),
     (384, 545, IC, 2, 128, False),
-    (16, 2100, OC, 3, 0, False),      # one launch, rows below a workgroup's
-    (4099, 300, OC, 3, 0, False),     # one launch, 16 rows per workgroup, the last with three
-    (6150, 290, OC, 3, 0, False),
+    (3, 2100, OC, 3, 0, False),       # one launch, rows below a workgroup's four
+    (16, 2100, OC, 3, 0, False),      # four whole workgroups
+    (4099, 300, OC, 3, 0, False),     # 24 rows per workgroup, the last with 19
+    (6150, 290, OC, 3, 0, False),     # 32 rows, the last with six
     (128, 400, IC, 4, 64, True),
     (256, 400, IC, 4, 128, True),
-    (4099, 300, OC, 4, 0, True),
 ])
 def test_update_of_later_channels_bit_exact(ctx, out_f, in_f, dim, bits, group, tiny):
     """The update of the channels behind a block at the edges of its tiles, against the oracle's one product and one
     difference per element and channel.  tiny: with a weight that is zero (of either sign) behind the first visited block, the
-    later channels consist of subnormal products alone, so that a lost or flushed product shows in scales and codes."""
+    later channels consist of subnormal products alone, so that a lost or flushed product shows in scales and codes (per-IC, where
+    the scales come from these channels; per-OC test_subnormal_products_decide_per_oc_codes)."""
     rng = np.random.default_rng(out_f * 7 + in_f)
     W = synth.make_weight(out_f, in_f, in_f, heavy_cols=2, heavy_scale=5.0)
     U = _synthetic_factor(in_f, rng, tiny)
@@ -199,6 +204,106 @@ def test_update_of_later_channels_bit_exact(ctx, out_f, in_f, dim, bits, group, 
     if tiny and dim == IC:
         late = ref["scales"][:, perm[128:]]
         assert ((late > 0) & (late < 1e-37)).any()
+
+
+def _sampled(rng, out_f, rows):
+    """Rows of a per-OC layer to compare: its first and last two and some between."""
+    return np.unique(np.r_[0, 1, out_f - 2, out_f - 1, rng.choice(out_f, min(out_f, rows), replace=False)])
+
+
+def _per_oc_matches_oracle(ctx, W, U, perm, dead, bits, group, rows, scale_round=None):
+    """A per-OC sweep with the oracle's static parameters against the oracle on the given rows (rows do not depend on each other)."""
+    static = oracle.quantize(np.where(dead[None, :], np.float16(0.0), W), OC, bits, group, scale_round=scale_round)
+    ref = G.sweep(W[rows], U, perm, dead, OC, bits, group, scale_round=scale_round)
+    assert np.array_equal(ref["scales"], static["scales"][rows])
+    got = gpu_sweep(ctx, W, OC, bits, group, dev(U), dev(perm.astype(np.int32)), dev(dead.astype(np.uint8)),
+                    static=(static["scales"], static["zeros"]))
+    assert np.array_equal(got["codes"][rows], ref["codes"])
+    assert np.array_equal(got["dW"][rows], ref["dW"])
+    return ref
+
+
+@pytest.mark.parametrize("form,out_f,in_f", [
+    (16, 4090, 3300),     # items of the update per wave: three; a last workgroup of ten rows
+    (32, 8100, 3300),     # six; a last workgroup of four, so that its second half has none
+    (24, 4099, 300),
+    (12, 3000, 1800),
+    (8, 2041, 1800),
+    (0, 9220, 420),       # a launch per block: the next block's columns, and behind those the update on the side stream
+    (0, 10007, 177),      # the same, an update of few columns
+])
+def test_several_pieces_of_the_update_per_wave(ctx, form, out_f, in_f):
+    """The per-OC forms with their update in several pieces for each wave, the last ones ragged, against the oracle."""
+    assert GPTQ_FORMS[(out_f, in_f)] == form
+    rng = np.random.default_rng(out_f)
+    W = synth.make_weight(out_f, in_f, out_f + in_f, heavy_cols=2, heavy_scale=5.0)
+    U, perm, dead = _synthetic_factor(in_f, rng), rng.permutation(in_f), np.zeros(in_f, dtype=bool)
+    dead[perm[7]] = True
+    _per_oc_matches_oracle(ctx, W, U, perm, dead, 3, 0, _sampled(rng, out_f, 60))
+
+
+@pytest.mark.parametrize("form,out_f,in_f,group", [
+    (16, 4090, 3300, 4),
+    (32, 8100, 3300, 4),
+    (24, 4099, 300, 4),
+    (12, 3000, 1800, 8),
+    (8, 2041, 1800, 8),
+    (4, 3, 2100, 4),
+    (0, 9220, 420, 4),
+    (0, 10050, 192, 8),
+])
+def test_subnormal_products_decide_per_oc_codes(ctx, form, out_f, in_f, group):
+    """Per-OC parameters are static, so products of the update that are subnormal, or zero of either sign, show in codes only where
+    the static scales are as small.  The first 128 visited channels are the first groups, the weight behind them is zero of either
+    sign and its groups' scale (1, as their range is zero) becomes a subnormal: the later codes are made of such products alone."""
+    assert GPTQ_FORMS[(out_f, in_f)] == form
+    rng = np.random.default_rng(out_f + in_f)
+    W = synth.make_weight(out_f, in_f, in_f, heavy_cols=2, heavy_scale=5.0)
+    U = _synthetic_factor(in_f, rng, tiny=True)
+    perm = np.r_[rng.permutation(128), 128 + rng.permutation(in_f - 128)]
+    dead = np.zeros(in_f, dtype=bool)
+    W[:, perm[128:]] = np.copysign(np.float16(0.0), rng.standard_normal((out_f, in_f - 128)).astype(np.float16))
+
+    def scale_round(s):
+        return np.where(s == 1.0, np.float32(2.0 ** -131), s).astype(np.float32)
+
+    rows = _sampled(rng, out_f, 60)
+    ref = _per_oc_matches_oracle(ctx, W, U, perm, dead, 3, group, rows, scale_round)
+    # the reference depends on those products, in every later block
+    U[:128, 128:] = 0.0
+    without = G.sweep(W[rows], U, perm, dead, OC, 3, group, scale_round=scale_round)
+    changed = ref["codes"] != without["codes"]
+    assert not changed[:, perm[:128]].any()
+    assert all(changed[:, perm[c]].any(axis=0).mean() > 0.5 for c in np.array_split(np.arange(128, in_f), -(-(in_f - 128) // 128)))
+
+
+@pytest.mark.parametrize("form,out_f,in_f,group", [
+    (4, 1000, 272, 16),
+    (8, 2041, 1800, 8),
+    (12, 3000, 1800, 8),
+    (16, 4090, 328, 8),
+    (24, 6100, 260, 4),
+    (32, 8100, 264, 8),
+    (0, 9000, 264, 8),
+])
+def test_per_oc_sub_blocks_with_plain_divisions(ctx, form, out_f, in_f, group):
+    """Whole sub-blocks of 16 channels in the chain's short form and with plain divisions by turns, as the workgroup's waves hand
+    them to each other.  Some channels' rows of U are 2^50 times larger, diagonal included, which takes them out of the short
+    quotient's range and changes nothing about the size of the updates; some rows' groups have a scale outside that range, which
+    only their workgroup sees."""
+    assert GPTQ_FORMS[(out_f, in_f)] == form
+    rng = np.random.default_rng(out_f + in_f)
+    W = synth.make_weight(out_f, in_f, in_f, heavy_cols=2, heavy_scale=5.0)
+    U, perm, dead = _synthetic_factor(in_f, rng), rng.permutation(in_f), np.zeros(in_f, dtype=bool)
+    for sub in range(0, in_f // 16):
+        if sub % 3 == 1 or sub % 7 == 5:
+            U[16 * sub + rng.integers(16)] *= np.float32(2.0 ** 50)
+    few = rng.choice(out_f, 25, replace=False)
+    W[few[:, None], group * (np.arange(25) % (in_f // group))[:, None] + np.arange(group)] = 0
+    rows = np.unique(np.r_[few, _sampled(rng, out_f, 60)])
+    ref = _per_oc_matches_oracle(ctx, W, U, perm, dead, 3, group, rows,
+                                 lambda s: np.where(s == 1.0, np.float32(2.0 ** -45), s).astype(np.float32))
+    assert np.isfinite(ref["E"]).all() and 0.3 < ((ref["codes"] > 0) & (ref["codes"] < 7)).mean()
 
 
 @pytest.mark.parametrize("dim,group", [(OC, 128), (IC, 128)])
@@ -412,15 +517,16 @@ def test_sweep_in_the_storage_format_random_shapes(ctx, out_f, in_f, dim, bits, 
 
 @pytest.mark.parametrize("out_f,in_f,bits,group", [
     (1000, 272, 3, 16),          # 4 rows per workgroup, whole blocks, in a multiple of 16 only
-    (2041, 200, 4, 40),          # 8 rows, the last workgroup short of one, ragged last sub-block
-    (3000, 129, 2, 43),          # 12 rows, a last block of one channel, odd row pitch
+    (2041, 200, 4, 40),          # 8 rows, the last workgroup short of seven, ragged last sub-block
+    (3000, 129, 2, 43),          # 16 rows, a last block of one channel, odd row pitch
     (4090, 328, 3, 0),           # 16 rows
     (6100, 260, 4, 65),          # 24 rows
     (8100, 520, 3, 130),         # 32 rows
     (8100, 136, 3, 136),         # 32 rows, a last block of eight channels
     (10100, 136, 3, 136),        # a launch per block: 64 rows, the last workgroup short, a ragged last block
     (9000, 264, 3, 24),          # the same, three blocks
-    (7000, 77, 2, 11),           # the same, less than a block, odd row pitch
+    (7000, 77, 2, 11),           # 32 rows, less than a block, odd row pitch
+    (9000, 77, 2, 11),           # the same with a launch for the block
 ])
 def test_per_oc_sweep_rows_per_workgroup(ctx, out_f, in_f, bits, group):
     """The per-OC sweep picks its form and its rows per workgroup by the layer's size; each choice, against the oracle bit for
@@ -474,8 +580,9 @@ def test_per_ic_sweep_of_many_rows(ctx, out_f, in_f, group):
 @pytest.mark.parametrize("out_f,in_f,bits,group,meta16,piece", [
     (16384, 4096, 3, 128, False, 4096),      # 32 rows per workgroup, two rounds of workgroups; pieces of 16 rows
     (1024, 24576, 4, 64, True, 64),          # 4 rows per workgroup; pieces with a launch per block
-    (30000, 512, 4, 32, False, 3000),        # a launch per block, 469 workgroups, the last short; pieces of 12 rows
-    (20011, 700, 2, 28, True, 5003),         # the same with a ragged last block, odd row counts
+    (30000, 512, 4, 32, False, 3000),        # a launch per block, 469 workgroups, the last short; pieces of 16 rows
+    (25011, 700, 2, 28, True, 5003),         # the same with a ragged last block, odd row counts; pieces of 24 rows
+    (20011, 700, 2, 28, True, 5003),         # 32 rows per workgroup, three rounds; pieces of 24 rows
 ])
 def test_per_oc_sweep_does_not_depend_on_its_rows_neighbours(ctx, out_f, in_f, bits, group, meta16, piece):
     """Rows are independent per-OC: a layer swept whole and in pieces of rows, which take other forms, gives the same bits."""

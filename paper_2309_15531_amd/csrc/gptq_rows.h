@@ -157,9 +157,11 @@ __device__ __forceinline__ void chain_slow(float* wrow, const float* ut, float* 
 }
 
 // One item of the update behind a block in vector instructions, for 4, 8 and 12 rows (24 as twice 12): columns c0 + lane + 64 q
-// of RT of the workgroup's rows (Wrows and es point at the first of them), with the errors of the block at k0.  A matrix
-// instruction makes 16 rows of products whether they exist or not, and it and the 16 differences take the pipes for as long
-// as 30 vector instructions: 2618 x 8541 in twelves 6.19 ms so, 6.74 with the products of update_behind.
+// of RT of the workgroup's rows (Wrows and es point at the first of them), with the errors of the block at k0.  The products of
+// update_behind make 16 rows whether they exist or not: 2618 x 8541 in twelves 6.19 ms so, 6.74 with them.  Matrix
+// instructions of 4 rows x 64 columns would fit the rows, but eight of them and their differences take a SIMD 166 cycles for 2048
+// elements, 64 of vector instructions 139 and one of 64 x 32 with its differences 134 (bare loops, two waves per SIMD);
+// whether their fewer reads of the errors would make up for that was not tried.
 // (offsets inside the workgroup's rows fit 32 bits: at most 32 rows of 46340)
 template <int R, int RT, int CPL>
 __device__ __forceinline__ void update_item(float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
@@ -431,7 +433,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
                                                          const int32_t* __restrict__ perm, int64_t out, int64_t in64, int g,
                                                          float qmax, int mfmt, const float* __restrict__ st_scales,
                                                          const uint8_t* __restrict__ st_zeros, uint8_t* __restrict__ Qp) {
-    // items of the update: RT rows x 64 columns on the matrix cores where RT is 16, else RT rows x 64 CPL columns (RT x CPL
+    // items of the update: RT rows x 128 columns on the matrix cores where RT is 16, else RT rows x 64 CPL columns (RT x CPL
     // accumulators; few rows take more columns, so that an LDS read of the errors serves as many products)
     constexpr int RR = pow2_rows<R>(), CL = 64 / RR, CPL = R <= 8 ? 4 : 2, RT = R <= 16 ? R : R / 2;
     // Two waves for the chain: with 16 rows a block's chain takes 23 us so and 31 alone.  Few rows have few columns per lane

@@ -6,9 +6,9 @@
 // becoming +0.  That sign decides at most the sign of a zero channel value, and neither codes, parameters nor dW depend on
 // the latter.  What it saves is operands: one register each of errors and of U makes 1024 or 2048 products, where the product
 // and the difference in vector instructions read an error from LDS for every two to four of them and waited for those
-// reads.  The fp32 matrix instruction does not run beside vector instructions: a bare loop of products and differences makes
-// 3.7e13 elements per second with two waves per SIMD (132 cycles per 2048), as the pair of vector instructions does from
-// registers alone (2.1 cycles each with two waves, 4.3 with one); with one wave it is 2.4e13 against 1.9e13.
+// reads.  The fp32 matrix instruction does not run beside vector instructions: with two waves per SIMD 2048 products alone
+// take 64 cycles, the differences alone 72, both 134, or 3.7e13 elements per second; products and differences in vector instructions
+// from registers alone 139 (2.2 cycles each; 4.3 with one wave), 3.5e13.  With one wave per SIMD it is 2.3e13 against 1.8e13.
 #pragma once
 
 #include "common.h"

@@ -104,7 +104,7 @@ def test_prepare_matches_fp64_factor(ctx, in_f, act_order):
 
 @pytest.mark.parametrize("n", [1, 15, 17, 63, 65, 79, 129, 511, 577, 640, 1025, 1601, 16384, 16400])
 def test_factor_at_block_edges(ctx, n):
-    """The factor at sizes beside its 16- and 64-wide blocks, its 512-wide panels (with and without the side stream) and the
+    """The factor at sizes beside its 16- and 64-wide blocks, its 512-wide panels (with and without jobs in the steps' launches) and the
     LDS row of the permuting copy (n > 16384).  U H' U^T = I for the damped, permuted H'.  U is rounded once to fp32 from
     fp64, so that the residual is at most 2 2^-24 |U|_F |U^-1|_2 <= 2^-23 sqrt(n cond(H')) (fp64 errors are far below)."""
     g = torch.Generator(device="cuda").manual_seed(n)
@@ -133,7 +133,7 @@ def test_factor_at_block_edges(ctx, n):
     (256, 264, IC, 3, 128),
     (192, 384, IC, 4, 64),
     (64, 96, OC, 2, 32),         # less than one block
-    (64, 1280, OC, 3, 128),      # ten blocks: the bulk of each block's trailing update runs on the side stream
+    (64, 1280, OC, 3, 128),      # ten blocks
     (128, 1160, IC, 4, 128),     # the same per-IC, ragged last block
 ])
 def test_sweep_bit_exact_given_u(ctx, out_f, in_f, dim, bits, group):

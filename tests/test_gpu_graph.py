@@ -166,7 +166,7 @@ def test_recorded_products_replay_as_eager(meta16):
     (1024, 520, 1, 64),          # the same, 16 groups
 ])
 def test_recorded_sweeps_replay_as_eager(out_f, in_f, dim, group):
-    """GPTQ sweeps recorded with the work they put on the context's side stream: every replay with a new weight, with eager
+    """GPTQ sweeps recorded, one form with work on the context's side stream: every replay with a new weight, with eager
     sweeps between the replays, gives the eager call's bits."""
     rng = torch.Generator(device="cuda").manual_seed(out_f)
     side = torch.cuda.Stream()
@@ -213,7 +213,7 @@ def test_recorded_sweeps_replay_as_eager(out_f, in_f, dim, group):
 
 @pytest.mark.parametrize("n", [700, 1025, 1700, 4700])       # one stream; the smallest with more; columns updated ahead; not
 def test_recorded_factor_replays_as_eager(n):
-    """The factor recorded with the work it puts on the context's side streams: every replay with a new H gives the eager call's
+    """The factor recorded with the jobs its launches carry: every replay with a new H gives the eager call's
     bits."""
     rng = torch.Generator(device="cuda").manual_seed(n)
     side = torch.cuda.Stream()

@@ -10,7 +10,7 @@
 //          least 2^-80 for that correction to be exact, and 1/d RN (block_reciprocal; NaN outside fastdiv's range, which the
 //          sweeps look for before they start a sub-block).
 // NaN, infinities and quotients above 2^21 fail the first check, which so bounds w, num (s is at most 2^40) and the error.
-// The three values below are kept as unsigned bit patterns (a compare per check would hold them in scalar registers,
+// Two of the values below are kept as unsigned bit patterns (a compare per check would hold them in scalar registers,
 // of which there are too few).
 #pragma once
 
@@ -26,16 +26,17 @@ constexpr int SB = 16;                 // channels per register sub-block of the
 constexpr int PITCH = GB + 4;          // LDS row pitch (floats) of a strip and of the transposed block of U
 
 struct Check {
-    uint32_t tie = 0u, off = 0u, num = 0xffffffffu;
+    uint32_t tie = 0u, num = 0xffffffffu;
+    bool same = true;
     __device__ __forceinline__ void code(float quo, float near) {
         tie = max(tie, __float_as_uint(fmaf(fabsf(quo), 0x1p-22f, fabsf(quo - near))));
     }
     __device__ __forceinline__ void error(float n, float d, float y, float e) {
-        off |= __float_as_uint(fastdiv_corrected(n, d, y, e)) ^ __float_as_uint(e);
+        same = same && fastdiv_corrected(n, d, y, e) == e;   // (false for a NaN, as without a reciprocal)
         num = min(num, (__float_as_uint(n) << 1) - 1u);       // zero wraps to the top
     }
     __device__ __forceinline__ bool fine() const {
-        return tie <= 0x3F000000u && off == 0u && num >= (0x17800000u << 1) - 1u;      // 0.5, 2^-80
+        return tie <= 0x3F000000u && same && num >= (0x17800000u << 1) - 1u;      // 0.5, 2^-80
     }
 };
 

@@ -1,24 +1,24 @@
 // The per-OC GPTQ sweep in one launch (gfx950).  Included by gptq.hip.
 //
 // With static groups (per-OC) the rows of W do not depend on each other, so a workgroup can take its R rows through
-// every channel without meeting another workgroup.  Eight waves:
-//   * wave 0 walks the 128 channels of block b: the chain of rounding decisions, latency bound; with 12 rows and more a
-//     second wave takes the block's columns behind the next 16;
-//   * meanwhile the others apply the errors of block b - 1 to the columns behind block b (a rounded product and a rounded
-//     difference per element and channel, which is the definition's sequence, so no fma); wave 0 joins them when its
-//     chain is done;
-//   * then all waves apply block b's errors to block b + 1's columns, on their way from memory into LDS.
-// Two barriers per block, two counters between the chain's waves, and nothing else to wait for.  The launches per block and the two streams this replaces
-// left the chip idle around every short launch.  The whole sweep of a 4096 x 4096 layer, 3 bits: 3.3 ms then, 2.1 ms
-// in one launch with products and differences in vector instructions, 1.7 ms with the products behind the block on the
-// matrix cores (16 and 32 rows per workgroup) and two waves at the chain; 64 to 1024 rows of that width 0.9 ms (the chain alone).
+// every channel without meeting another workgroup.  While block b of 128 channels is walked, its eight waves do what they can of
+// everything else:
+//   * a chain wave per 16 rows walks the block: the rounding decisions, latency bound; helpers bring the block's later columns up to date
+//     with each 16 channels' errors (chain_block, help_block);
+//   * strips: the columns of block b + 1 get the errors of block b - 1 and then, as they come, those of block b, so that they are
+//     finished as soon as the chain is; one more wave puts block b + 1's corner of U and its parameters where block b's have served;
+//   * pieces of the columns behind block b + 1 get the errors of block b - 1 (a rounded product and a rounded
+//     difference per element and channel, which is the definition's sequence, so no fma); everyone joins whose own work is done.
+// One barrier per block; in between counters in LDS that only grow.  What bounds a block: its chain (10.4 us: about 600 instructions
+// of one wave per 16 channels at 4 to 5 cycles each) where few columns are left or rows are few, else the update's arithmetic.  Whole calls, us,
+// before (the step from block to block, 11 to 19 us, behind the chain, which took 12 to 23) and so: 512 x 1024 196 / 111, 256 x 4096 914 / 687,
+// 2048 x 2048 507 / 439, 1000 x 272 65 / 38, 4096 x 4096 1758 / 1746 (bound by the update).
 //
 // Rows per workgroup: few enough that the chip's 256 compute units all have a workgroup (16 at 4096 rows), so that
 // the update is spread over the whole chip; the chain takes much the same time for 4 rows as for 64.  rows_per_group
 // picks R from the sizes.
 //
-// Registers: with 32 rows 26 vector registers do not fit and live in scratch, with 8 rows 12, otherwise none.  They are values
-// that hold over the block loop; none is read inside the sixteen channels' chain or the updates' product loops.
+// Registers: with 32 rows 8 vector registers do not fit and live in scratch, otherwise none.
 //
 // Order of the updates of one element: blocks in order, channels inside a block in order, whichever wave applies
 // them; every update is one product and one difference.  Hence the same bits as a plain channel-by-channel loop.
@@ -39,10 +39,18 @@ namespace rows {
 using namespace chain_ns;
 
 constexpr int WAVES = 8;
-constexpr int SECOND = 4;               // the wave beside wave 0's chain, on the same SIMD
+constexpr int STRIP = 32;               // columns of the next block that a wave brings up to date
 
+constexpr int PIECES_AT = 1 + GB / STRIP;                        // the first piece of the update in a block's list
+
+// A workgroup's waves: one of the chain for up to 16 rows, then the chain's helpers, then those that are free.
 template <int R>
-constexpr int pow2_rows() { return R <= 4 ? 4 : R <= 8 ? 8 : R <= 16 ? 16 : 32; }
+constexpr int CHAINS = R <= 16 ? 1 : 2;
+template <int R>
+constexpr int HELPERS = R == 12 || R == 16 ? 2 : 1;             // per chain
+template <int R>
+constexpr int CR = R / CHAINS<R>;                               // rows of a chain
+constexpr int pow2_rows(int r) { return r <= 4 ? 4 : r <= 8 ? 8 : 16; }
 
 // Errors in LDS: [row][channel] where the matrix cores make the products (four channels of a row in one read), else
 // [channel][row] (four rows of a channel).  Where channel c of row r is, and the words of a buffer.
@@ -56,88 +64,54 @@ constexpr int E_WORDS = BY_ROW<R> ? R * PITCH : R * GB;
 // LDS of one workgroup (dynamic)
 template <int R>
 struct Lds {
-    float ut[GB][PITCH];               // ut[c][k] = U[i1 + k][i1 + c], the block's corner, transposed
+    float ut[GB][PITCH];               // ut[c][k] = U[i1 + k][i1 + c] for k < c, else 0: the block's corner, transposed
     float w[R][PITCH];                 // the block's columns of the rows, as the chain finds them
     float e[2][E_WORDS<R>];            // errors (e_at) of this block and the last
     float2 sc[GB][R];                  // static scale of (channel, row) and its reciprocal (NaN: outside fastdiv's range)
-    float rd[GB];                      // 1 / U_ii of the block's channels (NaN likewise)
+    float2 dg[GB];                     // U_ii of the block's channels and its reciprocal (NaN likewise)
     int cg[2][GB];                     // static group of the channels of this block and the next
     uint8_t zp[GB][R];                 // static zero-point
-    int next;                          // next item of the update behind the block
-    int posted, done;                  // sub-blocks whose errors are in `e`; whose errors the second wave has applied
+    int next[2];                       // next item of this block's list, and of the next one's
+    int posted[CHAINS<R>], done[CHAINS<R> * HELPERS<R>];        // how far chains and helpers are (mark)
 };
 
-// A whole sub-block of 16 channels for one row per lane, everything in registers, with the short quotients
-// (gptq_chain.h).  Returns false in a lane whose checks failed: nothing of the result is then to be used.  e: the
-// errors; qpk: the codes.
-template <int R>
-__device__ __forceinline__ bool chain16(const float* wrow, const float* ut, const float* rd, const float2* sc, const uint8_t* zp,
-                                        float qmax, float (&e)[SB], uint32_t (&qpk)[SB / 4]) {
-    float w[SB], s[SB], y[SB], z[SB];
-#pragma unroll
-    for (int c = 0; c < SB; c += 4) {
-        const float4 t = *reinterpret_cast<const float4*>(wrow + c);
-        w[c] = t.x; w[c + 1] = t.y; w[c + 2] = t.z; w[c + 3] = t.w;
+// Progress within a block, always growing: 16 blk + n.  A chain has posted n sub-blocks' errors; a helper has brought the
+// sub-block n behind the first up to date with all before the one in front of it, and is through with the block at DONE.
+constexpr int DONE = 15;
+__device__ __forceinline__ constexpr int mark(int blk, int n) { return 16 * blk + n; }
+
+// One wave tells others of its workgroup how far it is (everything it has put into LDS included), and they wait for that.
+// Every wait of gq_rows ends: a chain waits only for what its helpers do with errors posted before, a helper only for its chain's
+// next sub-block, and a strip for both, which start with the block, each in a wave of its own, and wait for no strip.
+__device__ __forceinline__ void tell(int* count, int n) {
+    if ((threadIdx.x & 63) == 0) __hip_atomic_store(count, n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void wait_for(const int* count, int n) {
+    while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(count, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) < n) {
     }
-#pragma unroll
-    for (int c = 0; c < SB; ++c) {
-        const float2 t = sc[c * R];
-        s[c] = t.x;
-        y[c] = t.y;
-        z[c] = static_cast<float>(zp[c * R]);
-    }
-#pragma unroll
-    for (int c = 0; c < SB / 4; ++c) qpk[c] = 0u;
-    Check check;
-    // The corner of U (row cc of `ut` holds U[c][cc] for c <= cc) and the reciprocals of its diagonal, four columns at
-    // a time and two channels ahead of their use: all of it at once would not fit the registers.
-    float ub[SB][SB], yd[SB];
-    auto corner = [&](auto part_tag) {
-        constexpr int C0 = decltype(part_tag)::value * 4;
-#pragma unroll
-        for (int cc = 0; cc < SB; ++cc) {
-            if (cc >= C0) {
-                const float4 t = *reinterpret_cast<const float4*>(ut + cc * PITCH + C0);
-                ub[cc][C0] = t.x; ub[cc][C0 + 1] = t.y; ub[cc][C0 + 2] = t.z; ub[cc][C0 + 3] = t.w;
-            }
-        }
-        const float4 t = *reinterpret_cast<const float4*>(rd + C0);
-        yd[C0] = t.x; yd[C0 + 1] = t.y; yd[C0 + 2] = t.z; yd[C0 + 3] = t.w;
-    };
-    corner(std::integral_constant<int, 0>{});
-#pragma unroll
-    for (int c = 0; c < SB; ++c) {
-        if ((c & 3) == 2 && c < 12) {
-            asm volatile("" ::: "memory");                    // keeps these reads from moving up
-            if (c == 2) corner(std::integral_constant<int, 1>{});
-            if (c == 6) corner(std::integral_constant<int, 2>{});
-            if (c == 10) corner(std::integral_constant<int, 3>{});
-        }
-        const float d = ub[c][c];
-        // k = code - zero: clamping before or after the zero point is added is the same on integers
-        const float quo = w[c] * y[c], near = rintf(quo);
-        const float k = __builtin_amdgcn_fmed3f(near, -z[c], qmax - z[c]);
-        const float num = w[c] - s[c] * k;
-        e[c] = fastdiv(num, d, yd[c]);
-#pragma unroll
-        for (int cc = 0; cc < SB; ++cc) {
-            if (cc > c) {
-                const float upd = e[c] * ub[cc][c];
-                w[cc] = w[cc] - upd;
-            }
-        }
-        qpk[c / 4] = __builtin_amdgcn_cvt_pk_u8_f32(k + z[c], c & 3, qpk[c / 4]);
-        check.code(quo, near);
-        check.error(num, d, yd[c], e[c]);
-    }
-    return check.fine();
+}
+
+// lane i of each four
+template <int I>
+__device__ __forceinline__ float of_four(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x55 * I, 0xf, 0xf, true));
+}
+// the value is worked out here, in the order of these calls
+__device__ __forceinline__ void here(float& v) { asm volatile("" : "+v"(v)); }
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled(F f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F f) {
+    unrolled(f, std::make_integer_sequence<int, N>{});
 }
 
 // The same channel by channel in LDS with plain divisions: the ragged end of a row, and values outside the fast
 // quotient's range.  n <= 16 channels; `par(c)` gives channel c's scale and zero-point, `put(c, code)` takes its code.
 // Lanes that hold the same row do the same reads and writes in the same instruction.
 template <int R, typename Par, typename Put>
-__device__ __forceinline__ void chain_slow(float* wrow, const float* ut, float* es_col, int n, float qmax, Par par, Put put) {
+__device__ __forceinline__ void chain_slow(float* wrow, const float* ut, const float2* dg, float* es_col, int n, float qmax, Par par, Put put) {
 #pragma unroll 1
     for (int c = 0; c < n; ++c) {
         float sc, zp;
@@ -146,7 +120,7 @@ __device__ __forceinline__ void chain_slow(float* wrow, const float* ut, float* 
         float q = rintf(w / sc) + zp;
         q = fminf(fmaxf(q, 0.0f), qmax);
         put(c, static_cast<uint8_t>(q));
-        const float e = (w - sc * (q - zp)) / ut[c * PITCH + c];
+        const float e = (w - sc * (q - zp)) / dg[c].x;
         es_col[e_at<R>(c, 0)] = e;
 #pragma unroll 1
         for (int cc = c + 1; cc < n; ++cc) {
@@ -166,28 +140,20 @@ __device__ __forceinline__ void chain_slow(float* wrow, const float* ut, float* 
 template <int R, int RT, int CPL>
 __device__ __forceinline__ void update_item(float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
                                             int in_, int64_t k0, int c0) {
-    constexpr int KB = 8;                                      // channels per step: their U entries travel one step ahead
-    const int lane = threadIdx.x & 63, in = fresh_uniform(in_);
-    uint32_t col[CPL];
+    // Channels per step: their entries of U travel one step ahead.  From memory that is a microsecond, which 64 of them in flight cover
+    // (eight channels per step: 512 x 1024 in fours, 16 us per item).
+    constexpr int KB = 64 / CPL;
+    const int lane = fresh(threadIdx.x & 63), in = fresh_uniform(in_), c = c0 + CPL * lane;
+    const uint32_t pitch = 4u * static_cast<uint32_t>(in), col = 4u * static_cast<uint32_t>(min(c, in - 1));
+    const update::Matrix W(Wrows, int64_t(n_rows) * in), Urows(U + k0 * in, int64_t(in - k0) * in);
+    float v[RT][CPL], u[2][KB][CPL];
+    auto fetch = [&](int b, int k) {
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) col[q] = static_cast<uint32_t>(min(c0 + lane + 64 * q, in - 1));   // past the end: read, never stored
-    float v[RT][CPL];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) {
-        const uint32_t at = static_cast<uint32_t>(min(r, n_rows - 1)) * static_cast<uint32_t>(in);
-#pragma unroll
-        for (int q = 0; q < CPL; ++q) v[r][q] = Wrows[at + col[q]];
-    }
-    float u[2][KB][CPL];
-    const float* urow = U + k0 * in;                           // the row to fetch next
-    auto fetch = [&](int b) {
-#pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) u[b][kk][q] = urow[col[q]];
-            urow += in;
-        }
+        for (int kk = 0; kk < KB; ++kk) Urows.load(u[b][kk], col, (k + kk) * pitch);
     };
+#pragma unroll
+    for (int r = 0; r < RT; ++r) W.load(v[r], col, min(r, n_rows - 1) * pitch);      // past the end: read, never stored
+    fetch(0, 0);
     // a channel's errors are read one channel ahead of their use, and no further (registers)
     float4 ev[2][RT / 4];
     auto errors = [&](int b, int k) {
@@ -212,21 +178,29 @@ __device__ __forceinline__ void update_item(float* __restrict__ Wrows, const flo
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) here(v[r][q]);
     };
     errors(0, 0);
-    fetch(0);
 #pragma unroll 1
     for (int k = 0; k < GB; k += 2 * KB) {
-        fetch(1);
+        fetch(1, k + KB);
         step(0, k);
-        if (k + 2 * KB < GB) fetch(0);
+        if (k + 2 * KB < GB) fetch(0, k + 2 * KB);
         step(1, k + KB);
     }
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
+        if (r >= n_rows) break;
+        if (c + CPL <= in) {
+            W.store(v[r], col, r * pitch);
+        } else {
 #pragma unroll
-        for (int q = 0; q < CPL; ++q)
-            if (r < n_rows && c0 + lane + 64 * q < in) Wrows[static_cast<uint32_t>(r) * static_cast<uint32_t>(in) + col[q]] = v[r][q];
+            for (int q = 0; q < CPL; ++q)
+                if (c + q < in) W.store(v[r][q], col + 4 * q, r * pitch);
+        }
     }
 }
 
@@ -236,23 +210,17 @@ __device__ __forceinline__ void update_item(float* __restrict__ Wrows, const flo
 // their way while this one is worked on; and an instruction beside the differences costs a wave as much as one of them, so
 // two products share a channel's errors and row of U, and four channels a read of the errors (64 columns and a read per
 // channel: 12 us per pair of items, 90 us for the 3712 columns of the third block of 4096 x 4096, 16 rows; 83 so).
-template <int R>
-__device__ __forceinline__ void update_behind(float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
-                                              int in_, int64_t k0, int c_first, int* next) {
+template <int R, typename Take>
+__device__ __forceinline__ int update_behind(float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
+                                             int in_, int64_t k0, int c_first, int item, int n_items, Take take) {
     constexpr int RT = 16, COLS = 128, KB = 8;                 // KB channels per step: their U entries travel one step ahead
     const int lane = fresh(threadIdx.x & 63), in = fresh_uniform(in_);
     const uint32_t pitch = 4u * static_cast<uint32_t>(in);
     const update::Matrix W(Wrows), Urows(U + k0 * in);
-    const int halves = n_rows > RT ? 2 : 1, n_items = (in - c_first + COLS - 1) / COLS * halves;
-    auto take = [&] {
-        int item = 0;
-        if (lane == 0) item = atomicAdd(next, 1);
-        return __builtin_amdgcn_readfirstlane(item);
-    };
-    int item = take();
-    if (item >= n_items) return;
-    auto row0_of = [&](int item) { return halves == 1 ? 0 : (item & 1) * RT; };
-    auto col0_of = [&](int item) { return c_first + (halves == 1 ? item : item >> 1) * COLS; };
+    constexpr int HALVES = R / RT;
+    // (the second half of a workgroup without so many rows: read and not stored)
+    auto row0_of = [&](int item) { return HALVES == 1 ? 0 : (item & 1) * RT; };
+    auto col0_of = [&](int item) { return c_first + (HALVES == 1 ? item : item >> 1) * COLS; };
     auto u_offset = [&](int item, int q) { return 4u * static_cast<uint32_t>(min(col0_of(item) + 64 * q + lane, in - 1)); };
     auto e_first = [&](int item) { return es + e_at<R>(0, row0_of(item) + (lane & 15)); };
     // past the last row or column: read, never stored
@@ -333,7 +301,7 @@ __device__ __forceinline__ void update_behind(float* __restrict__ Wrows, const f
                             W.store(v[b >> 2][4 * (b & 3) + r], first, (rt + r) * pitch + 4 * (c0 + 16 * b));
             }
         }
-        if (!more) break;
+        if (!more) return taken;
         item = then;
         ucol[0] = ucol_next[0];
         ucol[1] = ucol_next[1];
@@ -343,90 +311,363 @@ __device__ __forceinline__ void update_behind(float* __restrict__ Wrows, const f
     }
 }
 
-// Columns of the next block (starting at c1, nbw of them) into the strip, with the errors of the block at k0 applied.
-// Wave w takes columns 16 w .. 16 w + 15, lane groups of 16 take R / 4 rows each.
+// The chain of a block, by one wave: CR rows (from r0 on) through its channels, 16 at a time.  Four lanes share a row: lane j holds the
+// columns 4 t + j of a sub-block, t = 0 .. 3, and of the next one.  At channel 4 t + i all four work on their own column t, of
+// which lane i's is the channel in turn: its error goes to the four by a DPP operand, and onto the columns that are left (`ut` is 0 for
+// channels at and behind a column, which leaves a column that has had its turn as it is).  So behind channel 4 t + 3
+// every lane holds its own column's decision, and the checks (gptq_chain.h) and codes cost a fourth of what they would for
+// each channel in each lane.  The next sub-block's columns get the errors four channels late, which leaves the helpers time.
+// With a lane per row, and sixteen columns
+// in each, a channel took 37 instructions beside what followed the sub-block; so 26 with the next sub-block's columns.
 template <int R>
-__device__ __forceinline__ void update_next(const float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
-                                            int in_, int64_t k0, int c1, int nbw, Lds<R>& lds) {
-    constexpr int RQ = R / 4, KB = 16;
-    const int tid = fresh(threadIdx.x), lane = tid & 63, wave = tid >> 6, in = fresh_uniform(in_);
-    const int c = 16 * wave + (lane & 15), rq = (lane >> 4) * RQ;
-    const uint32_t col = static_cast<uint32_t>(c1 + min(c, nbw - 1));
-    float v[RQ], u[2][KB];
-    const float* urow = U + k0 * in;
-    auto fetch = [&](int b) {
-#pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-            u[b][kk] = urow[col];
-            urow += in;
-        }
+__device__ __forceinline__ void chain_block(Lds<R>& lds, int ch, int blk, float* es, int n_rows, int nbw, float qmax,
+                                            uint8_t* __restrict__ Qrows, int in) {
+    constexpr int RR = pow2_rows(CR<R>);
+    const int lane = fresh(threadIdx.x & 63), j = lane & 3, row_l = (lane >> 2) & (RR - 1);
+    const bool row_in = row_l < CR<R>, first = lane < 4 * RR;               // (fewer than 16 rows: some lanes repeat others)
+    const int crow = ch * CR<R> + (row_in ? row_l : 0);
+    const bool row_ok = row_in && crow < n_rows, put_ok = row_ok && first;
+    float* wrow = &lds.w[crow][0];
+    uint8_t* q_row = Qrows + static_cast<uint32_t>(crow) * static_cast<uint32_t>(in);
+    const bool words = (reinterpret_cast<uintptr_t>(Qrows) & 3u) == 0 && (in & 3) == 0;
+    const int n_sub = (nbw + SB - 1) / SB;
+
+    float w[4], wn[4], s[4], y[4], z[4], zq[4], d[4], yd[4], u[4][SB], un[4][SB];
+    auto load_u = [&](int s0, int t, int q) {                // channels 4 q .. 4 q + 3 of column t
+        const float4 v = *reinterpret_cast<const float4*>(&lds.ut[s0 + 4 * t + j][s0 + 4 * q]);
+        u[t][4 * q] = v.x; u[t][4 * q + 1] = v.y; u[t][4 * q + 2] = v.z; u[t][4 * q + 3] = v.w;
     };
-    auto step = [&](int b, int k) {
-#pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-#pragma unroll
-            for (int r = 0; r < RQ; ++r) {
-                const float upd = es[e_at<R>(k + kk, rq + r)] * u[b][kk];
-                v[r] = v[r] - upd;
-            }
-            if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
+    auto load_par = [&](int s0, int t) {
+        const int c = s0 + 4 * t + j;
+        const float2 a = lds.sc[c][crow], b = lds.dg[c];
+        s[t] = a.x; y[t] = a.y; d[t] = b.x; yd[t] = b.y;
+        z[t] = static_cast<float>(lds.zp[c][crow]);
+        zq[t] = qmax - z[t];
     };
-    fetch(0);
 #pragma unroll
-    for (int r = 0; r < RQ; ++r)
-        v[r] = Wrows[static_cast<uint32_t>(min(rq + r, n_rows - 1)) * static_cast<uint32_t>(in) + col];
-#pragma unroll 1
-    for (int k = 0; k < GB; k += 2 * KB) {
-        fetch(1);
-        step(0, k);
-        if (k + 2 * KB < GB) fetch(0);
-        step(1, k + KB);
+    for (int t = 0; t < 4; ++t) {
+        load_par(0, t);
+#pragma unroll
+        for (int q = 0; q <= t; ++q) load_u(0, t, q);
+        w[t] = wrow[4 * t + j];
     }
+#pragma unroll 1
+    for (int sub = 0; sub < n_sub; ++sub) {
+        const int s0 = sub * SB, sbw = min(nbw - s0, SB), s1 = min(s0 + SB, GB - SB);      // (behind the last: read and not used)
+        const bool more = sub + 1 < n_sub;
+        bool fine = sbw == SB;
+        uint32_t pk = 0u;
+        int ready[HELPERS<R>];
 #pragma unroll
-    for (int r = 0; r < RQ; ++r) lds.w[rq + r][c] = v[r];
+        for (int h = 0; h < HELPERS<R>; ++h)
+            ready[h] = __hip_atomic_load(&lds.done[ch * HELPERS<R> + h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        asm volatile("" ::: "memory");                       // LDS serves a wave's reads in order: the counts first
+#pragma unroll
+        for (int t = 0; t < 4; ++t) wn[t] = wrow[s1 + 4 * t + j];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 v = *reinterpret_cast<const float4*>(&lds.ut[s1 + 4 * t + j][s0 + 4 * q]);
+                un[t][4 * q] = v.x; un[t][4 * q + 1] = v.y; un[t][4 * q + 2] = v.z; un[t][4 * q + 3] = v.w;
+            }
+        // One wave's instruction that needs the one before it waits 9 cycles, any other 4 to 5: so each step of a channel's decision
+        // is followed by its share of the work that waits for nothing: the last channel's error onto the later columns of the sub-block,
+        // the one four channels back onto the next sub-block's, the last four's checks.
+        float eb[SB], late_mul[3], next_mul[4];
+        float quo[4], near[4], k[4], num[4], e[4];            // as the columns' decisions left them
+        Check check;
+        auto besides = [&](auto c_tag, auto n_tag) {
+            constexpr int C = decltype(c_tag)::value, N = decltype(n_tag)::value, T = C / 4, I = C % 4;
+            if constexpr (N < 3) {                           // columns behind the one in turn: T + 1 .. 3
+                if constexpr (C > 0 && T + N < 3) here(late_mul[N] = eb[C - 1] * u[T + 1 + N][C - 1]);
+            } else if constexpr (N < 6) {
+                if constexpr (C > 0 && T + N < 6) here(w[T + N - 2] = w[T + N - 2] - late_mul[N - 3]);
+            } else if constexpr (N < 10) {
+                if constexpr (T > 0) here(next_mul[N - 6] = eb[C - 4] * un[N - 6][C - 4]);
+            } else if constexpr (N < 14) {
+                if constexpr (T > 0) here(wn[N - 10] = wn[N - 10] - next_mul[N - 10]);
+            } else {                                         // the four columns' decisions, each in its lane
+                if constexpr (T > 0 && I == 0) {
+                    if (row_in) es[e_at<R>(s0 + C - 4 + j, crow)] = e[T - 1];
+                }
+                if constexpr (T > 0 && I == 1) {
+                    pk = __builtin_amdgcn_cvt_pk_u8_f32(k[T - 1] + z[T - 1], T - 1, pk);
+                    check.code(quo[T - 1], near[T - 1]);
+                }
+                if constexpr (T > 0 && I == 2) check.error(num[T - 1], d[T - 1], yd[T - 1], e[T - 1]);
+                if constexpr (T > 0 && I == 3) {
+                    // the next sub-block's entries take the place of those that have served
+                    load_par(s1, T - 1);
+#pragma unroll
+                    for (int t = T - 1; t < 4; ++t) load_u(s1, t, T - 1);
+                }
+            }
+        };
+        unrolled<SB>([&](auto c_tag) {
+            constexpr int C = decltype(c_tag)::value, T = C / 4;
+            if constexpr (C == 4) {
+                if (sub > 0 && more) {
+                    bool late = false;
+#pragma unroll
+                    for (int h = 0; h < HELPERS<R>; ++h) late |= __builtin_amdgcn_readfirstlane(ready[h]) < mark(blk, sub);
+                    if (late) {
+#pragma unroll
+                        for (int h = 0; h < HELPERS<R>; ++h) wait_for(&lds.done[ch * HELPERS<R> + h], mark(blk, sub));
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) wn[t] = wrow[s1 + 4 * t + j];
+                    }
+                }
+            }
+#define GQ_ASIDE(N) besides(c_tag, std::integral_constant<int, N>{})
+            if constexpr (C > 0) {
+                constexpr int I1 = (C - 1) % 4, T1 = (C - 1) / 4;
+                float upd = of_four<I1>(e[T1]) * u[T][C - 1];
+                here(upd);
+                GQ_ASIDE(6);
+                here(w[T] = w[T] - upd);
+                // (two instructions after the error: what a DPP operand needs)
+                asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[%2,%2,%2,%2] row_mask:0xf bank_mask:0xf" : "=v"(eb[C - 1]) : "v"(e[T1]), "n"(I1));
+            }
+            here(quo[T] = w[T] * y[T]);
+            GQ_ASIDE(7);
+            here(near[T] = rintf(quo[T]));
+            GQ_ASIDE(8);
+            GQ_ASIDE(0);
+            // k = code - zero: clamping before or after the zero point is added is the same on integers
+            here(k[T] = __builtin_amdgcn_fmed3f(near[T], -z[T], zq[T]));
+            GQ_ASIDE(9);
+            GQ_ASIDE(1);
+            float sk = s[T] * k[T];
+            here(sk);
+            GQ_ASIDE(10);
+            GQ_ASIDE(2);
+            here(num[T] = w[T] - sk);
+            GQ_ASIDE(11);
+            GQ_ASIDE(3);
+            float t0 = num[T] * yd[T];                        // fastdiv's steps
+            here(t0);
+            GQ_ASIDE(12);
+            GQ_ASIDE(4);
+            float r0 = fmaf(-d[T], t0, num[T]);
+            here(r0);
+            GQ_ASIDE(13);
+            GQ_ASIDE(5);
+            here(e[T] = fmaf(r0, yd[T], t0));
+            GQ_ASIDE(14);
+#undef GQ_ASIDE
+        });
+        eb[SB - 1] = of_four<3>(e[3]);
+        if (row_in) es[e_at<R>(s0 + SB - 4 + j, crow)] = e[3];
+        pk = __builtin_amdgcn_cvt_pk_u8_f32(k[3] + z[3], 3, pk);
+        check.code(quo[3], near[3]);
+        check.error(num[3], d[3], yd[3], e[3]);
+        load_par(s1, 3);
+        load_u(s1, 3, 3);
+        auto onto_next = [&](int c) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float upd = eb[c] * un[t][c];
+                wn[t] = wn[t] - upd;
+            }
+        };
+        fine = fine && check.fine();
+        if (!__any(row_ok && !fine)) {
+            if (more) tell(&lds.posted[ch], mark(blk, sub + 1));
+#pragma unroll
+            for (int c = SB - 4; c < SB; ++c) onto_next(c);
+            // codes in visiting order: lane j has those of the channels 4 t + j and stores 4 j .. 4 j + 3
+            if (words) {
+                uint32_t q = 0u;
+                unrolled<4>([&](auto i_tag) {
+                    constexpr int I = decltype(i_tag)::value;
+                    const uint32_t v = __float_as_uint(of_four<I>(__uint_as_float(pk)));
+                    q |= ((v >> (8 * j)) & 0xffu) << (8 * I);
+                });
+                if (put_ok) *reinterpret_cast<uint32_t*>(q_row + s0 + 4 * j) = q;
+            } else if (put_ok) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) q_row[s0 + 4 * t + j] = static_cast<uint8_t>(pk >> (8 * t));
+            }
+        } else {
+            // A channel at a time; the strip holds this sub-block's columns as they were.  (Lanes of a row do the same.)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (row_in) {
+                chain_slow<R>(wrow + s0, &lds.ut[s0][s0], &lds.dg[s0], es + e_at<R>(s0, crow), sbw, qmax,
+                              [&](int c, float& a, float& b) { a = lds.sc[s0 + c][crow].x; b = static_cast<float>(lds.zp[s0 + c][crow]); },
+                              [&](int c, uint8_t q) { if (put_ok && j == 0) q_row[s0 + c] = q; });
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (more) {
+                tell(&lds.posted[ch], mark(blk, sub + 1));
+                if (sub > 0)
+#pragma unroll
+                    for (int h = 0; h < HELPERS<R>; ++h) wait_for(&lds.done[ch * HELPERS<R> + h], mark(blk, sub));
+#pragma unroll
+                for (int t = 0; t < 4; ++t) wn[t] = wrow[s1 + 4 * t + j];
+#pragma unroll
+                for (int c = 0; c < SB; ++c) {
+                    eb[c] = es[e_at<R>(s0 + c, crow)];
+                    onto_next(c);
+                }
+            }
+        }
+        if (more) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                wrow[s1 + 4 * t + j] = wn[t];                // (for chain_slow)
+                w[t] = wn[t];
+            }
+        }
+    }
+    tell(&lds.posted[ch], mark(blk, n_sub));
 }
 
-// The 16 errors e of the sub-block at s0 onto the columns c0, c0 + CL .. of a row of the strip, up to c_end, NC at a time: a
-// column's sixteen differences wait for each other.
-template <int R, int CL>
-__device__ __forceinline__ void apply16(const Lds<R>& lds, float* wrow, const float (&e)[SB], int s0, int c0, int c_end) {
-    constexpr int NC = 2;
-    for (int c = c0; c < c_end; c += NC * CL) {
-        float v[NC], u[NC][SB];
+// A chain's helper: a sub-block's errors onto the block's columns behind the next one, those behind that first.
+template <int R>
+__device__ __forceinline__ void help_block(Lds<R>& lds, int helper, int blk, const float* es, int nbw) {
+    constexpr int RR = pow2_rows(CR<R>), CL = 64 / RR, NC = SB / (CL * HELPERS<R>);      // NC columns of a sub-block per lane
+    const int lane = fresh(threadIdx.x & 63), ch = helper / HELPERS<R>, row_l = lane & (RR - 1);
+    const int crow = ch * CR<R> + (row_l < CR<R> ? row_l : 0);
+    const int cl = (lane / RR) + CL * NC * (helper % HELPERS<R>);
+    float* wrow = &lds.w[crow][0];
+    const int n_sub = (nbw + SB - 1) / SB;
+#pragma unroll 1
+    for (int sub = 0; sub + 2 < n_sub; ++sub) {
+        const int s0 = sub * SB;
+        wait_for(&lds.posted[ch], mark(blk, sub + 1));
+        float e[SB];
 #pragma unroll
-        for (int t = 0; t < NC; ++t) {
-            const int ct = min(c + t * CL, GB - 1);              // past the block: read, not stored
-            v[t] = wrow[ct];
-#pragma unroll
-            for (int k = 0; k < SB; k += 4) {
-                const float4 q = *reinterpret_cast<const float4*>(&lds.ut[ct][s0 + k]);
-                u[t][k] = q.x; u[t][k + 1] = q.y; u[t][k + 2] = q.z; u[t][k + 3] = q.w;
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < SB; ++k)
+        for (int k = 0; k < SB; ++k) e[k] = es[e_at<R>(s0 + k, crow)];
+#pragma unroll 1
+        for (int next = sub + 2; next < n_sub; ++next) {
+            float v[NC], u[NC][SB];
 #pragma unroll
             for (int t = 0; t < NC; ++t) {
-                const float upd = e[k] * u[t][k];
-                v[t] = v[t] - upd;
+                const int c = next * SB + cl + CL * t;
+                v[t] = wrow[c];
+#pragma unroll
+                for (int k = 0; k < SB; k += 4) {
+                    const float4 q = *reinterpret_cast<const float4*>(&lds.ut[c][s0 + k]);
+                    u[t][k] = q.x; u[t][k + 1] = q.y; u[t][k + 2] = q.z; u[t][k + 3] = q.w;
+                }
             }
 #pragma unroll
-        for (int t = 0; t < NC; ++t)
-            if (c + t * CL < c_end) wrow[c + t * CL] = v[t];
+            for (int k = 0; k < SB; ++k)
+#pragma unroll
+                for (int t = 0; t < NC; ++t) {
+                    const float upd = e[k] * u[t][k];
+                    v[t] = v[t] - upd;
+                }
+#pragma unroll
+            for (int t = 0; t < NC; ++t) wrow[next * SB + cl + CL * t] = v[t];
+            if (next == sub + 2) tell(&lds.done[helper], mark(blk, sub + 1));
+        }
     }
+    tell(&lds.done[helper], mark(blk, DONE));
 }
 
-// One wave tells another of its workgroup how far it is (everything it has put into LDS included), and waits for that.  Every
-// wait of gq_rows ends: wave 0 waits only for what the second wave does with errors posted before, and the second wave
-// only for wave 0's next sub-block.
-__device__ __forceinline__ void tell(int* count, int n) {
-    if ((threadIdx.x & 63) == 0) __hip_atomic_store(count, n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ void wait_for(const int* count, int n) {
-    while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(count, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) < n)
-        __builtin_amdgcn_s_sleep(1);
-}
+// What a sub-block of the next block (at i2, whose groups are in cg) needs of U and the parameters: fetched ahead by one wave, put into
+// LDS where this block no longer needs its own.
+template <int R>
+struct Stage {
+    static constexpr int NP = SB * R / 64;                     // parameters per lane
+    float u[2][SB], ps[NP], pz[NP], d;                         // u[q][k]: column lane + 64 q
+
+    __device__ __forceinline__ void fetch(const float* __restrict__ U, int in, int i2, int nbw, int sub, const int* cg, int64_t row0,
+                                          int n_rows, int n_cg, int mfmt, const float* __restrict__ st_scales,
+                                          const uint8_t* __restrict__ st_zeros) {
+        const int lane = fresh(threadIdx.x & 63), s0 = sub * SB;
+        const uint32_t pitch = 4u * static_cast<uint32_t>(in);
+        const update::Matrix corner(U + int64_t(i2) * in + i2);
+        // (past the end of the last block: read again, and met by no error)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const uint32_t col = 4u * static_cast<uint32_t>(min(lane + 64 * q, nbw - 1));
+#pragma unroll
+            for (int k = 0; k < SB; ++k) u[q][k] = corner.load(col, static_cast<uint32_t>(min(s0 + k, nbw - 1)) * pitch);
+        }
+        d = corner.load(static_cast<uint32_t>(min(s0 + (lane & 15), nbw - 1)) * (pitch + 4u), 0);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int idx = lane + 64 * q, c = s0 + idx / R, r = idx % R;
+            const int64_t at = (row0 + min(r, n_rows - 1)) * n_cg + cg[c];
+            if (mfmt) {
+                ps[q] = __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t*>(st_scales)[at]));
+                pz[q] = 0.0f;
+            } else {
+                ps[q] = st_scales[at];
+                pz[q] = static_cast<float>(st_zeros[at]);
+            }
+        }
+    }
+    __device__ __forceinline__ void put(Lds<R>& lds, int sub, int mfmt) const {
+        const int lane = fresh(threadIdx.x & 63), s0 = sub * SB;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int k = 0; k < SB; k += 4) {
+                const int c = lane + 64 * q;
+                auto above = [&](int i) { return s0 + k + i < c ? u[q][k + i] : 0.0f; };
+                *reinterpret_cast<float4*>(&lds.ut[c][s0 + k]) = make_float4(above(0), above(1), above(2), above(3));
+            }
+        if (lane < SB) lds.dg[s0 + lane] = make_float2(d, block_reciprocal(d));
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int idx = lane + 64 * q, c = s0 + idx / R, r = idx % R;
+            float sc = ps[q], zp = pz[q];
+            if (mfmt) {                                        // ps holds the group word's bits
+                const uint32_t wd = __float_as_uint(sc);
+                sc = word_scale(wd, mfmt);
+                zp = word_zero(wd, mfmt);
+            }
+            lds.sc[c][r] = make_float2(sc, fastdiv_ok(sc) ? 1.0f / sc : __builtin_nanf(""));
+            lds.zp[c][r] = static_cast<uint8_t>(zp);
+        }
+    }
+};
+
+// A strip of the next block's columns: four columns and RQ rows per lane.
+template <int R>
+struct Strip {
+    static constexpr int COLS = R == 4 ? 64 : 32, CL = COLS / 4, RQ = (R * CL + 63) / 64, COUNT = GB / COLS;
+    float v[RQ][4];
+
+    static __device__ __forceinline__ int row(int lane, int r) { return min(lane / CL * RQ + r, R - 1); }      // (the last ones repeat)
+
+    // Errors of the sixteen channels from k0 on (e_at) onto the columns: a product and a difference each.
+    __device__ __forceinline__ void apply(const float* es, int k0, int lane, const float (&u)[SB][4]) {
+#pragma unroll
+        for (int k = 0; k < SB; k += 4) {
+            float e[4][RQ];
+#pragma unroll
+            for (int r = 0; r < RQ; ++r) {
+                if constexpr (BY_ROW<R>) {
+                    const float4 t = *reinterpret_cast<const float4*>(es + e_at<R>(k0 + k, row(lane, r)));
+                    e[0][r] = t.x; e[1][r] = t.y; e[2][r] = t.z; e[3][r] = t.w;
+                } else {
+#pragma unroll
+                    for (int kk = 0; kk < 4; ++kk) e[kk][r] = es[e_at<R>(k0 + k + kk, row(lane, r))];
+                }
+            }
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                for (int r = 0; r < RQ; ++r)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float upd = e[kk][r] * u[k + kk][q];
+                        v[r][q] = v[r][q] - upd;
+                    }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // here, and not behind the next wait, where this one's entries of U would still be held
+#pragma unroll
+        for (int r = 0; r < RQ; ++r)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) here(v[r][q]);
+    }
+};
 
 template <int R>
 __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp, const float* __restrict__ U,
@@ -435,10 +676,9 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
                                                          const uint8_t* __restrict__ st_zeros, uint8_t* __restrict__ Qp) {
     // items of the update: RT rows x 128 columns on the matrix cores where RT is 16, else RT rows x 64 CPL columns (RT x CPL
     // accumulators; few rows take more columns, so that an LDS read of the errors serves as many products)
-    constexpr int RR = pow2_rows<R>(), CL = 64 / RR, CPL = R <= 8 ? 4 : 2, RT = R <= 16 ? R : R / 2;
-    // Two waves for the chain: with 16 rows a block's chain takes 23 us so and 31 alone.  Few rows have few columns per lane
-    // behind a sub-block, and telling and waiting costs more (4 and 8 rows: 2 % of the sweep).
-    constexpr bool TWO = R >= 12;
+    constexpr int CPL = R <= 8 ? 4 : 2, RT = R <= 16 ? R : R / 2, ITEM = RT == 16 ? 128 : 64 * CPL;
+    constexpr int HELPERS_ALL = CHAINS<R> * HELPERS<R>;
+    constexpr int PIECES_AT = 1 + Strip<R>::COUNT;             // the first piece of the update in a block's list
     extern __shared__ __align__(16) char smem[];
     Lds<R>& lds = *reinterpret_cast<Lds<R>*>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -448,71 +688,17 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
     const int in = static_cast<int>(in64), n_cg = in / g;
     float* __restrict__ Wrows = Wp + row0 * in64;
 
-    // static groups of the channels of the block at i1 (into buffer b)
-    auto stage_groups = [&](int i1, int b) {
-        const int tid = fresh(threadIdx.x);
-        if (tid < GB)
-            lds.cg[b][tid] = i1 + tid < in ? static_cast<int>(static_cast<uint32_t>(perm[i1 + tid]) / static_cast<uint32_t>(g)) : 0;
-    };
-    // The block's corner of U (transposed), the reciprocals of its diagonal, and its static parameters (groups in cg[b]):
-    // fetched into registers first, put into LDS when the last block's corner is no longer needed.
-    // 8 lanes along a row of U (one 128-byte line), 8 rows: two-way bank conflicts at most on the turned writes.
-    constexpr int NP = GB * R / (64 * WAVES);                  // parameters per thread
-    float cu[8][4], cd, ps[NP], pz[NP];
-    auto fetch_block = [&](int i1, int nbw, int b) {
-        const int tid = fresh(threadIdx.x), in = fresh_uniform(static_cast<int>(in64));
-        const int c4 = (tid & 7) * 4, kr = tid >> 3;           // 64 rows at a time
-        const float* corner = U + i1 * in64 + i1;
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int k = kr + 64 * h, c = c4 + 32 * cb + j;
-                    cu[4 * h + cb][j] = (k < nbw && c < nbw) ? corner[static_cast<uint32_t>(k) * static_cast<uint32_t>(in) + c] : 0.0f;
-                }
-        cd = tid < nbw ? corner[static_cast<uint32_t>(tid) * (static_cast<uint32_t>(in) + 1u)] : 1.0f;
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {
-            const int idx = tid + 64 * WAVES * j, c = idx / R, r = idx % R;
-            const int64_t at = (row0 + min(r, n_rows - 1)) * n_cg + lds.cg[b][c];
-            if (mfmt) {
-                ps[j] = __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t*>(st_scales)[at]));
-                pz[j] = 0.0f;
-            } else {
-                ps[j] = st_scales[at];
-                pz[j] = static_cast<float>(st_zeros[at]);
-            }
-        }
-    };
-    auto store_block = [&](int i1, int b) {
-        const int tid = fresh(threadIdx.x), c4 = (tid & 7) * 4, kr = tid >> 3;
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) lds.ut[c4 + 32 * cb + j][kr + 64 * h] = cu[4 * h + cb][j];
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {
-            const int idx = tid + 64 * WAVES * j, c = idx / R, r = idx % R;
-            float sc = ps[j], zp = pz[j];
-            if (mfmt) {                                        // ps holds the group word's bits
-                const uint32_t wd = __float_as_uint(sc);
-                sc = word_scale(wd, mfmt);
-                zp = word_zero(wd, mfmt);
-            }
-            lds.sc[c][r] = make_float2(sc, fastdiv_ok(sc) ? 1.0f / sc : __builtin_nanf(""));
-            lds.zp[c][r] = static_cast<uint8_t>(zp);
-        }
-        if (tid < GB) lds.rd[tid] = block_reciprocal(cd);
-        if (tid == 0) lds.next = lds.posted = lds.done = 0;
-        stage_groups(i1 + GB, b ^ 1);
+    // static groups of the channels of the block at i1
+    auto stage_groups = [&](int i1, int* cg) {
+        for (int c = fresh(threadIdx.x & 63); c < GB; c += 64)
+            cg[c] = i1 + c < in ? static_cast<int>(static_cast<uint32_t>(perm[i1 + c]) / static_cast<uint32_t>(g)) : 0;
     };
 
-    // first block: its columns straight into the strip
-    stage_groups(0, 0);
+    // first block: its columns straight into the strip; a wave per sub-block for the rest
+    if (wave < 2) stage_groups(GB * wave, lds.cg[wave]);
+    if (tid < 2) lds.next[tid] = 0;
+    if (tid < CHAINS<R>) lds.posted[tid] = 0;
+    if (tid < HELPERS_ALL) lds.done[tid] = 0;
     __syncthreads();
     {
         const int nbw = min(in, GB);
@@ -520,121 +706,140 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
             const int r = idx / GB, c = idx % GB;
             lds.w[r][c] = (c < nbw && r < n_rows) ? Wrows[static_cast<uint32_t>(r) * static_cast<uint32_t>(in) + c] : 0.0f;
         }
-        fetch_block(0, nbw, 0);
-        store_block(0, 0);
+        Stage<R> st;
+        st.fetch(U, in, 0, nbw, wave, lds.cg[0], row0, n_rows, n_cg, mfmt, st_scales, st_zeros);
+        st.put(lds, wave, mfmt);
     }
     __syncthreads();
 
-    const int crow = lane & (RR - 1), ccol = lane / RR;        // the chain's lane: row (replicated CL times), column lane
-    const bool row_in = crow < R, row_ok = crow < n_rows;
     for (int i1 = 0, blk = 0; i1 < in; i1 += GB, ++blk) {
         const int nbw = min(in - i1, GB), behind = i1 + nbw;
         float* es = lds.e[blk & 1];
         const float* es_last = lds.e[(blk & 1) ^ 1];
-        if (wave == 0) {
+        const int next_w = min(in - behind, GB), far = behind + GB;          // (the next block's width, if there is one)
+        if (wave < CHAINS<R>) {
             // the chain the workgroup waits for: ahead of the updates that share its SIMD
             __builtin_amdgcn_s_setprio(3);
-            float* wrow = &lds.w[row_in ? crow : 0][0];
-            for (int s0 = 0; s0 < nbw; s0 += SB) {
-                const int sbw = min(nbw - s0, SB);
-                float e[SB];
-                uint32_t qpk[SB / 4];
-                const float* ut = &lds.ut[s0][s0];
-                const float2* sc = &lds.sc[s0][row_in ? crow : 0];
-                const uint8_t* zp = &lds.zp[s0][row_in ? crow : 0];
-                uint8_t* q_out = Qp + (row0 + crow) * in64 + i1 + s0;
-                bool fine = sbw == SB && reciprocals_ok(&lds.rd[s0]);       // uniform
-                if (fine) fine = chain16<R>(wrow + s0, ut, &lds.rd[s0], sc, zp, qmax, e, qpk);
-                if (!__any(row_ok && !fine)) {
-                    // errors for the later updates (0 in rows past the end), codes in visiting order
-#pragma unroll
-                    for (int k = 0; k < SB; ++k) e[k] = row_ok ? e[k] : 0.0f;
-                    if (row_in && ccol == 0) {
-#pragma unroll
-                        for (int k = 0; k < SB; ++k) es[e_at<R>(s0 + k, crow)] = e[k];
-                    }
-                    if (row_ok && ccol == 0) {
-                        if ((reinterpret_cast<uintptr_t>(q_out) & 15u) == 0) {
-                            *reinterpret_cast<uint4*>(q_out) = make_uint4(qpk[0], qpk[1], qpk[2], qpk[3]);
-                        } else {
-#pragma unroll
-                            for (int c = 0; c < SB; ++c) q_out[c] = static_cast<uint8_t>(qpk[c / 4] >> (8 * (c % 4)));
-                        }
-                    }
-                } else if (row_in) {
-                    chain_slow<R>(wrow + s0, ut, es + e_at<R>(s0, crow), sbw, qmax,
-                                  [&](int c, float& a, float& b) { a = sc[c * R].x; b = static_cast<float>(zp[c * R]); },
-                                  [&](int c, uint8_t q) { if (row_ok && ccol == 0) q_out[c] = q; });
-#pragma unroll
-                    for (int k = 0; k < SB; ++k) e[k] = k < sbw && row_ok ? es[e_at<R>(s0 + k, crow)] : 0.0f;
-                    if (!row_ok)
-                        for (int k = 0; k < sbw; ++k) es[e_at<R>(s0 + k, crow)] = 0.0f;
-                }
-                // The block's columns behind the sub-block (only a whole sub-block has any); TWO: the next sub-block's, which
-                // the second wave has brought up to the sub-block before (the columns behind those are its business).
-                if (s0 + SB < nbw) {
-                    if constexpr (TWO) {
-                        tell(&lds.posted, s0 / SB + 1);
-                        if (s0 > 0) wait_for(&lds.done, s0 / SB);
-                    }
-                    if (row_in) apply16<R, CL>(lds, wrow, e, s0, s0 + SB + ccol, TWO ? min(nbw, s0 + 2 * SB) : nbw);
-                }
-                // these columns of the strip are this wave's alone while the chain runs, and LDS serves a wave's accesses in order
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            }
+            chain_block<R>(lds, wave, blk, es, n_rows, nbw, qmax, Qp + row0 * in64 + i1, in);
             __builtin_amdgcn_s_setprio(0);
-        } else if (TWO && wave == SECOND) {
-            // A sub-block's errors onto the columns behind the next one, beside the next one's chain
+        } else if (wave < CHAINS<R> + HELPERS_ALL) {
             __builtin_amdgcn_s_setprio(2);
-            float* wrow = &lds.w[row_in ? crow : 0][0];
-            for (int s0 = 0; s0 + 2 * SB < nbw; s0 += SB) {
-                wait_for(&lds.posted, s0 / SB + 1);
-                if (row_in) {
-                    float e[SB];
-#pragma unroll
-                    for (int k = 0; k < SB; ++k) e[k] = es[e_at<R>(s0 + k, crow)];
-                    apply16<R, CL>(lds, wrow, e, s0, s0 + 2 * SB + ccol, nbw);
-                }
-                tell(&lds.done, s0 / SB + 1);
-            }
+            help_block<R>(lds, wave - CHAINS<R>, blk, es, nbw);
             __builtin_amdgcn_s_setprio(0);
-        }
-        if (wave == WAVES - 1 && behind < in) {
-            // What the step after this block reads first, into the L2: the block's rows of U at the next block's columns,
-            // and the next block's corner (128 lines of 512 bytes each).
-            const int next_w = min(in - behind, GB);
-            for (int r = lane; r < 4 * (GB + next_w); r += 64) {
-                const int line = r >> 2, c = min((r & 3) * 32, next_w - 1);
-                const float t = U[(i1 + line) * in64 + behind + c];
-                asm volatile("" ::"v"(t));
-            }
-        }
-        // errors of the last block onto the columns behind this one, item by item
-        if (blk > 0 && behind < in) {
-            if constexpr (RT == 16) {
-                update_behind<R>(Wrows, U, es_last, n_rows, in, int64_t(i1) - GB, behind, &lds.next);
-            } else {
-                const int n_items = (in - behind + 64 * CPL - 1) / (64 * CPL) * (R / RT);
-                for (;;) {
-                    int item = 0;
-                    if (lane == 0) item = atomicAdd(&lds.next, 1);
-                    item = __builtin_amdgcn_readfirstlane(item);
-                    if (item >= n_items) break;
-                    const int rt = R == RT ? 0 : (item & 1) * RT, cc = R == RT ? item : item >> 1;
-                    if (rt < n_rows)
-                        update_item<R, RT, CPL>(Wrows + rt * in64, U, es_last + rt, n_rows - rt, in, int64_t(i1) - GB,
-                                                behind + cc * (64 * CPL));
-                }
-            }
         }
         if (behind >= in) break;                               // uniform: the last block
-        const int next_w = min(in - behind, GB), next_b = (blk + 1) & 1;
-        fetch_block(behind, next_w, next_b);
-        __syncthreads();
-        update_next<R>(Wrows, U, es, n_rows, in, i1, behind, next_w, lds);
-        store_block(behind, next_b);
+        if (wave == WAVES - 1) {
+            stage_groups(far, lds.cg[blk & 1]);
+            if (lane == 0) lds.next[(blk & 1) ^ 1] = 0;
+            // What the next block's strips read of U, into the L2: three blocks' rows at its columns, lines of 128 bytes.
+            if (far < in) {
+                const int far_w = min(in - far, GB);
+                for (int h = 0; h < 3 * GB; h += 2 * 64) {
+                    float t[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        const int l = 4 * h + 64 * q + lane, row = min(i1 + (l >> 2), in - 1), c = min(far + (l & 3) * 32, far + far_w - 1);
+                        t[q] = U[int64_t(row) * in64 + c];
+                    }
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) asm volatile("" ::"v"(t[q]));
+                }
+            }
+        }
+
+        // A list for the waves that are free: the next block's corner and parameters; the strips of its columns, which get the errors
+        // of the last block and then this one's, sub-block by sub-block; pieces of the last block's update of the columns behind it.
+        const int n_items = PIECES_AT + (blk > 0 && far < in ? (in - far + ITEM - 1) / ITEM * (R / RT) : 0);
+        int* next = &lds.next[blk & 1];
+        auto take = [&] {
+            int item = 0;
+            if (lane == 0) item = atomicAdd(next, 1);
+            return __builtin_amdgcn_readfirstlane(item);
+        };
+        auto posted = [&](int n) {
+#pragma unroll
+            for (int ch = 0; ch < CHAINS<R>; ++ch) wait_for(&lds.posted[ch], mark(blk, n));
+        };
+        int item = take();
+        while (item < n_items) {
+            if (item >= PIECES_AT) {
+                if constexpr (RT == 16) {
+                    item = update_behind<R>(Wrows, U, es_last, n_rows, in, int64_t(i1) - GB, far, item - PIECES_AT, n_items - PIECES_AT,
+                                            [&] { return take() - PIECES_AT; }) + PIECES_AT;
+                } else {
+                    const int piece = item - PIECES_AT;
+                    const int rt = R == RT ? 0 : (piece & 1) * RT, cc = R == RT ? piece : piece >> 1;
+                    if (rt < n_rows)
+                        update_item<R, RT, CPL>(Wrows + rt * in64, U, es_last + rt, n_rows - rt, in, int64_t(i1) - GB, far + cc * (64 * CPL));
+                    item = take();
+                }
+                continue;
+            }
+            if (item == 0) {
+                // This block's corner and parameters at a sub-block have served when the chain is through the next and the helpers with it.
+                Stage<R> st[2];
+                auto fetch = [&](int b, int sub) {
+                    st[b].fetch(U, in, behind, next_w, sub, lds.cg[(blk & 1) ^ 1], row0, n_rows, n_cg, mfmt, st_scales, st_zeros);
+                };
+                auto put = [&](int b, int sub) {
+                    posted(min(sub + 2, GB / SB));
+#pragma unroll
+                    for (int h = 0; h < HELPERS_ALL; ++h) wait_for(&lds.done[h], mark(blk, sub + 2));
+                    st[b].put(lds, sub, mfmt);
+                };
+                fetch(0, 0);
+#pragma unroll 1
+                for (int sub = 0; sub < GB / SB; sub += 2) {
+                    fetch(1, sub + 1);
+                    put(0, sub);
+                    if (sub + 2 < GB / SB) fetch(0, sub + 2);
+                    put(1, sub + 1);
+                }
+                item = take();
+                continue;
+            }
+            const int lane = fresh(tid & 63), c = Strip<R>::COLS * (item - 1) + 4 * (lane % Strip<R>::CL);
+            const uint32_t pitch = 4u * static_cast<uint32_t>(fresh_uniform(in)), col = 4u * static_cast<uint32_t>(min(c, next_w - 1));
+            const int u_row = blk > 0 ? i1 - GB : i1;
+            const update::Matrix W(Wrows + behind, int64_t(n_rows) * in - behind), Urows(U + int64_t(u_row) * in64 + behind, (in64 - u_row) * in64 - behind);
+            Strip<R> s;
+            float u[2][SB][4];
+#pragma unroll
+            for (int r = 0; r < Strip<R>::RQ; ++r)
+                W.load(s.v[r], static_cast<uint32_t>(min(Strip<R>::row(lane, r), n_rows - 1)) * pitch + col, 0);
+            uint32_t row = 0;                                  // offset of the row of U to fetch next
+            auto fetch = [&](int b) {
+#pragma unroll
+                for (int kk = 0; kk < SB; ++kk) {
+                    Urows.load(u[b][kk], col, row);
+                    row += pitch;
+                }
+            };
+            fetch(0);
+            if (blk > 0) {
+#pragma unroll 1
+                for (int k = 0; k < GB; k += 2 * SB) {
+                    fetch(1);
+                    s.apply(es_last, k, lane, u[0]);
+                    fetch(0);                                  // (at the end this block's first)
+                    s.apply(es_last, k + SB, lane, u[1]);
+                }
+            }
+#pragma unroll 1
+            for (int sub = 0; sub < GB / SB; sub += 2) {
+                fetch(1);
+                posted(sub + 1);
+                s.apply(es, sub * SB, lane, u[0]);
+                if (sub + 2 < GB / SB) fetch(0);
+                posted(sub + 2);
+                s.apply(es, (sub + 1) * SB, lane, u[1]);
+            }
+            // the chain is through, and the strip with it
+#pragma unroll
+            for (int r = 0; r < Strip<R>::RQ; ++r)
+                *reinterpret_cast<float4*>(&lds.w[Strip<R>::row(lane, r)][c]) = make_float4(s.v[r][0], s.v[r][1], s.v[r][2], s.v[r][3]);
+            item = take();
+        }
         __syncthreads();
     }
 }

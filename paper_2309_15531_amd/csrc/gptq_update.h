@@ -53,11 +53,37 @@ struct Matrix {
     __amdgpu_buffer_rsrc_t rsrc;
     __device__ __forceinline__ explicit Matrix(const float* p)
         : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, 0x7fffffff, 0x00020000)) {}
+    // with its end: what a load of several floats reads behind it is 0
+    __device__ __forceinline__ Matrix(const float* p, int64_t floats)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, static_cast<int>(min(floats, int64_t(0x1fffffff)) * 4), 0x00020000)) {}
     __device__ __forceinline__ float load(uint32_t lane_bytes, uint32_t uniform_bytes) const {
         return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_bytes, uniform_bytes, 0));
     }
     __device__ __forceinline__ void store(float v, uint32_t lane_bytes, uint32_t uniform_bytes) const {
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, lane_bytes, uniform_bytes, 0);
+    }
+    template <int N>
+    __device__ __forceinline__ void store(const float (&v)[N], uint32_t lane_bytes, uint32_t uniform_bytes) const {
+        typedef uint32_t words __attribute__((ext_vector_type(N)));
+        words t;
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = __float_as_uint(v[i]);
+        if constexpr (N == 4) __builtin_amdgcn_raw_buffer_store_b128(t, rsrc, lane_bytes, uniform_bytes, 0);
+        else __builtin_amdgcn_raw_buffer_store_b64(t, rsrc, lane_bytes, uniform_bytes, 0);
+    }
+    // N consecutive floats, at any multiple of 4 bytes
+    template <int N>
+    __device__ __forceinline__ void load(float (&v)[N], uint32_t lane_bytes, uint32_t uniform_bytes) const {
+        static_assert(N == 2 || N == 4, "");
+        if constexpr (N == 4) {
+            const auto t = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_bytes, uniform_bytes, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = __uint_as_float(t[i]);
+        } else {
+            const auto t = __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane_bytes, uniform_bytes, 0);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) v[i] = __uint_as_float(t[i]);
+        }
     }
 };
 

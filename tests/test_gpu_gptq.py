@@ -15,6 +15,7 @@ import oracle
 from gptq_forms import GPTQ_FORMS
 from oracle import OC, IC
 from oracle import gptq_oracle as G
+from oracle import meta16_oracle as M
 from paper_2309_15531_amd import binding as B
 from paper_2309_15531_amd import search as S
 from paper_2309_15531_amd import synth
@@ -539,6 +540,37 @@ def test_per_oc_sweep_rows_per_workgroup(ctx, out_f, in_f, bits, group):
     got = gpu_sweep(ctx, W, OC, bits, group, dev(U32), dev(perm.astype(np.int32)), dev(dead.astype(np.uint8)))
     assert np.array_equal(got["codes"], ref["codes"])
     assert np.array_equal(got["dW"], ref["dW"])
+
+
+@pytest.mark.parametrize("out_f,in_f,bits,meta16", [
+    (5, 391, 2, False),          # 4 rows per workgroup, the last with one; 7 columns in the last strip
+    (1000, 387, 4, True),        # 4 rows; pieces of the update of three columns, at any alignment
+    (2041, 517, 3, False),       # 8 rows
+    (3000, 1805, 3, True),       # 12 rows
+    (4090, 331, 3, False),       # 16 rows
+    (6100, 291, 3, False),       # 24 rows
+    (8100, 549, 2, True),        # 32 rows
+])
+def test_per_oc_sweep_strips_of_ragged_blocks(ctx, out_f, in_f, bits, meta16):
+    """The next block's columns are finished beside the chain, in strips of 32 or 64 columns, four in each lane, and the columns behind
+    them in wide pieces: last blocks that end inside a strip and inside a lane's four, rows at any alignment, against the oracle."""
+    rng = np.random.default_rng(out_f + in_f)
+    W, X = layer(out_f, in_f, 700, seed=out_f * 3 + in_f, dead=(5,))
+    H32 = oracle.hessian(X).astype(np.float32)
+    Hp, perm, dead = G.prepare(H32, 0.01, True)
+    U = G.factor(Hp).astype(np.float32)
+    if not meta16:
+        _per_oc_matches_oracle(ctx, W, U, perm, dead, bits, 0, _sampled(rng, out_f, 64))
+        return
+    rows = _sampled(rng, out_f, 64)
+    q = M.quantize(np.where(dead[None, :], np.float16(0.0), W), OC, bits, 0)
+    ref = M.gptq_sweep(W[rows], U, perm, dead, OC, bits, 0)
+    meta = dev(q["meta"].view(np.int16))
+    codes, dW = torch.empty((out_f, in_f), dtype=torch.uint8, device="cuda"), torch.empty((out_f, in_f), device="cuda")
+    ctx.adadim_gptq_quantize_meta16(dev(W), OC, bits, 0, dev(U), dev(perm.astype(np.int32)), dev(dead.astype(np.uint8)), codes, dW=dW,
+                                    static_meta=meta)
+    assert np.array_equal(codes.cpu().numpy()[rows], ref["codes"])
+    assert np.array_equal(dW.cpu().numpy()[rows], ref["dW"])
 
 
 @pytest.mark.parametrize("dim,group", [(OC, 64), (IC, 64), (IC, 128)])

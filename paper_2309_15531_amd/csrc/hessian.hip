@@ -154,7 +154,14 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
     // A tile's partials are two runs of slots with a constant stride each: the full pieces (one per split, a
     // split apart) and the pieces of the rest (next to each other).
     constexpr int64_t TILE = int64_t(BT) * BT;
-    struct Runs { const float* a; int na; int64_t sa; const float* b; int nb; };
+    struct Runs {
+        const float* a; int na; int64_t sa; const float* b; int nb;
+        __device__ __forceinline__ const float* at(int sp) const { return sp < na ? a + sp * sa : b + (sp - na) * TILE; }
+    };
+    // A launch of few blocks is a chain of waits: a batch of loads holds as many partials as most plans have, and the diagonal's are in
+    // flight with them (one partial after the other, and the diagonal behind them: Gram matrix with its prepared form, us, 512 wide,
+    // 2048 tokens 25.1 and now 16.6; 768, 3000 tokens 30 and 21; 1024, 8192 tokens 46 and 40; 2760, 3001 tokens 56 and 53).
+    constexpr int AHEAD = REGMAJOR ? 4 : 8;
     auto runs_of = [&](int tile_r) {
         const int n = gram_plan_parts(plan, tile_r);
         Runs r;
@@ -166,39 +173,33 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
         return r;
     };
     const Runs mine = whole ? Runs{part, 0, 0, part, 0} : runs_of(tile - n_whole);
-    if (whole) {
+    const int n_parts = mine.na + mine.nb;
+    const float* const part_one = mine.na > 0 ? mine.a : mine.b;
+    const int wave = (sr >> 2) * 2 + (sc >> 2);
+    // where this thread's four elements (rows 4 ty .. 4 ty + 3 of column tx) are in a partial tile
+    const int64_t at = REGMAJOR ? ((((sr & 3) * 4 + (sc & 3)) * 4 + (ty >> 1)) * 256 + wave * 64 + (ty & 1) * 32 + tx) * 4
+                                : int64_t(sr * 32 + ty * 4) * BT + sc * 32 + tx;
+    float p[AHEAD][4], v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto fetch = [&](int s0) {
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const int r = ty * 4 + rr;
-            s[r][tx] = (R0 + r < in && C0 + tx < in) ? H[(R0 + r) * in + C0 + tx] : 0.0f;
+        for (int q = 0; q < AHEAD; ++q) {
+            if (s0 + q >= n_parts) continue;                  // uniform
+            if constexpr (REGMAJOR) {
+                const float4 f = *reinterpret_cast<const float4*>(mine.at(s0 + q) + at);
+                p[q][0] = f.x; p[q][1] = f.y; p[q][2] = f.z; p[q][3] = f.w;
+            } else {
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) p[q][rr] = mine.at(s0 + q)[at + rr * BT];
+            }
         }
-    } else if constexpr (REGMAJOR) {
-        static_assert(!REGMAJOR || BT == 256, "register-major partials come from the 256-wide DMA kernel");
-        const int wave = (sr >> 2) * 2 + (sc >> 2);
-        const int64_t idx = (((sr & 3) * 4 + (sc & 3)) * 4 + (ty >> 1)) * 256 + wave * 64 + (ty & 1) * 32 + tx;
-        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        for (int sp = 0; sp < mine.na; ++sp) {
-            const float4 p = *reinterpret_cast<const float4*>(mine.a + sp * mine.sa + idx * 4);
-            v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-        }
-        for (int sp = 0; sp < mine.nb; ++sp) {
-            const float4 p = *reinterpret_cast<const float4*>(mine.b + sp * TILE + idx * 4);
-            v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-        }
-        s[ty * 4 + 0][tx] = v.x;
-        s[ty * 4 + 1][tx] = v.y;
-        s[ty * 4 + 2][tx] = v.z;
-        s[ty * 4 + 3][tx] = v.w;
+    };
+    // (one partial: nothing to have in flight beside it, and blocks this short feel every instruction)
+    const bool single = REGMAJOR && n_parts == 1;
+    if (single) {
+        const float4 f = *reinterpret_cast<const float4*>(part_one + at);
+        v[0] += f.x; v[1] += f.y; v[2] += f.z; v[3] += f.w;
     } else {
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const int r = ty * 4 + rr;
-            float v = 0.0f;
-            const int64_t at = (sr * 32 + r) * BT + sc * 32 + tx;
-            for (int sp = 0; sp < mine.na; ++sp) v += mine.a[sp * mine.sa + at];
-            for (int sp = 0; sp < mine.nb; ++sp) v += mine.b[sp * TILE + at];
-            s[r][tx] = v;
-        }
+        fetch(0);
     }
     const bool diag = R0 == C0;
     if constexpr (PREP) {
@@ -220,8 +221,15 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
                     h = H[j * in + j];
                 } else {
                     const Runs dg = runs_of(dtile - n_whole);
-                    for (int sp = 0; sp < dg.na; ++sp) h += dg.a[sp * dg.sa + off];
-                    for (int sp = 0; sp < dg.nb; ++sp) h += dg.b[sp * TILE + off];
+                    for (int s0 = 0; s0 < dg.na + dg.nb; s0 += AHEAD) {
+                        float p[AHEAD];
+#pragma unroll
+                        for (int q = 0; q < AHEAD; ++q)
+                            if (s0 + q < dg.na + dg.nb) p[q] = dg.at(s0 + q)[off];
+#pragma unroll
+                        for (int q = 0; q < AHEAD; ++q)
+                            if (s0 + q < dg.na + dg.nb) h += p[q];
+                    }
                 }
             }
             const float d = jacobi_scale(h);
@@ -231,6 +239,25 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
                 hmeta[in + j] = h;
             }
         }
+    }
+    if (whole) {
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+            const int r = ty * 4 + rr;
+            s[r][tx] = (R0 + r < in && C0 + tx < in) ? H[(R0 + r) * in + C0 + tx] : 0.0f;
+        }
+    } else {
+        static_assert(!REGMAJOR || BT == 256, "register-major partials come from the 256-wide DMA kernel");
+        for (int s0 = single ? n_parts : 0; s0 < n_parts; s0 += AHEAD) {
+            if (s0 > 0) fetch(s0);
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q)
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr)
+                    if (s0 + q < n_parts) v[rr] += p[q][rr];
+        }
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) s[ty * 4 + rr][tx] = v[rr];
     }
     __syncthreads();
     if constexpr (PREP) {

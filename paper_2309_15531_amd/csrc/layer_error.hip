@@ -86,6 +86,114 @@ __global__ __launch_bounds__(256) void error_prologue(SrcBatch src, int dW_dtype
     if (threadIdx.x == 0) diag[o] = s_red[0];
 }
 
+constexpr int SMALL_TILE = 64;
+
+// The tile kernel of small layers: no LDS, the operands' fragments straight from memory (they sit in the L2), tiles of 64 columns of
+// Hs x 64 rows of dW, the contraction dealt to the four waves in pairs of steps (the 64 bytes that a row of the scoring layout has
+// together).  The row sums are linear in the products, so each wave takes its own share of the contraction through the epilogue, and
+// only row sums meet.  What a small layer pays in the DMA kernel is latency: a ring to fill, eight stages and an epilogue of 256 x 256 per workgroup.
+__global__ __launch_bounds__(256) void error_small(edma::Batch batch, const __half* __restrict__ Hs, int64_t out, int64_t in,
+                                                   const float* __restrict__ hmeta_diag, float* __restrict__ part) {
+    constexpr int T = SMALL_TILE, AHEAD = 4;                   // steps of 16 on their way ahead of their products
+    __shared__ float s_rows[4][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int n_slots = gridDim.x, slot = n_slots - 1 - static_cast<int>(blockIdx.x), cand = blockIdx.z;      // the longest first
+    const __half* __restrict__ A = batch.A[cand];
+    const int64_t col0 = int64_t(slot) * T, row0 = int64_t(blockIdx.y) * T;
+    float sum[2] = {0.0f, 0.0f};
+    {
+        const int pairs = static_cast<int>((min(in, col0 + T) + 31) / 32);
+        // rows past the end: read again, never used
+        const __half* pn[2];
+        const __half* po[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            pn[i] = Hs + score_index(min(col0 + 32 * i + l32, in - 1), 8 * lh, in, in);
+            po[i] = A + score_index(min(row0 + 32 * i + l32, out - 1), 8 * lh, out, in);
+        }
+        const bool blocked = score_blocked(in);
+        half8 fn[AHEAD][2], fo[AHEAD][2];
+        auto fetch = [&](int b, int i_mine) {
+            const int s = 2 * (wave + 4 * (i_mine >> 1)) + (i_mine & 1);
+            const int64_t at = blocked ? int64_t(s >> 1) * (256 * 32) + (s & 1) * 16 : int64_t(s) * 16;
+            const bool have = 16 * s + 8 * lh < in;            // in % 8 == 0
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                fn[b][i] = have ? *reinterpret_cast<const half8*>(pn[i] + at) : half8{};
+                fo[b][i] = have ? *reinterpret_cast<const half8*>(po[i] + at) : half8{};
+            }
+        };
+        const int mine = 2 * ((pairs - wave + 3) / 4);         // (a half pair behind the end multiplies zeros)
+#pragma unroll
+        for (int b = 0; b < AHEAD; ++b)
+            if (b < mine) fetch(b, b);
+        // the entries of dW' that the row sums need: rows row0 + 32 j + l32, columns col0 + 32 i + 8 g + 4 lh ..+3
+        uint2 aw[2][4][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int64_t n0 = col0 + 32 * i + 8 * g + 4 * lh;
+                    aw[i][g][j] = n0 < in ? *reinterpret_cast<const uint2*>(A + score_index(min(row0 + 32 * j + l32, out - 1), n0, out, in))
+                                          : make_uint2(0u, 0u);
+                }
+        floatx16 acc[2][2] = {};
+        for (int s = 0; s < mine; s += AHEAD) {
+#pragma unroll
+            for (int b = 0; b < AHEAD; ++b) {
+                if (s + b < mine) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fn[b][i], fo[b][j], acc[i][j], 0, 0, 0);
+                    if (s + b + AHEAD < mine) fetch(b, s + b + AHEAD);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int64_t n0 = col0 + 32 * i + 8 * g + 4 * lh;
+                if (n0 >= in) continue;                        // in % 8 == 0: the four columns are inside together
+                float hq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                if (hmeta_diag && wave == 0) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        // d = 2^e: the bit pattern of 1/d is 0x7F000000 minus that of d
+                        const float r = __uint_as_float(0x7F000000u - __float_as_uint(hmeta_diag[n0 + e]));
+                        hq[e] = 0.5f * hmeta_diag[in + n0 + e] * r * r;
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const float2 a = __half22float2(*reinterpret_cast<const __half2*>(&aw[i][g][j].x));
+                    const float2 b = __half22float2(*reinterpret_cast<const __half2*>(&aw[i][g][j].y));
+                    sum[j] += (acc[i][j][4 * g + 0] + hq[0] * a.x) * a.x;
+                    sum[j] += (acc[i][j][4 * g + 1] + hq[1] * a.y) * a.y;
+                    sum[j] += (acc[i][j][4 * g + 2] + hq[2] * b.x) * b.x;
+                    sum[j] += (acc[i][j][4 * g + 3] + hq[3] * b.y) * b.y;
+                }
+            }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const float v = sum[j] + __shfl_xor(sum[j], 32, 64);
+        if (lane < 32) s_rows[wave][32 * j + lane] = v;
+    }
+    __syncthreads();
+    const int t = threadIdx.x;
+    const int64_t o = int64_t(blockIdx.y) * T + t;
+    if (t < T && o < out) {
+        const float v = (s_rows[0][t] + s_rows[1][t]) + (s_rows[2][t] + s_rows[3][t]);
+        part[(int64_t(cand) * n_slots + slot) * out + o] = v;
+    }
+}
+
 // sum over the block's 256 threads, in every thread
 __device__ __forceinline__ double finish_total(double v, double* s_red) {
 #pragma unroll
@@ -274,6 +382,21 @@ void error_slots(int nc, int MB, int NB, int64_t in, int& kb, int& n_slots) {
     }
 }
 
+// Small layers: by the steps of 64 columns x 64 rows x 64 of the contraction that a launch takes.  Scoring calls, us, DMA kernel / small:
+//     80 (2 x 256 x 256)     18.2 / 12.4      4352 (2 x 1024 x 1024) 26.7 / 20.2      4992 (2 x 2048 x 768)  24.5 / 28.3
+//    576 (2 x 512 x 512)     21.1 / 13.6      4224 (2 x 256 x 2048)  22.1 / 19.3      7488 (8 x 768 x 768)   24.9 / 35.3
+//   2304 (2 x 2048 x 512)    22.1 / 16.9      4608 (2 x 4096 x 512)  23.1 / 28.1     33792 (2 x 2048 x 2048) 40.8 / 90.7
+// Row-major operands cost the DMA kernel more: 4352 (2 x 1000 x 1000) 33.5 / 23.8, 5566 (2 x 700 x 1400) 31.4 / 28.9,
+// 7220 (2 x 1200 x 1200) 34.6 / 37.7.
+constexpr int64_t SMALL_STEPS = 4400, SMALL_STEPS_ROW_MAJOR = 5600;
+// Row partials and diagonal terms of the largest of these launches (one slot; with s slots a launch has 1 / s of the rows).
+constexpr size_t SMALL_SCRATCH_BYTES = size_t(SMALL_TILE) * 2 * SMALL_STEPS_ROW_MAJOR * sizeof(float);
+int error_small_slots(int64_t in) { return static_cast<int>((in + SMALL_TILE - 1) / SMALL_TILE); }
+bool error_is_small(int nc, int64_t out, int64_t in) {
+    const int64_t nb = error_small_slots(in);
+    return nc * ((out + SMALL_TILE - 1) / SMALL_TILE) * (nb * (nb + 1) / 2) <= (score_blocked(in) ? SMALL_STEPS : SMALL_STEPS_ROW_MAJOR);
+}
+
 int set_error_attr(adadim_ctx* ctx) {
     static PerDeviceOnce once;
     const hipError_t err = once.run([] {
@@ -289,7 +412,7 @@ int set_error_attr(adadim_ctx* ctx) {
 // call's loss array (for the fused selection, taken when best_dev is given).
 int run_error_batch(adadim_ctx* ctx, int nc, const void* const* dW, int dW_dtype, int64_t out, int64_t in,
                     const __half* Hs, const float* hmeta, float* loss_rows, float* losses, const float* losses_all,
-                    int n_all, int32_t* best_dev, const ErrScratch& sc, int kb, int n_slots) {
+                    int n_all, int32_t* best_dev, const ErrScratch& sc, bool small, int kb, int n_slots) {
     constexpr int BT = edma::BT;
     const int MB = static_cast<int>((out + BT - 1) / BT), NB = static_cast<int>((in + BT - 1) / BT);
     const int kc_len = kb * BT;
@@ -312,7 +435,11 @@ int run_error_batch(adadim_ctx* ctx, int nc, const void* const* dW, int dW_dtype
                            dW_dtype, out, in, hmeta, sc.dW16, sc.diag);
     }
     ADADIM_LAUNCH_CHECK(ctx, "error_prologue");
-    {
+    if (small) {
+        ProfScope prof(ctx, "error_tiles");
+        const dim3 grid(static_cast<unsigned>(n_slots), static_cast<unsigned>((out + SMALL_TILE - 1) / SMALL_TILE), static_cast<unsigned>(nc));
+        hipLaunchKernelGGL(error_small, grid, dim3(256), 0, ctx->stream, batch, Hs, out, in, direct ? hmeta : nullptr, sc.part);
+    } else {
         ProfScope prof(ctx, "error_tiles");
         // units of 4 slots x 8 (candidate, row block) pairs, 32 workgroups each, dealt to 8 XCDs
         const int n_units = ((n_slots + 3) / 4) * ((nc * MB + 7) / 8);
@@ -356,11 +483,19 @@ int launch_layer_error(adadim_ctx* ctx, int n, const void* const* dW, int dW_dty
         int kb = 0, n_slots = 0;
         error_slots_finest(nc, MB, NB, kb, n_slots);
         // scratch: per candidate [n_slots, out] row partials; then per candidate [out] diagonal terms.  Room for the finest cut,
-        // so that which calls can be recorded after which does not hang on the chunk that is chosen.
+        // so that which calls can be recorded after which does not hang on the chunk that is chosen, and of a size of its own for
+        // small layers, whatever this one is.
         sc.part = static_cast<float*>(adadim_workspace(
             ctx, WS_ERR_PART, size_t(nc) * size_t(n_slots + 1) * size_t(out) * sizeof(float)));
-        if (!sc.part) return ADADIM_EHIP;
-        error_slots(nc, MB, NB, in, kb, n_slots);
+        float* const small_part = static_cast<float*>(adadim_workspace(ctx, WS_ERR_SMALL, SMALL_SCRATCH_BYTES));
+        if (!sc.part || !small_part) return ADADIM_EHIP;
+        const bool small = error_is_small(nc, out, in);
+        if (small) {
+            n_slots = error_small_slots(in);
+            sc.part = small_part;
+        } else {
+            error_slots(nc, MB, NB, in, kb, n_slots);
+        }
         sc.diag = sc.part + size_t(nc) * size_t(n_slots) * size_t(out);
         // scratch of the final reduction: per candidate one double per 256 rows; then the tickets
         const unsigned fin_blocks = static_cast<unsigned>((out + 255) / 256);
@@ -382,7 +517,7 @@ int launch_layer_error(adadim_ctx* ctx, int n, const void* const* dW, int dW_dty
         }
         rc = run_error_batch(ctx, nc, dW + c0, dW_dtype, out, in, Hs, hmeta,
                              loss_rows ? loss_rows + size_t(c0) * size_t(out) : nullptr, losses + c0, losses, n,
-                             c0 + nc == n ? best_dev : nullptr, sc, kb, n_slots);
+                             c0 + nc == n ? best_dev : nullptr, sc, small, kb, n_slots);
         if (rc != ADADIM_OK) return rc;
     }
     return ADADIM_OK;
@@ -445,6 +580,7 @@ int64_t launch_layer_error_noalloc_bytes(int n, int64_t out, int64_t in) {
     const int MB = static_cast<int>((out + BT - 1) / BT), NB = static_cast<int>((in + BT - 1) / BT);
     int kb = 0, n_slots = 0;
     error_slots_finest(n, MB, NB, kb, n_slots);
+    if (error_is_small(n, out, in)) n_slots = error_small_slots(in);
     const int64_t fin_blocks = (out + 255) / 256;
     return 512 + int64_t(edma::MAX_BATCH) * fin_blocks * 8 + int64_t(n) * n_slots * out * 4;
 }
@@ -454,7 +590,9 @@ int launch_layer_error_noalloc(adadim_ctx* ctx, int n, const void* const* dW, in
     constexpr int BT = edma::BT;
     const int MB = static_cast<int>((out + BT - 1) / BT), NB = static_cast<int>((in + BT - 1) / BT);
     int kb = 0, n_slots = 0;
-    error_slots(n, MB, NB, in, kb, n_slots);
+    const bool small = error_is_small(n, out, in);
+    if (small) n_slots = error_small_slots(in);
+    else error_slots(n, MB, NB, in, kb, n_slots);
     const int64_t need = launch_layer_error_noalloc_bytes(n, out, in);
     if (need > int64_t(NOALLOC_SCRATCH_BYTES))
         return adadim_fail(ctx, ADADIM_EINVAL,
@@ -481,5 +619,5 @@ int launch_layer_error_noalloc(adadim_ctx* ctx, int n, const void* const* dW, in
     sc.diag = nullptr;
     sc.dW16 = nullptr;
     return run_error_batch(ctx, n, dW, ADADIM_DW_F16_SCALED, out, in, Hs, hmeta, loss_rows, losses, losses, n, best_dev, sc,
-                           kb, n_slots);
+                           small, kb, n_slots);
 }

@@ -361,6 +361,34 @@ def test_batch_error_with_cut_contractions(ctx, nc, out_f, in_f):
     assert best.item() == int(torch.argmin(losses))
 
 
+@pytest.mark.parametrize("nc,out_f,in_f", [(1, 1, 8), (2, 65, 72), (1, 64, 64), (8, 63, 520), (2, 130, 1000), (1, 5, 1208), (3, 200, 64),
+                                           (1, 257, 1376)])
+def test_batch_error_of_small_layers(ctx, nc, out_f, in_f):
+    """Tiles of 64 x 64 with the contraction dealt to four waves: fewer pairs of steps than waves, half pairs, ragged rows and columns, both
+    layouts; column-scaled input against the oracle row by row, and fp32 input, whose diagonal term comes from elsewhere."""
+    W = rand_w(out_f, in_f, seed=7 * out_f + in_f)
+    X = synth.make_activations(200, in_f, seed=in_f + 1, n_outliers=2, scale_lo=50, scale_hi=100)
+    hp = S.PreparedHessian(ctx, in_f).update(dev(X)).prepare()
+    H64 = oracle.hessian(X)
+    clips = S.clip_grid(max(nc, 2))[::-1][:nc]
+    dWs, dW32s = [ctx.alloc_score(out_f, in_f) for _ in clips], [torch.empty((out_f, in_f), device="cuda") for _ in clips]
+    for c, d, d32 in zip(clips, dWs, dW32s):
+        ctx.adadim_quantize(dev(W), OC, 3, 8, c, dW=d, dW_dtype=B.DW_F16_SCALED, colscale=hp.colscale)
+        ctx.adadim_quantize(dev(W), OC, 3, 8, c, dW=d32, dW_dtype=B.DW_F32)
+    losses, losses32 = (torch.full((nc,), -1.0, dtype=torch.float32, device="cuda") for _ in range(2))
+    rows = torch.full((nc, out_f), -1.0, dtype=torch.float32, device="cuda")
+    best = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    ctx.adadim_layer_error_batch_select(dWs, B.DW_F16_SCALED, hp.Hs, hp.hmeta, losses, best, loss_rows=rows, shape=(out_f, in_f))
+    ctx.adadim_layer_error_batch(dW32s, B.DW_F32, hp.Hs, hp.hmeta, losses32)
+    torch.cuda.synchronize()
+    for i, c in enumerate(clips):
+        ref = oracle.layer_error_rows(oracle.quantize(W, OC, 3, 8, c)["dW"], H64)
+        assert losses[i].item() == pytest.approx(ref.sum(), rel=LOSS_RTOL)
+        assert losses32[i].item() == pytest.approx(ref.sum(), rel=LOSS_RTOL)
+        assert np.abs(rows[i].cpu().numpy() - ref).max() <= LOSS_RTOL * ref.max()
+    assert best.item() == int(torch.argmin(losses))
+
+
 def test_layer_error_zero_and_identity(ctx):
     """dW = 0 gives exactly 0; H = I gives ||dW||_F^2."""
     n = 256

@@ -51,7 +51,11 @@ class PreparedHessian:
 class LayerSearch:
     """Buffers for searching layers of one shape; reused across layers and candidates.
 
-    Candidates are scored in batches of up to `batch` (one adadim_layer_error_batch call each).
+    Candidates are scored in batches of up to `batch` (one adadim_layer_error_batch call each).  A clip ratio's two
+    dimensions are quantized in one call, which reads the weight once where the shape allows (1024 x 8192 in groups of 64:
+    12 us a pair, one dimension after the other 19); with more candidates than one batch, `batch` ratios at a time then
+    and a batch per dimension each.
+
     With at most `batch` candidates and keep_winner, every candidate's packed codes, scales and
     zeros are written while it is scored, so the winner needs no second quantization.
 
@@ -66,7 +70,10 @@ class LayerSearch:
         self.clips = [float(np.float32(c)) for c in clips]
         self.cands = [(d, c) for d in (B.DIM_OC, B.DIM_IC) for c in self.clips]
         self.batch = max(1, min(batch, 8, len(self.cands)))
-        self.dWs = [ctx.alloc_score(out_f, in_f, device) for _ in range(self.batch)]   # scoring layout, flat
+        # More candidates than a batch: by ratios where a pair is one launch (else the last batches would be short for nothing).
+        self.rounds = len(self.cands) > self.batch and in_f % 32 == 0 and group in (32, 64, 128)
+        n_dw = 2 * min(len(self.clips), self.batch) if self.rounds else self.batch
+        self.dWs = [ctx.alloc_score(out_f, in_f, device) for _ in range(n_dw)]         # scoring layout, flat
         self.losses = torch.empty(len(self.cands), dtype=torch.float32, device=device)
         self.best = torch.empty(1, dtype=torch.int32, device=device)
         self.keep_winner = keep_winner
@@ -92,27 +99,47 @@ class LayerSearch:
     def score_all(self, W, hp: PreparedHessian, select: bool = False):
         """Quantizes and scores every candidate; losses stay on the device.  select: also leave the winning
         index in self.best (taken by the scoring call itself when the candidates fit one batch)."""
-        for c0 in range(0, len(self.cands), self.batch):
-            chunk = self.cands[c0:c0 + self.batch]
-            if len(self.cands) == 2 and self.inline:
-                # the plain search: its two candidates in one call (one launch where the shape allows)
-                key = "meta" if self.meta16 else "scales"
-                sets = [{"dW": self.dWs[k], "packed": self._packed[k], key: (self._meta if self.meta16 else self._scales)[k],
-                         "zeros": None if self.meta16 else self._zeros[k]} for k in (0, 1)]
-                self.ctx.adadim_quantize_both(W, self.bits, self.group, hp.colscale, sets[0], sets[1], clip=chunk[0][1],
-                                              meta16=self.meta16)
-            else:
-                for k, (dim, clip) in enumerate(chunk):
-                    self._quantize(W, dim, clip, c0 + k if self.inline else None, dW=self.dWs[k],
-                                   dW_dtype=B.DW_F16_SCALED, colscale=hp.colscale)
-            if select and len(chunk) == len(self.cands):
-                self.ctx.adadim_layer_error_batch_select(self.dWs[:len(chunk)], B.DW_F16_SCALED, hp.Hs, hp.hmeta,
-                                                         self.losses, self.best, shape=(self.out_f, self.in_f))
+        n_c, shape = len(self.clips), (self.out_f, self.in_f)
+
+        def pair(clip, k, dWs):
+            """Both dimensions of clip ratio k."""
+            sets = [self._outputs(dW, d * n_c + k) for d, dW in enumerate(dWs)]
+            self.ctx.adadim_quantize_both(W, self.bits, self.group, hp.colscale, sets[0], sets[1], clip=clip, meta16=self.meta16)
+
+        def score(dWs, at):
+            self.ctx.adadim_layer_error_batch(dWs, B.DW_F16_SCALED, hp.Hs, hp.hmeta, self.losses[at:at + len(dWs)], shape=shape)
+
+        if len(self.cands) <= self.batch:
+            for k, clip in enumerate(self.clips):
+                pair(clip, k, (self.dWs[k], self.dWs[n_c + k]))
+            if select:
+                self.ctx.adadim_layer_error_batch_select(self.dWs, B.DW_F16_SCALED, hp.Hs, hp.hmeta, self.losses, self.best, shape=shape)
                 return
-            self.ctx.adadim_layer_error_batch(self.dWs[:len(chunk)], B.DW_F16_SCALED, hp.Hs, hp.hmeta,
-                                              self.losses[c0:c0 + len(chunk)], shape=(self.out_f, self.in_f))
+            score(self.dWs, 0)
+        elif self.rounds:
+            per = len(self.dWs) // 2
+            for c0 in range(0, n_c, per):
+                clips = self.clips[c0:c0 + per]
+                for k, clip in enumerate(clips):
+                    pair(clip, c0 + k, (self.dWs[k], self.dWs[per + k]))
+                for d in (0, 1):
+                    score(self.dWs[d * per:d * per + len(clips)], d * n_c + c0)
+        else:
+            for c0 in range(0, len(self.cands), self.batch):
+                chunk = self.cands[c0:c0 + self.batch]
+                for k, (dim, clip) in enumerate(chunk):
+                    self._quantize(W, dim, clip, None, dW=self.dWs[k], dW_dtype=B.DW_F16_SCALED, colscale=hp.colscale)
+                score(self.dWs[:len(chunk)], c0)
         if select:
             self.ctx.adadim_select(self.losses, best_dev=self.best, to_host=False)
+
+    def _outputs(self, dW, cand):
+        """Where a candidate goes while it is scored: with every candidate's outputs kept, its parameters and packed codes too."""
+        if not self.inline:
+            return {"dW": dW}
+        if self.meta16:
+            return {"dW": dW, "meta": self._meta[cand], "packed": self._packed[cand]}
+        return {"dW": dW, "scales": self._scales[cand], "zeros": self._zeros[cand], "packed": self._packed[cand]}
 
     def _quantize(self, W, dim, clip, out_set, **kw):
         """One candidate; out_set names the output set that receives its parameters and packed codes."""

@@ -12,7 +12,7 @@
 // One barrier per block; in between counters in LDS that only grow.  What bounds a block: its chain (10.4 us: about 600 instructions
 // of one wave per 16 channels at 4 to 5 cycles each) where few columns are left or rows are few, else the update's arithmetic.  Whole calls, us,
 // before (the step from block to block, 11 to 19 us, behind the chain, which took 12 to 23) and so: 512 x 1024 196 / 111, 256 x 4096 914 / 687,
-// 2048 x 2048 507 / 439, 1000 x 272 65 / 38, 4096 x 4096 1758 / 1746 (bound by the update).
+// 2048 x 2048 507 / 439, 1000 x 272 65 / 38, 4096 x 4096 1751 / 1629 (bound by the update).
 //
 // Rows per workgroup: few enough that the chip's 256 compute units all have a workgroup (16 at 4096 rows), so that
 // the update is spread over the whole chip; the chain takes much the same time for 4 rows as for 64.  rows_per_group
@@ -205,15 +205,15 @@ __device__ __forceinline__ void update_item(float* __restrict__ Wrows, const flo
 }
 
 // The update behind a block for workgroups of 16 and 32 rows, the products on the matrix cores (gptq_update.h): items of 16
-// rows x 128 columns from column c_first on, as `next` gives them out.  Two waves per SIMD keep the
+// rows x 64 NQ columns from column c_first on, as `take` gives them out, up to n_items; returns what it took last.  Two waves per SIMD keep the
 // vector pipes busy only if neither waits for memory, so the next item's columns of W, and its first entries of U, are on
 // their way while this one is worked on; and an instruction beside the differences costs a wave as much as one of them, so
-// two products share a channel's errors and row of U, and four channels a read of the errors (64 columns and a read per
-// channel: 12 us per pair of items, 90 us for the 3712 columns of the third block of 4096 x 4096, 16 rows; 83 so).
-template <int R, typename Take>
+// NQ products share a channel's errors and row of U, and four channels a read of the errors (64 columns and a read per
+// channel: 90 us for 3712 columns, 83 with 128 and a read for four, before the last ones were halved).
+template <int R, int NQ, typename Take>
 __device__ __forceinline__ int update_behind(float* __restrict__ Wrows, const float* __restrict__ U, const float* es, int n_rows,
                                              int in_, int64_t k0, int c_first, int item, int n_items, Take take) {
-    constexpr int RT = 16, COLS = 128, KB = 8;                 // KB channels per step: their U entries travel one step ahead
+    constexpr int RT = 16, COLS = 64 * NQ, KB = 8;             // KB channels per step: their U entries travel one step ahead
     const int lane = fresh(threadIdx.x & 63), in = fresh_uniform(in_);
     const uint32_t pitch = 4u * static_cast<uint32_t>(in);
     const update::Matrix W(Wrows), Urows(U + k0 * in);
@@ -224,25 +224,27 @@ __device__ __forceinline__ int update_behind(float* __restrict__ Wrows, const fl
     auto u_offset = [&](int item, int q) { return 4u * static_cast<uint32_t>(min(col0_of(item) + 64 * q + lane, in - 1)); };
     auto e_first = [&](int item) { return es + e_at<R>(0, row0_of(item) + (lane & 15)); };
     // past the last row or column: read, never stored
-    auto load = [&](int item, update::f32x16 (&v)[2]) {
+    auto load = [&](int item, update::f32x16 (&v)[NQ]) {
         const int rt = row0_of(item), c0 = col0_of(item);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const uint32_t row = static_cast<uint32_t>(min(rt + 4 * (lane >> 4) + r, n_rows - 1)) * pitch;
 #pragma unroll
-            for (int b = 0; b < 8; ++b)
+            for (int b = 0; b < 4 * NQ; ++b)
                 v[b >> 2][4 * (b & 3) + r] = W.load(row + 4u * static_cast<uint32_t>(min(c0 + 16 * b + (lane & 15), in - 1)), 0);
         }
     };
-    float u[2][KB][2];
-    auto fetch = [&](int b, int k, const uint32_t (&col)[2]) {
+    float u[2][KB][NQ];
+    auto fetch = [&](int b, int k, const uint32_t (&col)[NQ]) {
 #pragma unroll
         for (int kk = 0; kk < KB; ++kk)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) u[b][kk][q] = Urows.load(col[q], (k + kk) * pitch);
+            for (int q = 0; q < NQ; ++q) u[b][kk][q] = Urows.load(col[q], (k + kk) * pitch);
     };
-    update::f32x16 v[2], v_next[2], p[2];
-    uint32_t ucol[2] = {u_offset(item, 0), u_offset(item, 1)};
+    update::f32x16 v[NQ], v_next[NQ], p[2];
+    uint32_t ucol[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) ucol[q] = u_offset(item, q);
     const float* e_row = e_first(item);
     fetch(0, 0, ucol);
     load(item, v);
@@ -253,14 +255,18 @@ __device__ __forceinline__ int update_behind(float* __restrict__ Wrows, const fl
         const int taken = take();
         const bool more = taken < n_items;
         const int then = more ? taken : item;                  // (none left: this one's are read again and not used)
-        const uint32_t ucol_next[2] = {u_offset(then, 0), u_offset(then, 1)};
+        uint32_t ucol_next[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) ucol_next[q] = u_offset(then, q);
         const float* e_next = e_first(then);
         auto steps = [&](int k_begin) {
 #pragma unroll 1
             for (int k = k_begin; k < k_begin + GB / 2; k += 2 * KB) {
                 const bool last = k + 2 * KB == GB;            // behind the block's last channel come the next item's first
                 const float* e_behind = last ? e_next : e_row + k + 2 * KB;
-                const uint32_t ucol2[2] = {last ? ucol_next[0] : ucol[0], last ? ucol_next[1] : ucol[1]};
+                uint32_t ucol2[NQ];
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) ucol2[q] = last ? ucol_next[q] : ucol[q];
 #pragma unroll
                 for (int kk = 0; kk < 2 * KB; ++kk) {
                     if (kk == 0) fetch(1, k + KB, ucol);
@@ -268,12 +274,12 @@ __device__ __forceinline__ int update_behind(float* __restrict__ Wrows, const fl
                     if ((kk & 3) == 0)
                         ev[((kk >> 2) + 1) & 1] = *reinterpret_cast<const update::f32x4*>(kk + 4 < 2 * KB ? e_row + k + kk + 4 : e_behind);
 #pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        const int nk = kk + q;
+                    for (int q = 0; q < NQ; ++q) {
+                        const int at = kk * NQ + q, nk = q + 1 == NQ ? kk + 1 : kk, nq = (q + 1) % NQ;
                         __builtin_amdgcn_sched_barrier(0);
-                        p[q ^ 1] = update::products16x64(ev[(nk >> 2) & 1][nk & 3], u[(nk / KB) & 1][nk % KB][q ^ 1]);
+                        p[(at + 1) & 1] = update::products16x64(ev[(nk >> 2) & 1][nk & 3], u[(nk / KB) & 1][nk % KB][nq]);
                         __builtin_amdgcn_sched_barrier(0);
-                        v[q] = v[q] - p[q];
+                        v[q] = v[q] - p[at & 1];
                         asm volatile("" : "+v"(v[q]));         // here, and not behind the next products
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -291,23 +297,24 @@ __device__ __forceinline__ int update_behind(float* __restrict__ Wrows, const fl
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
-                    for (int b = 0; b < 8; ++b) W.store(v[b >> 2][4 * (b & 3) + r], first, (rt + r) * pitch + 4 * (c0 + 16 * b));
+                    for (int b = 0; b < 4 * NQ; ++b) W.store(v[b >> 2][4 * (b & 3) + r], first, (rt + r) * pitch + 4 * (c0 + 16 * b));
             } else {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
-                    for (int b = 0; b < 8; ++b)
+                    for (int b = 0; b < 4 * NQ; ++b)
                         if (4 * (lane_s >> 4) + r < rows_here && 16 * b + (lane_s & 15) < cols_here)
                             W.store(v[b >> 2][4 * (b & 3) + r], first, (rt + r) * pitch + 4 * (c0 + 16 * b));
             }
         }
         if (!more) return taken;
         item = then;
-        ucol[0] = ucol_next[0];
-        ucol[1] = ucol_next[1];
         e_row = e_next;
-        v[0] = v_next[0];
-        v[1] = v_next[1];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            ucol[q] = ucol_next[q];
+            v[q] = v_next[q];
+        }
     }
 }
 
@@ -679,6 +686,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
     constexpr int CPL = R <= 8 ? 4 : 2, RT = R <= 16 ? R : R / 2, ITEM = RT == 16 ? 128 : 64 * CPL;
     constexpr int HELPERS_ALL = CHAINS<R> * HELPERS<R>;
     constexpr int PIECES_AT = 1 + Strip<R>::COUNT;             // the first piece of the update in a block's list
+    constexpr int NARROW = R == 16 ? 14 : 4;                   // pieces cut in two
     extern __shared__ __align__(16) char smem[];
     Lds<R>& lds = *reinterpret_cast<Lds<R>*>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -749,7 +757,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
 
         // A list for the waves that are free: the next block's corner and parameters; the strips of its columns, which get the errors
         // of the last block and then this one's, sub-block by sub-block; pieces of the last block's update of the columns behind it.
-        const int n_items = PIECES_AT + (blk > 0 && far < in ? (in - far + ITEM - 1) / ITEM * (R / RT) : 0);
+        // On the matrix cores the last pieces are half as wide, or those who end first would wait for a whole one (a piece takes 18 us).  Whole
+        // calls, us, none / 4 / 8 / 14 / all pieces halved: 16 rows, 4096 x 4096 1732 / 1672 / 1632 / 1629 / 1635, 3900 x 2048 629 / 574 / 560 / 552 /
+        // 550; 32 rows, 8100 x 3300 2208 / 2143 / 2144 / 2154 / 2183 (4 of them are 8 items there).
+        const int n_far = blk > 0 && far < in ? in - far : 0, halves = R / RT;
+        const int wide = RT == 16 ? max(0, (n_far + ITEM - 1) / ITEM - NARROW) : (n_far + ITEM - 1) / ITEM;
+        const int narrow_at = PIECES_AT + wide * halves, n_items = narrow_at + (max(0, n_far - wide * ITEM) + ITEM / 2 - 1) / (ITEM / 2) * halves;
         int* next = &lds.next[blk & 1];
         auto take = [&] {
             int item = 0;
@@ -764,8 +777,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
         while (item < n_items) {
             if (item >= PIECES_AT) {
                 if constexpr (RT == 16) {
-                    item = update_behind<R>(Wrows, U, es_last, n_rows, in, int64_t(i1) - GB, far, item - PIECES_AT, n_items - PIECES_AT,
-                                            [&] { return take() - PIECES_AT; }) + PIECES_AT;
+                    if (item < narrow_at)
+                        item = update_behind<R, 2>(Wrows, U, es_last, n_rows, in, int64_t(i1) - GB, far, item - PIECES_AT, narrow_at - PIECES_AT,
+                                                   [&] { return take() - PIECES_AT; }) + PIECES_AT;
+                    else
+                        item = update_behind<R, 1>(Wrows, U, es_last, n_rows, in, int64_t(i1) - GB, far + wide * ITEM, item - narrow_at,
+                                                   n_items - narrow_at, [&] { return take() - narrow_at; }) + narrow_at;
                 } else {
                     const int piece = item - PIECES_AT;
                     const int rt = R == RT ? 0 : (piece & 1) * RT, cc = R == RT ? piece : piece >> 1;

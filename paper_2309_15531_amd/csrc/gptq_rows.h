@@ -861,16 +861,16 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
     }
 }
 
-// Which form and how many rows per workgroup: the least of the models below, whose constants (us) are fitted to whole calls of 1341
-// sizes (8 to 152064 rows, 16 to 28672 channels, a quarter of them no multiple of 16; 2 to 4 bits), in launches per block and with every
-// number of rows within 1.3 of the best.  What they choose is 0.2 % slower than the best on average (0.1 % from 128 channels on) and
-// 9 % at worst, 14 % below 128 channels, where a call is 17 to 60 us.  They compare; neither estimates the call, which holds two
-// permuting copies as well.  The lines they draw, us, one launch [rows per workgroup] / a launch per block:
-//   rows in one round of workgroups   2048 x 2048  496 [8] / 1103      4096 x 4096  1729 [16] / 2659   8192 x 1024  385 [32] / 613
-//   more rows than that               9216 x 512   336 [24] / 295      28672 x 1024  1471 [32] / 1414  100000 x 256  1083 [32] / 809
-//   rounds of 32 rows nearly full     6676 x 384   141 [32] / 211      16384 x 2159  2216 [32] / 2652  40000 x 1000  1832 [32] / 2024
-//   many channels, updates dear       8704 x 8192  17220 [12] / 13210  5632 x 11008  17650 [24] / 15520  8 x 16384  10030 [4] / 8760
-//   rows per workgroup                3072 x 3072  1067 [12], 1102 [16]   50000 x 1280  4129 [24], 3515 [32]   12288 x 6144  12200 [24], 10373 [16]
+// Which form and how many rows per workgroup: the least of the models below, whose constants (us) were fitted to whole calls of 1341
+// sizes when the step from block to block was not beside the chain, and the choice of 8 rows since.  They compare; neither
+// estimates a call.  With the kernels as they are, over 161 sizes of up to 8192 rows (128 to 8192 channels) what they choose is 0.2 % slower
+// than the best on average and 9 % at worst (1816 x 128).  Above one round of 32 rows they are late in going back to one launch (10
+// sizes: 15 % on average): the launches per block have not become faster.  us, one launch [rows per workgroup] / a launch per block:
+//   rows in one round of workgroups   2048 x 2048  424 [8] / 1187      4096 x 4096  1657 [16] / 2833   8192 x 512   129 [32] / 302
+//   rows per workgroup                1888 x 304   50 [8], 58 [16]     3072 x 3072  978 [12], 1007 [16]  1024 x 4096  705 [4], 1099 [8]
+//   rounds of 32 rows nearly full     16384 x 1024  607 [32] / 835     12288 x 1024  548 [24] / 713
+//   more rows than that, late         20000 x 256  165 [32] / 247      28672 x 1024  1187 [32] / 1487   8208 x 672  336 [16] / 415
+//   many channels, updates dear (as measured before)   8704 x 8192  17220 [12] / 13210  5632 x 11008  17650 [24] / 15520
 //
 // In one launch: rounds of workgroups, each of which takes, block by block, the longer of its chain and the update of the
 // columns behind it, and a step to the next block.  With 16 and 32 rows the update's products are on the matrix cores, with 12 and
@@ -879,7 +879,7 @@ struct Parts {
     int rows;
     double chain, step, column;        // of a block; to the next one; of a block's update per column
 };
-constexpr Parts PARTS[] = {{4, 10.5, 11.4, 7.1e-3},  {8, 12.0, 14.6, 11.4e-3},  {12, 12.4, 15.6, 16.1e-3},
+constexpr Parts PARTS[] = {{4, 10.5, 11.4, 7.1e-3},  {8, 12.0, 13.6, 11.4e-3},  {12, 12.4, 15.6, 16.1e-3},
                            {16, 9.3, 16.7, 18.2e-3}, {24, 18.8, 18.4, 32.6e-3}, {32, 18.2, 19.2, 37.5e-3}};
 
 inline double rows_us(const Parts& p, int64_t out, int64_t in) {

@@ -16,7 +16,7 @@
 enum {
     WS_HESS_PART = 0,   // split-K partial tiles of the Gram matrix
     WS_ERR_PART,        // per-column-block partial row losses
-    WS_ERR_SMALL,       // the same of small layers (one size for all calls)
+    WS_ERR_SMALL,       // the same of tiles of 64 and 128 (one size for all calls)
     WS_DW16,            // fp16 column-scaled copy of dW
     WS_HS,              // prepared fp16 H when the caller passes the fp32 one
     WS_HMETA,           // column scales and diagonal of the above

@@ -86,6 +86,124 @@ __global__ __launch_bounds__(256) void error_prologue(SrcBatch src, int dW_dtype
     if (threadIdx.x == 0) diag[o] = s_red[0];
 }
 
+// The row sums of a wave's 64 columns (from col0) x 64 rows (from row0), accumulators as in the MFMA mapping with Hs as the first operand.
+// The entries of dW' they need: rows row0 + 32 j + lane % 32, columns col0 + 32 i + 8 g + 4 (lane / 32) ..+3.
+__device__ __forceinline__ void row_entries(const __half* __restrict__ A, int64_t col0, int64_t row0, int64_t out, int64_t in, uint2 (&aw)[2][4][2]) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int64_t n0 = col0 + 32 * i + 8 * g + 4 * (lane >> 5);
+                aw[i][g][j] = n0 < in ? *reinterpret_cast<const uint2*>(A + score_index(min(row0 + 32 * j + (lane & 31), out - 1), n0, out, in))
+                                      : make_uint2(0u, 0u);
+            }
+}
+// With hmeta_diag (column scales, diag H) half the diagonal term as well.
+__device__ __forceinline__ void row_sums(const floatx16 (&acc)[2][2], const uint2 (&aw)[2][4][2], int64_t col0, int64_t in,
+                                         const float* __restrict__ hmeta_diag, float (&sum)[2]) {
+    const int lh = (threadIdx.x & 63) >> 5;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int64_t n0 = col0 + 32 * i + 8 * g + 4 * lh;
+            if (n0 >= in) continue;                            // in % 8 == 0: the four columns are inside together
+            float hq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (hmeta_diag) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    // d = 2^e: the bit pattern of 1/d is 0x7F000000 minus that of d
+                    const float r = __uint_as_float(0x7F000000u - __float_as_uint(hmeta_diag[n0 + e]));
+                    hq[e] = 0.5f * hmeta_diag[in + n0 + e] * r * r;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float2 a = __half22float2(*reinterpret_cast<const __half2*>(&aw[i][g][j].x));
+                const float2 b = __half22float2(*reinterpret_cast<const __half2*>(&aw[i][g][j].y));
+                sum[j] += (acc[i][j][4 * g + 0] + hq[0] * a.x) * a.x;
+                sum[j] += (acc[i][j][4 * g + 1] + hq[1] * a.y) * a.y;
+                sum[j] += (acc[i][j][4 * g + 2] + hq[2] * b.x) * b.x;
+                sum[j] += (acc[i][j][4 * g + 3] + hq[3] * b.y) * b.y;
+            }
+        }
+}
+
+constexpr int MID_TILE = 128;
+
+// The tile kernel of middle-sized layers: 128 columns of Hs x 128 rows of dW per workgroup, 64 x 64 per wave, 64 of the contraction per stage
+// through 32 KB of LDS, the next stage's operands on their way in registers.  A tile's stages follow one another at the L2's latency (0.8 us
+// each with two or three tiles on a compute unit), which is what bounds these layers: contractions are cut into chunks of `cut` column blocks, and
+// three workgroups share a compute unit, so that one's barriers and epilogue are another's products.  Row-major rows come in pieces of 128 bytes,
+// the DMA kernel's in pieces of 64 (2 x 1720 x 2760 row-major 73 us there and 2 x 1720 x 2752 blocked 52; here 59 and 53).  The rows and candidates
+// of a slot are neighbours in the grid, the longest slots first, and each is on the XCD that has it in every slot, so that an XCD reads an eighth of
+// dW (dealt without that 1 x 7008 x 2280 takes 88 us instead of 71; slots dealt to XCDs in runs, 2 x 1720 x 2760 in whole contractions 97, not 66).
+__global__ __launch_bounds__(256, 3) void error_mid(edma::Batch batch, const __half* __restrict__ Hs, int64_t out, int64_t in,
+                                                    const float* __restrict__ hmeta_diag, float* __restrict__ part, int cut, int n_slots, int n_pairs) {
+    constexpr int N = MID_TILE * 8 / THREADS;                  // 16-byte pieces of an operand's stage per thread
+    __shared__ __align__(16) char sN[MID_TILE * ROW_BYTES], sO[MID_TILE * ROW_BYTES];
+    __shared__ float s_rows[4][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+    const int id = blockIdx.x, slot = id / n_pairs, nth = id - slot * n_pairs;
+    const int pair = nth < (n_pairs & ~7) ? (nth & ~7) | (id & 7) : nth;       // eight consecutive ids are on the eight XCDs
+    const int MB = static_cast<int>((out + MID_TILE - 1) / MID_TILE), nb = static_cast<int>((in + MID_TILE - 1) / MID_TILE);
+    const int cand = pair / MB;
+    int chunk = 0, back = slot;                                // slots: chunk 0 of the column blocks from the last, chunk 1 of those that have one, ...
+    for (; back >= nb - cut * chunk; ++chunk) back -= nb - cut * chunk;
+    const __half* __restrict__ A = batch.A[cand];
+    const int64_t col0 = int64_t(nb - 1 - back) * MID_TILE, row0 = int64_t(pair - cand * MB) * MID_TILE;
+    const int k_end = static_cast<int>(min(in, min(col0 + MID_TILE, int64_t(chunk + 1) * cut * MID_TILE)));
+    const int s_begin = chunk * cut * (MID_TILE / KT), s_end = (k_end + KT - 1) / KT;
+    const int c = tid & 7, r0 = tid >> 3;
+    const __half* pn[N];
+    const __half* po[N];
+#pragma unroll
+    for (int p = 0; p < N; ++p) {                              // rows past the end: read again, never used
+        pn[p] = Hs + score_index(min(col0 + r0 + 32 * p, in - 1), 0, in, in) + (score_blocked(in) ? (c >> 2) * (256 * 32) + 8 * (c & 3) : 8 * c);
+        po[p] = A + score_index(min(row0 + r0 + 32 * p, out - 1), 0, out, in) + (score_blocked(in) ? (c >> 2) * (256 * 32) + 8 * (c & 3) : 8 * c);
+    }
+    const int64_t step = score_blocked(in) ? KT / 32 * (256 * 32) : KT;
+    uint4 rn[N], ro[N];
+    auto fetch = [&](int s) {
+        const bool have = KT * s + 8 * c < in;                 // in % 8 == 0
+#pragma unroll
+        for (int p = 0; p < N; ++p) {
+            rn[p] = have ? *reinterpret_cast<const uint4*>(pn[p] + s * step) : make_uint4(0, 0, 0, 0);
+            ro[p] = have ? *reinterpret_cast<const uint4*>(po[p] + s * step) : make_uint4(0, 0, 0, 0);
+        }
+    };
+    floatx16 acc[2][2] = {};
+    fetch(s_begin);
+#pragma unroll 1
+    for (int s = s_begin; s < s_end; ++s) {
+#pragma unroll
+        for (int p = 0; p < N; ++p) {
+            *reinterpret_cast<uint4*>(sN + lds_off(r0 + 32 * p, c)) = rn[p];
+            *reinterpret_cast<uint4*>(sO + lds_off(r0 + 32 * p, c)) = ro[p];
+        }
+        __syncthreads();
+        if (s + 1 < s_end) fetch(s + 1);
+        mma_stage<2, 2>(sN, sO, 64 * wm, 64 * wn, lane, acc);
+        __syncthreads();
+    }
+    uint2 aw[2][4][2];
+    row_entries(A, col0 + 64 * wm, row0 + 64 * wn, out, in, aw);
+    float sum[2] = {0.0f, 0.0f};
+    row_sums(acc, aw, col0 + 64 * wm, in, chunk == 0 ? hmeta_diag : nullptr, sum);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const float v = sum[j] + __shfl_xor(sum[j], 32, 64);
+        if (lane < 32) s_rows[wave][32 * j + lane] = v;
+    }
+    __syncthreads();
+    const int64_t o = row0 + tid;
+    if (tid < MID_TILE && o < out)
+        part[(int64_t(cand) * n_slots + slot) * out + o] = s_rows[tid >> 6][tid & 63] + s_rows[2 + (tid >> 6)][tid & 63];
+}
+
 constexpr int SMALL_TILE = 64;
 
 // The tile kernel of small layers: no LDS, the operands' fragments straight from memory (they sit in the L2), tiles of 64 columns of
@@ -128,18 +246,8 @@ __global__ __launch_bounds__(256) void error_small(edma::Batch batch, const __ha
 #pragma unroll
         for (int b = 0; b < AHEAD; ++b)
             if (b < mine) fetch(b, b);
-        // the entries of dW' that the row sums need: rows row0 + 32 j + l32, columns col0 + 32 i + 8 g + 4 lh ..+3
         uint2 aw[2][4][2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int64_t n0 = col0 + 32 * i + 8 * g + 4 * lh;
-                    aw[i][g][j] = n0 < in ? *reinterpret_cast<const uint2*>(A + score_index(min(row0 + 32 * j + l32, out - 1), n0, out, in))
-                                          : make_uint2(0u, 0u);
-                }
+        row_entries(A, col0, row0, out, in, aw);
         floatx16 acc[2][2] = {};
         for (int s = 0; s < mine; s += AHEAD) {
 #pragma unroll
@@ -154,31 +262,7 @@ __global__ __launch_bounds__(256) void error_small(edma::Batch batch, const __ha
                 }
             }
         }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int64_t n0 = col0 + 32 * i + 8 * g + 4 * lh;
-                if (n0 >= in) continue;                        // in % 8 == 0: the four columns are inside together
-                float hq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (hmeta_diag && wave == 0) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        // d = 2^e: the bit pattern of 1/d is 0x7F000000 minus that of d
-                        const float r = __uint_as_float(0x7F000000u - __float_as_uint(hmeta_diag[n0 + e]));
-                        hq[e] = 0.5f * hmeta_diag[in + n0 + e] * r * r;
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const float2 a = __half22float2(*reinterpret_cast<const __half2*>(&aw[i][g][j].x));
-                    const float2 b = __half22float2(*reinterpret_cast<const __half2*>(&aw[i][g][j].y));
-                    sum[j] += (acc[i][j][4 * g + 0] + hq[0] * a.x) * a.x;
-                    sum[j] += (acc[i][j][4 * g + 1] + hq[1] * a.y) * a.y;
-                    sum[j] += (acc[i][j][4 * g + 2] + hq[2] * b.x) * b.x;
-                    sum[j] += (acc[i][j][4 * g + 3] + hq[3] * b.y) * b.y;
-                }
-            }
+        row_sums(acc, aw, col0, in, wave == 0 ? hmeta_diag : nullptr, sum);
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -339,11 +423,12 @@ void error_slots_finest(int nc, int MB, int NB, int& kb, int& n_slots) {
 // 2 x 256 x 16384 the choice is 1.1 % slower than the best chunk on average and 10 % at worst.  Against the finest cut:
 // 1 x 4096 x 4096 97 -> 75 us, 2 x 1720 x 2760 109 -> 66, 2 x 2048 x 2048 50 -> 33, 1 x 8192 x 1024 34 -> 25,
 // 2 x 1024 x 4096 66 -> 48, 1 x 256 x 11008 71 -> 41.  Choosing takes the host up to 1 us at ordinary sizes and 11 us at
-// 1 x 64 x 28672, on every call (profiles/scoring_chunks.md).
-void error_slots(int nc, int MB, int NB, int64_t in, int& kb, int& n_slots) {
+// 1 x 64 x 28672, on every call (profiles/scoring_chunks.md).  Returns the estimate of the chosen cut (with `estimate` for
+// whole contractions too).
+int error_slots(int nc, int MB, int NB, int64_t in, bool estimate, int& kb, int& n_slots) {
     constexpr int FIXED = 2, BLOCK = 5, EPILOGUE = 4;
     error_slots_finest(nc, MB, NB, kb, n_slots);
-    if (kb == NB) return;
+    if (kb == NB && !estimate) return 0;
     const int kb_min = kb, pairs = nc * MB;
     const bool in_loop = score_blocked(in) && in % edma::BT == 0;
     int best = 0;
@@ -380,21 +465,55 @@ void error_slots(int nc, int MB, int NB, int64_t in, int& kb, int& n_slots) {
             n_slots = slot;
         }
     }
+    return best;
 }
 
-// Small layers: by the steps of 64 columns x 64 rows x 64 of the contraction that a launch takes.  Scoring calls, us, DMA kernel / small:
-//     80 (2 x 256 x 256)     18.2 / 12.4      4352 (2 x 1024 x 1024) 26.7 / 20.2      4992 (2 x 2048 x 768)  24.5 / 28.3
-//    576 (2 x 512 x 512)     21.1 / 13.6      4224 (2 x 256 x 2048)  22.1 / 19.3      7488 (8 x 768 x 768)   24.9 / 35.3
-//   2304 (2 x 2048 x 512)    22.1 / 16.9      4608 (2 x 4096 x 512)  23.1 / 28.1     33792 (2 x 2048 x 2048) 40.8 / 90.7
-// Row-major operands cost the DMA kernel more: 4352 (2 x 1000 x 1000) 33.5 / 23.8, 5566 (2 x 700 x 1400) 31.4 / 28.9,
-// 7220 (2 x 1200 x 1200) 34.6 / 37.7.
-constexpr int64_t SMALL_STEPS = 4400, SMALL_STEPS_ROW_MAJOR = 5600;
-// Row partials and diagonal terms of the largest of these launches (one slot; with s slots a launch has 1 / s of the rows).
-constexpr size_t SMALL_SCRATCH_BYTES = size_t(SMALL_TILE) * 2 * SMALL_STEPS_ROW_MAJOR * sizeof(float);
-int error_small_slots(int64_t in) { return static_cast<int>((in + SMALL_TILE - 1) / SMALL_TILE); }
-bool error_is_small(int nc, int64_t out, int64_t in) {
-    const int64_t nb = error_small_slots(in);
-    return nc * ((out + SMALL_TILE - 1) / SMALL_TILE) * (nb * (nb + 1) / 2) <= (score_blocked(in) ? SMALL_STEPS : SMALL_STEPS_ROW_MAJOR);
+// The launch of a layer's tiles: tile edge, contraction chunk in blocks of that edge, (chunk, column block) slots.
+struct ErrPlan {
+    int tile, cut, n_slots;
+};
+constexpr int64_t SMALL_STEPS = 1200, MID_TILES = 2048, MID_WORK = 20000;
+// Row partials and diagonal terms of the largest launches of the smaller tiles (one slot; with s slots a launch has 1 / s of the rows).
+constexpr size_t SMALL_SCRATCH_BYTES = 2 * size_t(MID_TILE) * MID_TILES * sizeof(float);
+static_assert(SMALL_TILE * SMALL_STEPS <= MID_TILE * MID_TILES, "the scratch has room for the tiles of 64");
+
+// 64: up to 1200 steps of 64 columns x 64 rows x 64 of the contraction, and 10 of these in a row, where little but latency is left.  Scoring
+// calls of n candidates, us, tiles of 64 / 128 / 256: 2 x 256 x 256 12.7 / 13.5 / 18.9, 2 x 504 x 504 13.4 / 14.7 / 24.0, 2 x 512 x 512
+// 13.8 / 14.6 / 20.9; beyond, 1 x 1000 x 1000 14.5 / 14.7 / 25.8, 2 x 4000 x 264 18.2 / 14.9 / 26.3, 2 x 200 x 800 16.7 / 16.1 / 22.2.
+// 128: the chunk whose estimate, 5 per round of 256 tiles and 7 per column block that a compute unit has to go through one after the other or
+// in all, is the least (of the chunks 1 .. 12, 16 .. of 63 launches, up to 2 x 3000 x 3000, the choice is 3 % slower than the best on average),
+// if it is ahead of the DMA kernel's estimate.  The lines between the two are fits to 165 launches, blocked (time = 12.7 + 0.203 x this against
+// 9.9 + 0.081 x the DMA kernel's) and row-major (12.8 + 0.229 x against 12.0 + 0.096 x), set 10 and 5 % to the DMA kernel's side: no measured
+// launch is more than 2 % slower than there.  DMA kernel / 128, blocked: 2 x 1024 x 1024 25.8 / 17.0, 2 x 1536 x 1536 32.5 / 25.5, 1 x 2560 x 2560
+// 50.0 / 41.9, 2 x 5816 x 1056 60.2 / 36.8, but 2 x 8192 x 1024 36.4 / 41.5, 1 x 1024 x 4096 36.7 / 41.9 (tiles of 256 fit, in one round);
+// row-major: 2 x 1000 x 1000 34.3 / 17.3, 2 x 1448 x 1448 44.2 / 25.8, 2 x 1720 x 2760 73 / 59, 1 x 7008 x 2280 86 / 71, 1 x 60000 x 504 93.7 / 54.4,
+// but 1 x 1000 x 6000 72 / 84.
+ErrPlan error_plan(int nc, int64_t out, int64_t in) {
+    const int64_t nb64 = (in + SMALL_TILE - 1) / SMALL_TILE;
+    if (nc * ((out + SMALL_TILE - 1) / SMALL_TILE) * (nb64 * (nb64 + 1) / 2) <= SMALL_STEPS && nb64 <= 10)
+        return {SMALL_TILE, static_cast<int>(nb64), static_cast<int>(nb64)};
+    constexpr int BT = edma::BT;
+    const int MB = static_cast<int>((out + BT - 1) / BT), NB = static_cast<int>((in + BT - 1) / BT);
+    const int64_t nb = (in + MID_TILE - 1) / MID_TILE, pairs = nc * ((out + MID_TILE - 1) / MID_TILE), work = pairs * (nb * (nb + 1) / 2);
+    const bool mid = pairs * nb <= MID_TILES && work <= MID_WORK;
+    ErrPlan dma = {BT, 0, 0};
+    const int64_t dma_cost = error_slots(nc, MB, NB, in, mid, dma.cut, dma.n_slots);
+    if (!mid) return dma;
+    ErrPlan best = {};
+    int64_t best_cost = 0;                                     // x 256
+    for (int64_t cut = 1; cut <= nb; ++cut) {
+        int64_t n_slots = 0;
+        for (int64_t n = nb; n > 0; n -= cut) n_slots += n;
+        const int64_t tiles = pairs * n_slots;
+        if (tiles > MID_TILES) continue;
+        const int64_t cost = 5 * 256 * ((tiles + 255) / 256) + 7 * std::max(work, 256 * cut);
+        if (best.tile == 0 || cost < best_cost) {
+            best = {MID_TILE, static_cast<int>(cut), static_cast<int>(n_slots)};
+            best_cost = cost;
+        }
+    }
+    const bool ahead = score_blocked(in) ? 14 * best_cost < 256 * (5 * dma_cost - 260) : 5 * best_cost < 256 * (2 * dma_cost - 30);
+    return ahead ? best : dma;
 }
 
 int set_error_attr(adadim_ctx* ctx) {
@@ -412,10 +531,10 @@ int set_error_attr(adadim_ctx* ctx) {
 // call's loss array (for the fused selection, taken when best_dev is given).
 int run_error_batch(adadim_ctx* ctx, int nc, const void* const* dW, int dW_dtype, int64_t out, int64_t in,
                     const __half* Hs, const float* hmeta, float* loss_rows, float* losses, const float* losses_all,
-                    int n_all, int32_t* best_dev, const ErrScratch& sc, bool small, int kb, int n_slots) {
+                    int n_all, int32_t* best_dev, const ErrScratch& sc, const ErrPlan& plan) {
     constexpr int BT = edma::BT;
     const int MB = static_cast<int>((out + BT - 1) / BT), NB = static_cast<int>((in + BT - 1) / BT);
-    const int kc_len = kb * BT;
+    const int n_slots = plan.n_slots;
     const unsigned fin_blocks = static_cast<unsigned>((out + 255) / 256);
     SrcBatch src;
     edma::Batch batch;
@@ -435,17 +554,23 @@ int run_error_batch(adadim_ctx* ctx, int nc, const void* const* dW, int dW_dtype
                            dW_dtype, out, in, hmeta, sc.dW16, sc.diag);
     }
     ADADIM_LAUNCH_CHECK(ctx, "error_prologue");
-    if (small) {
+    if (plan.tile != BT) {
         ProfScope prof(ctx, "error_tiles");
-        const dim3 grid(static_cast<unsigned>(n_slots), static_cast<unsigned>((out + SMALL_TILE - 1) / SMALL_TILE), static_cast<unsigned>(nc));
-        hipLaunchKernelGGL(error_small, grid, dim3(256), 0, ctx->stream, batch, Hs, out, in, direct ? hmeta : nullptr, sc.part);
+        if (plan.tile == MID_TILE) {
+            const int n_pairs = nc * static_cast<int>((out + MID_TILE - 1) / MID_TILE);
+            hipLaunchKernelGGL(error_mid, dim3(static_cast<unsigned>(n_slots * n_pairs)), dim3(256), 0, ctx->stream, batch, Hs, out, in,
+                               direct ? hmeta : nullptr, sc.part, plan.cut, n_slots, n_pairs);
+        } else {
+            const dim3 grid(static_cast<unsigned>(n_slots), static_cast<unsigned>((out + SMALL_TILE - 1) / SMALL_TILE), static_cast<unsigned>(nc));
+            hipLaunchKernelGGL(error_small, grid, dim3(256), 0, ctx->stream, batch, Hs, out, in, direct ? hmeta : nullptr, sc.part);
+        }
     } else {
         ProfScope prof(ctx, "error_tiles");
         // units of 4 slots x 8 (candidate, row block) pairs, 32 workgroups each, dealt to 8 XCDs
         const int n_units = ((n_slots + 3) / 4) * ((nc * MB + 7) / 8);
         const unsigned grid = 8u * static_cast<unsigned>((n_units + 7) / 8) * 32u;
         hipLaunchKernelGGL(edma::error_tiles_dma<0>, dim3(grid), dim3(256), edma::SMEM_BYTES, ctx->stream, batch, Hs,
-                           out, in, MB, NB, kc_len, n_slots, sc.zero16, direct ? hmeta : nullptr, sc.part);
+                           out, in, MB, NB, plan.cut * BT, n_slots, sc.zero16, direct ? hmeta : nullptr, sc.part);
     }
     ADADIM_LAUNCH_CHECK(ctx, "error_tiles");
     {
@@ -484,19 +609,14 @@ int launch_layer_error(adadim_ctx* ctx, int n, const void* const* dW, int dW_dty
         error_slots_finest(nc, MB, NB, kb, n_slots);
         // scratch: per candidate [n_slots, out] row partials; then per candidate [out] diagonal terms.  Room for the finest cut,
         // so that which calls can be recorded after which does not hang on the chunk that is chosen, and of a size of its own for
-        // small layers, whatever this one is.
+        // the smaller tiles, whatever this call takes.
         sc.part = static_cast<float*>(adadim_workspace(
             ctx, WS_ERR_PART, size_t(nc) * size_t(n_slots + 1) * size_t(out) * sizeof(float)));
         float* const small_part = static_cast<float*>(adadim_workspace(ctx, WS_ERR_SMALL, SMALL_SCRATCH_BYTES));
         if (!sc.part || !small_part) return ADADIM_EHIP;
-        const bool small = error_is_small(nc, out, in);
-        if (small) {
-            n_slots = error_small_slots(in);
-            sc.part = small_part;
-        } else {
-            error_slots(nc, MB, NB, in, kb, n_slots);
-        }
-        sc.diag = sc.part + size_t(nc) * size_t(n_slots) * size_t(out);
+        const ErrPlan plan = error_plan(nc, out, in);
+        if (plan.tile != BT) sc.part = small_part;
+        sc.diag = sc.part + size_t(nc) * size_t(plan.n_slots) * size_t(out);
         // scratch of the final reduction: per candidate one double per 256 rows; then the tickets
         const unsigned fin_blocks = static_cast<unsigned>((out + 255) / 256);
         const size_t fin_bytes = size_t(edma::MAX_BATCH) * fin_blocks * sizeof(double) + 256;
@@ -517,7 +637,7 @@ int launch_layer_error(adadim_ctx* ctx, int n, const void* const* dW, int dW_dty
         }
         rc = run_error_batch(ctx, nc, dW + c0, dW_dtype, out, in, Hs, hmeta,
                              loss_rows ? loss_rows + size_t(c0) * size_t(out) : nullptr, losses + c0, losses, n,
-                             c0 + nc == n ? best_dev : nullptr, sc, small, kb, n_slots);
+                             c0 + nc == n ? best_dev : nullptr, sc, plan);
         if (rc != ADADIM_OK) return rc;
     }
     return ADADIM_OK;
@@ -580,19 +700,14 @@ int64_t launch_layer_error_noalloc_bytes(int n, int64_t out, int64_t in) {
     const int MB = static_cast<int>((out + BT - 1) / BT), NB = static_cast<int>((in + BT - 1) / BT);
     int kb = 0, n_slots = 0;
     error_slots_finest(n, MB, NB, kb, n_slots);
-    if (error_is_small(n, out, in)) n_slots = error_small_slots(in);
+    if (const ErrPlan plan = error_plan(n, out, in); plan.tile != BT) n_slots = plan.n_slots;
     const int64_t fin_blocks = (out + 255) / 256;
     return 512 + int64_t(edma::MAX_BATCH) * fin_blocks * 8 + int64_t(n) * n_slots * out * 4;
 }
 
 int launch_layer_error_noalloc(adadim_ctx* ctx, int n, const void* const* dW, int64_t out, int64_t in, const __half* Hs,
                                const float* hmeta, float* loss_rows, float* losses, int32_t* best_dev) {
-    constexpr int BT = edma::BT;
-    const int MB = static_cast<int>((out + BT - 1) / BT), NB = static_cast<int>((in + BT - 1) / BT);
-    int kb = 0, n_slots = 0;
-    const bool small = error_is_small(n, out, in);
-    if (small) n_slots = error_small_slots(in);
-    else error_slots(n, MB, NB, in, kb, n_slots);
+    const ErrPlan plan = error_plan(n, out, in);
     const int64_t need = launch_layer_error_noalloc_bytes(n, out, in);
     if (need > int64_t(NOALLOC_SCRATCH_BYTES))
         return adadim_fail(ctx, ADADIM_EINVAL,
@@ -619,5 +734,5 @@ int launch_layer_error_noalloc(adadim_ctx* ctx, int n, const void* const* dW, in
     sc.diag = nullptr;
     sc.dW16 = nullptr;
     return run_error_batch(ctx, n, dW, ADADIM_DW_F16_SCALED, out, in, Hs, hmeta, loss_rows, losses, losses, n, best_dev, sc,
-                           small, kb, n_slots);
+                           plan);
 }

@@ -362,10 +362,13 @@ def test_batch_error_with_cut_contractions(ctx, nc, out_f, in_f):
 
 
 @pytest.mark.parametrize("nc,out_f,in_f", [(1, 1, 8), (2, 65, 72), (1, 64, 64), (8, 63, 520), (2, 130, 1000), (1, 5, 1208), (3, 200, 64),
-                                           (1, 257, 1376)])
+                                           (1, 257, 1376), (2, 513, 1000), (1, 1025, 1288), (4, 130, 1544), (1, 7, 4096), (8, 256, 2048),
+                                           (1, 16384, 256), (2, 9001, 264), (1, 264, 6176), (1, 500, 5000)])
 def test_batch_error_of_small_layers(ctx, nc, out_f, in_f):
-    """Tiles of 64 x 64 with the contraction dealt to four waves: fewer pairs of steps than waves, half pairs, ragged rows and columns, both
-    layouts; column-scaled input against the oracle row by row, and fp32 input, whose diagonal term comes from elsewhere."""
+    """Tiles of 64 x 64 with the contraction dealt to four waves: fewer pairs of steps than waves, half pairs, ragged rows and columns.  Tiles of
+    128 x 128 (from 130 x 1000): chunks of one block, of several, whole contractions, a ragged last stage, chunk and row block, row blocks that are
+    not a multiple of eight.  The last two are the DMA kernel's, whose chunks no smaller layer takes.  Both layouts; column-scaled input against
+    the oracle row by row, and fp32 input, whose diagonal term comes from elsewhere."""
     W = rand_w(out_f, in_f, seed=7 * out_f + in_f)
     X = synth.make_activations(200, in_f, seed=in_f + 1, n_outliers=2, scale_lo=50, scale_hi=100)
     hp = S.PreparedHessian(ctx, in_f).update(dev(X)).prepare()

@@ -160,7 +160,9 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
     };
     // A launch of few blocks is a chain of waits: a batch of loads holds as many partials as most plans have, and the diagonal's are in
     // flight with them (one partial after the other, and the diagonal behind them: Gram matrix with its prepared form, us, 512 wide,
-    // 2048 tokens 25.1 and now 16.6; 768, 3000 tokens 30 and 21; 1024, 8192 tokens 46 and 40; 2760, 3001 tokens 56 and 53).
+    // 2048 tokens 25.1 and now 16.6; 768, 3000 tokens 30 and 21; 1024, 8192 tokens 46 and 40).  The 256-wide kernel's partials, of which a plan has
+    // few, are added as they come (2760, 3001 tokens 55.5 and 53.7; batches of four took 53.1 there but 22.6 -> 23.6 at 1600, 640 tokens,
+    // accumulating): with their registers fewer blocks are resident.
     constexpr int AHEAD = REGMAJOR ? 4 : 8;
     auto runs_of = [&](int tile_r) {
         const int n = gram_plan_parts(plan, tile_r);
@@ -193,11 +195,15 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
             }
         }
     };
-    // (one partial: nothing to have in flight beside it, and blocks this short feel every instruction)
-    const bool single = REGMAJOR && n_parts == 1;
-    if (single) {
-        const float4 f = *reinterpret_cast<const float4*>(part_one + at);
-        v[0] += f.x; v[1] += f.y; v[2] += f.z; v[3] += f.w;
+    if constexpr (REGMAJOR) {
+        if (n_parts > 0) {
+            const float4 f = *reinterpret_cast<const float4*>(part_one + at);
+            v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+        }
+        for (int sp = 1; sp < n_parts; ++sp) {
+            const float4 f = *reinterpret_cast<const float4*>(mine.at(sp) + at);
+            v[0] += f.x; v[1] += f.y; v[2] += f.z; v[3] += f.w;
+        }
     } else {
         fetch(0);
     }
@@ -248,7 +254,7 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
         }
     } else {
         static_assert(!REGMAJOR || BT == 256, "register-major partials come from the 256-wide DMA kernel");
-        for (int s0 = single ? n_parts : 0; s0 < n_parts; s0 += AHEAD) {
+        for (int s0 = REGMAJOR ? n_parts : 0; s0 < n_parts; s0 += AHEAD) {
             if (s0 > 0) fetch(s0);
 #pragma unroll
             for (int q = 0; q < AHEAD; ++q)
@@ -257,7 +263,7 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
                     if (s0 + q < n_parts) v[rr] += p[q][rr];
         }
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) s[ty * 4 + rr][tx] = v[rr];
+        for (int rr = 0; rr < 4; ++rr) s[ty * 4 + rr][tx] = v[rr] + 0.0f;
     }
     __syncthreads();
     if constexpr (PREP) {

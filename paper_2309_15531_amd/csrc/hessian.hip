@@ -49,21 +49,23 @@ __global__ __launch_bounds__(THREADS) void gram_tiles(const __half* __restrict__
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
+    // the ragged stage comes first, as in the 256-wide kernel, while the sums are small
+    const int64_t t_first = t_end - (t_end - t_begin + KT - 1) / KT * KT;
     TransposeStage<BT> ga, gb;
     const int64_t rowA = int64_t(I) * BT, rowB = int64_t(J) * BT;
     if (t_begin < t_end) {
-        ga.load(X, ldx, rowA, in, t_begin, t_end, tid);
-        gb.load(X, ldx, rowB, in, t_begin, t_end, tid);
+        ga.load(X, ldx, rowA, in, t_first, t_begin, tid);
+        gb.load(X, ldx, rowB, in, t_first, t_begin, tid);
         ga.store(sA(0), tid);
         gb.store(sB(0), tid);
     }
     __syncthreads();
     int buf = 0;
-    for (int64_t k0 = t_begin; k0 < t_end; k0 += KT) {
+    for (int64_t k0 = t_first; k0 < t_end; k0 += KT) {
         const bool more = k0 + KT < t_end;
         if (more) {
-            ga.load(X, ldx, rowA, in, k0 + KT, t_end, tid);
-            gb.load(X, ldx, rowB, in, k0 + KT, t_end, tid);
+            ga.load(X, ldx, rowA, in, k0 + KT, t_begin, tid);
+            gb.load(X, ldx, rowB, in, k0 + KT, t_begin, tid);
         }
         mma_stage<TM, TM>(sA(buf), sB(buf), wm * WM, wn * WM, lane, acc);
         if (more) {
@@ -418,72 +420,93 @@ __global__ __launch_bounds__(256) void hprep_scale(const float* __restrict__ H, 
     *reinterpret_cast<uint4*>(Hs + c * 8) = o;
 }
 
+// The 256-wide kernel's plan for these tiles, chosen by simulation (gram_plan.h) and kept per context.
+int wide_plan(adadim_ctx* ctx, int64_t tokens, int n_tiles, bool whole_ok) {
+    for (int k = 0; k < ctx->gram_split_n; ++k)
+        if (ctx->gram_split[k].plan.tokens == tokens && ctx->gram_split[k].plan.n_tiles == n_tiles &&
+            ctx->gram_split[k].whole_ok == whole_ok)
+            return k;
+    const int hit = ctx->gram_split_next;                           // the oldest entry makes room
+    ctx->gram_split[hit].plan = gram_plan_choose(tokens, n_tiles, whole_ok);
+    gram_plan_order(ctx->gram_split[hit].plan, ctx->gram_split[hit].order);
+    ctx->gram_split[hit].whole_ok = whole_ok;
+    ctx->gram_split_next = (hit + 1) % 8;
+    if (ctx->gram_split_n < 8) ++ctx->gram_split_n;
+    return hit;
+}
+
+size_t part_bytes_of(const GramPlan& plan, int bt) {
+    return std::max<size_t>(256, size_t(gram_plan_slots(plan)) * size_t(bt) * bt * sizeof(float));
+}
+
+// Zero-filled source of the 256-wide kernel for rows past the end of the token range: the DMA of a surplus stage reads up to 32 token rows
+// of pitch ldx from it.
+int zero_rows(adadim_ctx* ctx, int64_t ldx, void** zero16) {
+    *zero16 = adadim_workspace(ctx, WS_ZERO, size_t(32) * size_t(ldx) * 2 + 512);
+    if (!*zero16) return ADADIM_EHIP;
+    if (ctx->zero_ready_bytes != ctx->ws_bytes[WS_ZERO]) {
+        const int64_t n = static_cast<int64_t>(ctx->ws_bytes[WS_ZERO] / 4);
+        hipLaunchKernelGGL(zero_f32, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, ctx->stream,
+                           static_cast<float*>(*zero16), n);
+        ADADIM_LAUNCH_CHECK(ctx, "zero_f32");
+        ctx->zero_ready_bytes = ctx->ws_bytes[WS_ZERO];
+    }
+    return ADADIM_OK;
+}
+
+// The 128-wide kernel's grid of (tile, token split): about ceil(workgroups / 256) rounds of stages / n_split stages each, while every split adds
+// one partial tile per tile to write and to read back.  The split count with the lowest estimate (unit: the time of one stage; a partial costs
+// about a fifth of that per split in traffic), of those whose pieces have up to `longest` tokens if there are any.
+GramPlan narrow_plan(int64_t tokens, int n_tiles, int64_t longest) {
+    const int64_t stages = (tokens + KT - 1) / KT;
+    int n_split = 1;
+    double best_cost = 0.0;
+    for (int n = 1; n <= 32 && n <= stages; ++n) {
+        const int64_t per = (stages + n - 1) / n;
+        if (std::min(tokens, per * KT) > longest) continue;
+        const int64_t rounds = (int64_t(n_tiles) * n + 255) / 256;
+        const double cost = double(rounds) * double(per) + 0.19 * double(n) * double(n_tiles) * (128 * 128 / 65536.0);
+        if (best_cost == 0.0 || cost < best_cost) {
+            best_cost = cost;
+            n_split = n;
+        }
+    }
+    const int64_t t_per_split = ((stages + n_split - 1) / n_split) * KT;
+    return {n_tiles, 0, static_cast<int>(tokens / t_per_split), 0, 1, tokens, t_per_split, KT};
+}
+
+int gram_tile_count(int64_t in, int bt) {
+    const int nb = static_cast<int>((in + bt - 1) / bt);
+    return nb * (nb + 1) / 2;
+}
+
 template <int BT>
 int run_gram(adadim_ctx* ctx, const __half* X, int64_t tokens, int64_t in, int64_t ldx, float* H, int accumulate,
-             __half* Hs, float* hmeta) {
+             __half* Hs, float* hmeta, int64_t longest = INT64_MAX, size_t part_bytes = 0) {
     const int nb = static_cast<int>((in + BT - 1) / BT);
     const int n_tiles = nb * (nb + 1) / 2;
-    // The 128-wide kernel takes a grid of (tile, token split): about ceil(workgroups / 256) rounds of stages/n_split
-    // stages each, while every split adds one partial tile per tile to write and to read back.  Take the split
-    // count with the lowest estimate (unit: the time of one stage; a partial costs about a fifth of that per split
-    // in traffic).  The 256-wide kernel's launch is planned by simulation (gram_plan.h); plans are kept per context.
     GramPlan plan;
     const GramOrder* order = nullptr;
     if constexpr (BT == 256) {
-        int hit = -1;
-        for (int k = 0; k < ctx->gram_split_n; ++k)
-            if (ctx->gram_split[k].plan.tokens == tokens && ctx->gram_split[k].plan.n_tiles == n_tiles &&
-                ctx->gram_split[k].whole_ok == (accumulate == 0))
-                hit = k;
-        if (hit < 0) {
-            hit = ctx->gram_split_next;                             // the oldest entry makes room
-            ctx->gram_split[hit].plan = gram_plan_choose(tokens, n_tiles, accumulate == 0);
-            gram_plan_order(ctx->gram_split[hit].plan, ctx->gram_split[hit].order);
-            ctx->gram_split[hit].whole_ok = accumulate == 0;
-            ctx->gram_split_next = (hit + 1) % 8;
-            if (ctx->gram_split_n < 8) ++ctx->gram_split_n;
-        }
+        const int hit = wide_plan(ctx, tokens, n_tiles, accumulate == 0);
         plan = ctx->gram_split[hit].plan;
         order = &ctx->gram_split[hit].order;
     } else {
-        const int64_t stages = (tokens + KT - 1) / KT;
-        int n_split = 1;
-        double best_cost = 0.0;
-        for (int n = 1; n <= 32 && n <= stages; ++n) {
-            const int64_t per = (stages + n - 1) / n;
-            const int64_t rounds = (int64_t(n_tiles) * n + 255) / 256;
-            const double cost = double(rounds) * double(per) + 0.19 * double(n) * double(n_tiles) * (BT * BT / 65536.0);
-            if (n == 1 || cost < best_cost) {
-                best_cost = cost;
-                n_split = n;
-            }
-        }
-        const int64_t t_per_split = ((stages + n_split - 1) / n_split) * KT;
-        plan = {n_tiles, 0, static_cast<int>(tokens / t_per_split), 0, 1, tokens, t_per_split, KT};
+        plan = narrow_plan(tokens, n_tiles, longest);
     }
     const int n_whole = plan.n_whole, n_rest = n_tiles - n_whole;
-    const size_t part_bytes = std::max<size_t>(256, size_t(gram_plan_slots(plan)) * BT * BT * sizeof(float));
-    float* part = static_cast<float*>(adadim_workspace(ctx, WS_HESS_PART, part_bytes));
+    float* part = static_cast<float*>(adadim_workspace(ctx, WS_HESS_PART, std::max(part_bytes, part_bytes_of(plan, BT))));
     if (!part) return ADADIM_EHIP;
 
     if constexpr (BT == 256) {
-        // zero-filled source for rows past the end of the token range: the DMA of a surplus stage
-        // reads up to 32 token rows of pitch ldx from it
-        const size_t zero_bytes = size_t(32) * size_t(ldx) * 2 + 512;
-        void* zero16 = adadim_workspace(ctx, WS_ZERO, zero_bytes);
-        if (!zero16) return ADADIM_EHIP;
+        void* zero16 = nullptr;
+        const int rc = zero_rows(ctx, ldx, &zero16);
+        if (rc != ADADIM_OK) return rc;
         static PerDeviceOnce once;
         ADADIM_HIP_TRY(ctx, once.run([] {
             return hipFuncSetAttribute(reinterpret_cast<const void*>(dma::gram_tiles_dma<2, 2>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, dma::SMEM_BYTES);
         }));
-        if (ctx->zero_ready_bytes != ctx->ws_bytes[WS_ZERO]) {
-            const int64_t n = static_cast<int64_t>(ctx->ws_bytes[WS_ZERO] / 4);
-            hipLaunchKernelGGL(zero_f32, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, ctx->stream,
-                               static_cast<float*>(zero16), n);
-            ADADIM_LAUNCH_CHECK(ctx, "zero_f32");
-            ctx->zero_ready_bytes = ctx->ws_bytes[WS_ZERO];
-        }
         {
             ProfScope prof(ctx, "gram_tiles");
             // 32 workgroups per XCD walking their own items, or one workgroup per item where there is no order
@@ -532,6 +555,29 @@ int run_gram(adadim_ctx* ctx, const __half* X, int64_t tokens, int64_t in, int64
     return ADADIM_OK;
 }
 
+// Which kernel: up to 1024 columns the 128-wide one.  Beyond that it is ahead while there are few tokens: with the preparation, us, 256-wide / 128-wide,
+// 1032 x 64 tokens 15.7 / 12.3, 1200 x 128 16.1 / 14.1, 1280 x 256 18.4 / 16.1, 1448 x 500 22.5 / 20.7, 1600 x 400 24.4 / 23.6, but 1200 x 1000
+// 23.6 / 24.1, 1800 x 500 25.9 / 27.7, 2760 x 64 28.9 / 29.5.
+// The 128-wide kernel then cuts the tokens into pieces no longer than the 256-wide one's, so that the fp32 sums are as short, and takes the
+// 256-wide one's scratch all the same, only where its own fits, so that which call can be recorded after which does not depend on the line.
+int run_gram_of_size(adadim_ctx* ctx, const __half* X, int64_t tokens, int64_t in, int64_t ldx, float* H, int accumulate, __half* Hs,
+                     float* hmeta) {
+    if (in <= 1024) return run_gram<128>(ctx, X, tokens, in, ldx, H, accumulate, Hs, hmeta);
+    const int n_tiles = gram_tile_count(in, 128);
+    if (in <= 1600 && n_tiles * ((tokens + KT - 1) / KT) <= 640) {
+        const GramPlan wide = ctx->gram_split[wide_plan(ctx, tokens, gram_tile_count(in, 256), accumulate == 0)].plan;
+        const size_t bytes = part_bytes_of(wide, 256);
+        const int64_t longest = std::min(tokens, wide.t_per_split);
+        const GramPlan narrow = narrow_plan(tokens, n_tiles, longest);
+        if (wide.n_whole == 0 && part_bytes_of(narrow, 128) <= bytes && std::min(tokens, narrow.t_per_split) <= longest) {
+            void* zero16 = nullptr;
+            const int rc = zero_rows(ctx, ldx, &zero16);
+            return rc != ADADIM_OK ? rc : run_gram<128>(ctx, X, tokens, in, ldx, H, accumulate, Hs, hmeta, longest, bytes);
+        }
+    }
+    return run_gram<256>(ctx, X, tokens, in, ldx, H, accumulate, Hs, hmeta);
+}
+
 }  // namespace
 
 int launch_hessian(adadim_ctx* ctx, const __half* X, int64_t tokens, int64_t in, int64_t ldx, float* H,
@@ -548,8 +594,7 @@ int launch_hessian(adadim_ctx* ctx, const __half* X, int64_t tokens, int64_t in,
         }
         return ADADIM_OK;
     }
-    if (in <= 1024) return run_gram<128>(ctx, X, tokens, in, ldx, H, accumulate, nullptr, nullptr);
-    return run_gram<256>(ctx, X, tokens, in, ldx, H, accumulate, nullptr, nullptr);
+    return run_gram_of_size(ctx, X, tokens, in, ldx, H, accumulate, nullptr, nullptr);
 }
 
 // H = X^T X together with its prepared form (see gram_reduce, PREP)
@@ -559,8 +604,7 @@ int launch_hessian_prepared(adadim_ctx* ctx, const __half* X, int64_t tokens, in
         const int rc = launch_hessian(ctx, X, tokens, in, ldx, H, 0);
         return rc != ADADIM_OK ? rc : launch_hessian_prepare(ctx, H, in, Hs, hmeta);
     }
-    if (in <= 1024) return run_gram<128>(ctx, X, tokens, in, ldx, H, 0, Hs, hmeta);
-    return run_gram<256>(ctx, X, tokens, in, ldx, H, 0, Hs, hmeta);
+    return run_gram_of_size(ctx, X, tokens, in, ldx, H, 0, Hs, hmeta);
 }
 
 // Measurement aid: one launch of the 256-wide tile kernel built with time stamps around every piece.

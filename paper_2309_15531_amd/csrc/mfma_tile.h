@@ -69,7 +69,7 @@ struct DirectStage {
 // Operand whose contraction index is the slow axis in memory: element (row, k)
 // at base[k*ld + row] (the Gram matrix reads X[t, i] with k = t, row = i).
 // Each thread loads an 8(k) x 8(row) block with eight 16-byte loads, transposes
-// it in registers and writes eight 16-byte LDS chunks.
+// it in registers and writes eight 16-byte LDS chunks.  k < k_begin reads as zero.
 template <int ROWS>
 struct TransposeStage {
     static constexpr int IB = ROWS / 8;                       // row blocks per tile
@@ -78,7 +78,7 @@ struct TransposeStage {
     uint4 r[N][8];
 
     __device__ __forceinline__ void load(const __half* __restrict__ base, int64_t ld, int64_t row0,
-                                         int64_t n_rows, int64_t k0, int64_t k_end, int tid) {
+                                         int64_t n_rows, int64_t k0, int64_t k_begin, int tid) {
 #pragma unroll
         for (int p = 0; p < N; ++p) {
             const int b = tid + THREADS * p;
@@ -89,7 +89,7 @@ struct TransposeStage {
             for (int rr = 0; rr < 8; ++rr) {
                 const int64_t k = k0 + tb * 8 + rr;
                 uint4 v = make_uint4(0, 0, 0, 0);
-                if (row_ok && k < k_end) v = *reinterpret_cast<const uint4*>(base + k * ld + row);
+                if (row_ok && k >= k_begin) v = *reinterpret_cast<const uint4*>(base + k * ld + row);
                 r[p][rr] = v;
             }
         }

@@ -241,6 +241,25 @@ def test_hessian_accumulate_and_pitch(ctx):
     assert not H.cpu().numpy().any()
 
 
+@pytest.mark.parametrize("tokens,in_f", [(1, 1032), (40, 1096), (100, 1280), (257, 1152), (700, 1032), (400, 1600), (449, 1600), (130, 1608)])
+def test_hessian_of_few_tokens(ctx, tokens, in_f):
+    """Beyond 1024 columns the 128-wide kernel while there are few tokens, up to its last size and one behind it: ragged first stages, one piece and
+    several, plain, accumulated, from a pitched matrix; the prepared form's H has the plain call's bits."""
+    X = synth.make_activations(tokens, in_f, seed=tokens + in_f, n_outliers=3, scale_lo=30, scale_hi=80)
+    Href = oracle.hessian(X)
+    plain = gpu_hessian(ctx, X)
+    check_hessian(plain, Href)
+    assert np.array_equal(plain, plain.T)
+    if tokens > 2:
+        check_hessian(gpu_hessian(ctx, X, accumulate_chunks=2), Href)
+    assert np.array_equal(gpu_hessian(ctx, X, ld_pad=24), plain)
+    H = torch.full((in_f, in_f), float("nan"), dtype=torch.float32, device="cuda")
+    Hs, hmeta = ctx.alloc_score(in_f, in_f), torch.empty((2, in_f), dtype=torch.float32, device="cuda")
+    ctx.adadim_hessian_prepared(dev(X), H, Hs, hmeta)
+    torch.cuda.synchronize()
+    assert np.array_equal(H.cpu().numpy(), plain)
+
+
 def test_hessian_with_cut_rests(ctx):
     """A shape whose launch plan cuts the token range three ways (17 tiles per XCD on 32 units: one full piece per
     tile, the rest whole for most tiles and in four short pieces for sixteen of them; tests/host/gram_plan_check

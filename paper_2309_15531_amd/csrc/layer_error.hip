@@ -423,7 +423,7 @@ void error_slots_finest(int nc, int MB, int NB, int& kb, int& n_slots) {
 // 2 x 256 x 16384 the choice is 1.1 % slower than the best chunk on average and 10 % at worst.  Against the finest cut:
 // 1 x 4096 x 4096 97 -> 75 us, 2 x 1720 x 2760 109 -> 66, 2 x 2048 x 2048 50 -> 33, 1 x 8192 x 1024 34 -> 25,
 // 2 x 1024 x 4096 66 -> 48, 1 x 256 x 11008 71 -> 41.  Choosing takes the host up to 1 us at ordinary sizes and 11 us at
-// 1 x 64 x 28672, on every call (profiles/scoring_chunks.md).  Returns the estimate of the chosen cut (with `estimate` for
+// 1 x 64 x 28672, on every call (profiles/scoring_chunks.md; every launch there is this kernel's).  Returns the estimate of the chosen cut (with `estimate` for
 // whole contractions too).
 int error_slots(int nc, int MB, int NB, int64_t in, bool estimate, int& kb, int& n_slots) {
     constexpr int FIXED = 2, BLOCK = 5, EPILOGUE = 4;

@@ -873,8 +873,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
 //   many channels, updates dear (as measured before)   8704 x 8192  17220 [12] / 13210  5632 x 11008  17650 [24] / 15520
 //
 // In one launch: rounds of workgroups, each of which takes, block by block, the longer of its chain and the update of the
-// columns behind it, and a step to the next block.  With 16 and 32 rows the update's products are on the matrix cores, with 12 and
-// more the chain has two waves.  (few: a workgroup or two alone wait for U by themselves.)
+// columns behind it, and a step to the next block.  With 16 and 32 rows the update's products are on the matrix cores, with 12
+// and 16 the chain has two helpers, with 24 and 32 rows are two chains'.  (few: a workgroup or two alone wait for U by themselves.)
 struct Parts {
     int rows;
     double chain, step, column;        // of a block; to the next one; of a block's update per column

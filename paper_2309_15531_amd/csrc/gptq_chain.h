@@ -10,8 +10,9 @@
 //          least 2^-80 for that correction to be exact, and 1/d RN (block_reciprocal; NaN outside fastdiv's range, which the
 //          sweeps look for before they start a sub-block).
 // NaN, infinities and quotients above 2^21 fail the first check, which so bounds w, num (s is at most 2^40) and the error.
-// Two of the values below are kept as unsigned bit patterns (a compare per check would hold them in scalar registers,
-// of which there are too few).
+// What was seen is kept as unsigned bit patterns (a compare per check would hold it in scalar registers, of which there are too few); with MASK
+// the second check's outcome is a lane mask, one vector instruction less per channel where one row's chain leaves the registers for it
+// (per IC, groups of 64, the mask costs 2.4 %: 512 x 2272 764 us and 783).
 #pragma once
 
 #include "common.h"
@@ -25,18 +26,20 @@ constexpr int GB = 128;                // channels per block
 constexpr int SB = 16;                 // channels per register sub-block of the chain
 constexpr int PITCH = GB + 4;          // LDS row pitch (floats) of a strip and of the transposed block of U
 
+template <bool MASK = false>
 struct Check {
-    uint32_t tie = 0u, num = 0xffffffffu;
+    uint32_t tie = 0u, off = 0u, num = 0xffffffffu;
     bool same = true;
     __device__ __forceinline__ void code(float quo, float near) {
         tie = max(tie, __float_as_uint(fmaf(fabsf(quo), 0x1p-22f, fabsf(quo - near))));
     }
     __device__ __forceinline__ void error(float n, float d, float y, float e) {
-        same = same && fastdiv_corrected(n, d, y, e) == e;   // (false for a NaN, as without a reciprocal)
+        if constexpr (MASK) same = same && fastdiv_corrected(n, d, y, e) == e;         // (false for a NaN, as without a reciprocal)
+        else off |= __float_as_uint(fastdiv_corrected(n, d, y, e)) ^ __float_as_uint(e);
         num = min(num, (__float_as_uint(n) << 1) - 1u);       // zero wraps to the top
     }
     __device__ __forceinline__ bool fine() const {
-        return tie <= 0x3F000000u && same && num >= (0x17800000u << 1) - 1u;      // 0.5, 2^-80
+        return tie <= 0x3F000000u && same && off == 0u && num >= (0x17800000u << 1) - 1u;      // 0.5, 2^-80
     }
 };
 

@@ -132,7 +132,7 @@ __device__ __forceinline__ bool chain(const float* w_lds, const float* ut, const
 #pragma unroll
         for (int c = 0; c < SB / 4; ++c) qpk[p][c] = 0u;
     }
-    Check check;
+    Check<> check;
     uint32_t r_lo = 0xffffffffu, r_hi = 0u;                   // of the ranges (bit patterns; zero is allowed)
     // the corner of U (row cc of `ut` holds U[c][cc] for c <= cc) four columns at a time, two channels ahead of their use
     float ub[SB][SB], yd[SB];

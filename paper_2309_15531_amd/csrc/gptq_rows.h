@@ -383,7 +383,7 @@ __device__ __forceinline__ void chain_block(Lds<R>& lds, int ch, int blk, float*
         // the one four channels back onto the next sub-block's, the last four's checks.
         float eb[SB], late_mul[3], next_mul[4];
         float quo[4], near[4], k[4], num[4], e[4];            // as the columns' decisions left them
-        Check check;
+        Check<true> check;
         auto besides = [&](auto c_tag, auto n_tag) {
             constexpr int C = decltype(c_tag)::value, N = decltype(n_tag)::value, T = C / 4, I = C % 4;
             if constexpr (N < 3) {                           // columns behind the one in turn: T + 1 .. 3

@@ -163,8 +163,8 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
     // A launch of few blocks is a chain of waits: a batch of loads holds as many partials as most plans have, and the diagonal's are in
     // flight with them (one partial after the other, and the diagonal behind them: Gram matrix with its prepared form, us, 512 wide,
     // 2048 tokens 25.1 and now 16.6; 768, 3000 tokens 30 and 21; 1024, 8192 tokens 46 and 40).  The 256-wide kernel's partials, of which a plan has
-    // few, are added as they come (2760, 3001 tokens 55.5 and 53.7; batches of four took 53.1 there but 22.6 -> 23.6 at 1600, 640 tokens,
-    // accumulating): with their registers fewer blocks are resident.
+    // few, are added as they come behind the diagonal, whose loads alone are batched (2760, 3001 tokens 54.4 and 52.9, 2048, 4096 tokens 41.9 and
+    // 39.9; theirs in batches of four took 22.6 -> 23.6 at 1600, 640 tokens, accumulating: with the registers fewer blocks are resident).
     constexpr int AHEAD = REGMAJOR ? 4 : 8;
     auto runs_of = [&](int tile_r) {
         const int n = gram_plan_parts(plan, tile_r);
@@ -178,37 +178,20 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
     };
     const Runs mine = whole ? Runs{part, 0, 0, part, 0} : runs_of(tile - n_whole);
     const int n_parts = mine.na + mine.nb;
-    const float* const part_one = mine.na > 0 ? mine.a : mine.b;
     const int wave = (sr >> 2) * 2 + (sc >> 2);
     // where this thread's four elements (rows 4 ty .. 4 ty + 3 of column tx) are in a partial tile
     const int64_t at = REGMAJOR ? ((((sr & 3) * 4 + (sc & 3)) * 4 + (ty >> 1)) * 256 + wave * 64 + (ty & 1) * 32 + tx) * 4
                                 : int64_t(sr * 32 + ty * 4) * BT + sc * 32 + tx;
-    float p[AHEAD][4], v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    float p[AHEAD][4];
     auto fetch = [&](int s0) {
 #pragma unroll
         for (int q = 0; q < AHEAD; ++q) {
             if (s0 + q >= n_parts) continue;                  // uniform
-            if constexpr (REGMAJOR) {
-                const float4 f = *reinterpret_cast<const float4*>(mine.at(s0 + q) + at);
-                p[q][0] = f.x; p[q][1] = f.y; p[q][2] = f.z; p[q][3] = f.w;
-            } else {
 #pragma unroll
-                for (int rr = 0; rr < 4; ++rr) p[q][rr] = mine.at(s0 + q)[at + rr * BT];
-            }
+            for (int rr = 0; rr < 4; ++rr) p[q][rr] = mine.at(s0 + q)[at + rr * BT];
         }
     };
-    if constexpr (REGMAJOR) {
-        if (n_parts > 0) {
-            const float4 f = *reinterpret_cast<const float4*>(part_one + at);
-            v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
-        }
-        for (int sp = 1; sp < n_parts; ++sp) {
-            const float4 f = *reinterpret_cast<const float4*>(mine.at(sp) + at);
-            v[0] += f.x; v[1] += f.y; v[2] += f.z; v[3] += f.w;
-        }
-    } else {
-        fetch(0);
-    }
+    if constexpr (!REGMAJOR) fetch(0);
     const bool diag = R0 == C0;
     if constexpr (PREP) {
         if (threadIdx.x < 64) {
@@ -229,7 +212,9 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
                     h = H[j * in + j];
                 } else {
                     const Runs dg = runs_of(dtile - n_whole);
-                    for (int s0 = 0; s0 < dg.na + dg.nb; s0 += AHEAD) {
+                    const bool one = REGMAJOR && dg.na + dg.nb == 1;    // (no batch for one: blocks this short feel every instruction)
+                    if (one) h += (dg.na > 0 ? dg.a : dg.b)[off];
+                    for (int s0 = one ? 1 : 0; s0 < dg.na + dg.nb; s0 += AHEAD) {
                         float p[AHEAD];
 #pragma unroll
                         for (int q = 0; q < AHEAD; ++q)
@@ -254,9 +239,24 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
             const int r = ty * 4 + rr;
             s[r][tx] = (R0 + r < in && C0 + tx < in) ? H[(R0 + r) * in + C0 + tx] : 0.0f;
         }
-    } else {
+    } else if constexpr (REGMAJOR) {
         static_assert(!REGMAJOR || BT == 256, "register-major partials come from the 256-wide DMA kernel");
-        for (int s0 = REGMAJOR ? n_parts : 0; s0 < n_parts; s0 += AHEAD) {
+        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        for (int sp = 0; sp < mine.na; ++sp) {
+            const float4 p = *reinterpret_cast<const float4*>(mine.a + sp * mine.sa + at);
+            v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+        }
+        for (int sp = 0; sp < mine.nb; ++sp) {
+            const float4 p = *reinterpret_cast<const float4*>(mine.b + sp * TILE + at);
+            v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+        }
+        s[ty * 4 + 0][tx] = v.x;
+        s[ty * 4 + 1][tx] = v.y;
+        s[ty * 4 + 2][tx] = v.z;
+        s[ty * 4 + 3][tx] = v.w;
+    } else {
+        float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int s0 = 0; s0 < n_parts; s0 += AHEAD) {
             if (s0 > 0) fetch(s0);
 #pragma unroll
             for (int q = 0; q < AHEAD; ++q)
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
                     if (s0 + q < n_parts) v[rr] += p[q][rr];
         }
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) s[ty * 4 + rr][tx] = v[rr] + 0.0f;
+        for (int rr = 0; rr < 4; ++rr) s[ty * 4 + rr][tx] = v[rr];
     }
     __syncthreads();
     if constexpr (PREP) {

@@ -223,6 +223,14 @@ int adadim_layer_error_batch(adadim_ctx* ctx, int n, const void* const* dW, int 
                              int64_t in, const void* Hs, const float* hmeta, float* loss_rows, float* losses);
 
 /*
+ * The same with candidate c's loss at losses[at[c]]: for candidates that are scored in another order than they are
+ * kept and selected in.  at is a HOST array of n indices, none of them negative; losses must reach the largest.
+ */
+int adadim_layer_error_batch_at(adadim_ctx* ctx, int n, const void* const* dW, int dW_dtype, int64_t out,
+                                int64_t in, const void* Hs, const float* hmeta, float* loss_rows, float* losses,
+                                const int32_t* at);
+
+/*
  * adadim_layer_error_batch followed by adadim_select(losses, n, best_dev) in one call: the block that writes the
  * last loss also takes the argmin (same rule as adadim_select), one launch less per layer.  best_dev is a device
  * int32 and is required.

@@ -20,7 +20,7 @@ DW_F32, DW_F16, DW_F16_SCALED = 0, 1, 2
 EXPORTS = (
     "adadim_create", "adadim_destroy", "adadim_last_error", "adadim_version", "adadim_score_elems",
     "adadim_hessian", "adadim_quantize", "adadim_hessian_prepare",
-    "adadim_layer_error", "adadim_layer_error_prepared", "adadim_layer_error_batch", "adadim_select",
+    "adadim_layer_error", "adadim_layer_error_prepared", "adadim_layer_error_batch", "adadim_layer_error_batch_at", "adadim_select",
     "adadim_gemv_ic", "adadim_gptq_prepare", "adadim_gptq_quantize",
     "adadim_quantize_meta16", "adadim_gemv_ic_meta16",
     "adadim_hessian_prepared", "adadim_layer_error_batch_select", "adadim_quantize_both", "adadim_gptq_quantize_meta16", "adadim_capture_begin", "adadim_capture_end", "adadim_graph_launch", "adadim_graph_destroy",
@@ -112,6 +112,9 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     lib.adadim_layer_error_batch.argtypes = [c_void_p, c_int, POINTER(c_void_p), c_int, c_int64, c_int64, c_void_p,
                                              c_void_p, c_void_p, c_void_p]
     lib.adadim_layer_error_batch.restype = c_int
+    lib.adadim_layer_error_batch_at.argtypes = [c_void_p, c_int, POINTER(c_void_p), c_int, c_int64, c_int64, c_void_p,
+                                                c_void_p, c_void_p, c_void_p, POINTER(c_int32)]
+    lib.adadim_layer_error_batch_at.restype = c_int
     lib.adadim_layer_error_batch_select.argtypes = [c_void_p, c_int, POINTER(c_void_p), c_int, c_int64, c_int64,
                                                     c_void_p, c_void_p, c_void_p, c_void_p, c_void_p]
     lib.adadim_layer_error_batch_select.restype = c_int
@@ -298,15 +301,22 @@ class Context:
         self._check(self._lib.adadim_layer_error_prepared(self._h, _ptr(dW), dW_dtype, out_f, in_f, _ptr(Hs),
                                                           _ptr(hmeta), _ptr(loss_rows), _ptr(loss)))
 
-    def adadim_layer_error_batch(self, dWs, dW_dtype: int, Hs, hmeta, losses, loss_rows=None, shape=None):
+    def adadim_layer_error_batch(self, dWs, dW_dtype: int, Hs, hmeta, losses, loss_rows=None, shape=None, at=None):
+        """at: indices in losses, one per candidate (adadim_layer_error_batch_at); without it losses[0], losses[1], ..."""
         out_f, in_f = dWs[0].shape if shape is None else shape
         for t in dWs:
             _need(t, "dW", "float32" if dW_dtype == DW_F32 else "float16")
         _need(Hs, "Hs", "float16"); _need(hmeta, "hmeta", "float32"); _need(losses, "losses", "float32")
         _need(loss_rows, "loss_rows", "float32")
         arr = (c_void_p * len(dWs))(*[t.data_ptr() for t in dWs])
-        self._check(self._lib.adadim_layer_error_batch(self._h, len(dWs), arr, dW_dtype, out_f, in_f, _ptr(Hs),
-                                                       _ptr(hmeta), _ptr(loss_rows), _ptr(losses)))
+        if at is None:
+            self._check(self._lib.adadim_layer_error_batch(self._h, len(dWs), arr, dW_dtype, out_f, in_f, _ptr(Hs),
+                                                           _ptr(hmeta), _ptr(loss_rows), _ptr(losses)))
+            return
+        if len(at) != len(dWs) or not all(0 <= i < losses.numel() for i in at):
+            raise ValueError(f"{len(dWs)} candidates, {losses.numel()} losses: no places {list(at)}")
+        self._check(self._lib.adadim_layer_error_batch_at(self._h, len(dWs), arr, dW_dtype, out_f, in_f, _ptr(Hs), _ptr(hmeta),
+                                                          _ptr(loss_rows), _ptr(losses), (c_int32 * len(at))(*at)))
 
     def adadim_layer_error_batch_select(self, dWs, dW_dtype: int, Hs, hmeta, losses, best_dev, loss_rows=None, shape=None):
         out_f, in_f = dWs[0].shape if shape is None else shape

@@ -403,7 +403,8 @@ int adadim_layer_error_prepared(adadim_ctx* ctx, const void* dW, int dW_dtype, i
 }
 
 static int error_batch_checked(adadim_ctx* ctx, int n, const void* const* dW, int dW_dtype, int64_t out, int64_t in,
-                               const void* Hs, const float* hmeta, float* loss_rows, float* losses, int32_t* best_dev) {
+                               const void* Hs, const float* hmeta, float* loss_rows, float* losses, int32_t* best_dev,
+                               const int32_t* at = nullptr) {
     if (!ctx) return ADADIM_ENULL;
     if (n <= 0 || n > 4096) return adadim_fail(ctx, ADADIM_EINVAL, "adadim_layer_error_batch: bad n=%d", n);
     if (!dW) return adadim_fail(ctx, ADADIM_ENULL, "adadim_layer_error_batch: dW is NULL");
@@ -415,12 +416,20 @@ static int error_batch_checked(adadim_ctx* ctx, int n, const void* const* dW, in
     if (!aligned16(hmeta))
         return adadim_fail(ctx, ADADIM_EALIGN, "adadim_layer_error_batch: hmeta must be 16-byte aligned");
     return launch_layer_error(ctx, n, dW, dW_dtype, out, in, static_cast<const __half*>(Hs), hmeta, loss_rows,
-                              losses, best_dev);
+                              losses, best_dev, at);
 }
 
 int adadim_layer_error_batch(adadim_ctx* ctx, int n, const void* const* dW, int dW_dtype, int64_t out, int64_t in,
                              const void* Hs, const float* hmeta, float* loss_rows, float* losses) {
     return error_batch_checked(ctx, n, dW, dW_dtype, out, in, Hs, hmeta, loss_rows, losses, nullptr);
+}
+
+int adadim_layer_error_batch_at(adadim_ctx* ctx, int n, const void* const* dW, int dW_dtype, int64_t out, int64_t in,
+                                const void* Hs, const float* hmeta, float* loss_rows, float* losses, const int32_t* at) {
+    if (ctx && !at) return adadim_fail(ctx, ADADIM_ENULL, "adadim_layer_error_batch_at: at is NULL");
+    for (int c = 0; ctx && c < n && c < 4096; ++c)
+        if (at[c] < 0) return adadim_fail(ctx, ADADIM_EINVAL, "adadim_layer_error_batch_at: at[%d] is %d", c, at[c]);
+    return error_batch_checked(ctx, n, dW, dW_dtype, out, in, Hs, hmeta, loss_rows, losses, nullptr, at);
 }
 
 int adadim_layer_error_batch_select(adadim_ctx* ctx, int n, const void* const* dW, int dW_dtype, int64_t out,

@@ -164,7 +164,7 @@ int launch_hessian_prepared(adadim_ctx* ctx, const __half* X, int64_t tokens, in
                             __half* Hs, float* hmeta);
 int launch_layer_error(adadim_ctx* ctx, int n, const void* const* dW, int dW_dtype, int64_t out, int64_t in,
                        const __half* Hs, const float* hmeta, float* loss_rows, float* losses,
-                       int32_t* best_dev = nullptr);
+                       int32_t* best_dev = nullptr, const int32_t* at = nullptr);   // at (host): candidate c's loss goes to losses[at[c]]
 // The same launch group (n <= 8 candidates, column-scaled fp16 dW) with its scratch in the library's fixed device
 // array; _bytes gives what such a launch needs of it.
 int launch_layer_error_noalloc(adadim_ctx* ctx, int n, const void* const* dW, int64_t out, int64_t in, const __half* Hs,

@@ -291,17 +291,20 @@ __device__ __forceinline__ double finish_total(double v, double* s_red) {
 // loss_rows[o] = diag[o] + 2*sum_slot part[slot,o] (no diag array: the tile kernel has put half
 // the diagonal term into its row sums) for 256 rows per block, a per-block total,
 // and, in the block that finishes last, loss = sum of the block totals in block order (so the
-// result does not depend on which block that is).  `ticket` must be zero on entry and is zero
-// again on exit.  With `best` given, the block that writes the launch's last loss also takes the
+// result does not depend on which block that is), which goes to loss_all[at.i[candidate]].
+// `ticket` must be zero on entry and is zero again on exit.  With `best` given, the block that writes the launch's last loss also takes the
 // argmin of sel_losses[0..n_sel) (first minimum, NaN never wins, as select_first_min): one launch
 // and one kernel boundary less than a separate selection.
 // Few blocks and little data: what counts is the chain of dependent latencies.  A row's slots are loaded sixteen at a
 // time, the totals go through lane exchanges, and what blocks hand to each other are relaxed device-scope atomics that
 // bypass the caches, ordered by the wait behind them (loads one behind the other, trees of barriers and cache write-backs:
 // 9 us at 4 slots, 11 at 16, 45 at 136; now 6 to 9).
+struct LossPlaces {
+    int32_t i[edma::MAX_BATCH];
+};
 __global__ __launch_bounds__(256) void error_finish(const float* __restrict__ diag_all,
                                                     const float* __restrict__ part_all, int64_t out, int n_slots,
-                                                    float* __restrict__ loss_rows_all, float* __restrict__ loss_all,
+                                                    float* __restrict__ loss_rows_all, float* __restrict__ loss_all, LossPlaces at,
                                                     double* __restrict__ block_tot_all,
                                                     unsigned int* __restrict__ ticket_all,
                                                     const float* __restrict__ sel_losses, int n_sel,
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(256) void error_finish(const float* __restrict__ di
     const float* __restrict__ diag = diag_all + int64_t(blockIdx.y) * out;
     const float* __restrict__ part = part_all + int64_t(blockIdx.y) * n_slots * out;
     float* __restrict__ loss_rows = loss_rows_all ? loss_rows_all + int64_t(blockIdx.y) * out : nullptr;
-    float* __restrict__ loss = loss_all + blockIdx.y;
+    float* __restrict__ loss = loss_all + at.i[blockIdx.y];
     double* __restrict__ block_tot = block_tot_all + int64_t(blockIdx.y) * gridDim.x;
     unsigned int* __restrict__ ticket = ticket_all + blockIdx.y;
     const int64_t o = int64_t(blockIdx.x) * 256 + threadIdx.x;
@@ -527,10 +530,10 @@ int set_error_attr(adadim_ctx* ctx) {
     return ADADIM_OK;
 }
 
-// One launch group: nc <= MAX_BATCH candidates dW[0..nc) scored against Hs; losses_all / n_all are the whole
-// call's loss array (for the fused selection, taken when best_dev is given).
+// One launch group: nc <= MAX_BATCH candidates dW[0..nc) scored against Hs; losses / n_all are the whole
+// call's loss array (n_all for the fused selection, taken when best_dev is given), `at` the candidates' places in it.
 int run_error_batch(adadim_ctx* ctx, int nc, const void* const* dW, int dW_dtype, int64_t out, int64_t in,
-                    const __half* Hs, const float* hmeta, float* loss_rows, float* losses, const float* losses_all,
+                    const __half* Hs, const float* hmeta, float* loss_rows, float* losses, const LossPlaces& at,
                     int n_all, int32_t* best_dev, const ErrScratch& sc, const ErrPlan& plan) {
     constexpr int BT = edma::BT;
     const int MB = static_cast<int>((out + BT - 1) / BT), NB = static_cast<int>((in + BT - 1) / BT);
@@ -577,7 +580,7 @@ int run_error_batch(adadim_ctx* ctx, int nc, const void* const* dW, int dW_dtype
         ProfScope prof(ctx, "error_finish");
         hipLaunchKernelGGL(error_finish, dim3(fin_blocks, nc), dim3(256), 0, ctx->stream,
                            direct ? static_cast<const float*>(nullptr) : sc.diag, sc.part, out, n_slots, loss_rows,
-                           losses, sc.block_tot, sc.ticket, losses_all, n_all, best_dev);
+                           losses, at, sc.block_tot, sc.ticket, losses, n_all, best_dev);
     }
     ADADIM_LAUNCH_CHECK(ctx, "error_finish");
     return ADADIM_OK;
@@ -586,7 +589,8 @@ int run_error_batch(adadim_ctx* ctx, int nc, const void* const* dW, int dW_dtype
 }  // namespace
 
 int launch_layer_error(adadim_ctx* ctx, int n, const void* const* dW, int dW_dtype, int64_t out, int64_t in,
-                       const __half* Hs, const float* hmeta, float* loss_rows, float* losses, int32_t* best_dev) {
+                       const __half* Hs, const float* hmeta, float* loss_rows, float* losses, int32_t* best_dev,
+                       const int32_t* at) {
     constexpr int BT = edma::BT;
     const int MB = static_cast<int>((out + BT - 1) / BT), NB = static_cast<int>((in + BT - 1) / BT);
     ErrScratch sc{};
@@ -635,8 +639,10 @@ int launch_layer_error(adadim_ctx* ctx, int n, const void* const* dW, int dW_dty
                 adadim_workspace(ctx, WS_DW16, size_t(nc) * size_t(score_elems(out, in)) * sizeof(__half)));
             if (!sc.dW16) return ADADIM_EHIP;
         }
+        LossPlaces places{};
+        for (int c = 0; c < nc; ++c) places.i[c] = at ? at[c0 + c] : c0 + c;
         rc = run_error_batch(ctx, nc, dW + c0, dW_dtype, out, in, Hs, hmeta,
-                             loss_rows ? loss_rows + size_t(c0) * size_t(out) : nullptr, losses + c0, losses, n,
+                             loss_rows ? loss_rows + size_t(c0) * size_t(out) : nullptr, losses, places, n,
                              c0 + nc == n ? best_dev : nullptr, sc, plan);
         if (rc != ADADIM_OK) return rc;
     }
@@ -733,6 +739,8 @@ int launch_layer_error_noalloc(adadim_ctx* ctx, int n, const void* const* dW, in
     sc.part = reinterpret_cast<float*>(ptr + 512 + size_t(edma::MAX_BATCH) * size_t(fin_blocks) * 8);
     sc.diag = nullptr;
     sc.dW16 = nullptr;
-    return run_error_batch(ctx, n, dW, ADADIM_DW_F16_SCALED, out, in, Hs, hmeta, loss_rows, losses, losses, n, best_dev, sc,
+    LossPlaces places{};
+    for (int c = 0; c < n; ++c) places.i[c] = c;
+    return run_error_batch(ctx, n, dW, ADADIM_DW_F16_SCALED, out, in, Hs, hmeta, loss_rows, losses, places, n, best_dev, sc,
                            plan);
 }

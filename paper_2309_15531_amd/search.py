@@ -51,10 +51,9 @@ class PreparedHessian:
 class LayerSearch:
     """Buffers for searching layers of one shape; reused across layers and candidates.
 
-    Candidates are scored in batches of up to `batch` (one adadim_layer_error_batch call each).  A clip ratio's two
-    dimensions are quantized in one call, which reads the weight once where the shape allows (1024 x 8192 in groups of 64:
-    12 us a pair, one dimension after the other 19); with more candidates than one batch, `batch` ratios at a time then
-    and a batch per dimension each.
+    Candidates are scored in batches of up to `batch` (one scoring call each); as many scoring buffers are held, of the
+    layer's size in fp16.  A clip ratio's two dimensions are quantized in one call where a batch holds both, which reads
+    the weight once where the shape allows (1024 x 8192 in groups of 64: 15 us a pair, one dimension after the other 19).
 
     With at most `batch` candidates and keep_winner, every candidate's packed codes, scales and
     zeros are written while it is scored, so the winner needs no second quantization.
@@ -70,10 +69,7 @@ class LayerSearch:
         self.clips = [float(np.float32(c)) for c in clips]
         self.cands = [(d, c) for d in (B.DIM_OC, B.DIM_IC) for c in self.clips]
         self.batch = max(1, min(batch, 8, len(self.cands)))
-        # More candidates than a batch: by ratios where a pair is one launch (else the last batches would be short for nothing).
-        self.rounds = len(self.cands) > self.batch and in_f % 32 == 0 and group in (32, 64, 128)
-        n_dw = 2 * min(len(self.clips), self.batch) if self.rounds else self.batch
-        self.dWs = [ctx.alloc_score(out_f, in_f, device) for _ in range(n_dw)]         # scoring layout, flat
+        self.dWs = [ctx.alloc_score(out_f, in_f, device) for _ in range(self.batch)]   # scoring layout, flat
         self.losses = torch.empty(len(self.cands), dtype=torch.float32, device=device)
         self.best = torch.empty(1, dtype=torch.int32, device=device)
         self.keep_winner = keep_winner
@@ -95,62 +91,60 @@ class LayerSearch:
             self._packed = [torch.empty(words, dtype=torch.int32, device=device) for _ in range(n_sets)]
         else:
             self.inline = False
+        self._batches = self._plan()
 
     def score_all(self, W, hp: PreparedHessian, select: bool = False):
         """Quantizes and scores every candidate; losses stay on the device.  select: also leave the winning
         index in self.best (taken by the scoring call itself when the candidates fit one batch)."""
-        n_c, shape = len(self.clips), (self.out_f, self.in_f)
-
-        def pair(clip, k, dWs):
-            """Both dimensions of clip ratio k."""
-            sets = [self._outputs(dW, d * n_c + k) for d, dW in enumerate(dWs)]
-            self.ctx.adadim_quantize_both(W, self.bits, self.group, hp.colscale, sets[0], sets[1], clip=clip, meta16=self.meta16)
-
-        def score(dWs, at):
-            self.ctx.adadim_layer_error_batch(dWs, B.DW_F16_SCALED, hp.Hs, hp.hmeta, self.losses[at:at + len(dWs)], shape=shape)
-
-        if len(self.cands) <= self.batch:
-            for k, clip in enumerate(self.clips):
-                pair(clip, k, (self.dWs[k], self.dWs[n_c + k]))
-            if select:
-                self.ctx.adadim_layer_error_batch_select(self.dWs, B.DW_F16_SCALED, hp.Hs, hp.hmeta, self.losses, self.best, shape=shape)
+        shape = (self.out_f, self.in_f)
+        for steps, dWs, at in self._batches:
+            for clip, dim, sets in steps:
+                if dim is None:
+                    self.ctx.adadim_quantize_both(W, self.bits, self.group, hp.colscale, *sets, clip=clip, meta16=self.meta16)
+                else:
+                    self._quantize(W, dim, clip, dW_dtype=B.DW_F16_SCALED, colscale=hp.colscale, **sets[0])
+            if at is not None:
+                self.ctx.adadim_layer_error_batch(dWs, B.DW_F16_SCALED, hp.Hs, hp.hmeta, self.losses, shape=shape, at=at)
+            elif select:
+                self.ctx.adadim_layer_error_batch_select(dWs, B.DW_F16_SCALED, hp.Hs, hp.hmeta, self.losses, self.best, shape=shape)
                 return
-            score(self.dWs, 0)
-        elif self.rounds:
-            per = len(self.dWs) // 2
-            for c0 in range(0, n_c, per):
-                clips = self.clips[c0:c0 + per]
-                for k, clip in enumerate(clips):
-                    pair(clip, c0 + k, (self.dWs[k], self.dWs[per + k]))
-                for d in (0, 1):
-                    score(self.dWs[d * per:d * per + len(clips)], d * n_c + c0)
-        else:
-            for c0 in range(0, len(self.cands), self.batch):
-                chunk = self.cands[c0:c0 + self.batch]
-                for k, (dim, clip) in enumerate(chunk):
-                    self._quantize(W, dim, clip, None, dW=self.dWs[k], dW_dtype=B.DW_F16_SCALED, colscale=hp.colscale)
-                score(self.dWs[:len(chunk)], c0)
+            else:
+                self.ctx.adadim_layer_error_batch(dWs, B.DW_F16_SCALED, hp.Hs, hp.hmeta, self.losses, shape=shape)
         if select:
             self.ctx.adadim_select(self.losses, best_dev=self.best, to_host=False)
 
-    def _outputs(self, dW, cand):
-        """Where a candidate goes while it is scored: with every candidate's outputs kept, its parameters and packed codes too."""
-        if not self.inline:
-            return {"dW": dW}
-        if self.meta16:
-            return {"dW": dW, "meta": self._meta[cand], "packed": self._packed[cand]}
-        return {"dW": dW, "scales": self._scales[cand], "zeros": self._zeros[cand], "packed": self._packed[cand]}
+    def _plan(self):
+        """The batches: ([(clip ratio, dimension or None for both, output sets)], scoring buffers, their candidates' indices
+        in `cands` or None if they are all candidates in that order).  Ratio by ratio, so that both dimensions of a ratio
+        meet in a batch (one of an odd size holds one dimension of its last ratio).  Search on a prepared H with 8
+        buffers, us, all ratios of one dimension before the other's / so: 1024 x 8192, 20 ratios 2779 / 2705;
+        4096 x 4096, 10 ratios 1690 / 1616; 256 x 11008, 10 ratios 798 / 763; 128 x 4096, 9 ratios 207 / 162."""
+        n_c, batches = len(self.clips), []
+        order = [d * n_c + k for k in range(n_c) for d in (0, 1)]
+        for c0 in range(0, len(order), self.batch):
+            chunk = order[c0:c0 + self.batch]
+            sets = [{"dW": dW, **(self._kept(cand) if self.inline else {})} for cand, dW in zip(chunk, self.dWs)]
+            steps, k = [], 0
+            while k < len(chunk):
+                dim, clip = self.cands[chunk[k]]
+                both = dim == B.DIM_OC and k + 1 < len(chunk)
+                steps.append((clip, None, sets[k:k + 2]) if both else (clip, dim, sets[k:k + 1]))
+                k += 2 if both else 1
+            if len(chunk) == len(order):
+                batches.append((steps, self.dWs[0::2] + self.dWs[1::2], None))
+            else:
+                batches.append((steps, self.dWs[:len(chunk)], chunk))
+        return batches
 
-    def _quantize(self, W, dim, clip, out_set, **kw):
-        """One candidate; out_set names the output set that receives its parameters and packed codes."""
+    def _kept(self, k):
+        """Output set k."""
         if self.meta16:
-            if out_set is not None:
-                kw.update(meta=self._meta[out_set], packed=self._packed[out_set])
-            self.ctx.adadim_quantize_meta16(W, dim, self.bits, self.group, clip, **kw)
-        else:
-            if out_set is not None:
-                kw.update(scales=self._scales[out_set], zeros=self._zeros[out_set], packed=self._packed[out_set])
-            self.ctx.adadim_quantize(W, dim, self.bits, self.group, clip, **kw)
+            return {"meta": self._meta[k], "packed": self._packed[k]}
+        return {"scales": self._scales[k], "zeros": self._zeros[k], "packed": self._packed[k]}
+
+    def _quantize(self, W, dim, clip, **outputs):
+        quantize = self.ctx.adadim_quantize_meta16 if self.meta16 else self.ctx.adadim_quantize
+        quantize(W, dim, self.bits, self.group, clip, **outputs)
 
     def launch(self, W, hp: PreparedHessian):
         """Queues the whole search for one layer and returns at once: the losses and the winning index stay on
@@ -180,7 +174,7 @@ class LayerSearch:
             else:
                 self.scales, self.zeros = self._scales[k], self._zeros[k]
             if not self.inline:
-                self._quantize(W, dim, clip, 0)
+                self._quantize(W, dim, clip, **self._kept(0))
         return best, dim, clip
 
 

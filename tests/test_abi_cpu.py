@@ -94,11 +94,39 @@ def test_error_and_select_validation(ctx):
     ep = lambda *a: ctx.raw("adadim_layer_error_prepared", *a)
     assert ep(A16, B.DW_F16_SCALED, 64, 64, A16, None, None, A16) == B.ENULL
     assert ep(A16, 5, 64, 64, A16, A16, None, A16) == B.EINVAL
+    three = (ctypes.c_void_p * 3)(*[0x1000] * 3)
+    places = lambda *i: (ctypes.c_int32 * len(i))(*i)
+    ea = lambda *a: ctx.raw("adadim_layer_error_batch_at", *a)
+    assert ea(3, three, 0, 64, 64, A16, A16, None, A16, None) == B.ENULL
+    assert ea(3, three, 0, 64, 64, A16, A16, None, A16, places(0, 2, -1)) == B.EINVAL
+    assert "at[2]" in ctx.last_error()
+    assert ea(0, three, 0, 64, 64, A16, A16, None, A16, places(0)) == B.EINVAL
+    assert ea(3, three, 0, 64, 64, A16, A16, None, None, places(0, 1, 2)) == B.ENULL
     s = lambda *a: ctx.raw("adadim_select", *a)
     assert s(None, 2, A16, None) == B.ENULL
     assert s(A16, 0, A16, None) == B.EINVAL
     assert s(A16, 2, None, None) == B.ENULL
     assert "adadim_select" in ctx.last_error()
+
+
+def test_places_of_losses_are_checked_against_the_losses():
+    class Fake(B.Context):
+        def __init__(self):
+            self._lib = self._h = None
+
+    class Tensor:                                                        # on the device, as far as the binding looks
+        is_cuda, dtype = True, None
+        def __init__(self, n): self.n = n
+        def numel(self): return self.n
+        def dim(self): return 1
+        def stride(self, d): return 1
+        def is_contiguous(self): return True
+        def data_ptr(self): return 0x1000
+    half, single = Tensor(64), Tensor(4)
+    half.dtype, single.dtype = "torch.float16", "torch.float32"
+    for at in ([0], [0, 4], [-1, 0], [0, 1, 2]):
+        with pytest.raises(ValueError, match="places"):
+            Fake().adadim_layer_error_batch([half, half], B.DW_F16_SCALED, half, single, single, shape=(8, 8), at=at)
 
 
 def test_gemv_validation(ctx):

@@ -188,7 +188,8 @@ def test_quantize_then_gemv_on_device(ctx):
     assert (np.abs(got - ref) <= 2.0 ** -10 * np.abs(ref) + 2e-5 * mag).all()
 
 
-@pytest.mark.parametrize("bits,group,clips", [(4, 128, (1.0,)), (3, 64, (1.0, 0.9, 0.8))])
+@pytest.mark.parametrize("bits,group,clips", [(4, 128, (1.0,)), (3, 64, (1.0, 0.9, 0.8)),
+                                              (2, 64, (1.0, 0.95, 0.9, 0.85, 0.8, 0.75, 0.7, 0.65, 0.6))])
 def test_search_in_the_storage_format(ctx, bits, group, clips):
     """The whole search (Sec. 3.3, Eq. 1) with every candidate quantized into the format: losses against the oracle's
     (its quantizer with the rounded scale, its fp64 error through H), winner's words and packed codes bit-exact."""

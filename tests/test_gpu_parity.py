@@ -485,6 +485,35 @@ def test_clip_grid_search(ctx):
         assert ref["losses"][best] <= srt[0] * 1.01
 
 
+@pytest.mark.parametrize("out_f,in_f,group,n_clips,batch", [(256, 512, 64, 9, 8), (240, 520, 40, 10, 8), (256, 512, 0, 10, 8),
+                                                            (256, 512, 64, 5, 3), (128, 256, 32, 2, 1)])
+def test_clip_grid_in_batches(ctx, out_f, in_f, group, n_clips, batch):
+    """Grids of more candidates than a batch: a last batch of one ratio, ratios whose two dimensions are two launches, batches that
+    split a ratio, one candidate at a time.  Every loss in its candidate's place, the selection and the winner's outputs; with the index
+    from the host and from the device."""
+    W = rand_w(out_f, in_f, seed=33 + n_clips)
+    X = synth.make_activations(300, in_f, seed=34, n_outliers=4, scale_lo=50, scale_hi=100)
+    clips = S.clip_grid(n_clips)
+    ref = oracle.search(W, X, 3, group, clips=[np.float32(c) for c in clips])
+    hp = S.PreparedHessian(ctx, in_f).update(dev(X)).prepare()
+    ls = S.LayerSearch(ctx, out_f, in_f, 3, group, clips, batch=batch)
+    Wd = dev(W)
+    for queued in (False, True):
+        ls.losses.fill_(-1.0)
+        if queued:
+            ls.launch(Wd, hp)
+        best, dim, clip = ls.result() if queued else ls.run(Wd, hp)
+        torch.cuda.synchronize()
+        got = ls.losses.cpu().numpy()
+        assert got == pytest.approx(ref["losses"], rel=LOSS_RTOL)
+        assert best == int(np.argmin(got)) and (dim, clip) == ls.cands[best]
+        q = oracle.quantize(W, dim, 3, group, np.float32(clip))
+        assert np.array_equal(ls.scales[:q["scales"].size].cpu().numpy(), q["scales"].ravel())
+        assert np.array_equal(ls.zeros[:q["zeros"].size].cpu().numpy(), q["zeros"].ravel())
+        pk = oracle.pack(q["codes"], dim, 3)
+        assert np.array_equal(ls.packed[:pk.size].cpu().numpy().view(np.uint32), pk.ravel())
+
+
 def test_choice_flips_under_transpose_gpu(ctx):
     n = 256
     X = np.eye(n, dtype=np.float16)

@@ -91,10 +91,11 @@ __device__ __forceinline__ void wait_for(const int* count, int n) {
     }
 }
 
-// lane i of each four
-template <int I>
+// lane i of each four (AGAIN: an instruction of its own; a bit without effect on lanes of four keeps the compiler from
+// joining the two)
+template <int I, bool AGAIN = false>
 __device__ __forceinline__ float of_four(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x55 * I, 0xf, 0xf, true));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x55 * I, 0xf, 0xf, !AGAIN));
 }
 // the value is worked out here, in the order of these calls
 __device__ __forceinline__ void here(float& v) { asm volatile("" : "+v"(v)); }
@@ -433,8 +434,7 @@ __device__ __forceinline__ void chain_block(Lds<R>& lds, int ch, int blk, float*
                 here(upd);
                 GQ_ASIDE(6);
                 here(w[T] = w[T] - upd);
-                // (two instructions after the error: what a DPP operand needs)
-                asm volatile("v_mov_b32_dpp %0, %1 quad_perm:[%2,%2,%2,%2] row_mask:0xf bank_mask:0xf" : "=v"(eb[C - 1]) : "v"(e[T1]), "n"(I1));
+                here(eb[C - 1] = of_four<I1, true>(e[T1]));  // (again: the product above reads the four's lane by itself)
             }
             here(quo[T] = w[T] * y[T]);
             GQ_ASIDE(7);

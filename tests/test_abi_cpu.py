@@ -43,6 +43,20 @@ def test_no_torch_types_in_header():
     assert 'extern "C"' in text
 
 
+def test_lane_moves_in_inline_assembly_bring_their_wait():
+    """A DPP operand needs two instructions behind the write of its register.  The compiler sees to that for its own instructions and
+    does not look into inline assembly, where a copy it puts in front would give a wrong value: such a block starts with the wait."""
+    csrc, blocks = os.path.join(ROOT, "paper_2309_15531_amd", "csrc"), []
+    for f in sorted(os.listdir(csrc)):
+        if f.endswith((".h", ".hip")):
+            for m in re.finditer(r"\basm\b[^;]*?\(((?:\s*\"(?:[^\"\\]|\\.)*\")+)", open(os.path.join(csrc, f)).read()):
+                blocks.append((f, "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', m.group(1)))))
+    assert len(blocks) > 20
+    for f, text in blocks:
+        if "dpp" in text or "quad_perm" in text or "row_" in text:
+            assert text.startswith("s_nop 1"), (f, text)
+
+
 A16 = ctypes.c_void_p(0x1000)      # fake, aligned, never dereferenced: validation fails first
 ODD = ctypes.c_void_p(0x1004)
 F1 = ctypes.c_float(1.0)

@@ -30,6 +30,7 @@
 #include "gptq_update.h"
 #include "scale_format.h"
 
+#include <cmath>
 #include <type_traits>
 
 namespace {
@@ -861,36 +862,34 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gq_rows(float* __restrict__ Wp,
     }
 }
 
-// Which form and how many rows per workgroup: the least of the models below, whose constants (us) were fitted to whole calls of 1341
-// sizes when the step from block to block was not beside the chain, and the choice of 8 rows since.  They compare; neither
-// estimates a call.  With the kernels as they are, over 161 sizes of up to 8192 rows (128 to 8192 channels) what they choose is 0.2 % slower
-// than the best on average and 9 % at worst (1816 x 128).  Above one round of 32 rows they are late in going back to one launch (10
-// sizes: 15 % on average): the launches per block have not become faster.  us, one launch [rows per workgroup] / a launch per block:
-//   rows in one round of workgroups   2048 x 2048  424 [8] / 1187      4096 x 4096  1657 [16] / 2833   8192 x 512   129 [32] / 302
-//   rows per workgroup                1888 x 304   50 [8], 58 [16]     3072 x 3072  978 [12], 1007 [16]  1024 x 4096  705 [4], 1099 [8]
-//   rounds of 32 rows nearly full     16384 x 1024  607 [32] / 835     12288 x 1024  548 [24] / 713
-//   more rows than that, late         20000 x 256  165 [32] / 247      28672 x 1024  1187 [32] / 1487   8208 x 672  336 [16] / 415
-//   many channels, updates dear (as measured before)   8704 x 8192  17220 [12] / 13210  5632 x 11008  17650 [24] / 15520
+// Which form and how many rows per workgroup: the least of the models below, in us without what all forms share (the copies around the
+// sweep).  Their constants were fitted to whole calls at 760 sizes (8 to 100000 rows, 16 to 28672 channels) and then moved by a few percent to
+// where the choice is best.  At 300 other sizes it is 0.50 % slower than the best form on average (0.17 % from 128 channels on) and 11 % at worst
+// there (17590 x 6192); constants from before the step between blocks ran beside the chain took one launch too rarely, 1.13 times
+// the present time above 8192 rows.  us, one launch [rows per workgroup] / a launch per block (all of them: profiles/gptq_per_oc_forms.md):
+//   one round of workgroups           2048 x 2048  420 [8] / 1098      4096 x 4096  1612 [16] / 2653   8192 x 512  126 [32] / 302
+//   rows per workgroup                3072 x 3072  950 [12], 987 [16]  1024 x 4096  697 [4], 1100 [8]  9216 x 1024  531 [24], 580 [32]
+//   several rounds                    20000 x 256  157 [32] / 233      28672 x 1024  1162 [32] / 1409  100000 x 256  616 [32] / 801
+//   many channels, updates dear       8704 x 8192  15910 [12] / 13220  5632 x 11008  16860 [24] / 15270  9216 x 4096  4571 [12] / 4322
+//   few rows and very many channels   8 x 16384  9926 [4] / 8689
 //
-// In one launch: rounds of workgroups, each of which takes, block by block, the longer of its chain and the update of the
-// columns behind it, and a step to the next block.  With 16 and 32 rows the update's products are on the matrix cores, with 12
-// and 16 the chain has two helpers, with 24 and 32 rows are two chains'.  (few: a workgroup or two alone wait for U by themselves.)
+// In one launch: rounds of workgroups, each of which takes a block's chain and the strips and the update of the columns behind the next
+// block, spread over its waves, and at the last block its chain alone.  Beyond 10000 channels a block's rows of U no longer fit an XCD's L2, and
+// few workgroups wait for them by themselves.
 struct Parts {
     int rows;
-    double chain, step, column;        // of a block; to the next one; of a block's update per column
+    double start, last, block, behind, column;  // of a round; of the last block's chain; of another block; more with columns behind the next; per such column
 };
-constexpr Parts PARTS[] = {{4, 10.5, 11.4, 7.1e-3},  {8, 12.0, 13.6, 11.4e-3},  {12, 12.4, 15.6, 16.1e-3},
-                           {16, 9.3, 16.7, 18.2e-3}, {24, 18.8, 18.4, 32.6e-3}, {32, 18.2, 19.2, 37.5e-3}};
+constexpr Parts PARTS[] = {{4, 4.9, 7.8, 11.4, 0.4, 6.0e-3},    {8, 5.4, 8.7, 11.9, 8.8, 8.95e-3},  {12, 6.0, 10.0, 14.8, 7.0, 15.0e-3},
+                           {16, 6.3, 10.1, 15.9, 2.9, 18.0e-3}, {24, 7.3, 13.3, 24.5, 0.8, 31.8e-3}, {32, 8.7, 12.8, 26.8, 0.0, 35.7e-3}};
 
 inline double rows_us(const Parts& p, int64_t out, int64_t in) {
-    const int64_t wgs = (out + p.rows - 1) / p.rows;
-    const double few = 1.0 + 0.14 / double(wgs);
-    double us = 9.3 + 0.265 * p.rows;
-    for (int64_t i1 = 0; i1 < in; i1 += GB) {
-        const int64_t w = std::min<int64_t>(in - i1, GB), behind = in - i1 - w;
-        const double update = i1 > 0 ? few * p.column * double(behind) : 0.0;
-        us += std::max(p.chain * double(w) / GB, update) + (behind > 0 ? p.step : 0.0);
-    }
+    const int64_t wgs = (out + p.rows - 1) / p.rows, last = in - (in - 1) / GB * GB;
+    const double column = p.column * (in > 10000 ? 1.0 + 0.54 / std::sqrt(double(wgs)) : 1.0);
+    // blocks before the last, and those behind the first with columns (in - 2 GB - GB k of them, k = 1 .. n_far) behind the next block
+    const int64_t n = (in - 1) / GB, n_far = in > 2 * GB ? (in - 2 * GB - 1) / GB : 0, far = n_far * (in - 2 * GB) - GB * n_far * (n_far + 1) / 2;
+    const double us = p.start + double(n) * p.block + double(n_far) * p.behind + column * double(far) +
+                      p.last * double(last / SB * SB) / GB + 0.36 * double(last % SB);
     return us * double((wgs + 255) / 256);
 }
 inline const Parts& best_parts(int64_t out, int64_t in) {
@@ -904,25 +903,30 @@ inline const Parts& best_parts(int64_t out, int64_t in) {
 // the update beside the next block's chain, most of the shorter one of the two showing where the chain's workgroups fill the chip.  Channels
 // that are no multiple of 16 or of four store codes and errors in smaller pieces.
 // (Fitted with the side stream on a hardware queue of its own; where it shares the context's, this form takes up to 1.15 times as
-// long: 8704 x 8192 13100 us and 15000, in one launch 16900; 9216 x 512 295 and 339, 335.)
+// long: 8704 x 8192 13100 us and 15000.)
 inline double blocks_us(int64_t out, int64_t in) {
     const int64_t wgs = (out + 63) / 64;
-    const double rounds = double((wgs + 255) / 256), full = std::min(1.0, double(wgs) / 256.0), column = 4.54e-6 * double(out);
-    const double block = 44.0 + (in % 4 ? 3.6 : 0.0) + (in % 16 ? 6.5 : 0.0);
-    double us = 7.0, bulk = 0.0;
+    const double rounds = double((wgs + 255) / 256), full = std::min(1.0, double(wgs) / 256.0), column = 4.51e-6 * double(out);
+    const double block = (49.2 + (in % 4 ? 4.2 : 0.0) + (in % 16 ? 7.6 : 0.0)) * rounds;
+    double us = 4.6, bulk = 0.0;
     for (int64_t i1 = 0; i1 < in; i1 += GB) {
         const int64_t w = std::min<int64_t>(in - i1, GB), behind = in - i1 - w;
-        const double chain = std::max(0.0, block * double(w) / GB - 4.6) * rounds;
-        us += std::max(bulk, chain) + 0.645 * full * std::min(bulk, chain);
-        if (behind > 0) us += 22.4 + 0.62e-3 * double(in) + column * double(std::min<int64_t>(behind, GB));
+        const double chain = block * double(w) / GB;
+        us += std::max(bulk, chain) + 0.73 * full * std::min(bulk, chain);
+        if (behind > 0) us += 20.2 + 0.086e-3 * double(in) + column * double(std::min<int64_t>(behind, GB));
         bulk = column * double(std::max<int64_t>(behind - GB, 0));
     }
     return us;
 }
 
 inline int rows_per_group(int64_t out, int64_t in) { return best_parts(out, in).rows; }
-// Whether this form is the faster one for [out, in]; else a launch per block.
-inline bool better(int64_t out, int64_t in) { return rows_us(best_parts(out, in), out, in) <= blocks_us(out, in); }
+// Whether this form is the faster one for [out, in]; else a launch per block.  (Of two alike, the one that needs no second stream.)  Up to 32
+// channels all calls are starts and ends of launches, and this form takes 8 to 10 us more at some sizes than at others, for a reason that was not
+// found: 2048 x 16 15.8 us and 3072 x 16 24.3, a launch per block 17.7 and 18.9.
+inline bool better(int64_t out, int64_t in) {
+    if (in <= 32 && out >= 2048) return false;
+    return rows_us(best_parts(out, in), out, in) <= 1.03 * blocks_us(out, in);
+}
 
 template <int R>
 hipError_t allow_lds_of() {

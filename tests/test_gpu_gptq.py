@@ -166,10 +166,10 @@ def _synthetic_factor(in_f, rng, tiny=False):
 
 
 @pytest.mark.parametrize("out_f,in_f,dim,bits,group,tiny", [
-    (9220, 260, OC, 3, 0, False),     # a launch per block; 4 rows and 4 columns past whole tiles of the update
+    (9220, 260, OC, 3, 0, False),     # in one launch of two rounds of 24 rows; the next block of 4 columns
     (9217, 259, OC, 4, 0, False),     # the same with rows of Wp at any alignment
-    (9220, 420, OC, 4, 0, False),     # with an update on the side stream
-    (10007, 129, OC, 3, 0, False),    # updates of 1, 49, 64 and 65 columns, rows short of a tile
+    (9220, 420, OC, 4, 0, False),     # with columns behind the next block
+    (10007, 129, OC, 3, 0, False),    # next blocks of 1, 49, 64 and 65 columns
     (10007, 177, OC, 4, 0, False),
     (10050, 192, OC, 3, 0, False),
     (10050, 193, OC, 3, 0, False),
@@ -188,6 +188,7 @@ def test_update_of_later_channels_bit_exact(ctx, out_f, in_f, dim, bits, group, 
     difference per element and channel.  tiny: with a weight that is zero (of either sign) behind the first visited block, the
     later channels consist of subnormal products alone, so that a lost or flushed product shows in scales and codes (per-IC, where
     the scales come from these channels; per-OC test_subnormal_products_decide_per_oc_codes)."""
+    assert dim == IC or (out_f, in_f) in GPTQ_FORMS
     rng = np.random.default_rng(out_f * 7 + in_f)
     W = synth.make_weight(out_f, in_f, in_f, heavy_cols=2, heavy_scale=5.0)
     U = _synthetic_factor(in_f, rng, tiny)
@@ -228,10 +229,17 @@ def _per_oc_matches_oracle(ctx, W, U, perm, dead, bits, group, rows, scale_round
     (16, 4090, 3300),     # items of the update per wave: three; a last workgroup of ten rows
     (32, 8100, 3300),     # six; a last workgroup of four, so that its second half has none
     (24, 4099, 300),
-    (12, 3000, 1800),
+    (12, 3000, 3300),
+    (16, 3000, 1800),
     (8, 2041, 1800),
-    (0, 9220, 420),       # a launch per block: the next block's columns, and behind those the update on the side stream
-    (0, 10007, 177),      # the same, an update of few columns
+    (24, 9220, 420),      # two rounds of workgroups
+    (24, 10007, 177),
+    (0, 8300, 3300),      # a launch per block: the next block's columns, and behind those the update on the side stream, 100 columns at last
+    (0, 8260, 3204),      # the same, an update of 4 columns at last, 4 rows past whole tiles of the update
+    (0, 9001, 3201),      # one column, rows of Wp at any alignment
+    (0, 8257, 3249),      # 49 columns, one row past whole tiles
+    (0, 8300, 3264),      # 64, the last that the four waves share by rows
+    (0, 8300, 3265),
 ])
 def test_several_pieces_of_the_update_per_wave(ctx, form, out_f, in_f):
     """The per-OC forms with their update in several pieces for each wave, the last ones ragged, against the oracle."""
@@ -247,11 +255,13 @@ def test_several_pieces_of_the_update_per_wave(ctx, form, out_f, in_f):
     (16, 4090, 3300, 4),
     (32, 8100, 3300, 4),
     (24, 4099, 300, 4),
-    (12, 3000, 1800, 8),
+    (12, 3000, 3300, 4),
+    (16, 3000, 1800, 8),
     (8, 2041, 1800, 8),
     (4, 3, 2100, 4),
-    (0, 9220, 420, 4),
-    (0, 10050, 192, 8),
+    (24, 9220, 420, 4),
+    (24, 10050, 192, 8),
+    (0, 8300, 3300, 4),
 ])
 def test_subnormal_products_decide_per_oc_codes(ctx, form, out_f, in_f, group):
     """Per-OC parameters are static, so products of the update that are subnormal, or zero of either sign, show in codes only where
@@ -281,11 +291,13 @@ def test_subnormal_products_decide_per_oc_codes(ctx, form, out_f, in_f, group):
 @pytest.mark.parametrize("form,out_f,in_f,group", [
     (4, 1000, 272, 16),
     (8, 2041, 1800, 8),
-    (12, 3000, 1800, 8),
+    (12, 3000, 3300, 4),
+    (16, 3000, 1800, 8),
     (16, 4090, 328, 8),
     (24, 6100, 260, 4),
     (32, 8100, 264, 8),
-    (0, 9000, 264, 8),
+    (12, 9000, 264, 8),
+    (0, 8300, 3300, 4),
 ])
 def test_per_oc_sub_blocks_with_plain_divisions(ctx, form, out_f, in_f, group):
     """Whole sub-blocks of 16 channels in the chain's short form and with plain divisions by turns, as the workgroup's waves hand
@@ -519,19 +531,21 @@ def test_sweep_in_the_storage_format_random_shapes(ctx, out_f, in_f, dim, bits, 
 @pytest.mark.parametrize("out_f,in_f,bits,group", [
     (1000, 272, 3, 16),          # 4 rows per workgroup, whole blocks, in a multiple of 16 only
     (2041, 200, 4, 40),          # 8 rows, the last workgroup short of seven, ragged last sub-block
-    (3000, 129, 2, 43),          # 16 rows, a last block of one channel, odd row pitch
+    (3000, 129, 2, 43),          # 12 rows, a last block of one channel, odd row pitch
     (4090, 328, 3, 0),           # 16 rows
     (6100, 260, 4, 65),          # 24 rows
     (8100, 520, 3, 130),         # 32 rows
     (8100, 136, 3, 136),         # 32 rows, a last block of eight channels
-    (10100, 136, 3, 136),        # a launch per block: 64 rows, the last workgroup short, a ragged last block
-    (9000, 264, 3, 24),          # the same, three blocks
+    (10100, 136, 3, 136),        # 24 rows, two rounds of workgroups
+    (9000, 264, 3, 24),          # 12 rows, three rounds
     (7000, 77, 2, 11),           # 32 rows, less than a block, odd row pitch
-    (9000, 77, 2, 11),           # the same with a launch for the block
+    (9000, 77, 2, 11),           # 24 rows
+    (9000, 27, 2, 9),            # a launch per block: 64 rows, the last workgroup short, less than a block
 ])
 def test_per_oc_sweep_rows_per_workgroup(ctx, out_f, in_f, bits, group):
     """The per-OC sweep picks its form and its rows per workgroup by the layer's size; each choice, against the oracle bit for
     bit."""
+    assert (out_f, in_f) in GPTQ_FORMS                        # whose form the host's tests check
     W, X = layer(out_f, in_f, 600, seed=out_f + in_f, dead=(3,))
     H32 = oracle.hessian(X).astype(np.float32)
     Hp, perm, dead = G.prepare(H32, 0.01, True)
@@ -546,7 +560,8 @@ def test_per_oc_sweep_rows_per_workgroup(ctx, out_f, in_f, bits, group):
     (5, 391, 2, False),          # 4 rows per workgroup, the last with one; 7 columns in the last strip
     (1000, 387, 4, True),        # 4 rows; pieces of the update of three columns, at any alignment
     (2041, 517, 3, False),       # 8 rows
-    (3000, 1805, 3, True),       # 12 rows
+    (3000, 1805, 3, True),       # 16 rows, and 12
+    (3000, 3301, 3, False),
     (4090, 331, 3, False),       # 16 rows
     (6100, 291, 3, False),       # 24 rows
     (8100, 549, 2, True),        # 32 rows
@@ -554,6 +569,7 @@ def test_per_oc_sweep_rows_per_workgroup(ctx, out_f, in_f, bits, group):
 def test_per_oc_sweep_strips_of_ragged_blocks(ctx, out_f, in_f, bits, meta16):
     """The next block's columns are finished beside the chain, in strips of 32 or 64 columns, four in each lane, and the columns behind
     them in wide pieces: last blocks that end inside a strip and inside a lane's four, rows at any alignment, against the oracle."""
+    assert (out_f, in_f) in GPTQ_FORMS
     rng = np.random.default_rng(out_f + in_f)
     W, X = layer(out_f, in_f, 700, seed=out_f * 3 + in_f, dead=(5,))
     H32 = oracle.hessian(X).astype(np.float32)
@@ -612,8 +628,10 @@ def test_per_ic_sweep_of_many_rows(ctx, out_f, in_f, group):
 @pytest.mark.parametrize("out_f,in_f,bits,group,meta16,piece", [
     (16384, 4096, 3, 128, False, 4096),      # 32 rows per workgroup, two rounds of workgroups; pieces of 16 rows
     (1024, 24576, 4, 64, True, 64),          # 4 rows per workgroup; pieces with a launch per block
-    (30000, 512, 4, 32, False, 3000),        # a launch per block, 469 workgroups, the last short; pieces of 16 rows
+    (30000, 512, 4, 32, False, 3000),        # 32 rows, four rounds; pieces of 16 rows
     (25011, 700, 2, 28, True, 5003),         # the same with a ragged last block, odd row counts; pieces of 24 rows
+    (9000, 4100, 4, 41, False, 3000),        # a launch per block, the last workgroup short; pieces of 12 rows
+    (8300, 3300, 2, 44, True, 5003),         # the same with a ragged last block; pieces of 24 rows
     (20011, 700, 2, 28, True, 5003),         # 32 rows per workgroup, three rounds; pieces of 24 rows
 ])
 def test_per_oc_sweep_does_not_depend_on_its_rows_neighbours(ctx, out_f, in_f, bits, group, meta16, piece):

@@ -160,7 +160,8 @@ def test_recorded_products_replay_as_eager(meta16):
 
 
 @pytest.mark.parametrize("out_f,in_f,dim,group", [
-    (9216, 520, 0, 65),          # per-OC, a launch per block, updates on the side stream
+    (8300, 3300, 0, 66),         # per-OC, a launch per block, updates on the side stream
+    (9216, 520, 0, 65),          # per-OC in one launch of two rounds
     (1024, 520, 0, 65),          # per-OC in one launch
     (10560, 392, 1, 64),         # per-IC, walks and update in one launch per block: 165 groups
     (1024, 520, 1, 64),          # the same, 16 groups

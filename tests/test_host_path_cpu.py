@@ -168,36 +168,35 @@ def test_per_oc_sweep_takes_the_form_that_is_faster(run):
         return int(rows[0].split("gq_rowsILi")[1].split("E")[0])
     for (out, inn), want in {
         # in one launch / a launch per block
-        (300, 2048): 4,         # 382 / 1041
-        (2048, 2048): 8,        # 496 / 1103
-        (3072, 3072): 12,       # 1067 / 1746; 16 rows 1102
-        (4096, 4096): 16,       # 1729 / 2659
-        (4096, 11008): 16,      # 10280 / 12000
-        (4608, 4096): 24,       # 2762 / 2875
-        (8192, 1024): 32,       # 385 / 613
-        (8192, 256): 32,        # 102 / 128
-        (6676, 384): 32,        # 141 / 211
-        (12288, 6144): 16,      # 10370 / 10540; 24 rows 12200
-        (1024, 16384): 4,       # 9710 / 10650
-        (16384, 2159): 32,      # 2216 / 2652
-        (40000, 1000): 32,      # 1832 / 2024
-        (100000, 256): 0,       # 1083 / 809
-        (28672, 1024): 0,       # 1471 / 1414
-        (9216, 512): 0,         # 336 / 295
-        (9216, 264): 0,         # 195 / 185
-        (12288, 384): 0,        # 259 / 223
-        (8704, 8192): 0,        # 17220 / 13210
-        (5632, 11008): 0,       # 17650 / 15520
-        (256, 28672): 0,        # 24670 / 16470
-        (8, 16384): 0,          # 10030 / 8760
+        (300, 2048): 4,          # 270 / 1036
+        (2048, 2048): 8,         # 419 / 1104
+        (3072, 3072): 12,        # 948 / 1728; 16 rows 990
+        (4096, 4096): 16,        # 1611 / 2644
+        (4096, 11008): 16,       # 9992 / 12040
+        (4608, 4096): 24,        # 2538 / 2868
+        (8192, 1024): 32,        # 304 / 616
+        (8192, 256): 32,         # 64 / 125
+        (6676, 384): 32,         # 96 / 212
+        (12288, 6144): 16,       # 10020 / 10620
+        (1024, 16384): 4,        # 8539 / 10670
+        (16384, 2159): 32,       # 1967 / 2797
+        (40000, 1000): 32,       # 1481 / 1999
+        (100000, 256): 32,       # 615 / 803
+        (28672, 1024): 32,       # 1163 / 1411
+        (20000, 256): 32,        # 157 / 236
+        (12288, 384): 24,        # 163 / 225; 16 rows 167
+        (9216, 4096): 0,         # 4588 / 4305
+        (8300, 3300): 0,         # 3230 / 3130
+        (8704, 8192): 0,         # 15910 / 13220
+        (5632, 11008): 0,        # 16860 / 15270
+        (256, 28672): 0,         # 20510 / 16470
+        (8, 16384): 0,           # 9868 / 8650
     }.items():
         assert form(out, inn) == want, (out, inn, form(out, inn))
     # channels that are no multiple of four, which the launches per block store element by element, and narrow last blocks
-    for shape in ((8192, 131), (7280, 493), (40000, 1533), (8192, 260), (7168, 320), (8192, 200), (7680, 448)):
+    for shape in ((8192, 131), (7280, 493), (40000, 1533), (8192, 260), (7168, 320), (8192, 200), (7680, 448), (28672, 3003)):
         assert form(*shape) == 32, shape
-    for shape in ((9216, 493), (28672, 3003), (9216, 260)):
-        assert form(*shape) == 0, shape
-    for shape, rows in (((64, 2048), 4), ((3072, 128), 16), ((16384, 8192), 32)):
+    for shape, rows in (((64, 2048), 4), ((3072, 128), 12), ((16384, 8192), 32), ((9216, 493), 24), ((9216, 260), 12)):
         assert form(*shape) == rows, shape
     # the sizes whose tests on the GPU aim at a form
     for (out, inn), want in FORMS.items():
@@ -207,8 +206,8 @@ def test_per_oc_sweep_takes_the_form_that_is_faster(run):
 
 def test_narrow_updates_keep_every_wave_busy(run):
     """The update behind a block of the per-OC sweep's launches per block: up to 64 columns the four waves share the rows, beyond
-    that the columns (two or three of them had none, and sweeps of 129 to 192 channels took up to 1.03 times as long as with
-    vector instructions)."""
+    that the columns (two or three of them had none, and sweeps of 129 to 192 channels, which took this form then, took up to 1.03 times as
+    long as with vector instructions)."""
     run("""
     def forms(out, inn):
         ctx = context()
@@ -216,8 +215,9 @@ def test_narrow_updates_keep_every_wave_busy(run):
         assert lib.adadim_gptq_quantize(ctx, A, c_int64(out), c_int64(inn), 0, 3, inn, A, A, A, A, A, A, None, None, None, None) == OK
         assert launched("gq_block")
         return ["ILb1E" in c for c in launched("gq_trailing")]
-    for inn, want in ((129, [True]), (148, [True]), (192, [True]), (193, [False]), (256, [False]), (257, [True]), (448, [False, True])):
-        assert forms(100000, inn) == want, (inn, forms(100000, inn))
+    for inn, last in ((3201, True), (3249, True), (3264, True), (3265, False), (3300, False)):
+        got = forms(8300, inn)
+        assert got == [False] * (len(got) - 1) + [last] and len(got) == 24, (inn, got)
     """)
 
 

@@ -1,5 +1,6 @@
 // A HIP runtime that runs nothing: loaded ahead of the library in a process of its own, it lets the library's host path run
-// without a GPU and fail where a test wants it to.  Device memory is host memory; launches and copies are written down.
+// without a GPU and fail where a test wants it to.  Device memory is host memory; launches and copies are written down, with the
+// arguments that the test asked for.
 #include <cstddef>
 #include <cstdint>
 #include <cstdlib>
@@ -15,6 +16,7 @@ std::vector<std::string> calls;
 std::string joined;
 std::map<std::string, std::vector<int>> fail;                // call or kernel (part of its name) -> which of the next calls fail
 std::map<std::string, int> seen;
+std::map<std::string, std::vector<int>> watched;             // kernel (part of its name) -> its int arguments to write down
 int last_error = 0;
 struct { Dim3 grid, block; size_t shared; void* stream; } config;
 
@@ -36,6 +38,7 @@ int answer(const char* name) {
 extern "C" {
 
 void fake_fail(const char* name, int nth) { fail[name].push_back(nth); seen[name] = 0; }
+void fake_watch(const char* kernel, int argument) { watched[kernel].push_back(argument); }
 void fake_reset() { calls.clear(); fail.clear(); seen.clear(); last_error = 0; }
 const char* fake_calls() {
     joined.clear();
@@ -52,10 +55,13 @@ int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* sh, void** st) {
     *g = config.grid; *b = config.block; *sh = config.shared; *st = config.stream;
     return 0;
 }
-int hipLaunchKernel(const void* stub, Dim3 g, Dim3 b, void**, size_t, void*) {
+int hipLaunchKernel(const void* stub, Dim3 g, Dim3 b, void** args, size_t, void*) {
     const std::string& name = kernels[stub];
     if (fails(name)) return last_error = 719;                 // hipErrorLaunchFailure
     calls.push_back("launch " + name + " " + std::to_string(g.x) + " " + std::to_string(g.y) + " " + std::to_string(b.x));
+    for (auto& w : watched)
+        if (name.find(w.first) != std::string::npos)
+            for (int k : w.second) calls.back() += " " + std::to_string(*static_cast<const int*>(args[k]));
     return 0;
 }
 int hipGetLastError() { const int e = last_error; last_error = 0; return e; }

@@ -16,6 +16,7 @@ from oracle import OC, IC
 from paper_2309_15531_amd import binding as B
 from paper_2309_15531_amd import search as S
 from paper_2309_15531_amd import synth
+from scoring_forms import GRAM_FORMS, SCORING_FORMS
 
 pytestmark = pytest.mark.gpu
 
@@ -245,6 +246,7 @@ def test_hessian_accumulate_and_pitch(ctx):
 def test_hessian_of_few_tokens(ctx, tokens, in_f):
     """Beyond 1024 columns the 128-wide kernel while there are few tokens, up to its last size and one behind it: ragged first stages, one piece and
     several, plain, accumulated, from a pitched matrix; the prepared form's H has the plain call's bits."""
+    assert (tokens, in_f) in GRAM_FORMS
     X = synth.make_activations(tokens, in_f, seed=tokens + in_f, n_outliers=3, scale_lo=30, scale_hi=80)
     Href = oracle.hessian(X)
     plain = gpu_hessian(ctx, X)
@@ -293,12 +295,14 @@ def test_hessian_reproducible(ctx):
     assert np.array_equal(a, b)
 
 
-ERR_CASES = [(512, 512, 256), (384, 640, 1000), (264, 328, 300), (1288, 264, 500), (96, 2056, 2048)]
+ERR_CASES = [(512, 512, 256), (384, 640, 1000), (264, 328, 300), (1288, 264, 500), (96, 2056, 2048),
+             (504, 5000, 300), (264, 5024, 300)]     # tiles of 256, row-major and blocked
 
 
 @pytest.mark.parametrize("out_f,in_f,tokens", ERR_CASES)
 @pytest.mark.parametrize("dW_dtype", [B.DW_F32, B.DW_F16])
 def test_layer_error(ctx, out_f, in_f, tokens, dW_dtype):
+    assert (1, out_f, in_f) in SCORING_FORMS
     W = rand_w(out_f, in_f, seed=out_f + in_f)
     X = synth.make_activations(tokens, in_f, seed=in_f, n_outliers=4, scale_lo=50, scale_hi=100,
                                relu=(in_f == 2056))
@@ -356,10 +360,14 @@ def test_layer_error_prepared_matches_and_scaled_input(ctx, in_f):
 
 
 @pytest.mark.parametrize("nc,out_f,in_f", [(1, 8, 264), (2, 520, 2048), (1, 300, 2312), (3, 264, 1504), (1, 2056, 768),
-                                           (2, 264, 3328), (8, 1032, 1280)])
+                                           (2, 264, 3328), (8, 1032, 1280),
+                                           (2, 264, 2560), (2, 1024, 4096), (2, 264, 4128), (3, 250, 4128), (2, 500, 4104),
+                                           (8, 1536, 1024), (8, 520, 4104)])
 def test_batch_error_with_cut_contractions(ctx, nc, out_f, in_f):
-    """Launches too small for whole contractions: chunks of several lengths, with and without the in-loop epilogue, both
-    layouts, ragged last chunks and row blocks; every candidate's rows against the oracle, and the fused selection."""
+    """Contractions in chunks of several lengths and whole, ragged last chunks and row blocks, both layouts: tiles of 64 and 128 at the first
+    sizes, of 256 from 8 x 1032 x 1280 on, with and without their in-loop epilogue (SCORING_FORMS says which); every candidate's rows
+    against the oracle, and the fused selection."""
+    assert (nc, out_f, in_f) in SCORING_FORMS                 # whose form the host's tests check
     W = rand_w(out_f, in_f, seed=out_f + in_f)
     X = synth.make_activations(300, in_f, seed=in_f, n_outliers=4, scale_lo=50, scale_hi=100)
     hp = S.PreparedHessian(ctx, in_f).update(dev(X)).prepare()
@@ -386,8 +394,9 @@ def test_batch_error_with_cut_contractions(ctx, nc, out_f, in_f):
 def test_batch_error_of_small_layers(ctx, nc, out_f, in_f):
     """Tiles of 64 x 64 with the contraction dealt to four waves: fewer pairs of steps than waves, half pairs, ragged rows and columns.  Tiles of
     128 x 128 (from 130 x 1000): chunks of one block, of several, whole contractions, a ragged last stage, chunk and row block, row blocks that are
-    not a multiple of eight.  The last two are the DMA kernel's, whose chunks no smaller layer takes.  Both layouts; column-scaled input against
+    not a multiple of eight.  The last two are the DMA kernel's.  Both layouts; column-scaled input against
     the oracle row by row, and fp32 input, whose diagonal term comes from elsewhere."""
+    assert (nc, out_f, in_f) in SCORING_FORMS
     W = rand_w(out_f, in_f, seed=7 * out_f + in_f)
     X = synth.make_activations(200, in_f, seed=in_f + 1, n_outliers=2, scale_lo=50, scale_hi=100)
     hp = S.PreparedHessian(ctx, in_f).update(dev(X)).prepare()

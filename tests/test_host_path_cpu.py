@@ -10,6 +10,7 @@ import pytest
 
 from gptq_forms import GPTQ_FORMS
 from paper_2309_15531_amd import binding as B
+from scoring_forms import GRAM_FORMS, SCORING_FORMS
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -330,18 +331,60 @@ def test_sweep_recording_depends_on_sizes_alone(run):
     def sweep(ctx, out, inn, dim):
         tail = (A, A, A, None, None, None, None) if dim == 0 else (None, None, A, A, A, None, None)
         return lib.adadim_gptq_quantize(ctx, A, c_int64(out), c_int64(inn), dim, 3, 64, A, A, A, *tail)
-    for warm in ((16384, 4096, 0), (16384, 4096, 1), (100032, 512, 0), (4096, 4096, 0)):
-        for call in ((9216, 512, 0), (4096, 4096, 0), (4096, 4096, 1), (100032, 128, 0), (300, 8192, 0)):
+    by_block = []
+    for warm in ((16384, 4096, 0), (16384, 4096, 1), (100032, 512, 0), (4096, 4096, 0), (9024, 4096, 0)):
+        for call in ((9216, 512, 0), (4096, 4096, 0), (4096, 4096, 1), (100032, 128, 0), (300, 8192, 0), (8320, 3328, 0)):
             ctx = context()
             assert sweep(ctx, *warm) == OK
             assert lib.adadim_capture_begin(ctx) == OK
+            fake.fake_reset()
             rc = sweep(ctx, *call)
+            by_block.append(bool(launched("gq_block")))
             assert (rc == OK) == (call[0] * call[1] <= warm[0] * warm[1] and call[1] <= warm[1]), (warm, call, rc)
             g = c_void_p()
             assert lib.adadim_capture_end(ctx, byref(g)) == OK
             lib.adadim_graph_destroy(g)
             lib.adadim_destroy(ctx)
+    assert any(by_block) and not all(by_block)                    # both forms
     """)
+
+
+def test_scoring_and_gram_sizes_take_the_tiles_their_tests_name(run):
+    """The edge of the scoring tiles, the chunk of the contraction and the slots of each size in the tests' table, whichever entry point and input
+    it comes by; and the edge of the Gram matrix's tiles.  (Lines between the kernels that move take the tables with them, and with these
+    the sizes of the tests on the GPU.)"""
+    run("""
+    for k in (b"error_tiles_dma", b"error_mid"):
+        fake.fake_watch(k, 6)                                     # chunk (in columns; in blocks)
+        fake.fake_watch(k, 7)                                     # slots
+    def form(call):
+        fake.fake_reset()
+        assert call() == OK, lib.adadim_last_error(ctx)
+        tiles = [c.split() for c in launched("error_") if "finish" not in c and "prologue" not in c]
+        assert len(tiles) == 1, tiles
+        _, name, gx, gy, block, *seen = tiles[0]
+        if "error_small" in name:
+            return 64, int(gx), int(gx)
+        return (128, int(seen[0]), int(seen[1])) if "error_mid" in name else (256, int(seen[0]) // 256, int(seen[1]))
+    ctx = context()
+    for (n, out, inn), want in SCORING.items():
+        arr = (c_void_p * n)(*[A.value] * n)
+        shape = (c_int64(out), c_int64(inn))
+        for dtype in (0, 1, 2):
+            got = form(lambda: lib.adadim_layer_error_batch(ctx, n, arr, dtype, *shape, A, A, None, A))
+            assert got == want, (n, out, inn, dtype, got, want)
+        assert form(lambda: lib.adadim_layer_error_batch_select(ctx, n, arr, 2, *shape, A, A, None, A, A)) == want
+        if n == 1:
+            assert form(lambda: lib.adadim_layer_error_prepared(ctx, A, 0, *shape, A, A, None, A)) == want
+    for (tokens, inn), want in GRAM.items():
+        t, i = c_int64(tokens), c_int64(inn)
+        for call in (lambda: lib.adadim_hessian(ctx, A, t, i, i, A, 0), lambda: lib.adadim_hessian(ctx, A, t, i, i, A, 1),
+                     lambda: lib.adadim_hessian_prepared(ctx, A, t, i, i, A, A, A)):
+            fake.fake_reset()
+            assert call() == OK, lib.adadim_last_error(ctx)
+            names = [c.split()[1] for c in launched("gram_tiles")]
+            assert len(names) == 1 and ("gram_tiles_dma" in names[0]) == (want == 256), (tokens, inn, names)
+    """.replace("SCORING", repr(SCORING_FORMS)).replace("GRAM", repr(GRAM_FORMS)))
 
 
 def test_scoring_recording_depends_on_the_finest_cut(run):

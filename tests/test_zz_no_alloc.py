@@ -1,9 +1,9 @@
 """The scoring entry point that allocates nothing (adadim_layer_error_batch_select_noalloc) against the
-entry point it is a variant of (adadim_layer_error_batch_select), through the C ABI: two calls in a row on
-one context, the second on a smaller layer, so that the second call finds the first call's contents in the
+entry point it is a variant of (adadim_layer_error_batch_select), through the C ABI: calls in a row on
+one context, on smaller and larger layers, so that each finds the last one's contents in the
 fixed scratch array.  Same kernels and launch shape, so losses, row losses and the winner are compared
 bit for bit (the bar of the existing entry point against the oracle is 1e-3 relative; it is checked too,
-on the oracle's fp64 losses, for the first layer)."""
+on the oracle's fp64 losses)."""
 import ctypes
 
 import numpy as np
@@ -14,6 +14,7 @@ import oracle
 from oracle import OC, IC
 from paper_2309_15531_amd import binding as B
 from paper_2309_15531_amd import synth
+from scoring_forms import SCORING_FORMS
 
 pytestmark = pytest.mark.gpu
 
@@ -55,16 +56,18 @@ def test_noalloc_matches_allocating_entry_point_twice():
     lib = B.load_library()
     ctx = B.Context()
     try:
-        # first call: 3 x 2 row blocks, ragged 640-wide contraction (2.5 column blocks)
-        shapes = [(768, 640, 1536, 3, 128, 11), (256, 384, 512, 4, 64, 23)]
+        # first call: ragged 640-wide contraction; tiles of 128, of 64, then of 256 with cut contractions, blocked and row-major operands
+        shapes = [(768, 640, 1536, 3, 128, 11), (256, 384, 512, 4, 64, 23), (1024, 4096, 512, 3, 64, 31), (500, 5000, 512, 3, 20, 41),
+                  (256, 384, 512, 4, 64, 23)]
         for k, (out_f, in_f, tokens, bits, group, seed) in enumerate(shapes):
             print("case", k, out_f, in_f, tokens, bits, group, seed, flush=True)
+            assert (2, out_f, in_f) in SCORING_FORMS
             W, X, dWs, Hs, hmeta = _layer(ctx, out_f, in_f, tokens, bits, group, seed)
             assert 0 < lib.adadim_noalloc_scratch_bytes(2, out_f, in_f) <= 16 << 20
             (l0, r0, b0), (l1, r1, b1) = _both_ways(ctx, lib, out_f, in_f, dWs, Hs, hmeta)
             assert np.array_equal(l0, l1) and np.array_equal(r0, r1) and b0 == b1
             assert (l1 > 0).all() and b1 in (0, 1)
-            if k == 0:
+            if k in (0, 2, 3):
                 H64 = oracle.hessian(X)
                 ref = [oracle.layer_error(oracle.quantize(W, dm, bits, group)["dW"], H64) for dm in (OC, IC)]
                 assert l1 == pytest.approx(ref, rel=1e-3)

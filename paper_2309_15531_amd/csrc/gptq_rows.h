@@ -40,9 +40,6 @@ namespace rows {
 using namespace chain_ns;
 
 constexpr int WAVES = 8;
-constexpr int STRIP = 32;               // columns of the next block that a wave brings up to date
-
-constexpr int PIECES_AT = 1 + GB / STRIP;                        // the first piece of the update in a block's list
 
 // A workgroup's waves: one of the chain for up to 16 rows, then the chain's helpers, then those that are free.
 template <int R>

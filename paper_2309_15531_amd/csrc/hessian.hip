@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 #include "mfma_tile.h"
 #include "gram_dma.h"
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
     // 2048 tokens 25.1 and now 16.6; 768, 3000 tokens 30 and 21; 1024, 8192 tokens 46 and 40).  The 256-wide kernel's partials, of which a plan has
     // few, are added as they come behind the diagonal, whose loads alone are batched (2760, 3001 tokens 54.4 and 52.9, 2048, 4096 tokens 41.9 and
     // 39.9; theirs in batches of four took 22.6 -> 23.6 at 1600, 640 tokens, accumulating: with the registers fewer blocks are resident).
-    constexpr int AHEAD = REGMAJOR ? 4 : 8;
+    constexpr int AHEAD = 8, DIAG_AHEAD = REGMAJOR ? 4 : 8;
     auto runs_of = [&](int tile_r) {
         const int n = gram_plan_parts(plan, tile_r);
         Runs r;
@@ -182,8 +183,9 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
     // where this thread's four elements (rows 4 ty .. 4 ty + 3 of column tx) are in a partial tile
     const int64_t at = REGMAJOR ? ((((sr & 3) * 4 + (sc & 3)) * 4 + (ty >> 1)) * 256 + wave * 64 + (ty & 1) * 32 + tx) * 4
                                 : int64_t(sr * 32 + ty * 4) * BT + sc * 32 + tx;
-    float p[AHEAD][4];
-    auto fetch = [&](int s0) {
+    // a batch of the 128-wide kernel's partials on its way (generic, so that the 256-wide one has no such code)
+    [[maybe_unused]] std::conditional_t<REGMAJOR, char, float[AHEAD][4]> ahead;
+    auto fetch = [&](auto& p, int s0) {
 #pragma unroll
         for (int q = 0; q < AHEAD; ++q) {
             if (s0 + q >= n_parts) continue;                  // uniform
@@ -191,7 +193,7 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
             for (int rr = 0; rr < 4; ++rr) p[q][rr] = mine.at(s0 + q)[at + rr * BT];
         }
     };
-    if constexpr (!REGMAJOR) fetch(0);
+    if constexpr (!REGMAJOR) fetch(ahead, 0);
     const bool diag = R0 == C0;
     if constexpr (PREP) {
         if (threadIdx.x < 64) {
@@ -214,13 +216,13 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
                     const Runs dg = runs_of(dtile - n_whole);
                     const bool one = REGMAJOR && dg.na + dg.nb == 1;    // (no batch for one: blocks this short feel every instruction)
                     if (one) h += (dg.na > 0 ? dg.a : dg.b)[off];
-                    for (int s0 = one ? 1 : 0; s0 < dg.na + dg.nb; s0 += AHEAD) {
-                        float p[AHEAD];
+                    for (int s0 = one ? 1 : 0; s0 < dg.na + dg.nb; s0 += DIAG_AHEAD) {
+                        float p[DIAG_AHEAD];
 #pragma unroll
-                        for (int q = 0; q < AHEAD; ++q)
+                        for (int q = 0; q < DIAG_AHEAD; ++q)
                             if (s0 + q < dg.na + dg.nb) p[q] = dg.at(s0 + q)[off];
 #pragma unroll
-                        for (int q = 0; q < AHEAD; ++q)
+                        for (int q = 0; q < DIAG_AHEAD; ++q)
                             if (s0 + q < dg.na + dg.nb) h += p[q];
                     }
                 }
@@ -257,12 +259,12 @@ __global__ __launch_bounds__(256) void gram_reduce(const float* __restrict__ par
     } else {
         float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         for (int s0 = 0; s0 < n_parts; s0 += AHEAD) {
-            if (s0 > 0) fetch(s0);
+            if (s0 > 0) fetch(ahead, s0);
 #pragma unroll
             for (int q = 0; q < AHEAD; ++q)
 #pragma unroll
                 for (int rr = 0; rr < 4; ++rr)
-                    if (s0 + q < n_parts) v[rr] += p[q][rr];
+                    if (s0 + q < n_parts) v[rr] += ahead[q][rr];
         }
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) s[ty * 4 + rr][tx] = v[rr];

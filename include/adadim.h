@@ -251,7 +251,7 @@ int adadim_layer_error_batch_select(adadim_ctx* ctx, int n, const void* const* d
  *           does not fit a fixed array.
  *   Sizes whose scratch exceeds the array are rejected with ADADIM_EINVAL and touch nothing;
  *   adadim_noalloc_scratch_bytes(n, out, in) gives the need (-1 for arguments out of range), the limit is
- *   16 MiB = 16777216 bytes: 512 + 64*ceil(out/256) + 4*n*slots*out with slots about ceil(in/256), e.g. 1.4 MB for
+ *   16 MiB = 16777216 bytes: 512 + 64*ceil(out/256) + 4*n*slots*out with slots about ceil(in/256) for large layers, e.g. 1.4 MB for
  *   two candidates of a 4096 x 11008 layer, 8.4 MB for eight of an 8192 x 8192 layer.
  *   Every call on a GPU shares that GPU's array: calls that overlap in time on one GPU (two streams, two
  *   contexts, two threads) race and give undefined losses; calls on one stream, one after the other, are safe.

@@ -558,8 +558,9 @@ int run_gram(adadim_ctx* ctx, const __half* X, int64_t tokens, int64_t in, int64
 }
 
 // Which kernel: up to 1024 columns the 128-wide one.  Beyond that it is ahead while there are few tokens: with the preparation, us, 256-wide / 128-wide,
-// 1032 x 64 tokens 15.7 / 12.3, 1200 x 128 16.1 / 14.1, 1280 x 256 18.4 / 16.1, 1448 x 500 22.5 / 20.7, 1600 x 400 24.4 / 23.6, but 1200 x 1000
-// 23.6 / 24.1, 1800 x 500 25.9 / 27.7, 2760 x 64 28.9 / 29.5.
+// 1032 x 64 tokens 15.5 / 12.2, 1200 x 128 16.1 / 14.4, 1280 x 256 18.1 / 15.9, 1448 x 500 22.3 / 20.4, 1600 x 400 24.2 / 23.5; at 85 sizes 0.88 of
+// the time on average and 1.008 at most (profiles/gram_few_tokens.md).  The lines are on the safe side: 1800 x 64 20.1 / 18.0 and 1448 x 640 23.8 / 21.4
+// lie beyond them, but so do 1200 x 1000 23.3 / 23.9 and 2760 x 64 27.8 / 29.2.
 // The 128-wide kernel then cuts the tokens into pieces no longer than the 256-wide one's, so that the fp32 sums are as short, and takes the
 // 256-wide one's scratch all the same, only where its own fits, so that which call can be recorded after which does not depend on the line.
 int run_gram_of_size(adadim_ctx* ctx, const __half* X, int64_t tokens, int64_t in, int64_t ldx, float* H, int accumulate, __half* Hs,

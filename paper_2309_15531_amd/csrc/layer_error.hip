@@ -486,9 +486,9 @@ static_assert(SMALL_TILE * SMALL_STEPS <= MID_TILE * MID_TILES, "the scratch has
 // 128: the chunk whose estimate, 5 per round of 256 tiles and 7 per column block that a compute unit has to go through one after the other or
 // in all, is the least (of the chunks 1 .. 12, 16 .. of 63 launches, up to 2 x 3000 x 3000, the choice is 3 % slower than the best on average),
 // if it is ahead of the DMA kernel's estimate.  The lines between the two are fits to 165 launches, blocked (time = 12.7 + 0.203 x this against
-// 9.9 + 0.081 x the DMA kernel's) and row-major (12.8 + 0.229 x against 12.0 + 0.096 x), set 10 and 5 % to the DMA kernel's side: no measured
-// launch is more than 2 % slower than there.  DMA kernel / 128, blocked: 2 x 1024 x 1024 25.8 / 17.0, 2 x 1536 x 1536 32.5 / 25.5, 1 x 2560 x 2560
-// 50.0 / 41.9, 2 x 5816 x 1056 60.2 / 36.8, but 2 x 8192 x 1024 36.4 / 41.5, 1 x 1024 x 4096 36.7 / 41.9 (tiles of 256 fit, in one round);
+// 9.9 + 0.081 x the DMA kernel's) and row-major (12.8 + 0.229 x against 12.0 + 0.096 x), set 10 and 5 % to the DMA kernel's side: of 172
+// launches none with a smaller tile is slower than there, and 12 that stay there would gain more than 5 % (profiles/scoring_tiles.md).
+// DMA kernel / 128, blocked: 2 x 1024 x 1024 25.8 / 17.0, 2 x 1536 x 1536 32.5 / 25.5, 1 x 2560 x 2560 50.0 / 41.9, 2 x 5816 x 1056 60.2 / 36.8, but 2 x 8192 x 1024 36.4 / 41.5, 1 x 1024 x 4096 36.7 / 41.9 (tiles of 256 fit, in one round);
 // row-major: 2 x 1000 x 1000 34.3 / 17.3, 2 x 1448 x 1448 44.2 / 25.8, 2 x 1720 x 2760 73 / 59, 1 x 7008 x 2280 86 / 71, 1 x 60000 x 504 93.7 / 54.4,
 // but 1 x 1000 x 6000 72 / 84.
 ErrPlan error_plan(int nc, int64_t out, int64_t in) {

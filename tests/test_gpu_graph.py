@@ -63,6 +63,32 @@ def test_graph_replays_match_eager(meta16):
         ctx.close(); eager_ctx.close()
 
 
+@pytest.mark.parametrize("out_f,in_f,group,batch", [(256, 512, 64, 8), (240, 520, 40, 3)])
+def test_recorded_clip_grid_replays_as_eager(out_f, in_f, group, batch):
+    """A grid of more candidates than a batch, recorded (losses and index only): several batches into the same buffers, each loss put in
+    its candidate's place, every replay as the eager calls."""
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ctx, eager_ctx = B.Context(), B.Context()
+        Wd = torch.empty((out_f, in_f), dtype=torch.float16, device="cuda")
+        Xd = torch.empty((300, in_f), dtype=torch.float16, device="cuda")
+        hp, hp2 = S.PreparedHessian(ctx, in_f), S.PreparedHessian(eager_ctx, in_f)
+        ls, ls2 = (S.LayerSearch(c, out_f, in_f, 3, group, S.clip_grid(5), keep_winner=False, batch=batch) for c in (ctx, eager_ctx))
+        gs = None
+        for rep in range(4):
+            W, X = _inputs(7 * rep + 1, out_f, in_f, 300)
+            Wd.copy_(torch.from_numpy(W)); Xd.copy_(torch.from_numpy(X))
+            torch.cuda.synchronize()
+            gs = gs or S.GraphedSearch(ctx, ls, hp, Wd, Xd)
+            best2, dim2, clip2 = ls2.run(Wd, hp2.update_prepared(Xd))
+            ls.losses.fill_(float("nan")); ls.best.fill_(-1)
+            assert gs.run() == (best2, dim2, clip2)
+            assert torch.equal(ls.losses, ls2.losses)
+        gs.close()
+        torch.cuda.synchronize()
+        ctx.close(); eager_ctx.close()
+
+
 def test_capture_refuses_what_it_cannot_record():
     side = torch.cuda.Stream()
     with torch.cuda.stream(side):
